@@ -274,7 +274,7 @@ def main():
         if rec.get("attn_bf16_hip_sha16") == sha:
             traffic = rec.get("attn_bytes_per_launch")
     roofline = {
-        "bound": "mfma" if is_bf16 else "alu", "kernel": "attn_bf16_kernel" if is_bf16 else "attn_fp32_kernel",
+        "bound": "mfma" if is_bf16 else "alu", "kernel": "attn_bf16_kernel" if is_bf16 else "attn_tile_kernel",
         "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak, "traffic": traffic,
         "avg_launch_ms": attn_avg_ms, "launches_per_call": attn_n // n_prof,
     }

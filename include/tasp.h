@@ -136,7 +136,9 @@ int tasp_step_segments(const tasp_schedule_t* s, int64_t S, int32_t mask_mode, i
  *   workspace device, >= tasp_chunk_attn_workspace_bytes() bytes, 256-byte aligned, caller-owned,
  *             contents undefined on entry and exit.
  *   fuse_steps 0: one attention launch per step, each followed by update_out_lse as above (the
- *                 form in which a step can start as soon as its sub-chunks have arrived);
+ *                 form in which a step can start as soon as its sub-chunks have arrived).  With few
+ *                 local rows (L <= 4096) the library joins the steps as for 1 where the lists allow
+ *                 it: K and V are there, and the launches would cost more than their work;
  *              1: ONE launch walks the sub-chunks of all N steps in arrival order and carries the
  *                 running max / sum / output across them, so no partial pair is ever written or
  *                 merged (the log-sum-exp rescale happens in registers).  For callers whose K and V
@@ -176,6 +178,11 @@ typedef struct tasp_attn_args {
 #define TASP_MAX_FUSED_SEGMENTS 1024
 
 size_t tasp_chunk_attn_workspace_bytes(const tasp_schedule_t* s, const tasp_attn_args* a);
+/* The workspace with which the call runs fastest, at least the one above and at most that or
+ * TASP_STATIC_SCRATCH_BYTES: a call with few local rows deals the keys of a query tile to several
+ * workgroups, as many as the workspace has room for partial pairs.  tasp_chunk_attn takes any size from
+ * the smaller to the larger one; results differ in rounding only. */
+size_t tasp_chunk_attn_best_workspace_bytes(const tasp_schedule_t* s, const tasp_attn_args* a);
 int    tasp_chunk_attn(const tasp_schedule_t* s, const tasp_attn_args* a, void* hip_stream);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving loops,
@@ -199,7 +206,8 @@ int tasp_chunk_attn_static(const tasp_schedule_t* s, const tasp_attn_args* a, vo
 
 /* The same call with every kernel launch bracketed by HIP events on `hip_stream`, for measurement.
  * Synchronises the stream before returning.  Times are sums over launches, in milliseconds:
- * attn = step-attention kernels, merge = update_out_lse kernels, other = the final bf16 cast. */
+ * attn = attention kernels, merge = update_out_lse kernels, other = the final bf16 cast, or what a call
+ * with joined steps launches beside the attention kernel (segment lists, the sum over shares of the keys). */
 typedef struct tasp_profile {
   double  attn_ms, merge_ms, other_ms;
   int32_t attn_launches, merge_launches, other_launches;

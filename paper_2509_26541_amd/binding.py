@@ -27,7 +27,7 @@ EXPORTS = [
     "tasp_lse_merge", "tasp_chunk_attn_flops", "tasp_chunk_attn_profile", "tasp_last_hip_error", "tasp_calibration_copy",
     "tasp_lse_merge_many", "tasp_calibration_mfma", "tasp_calibration_issue", "tasp_schedule_create_multinode",
     "tasp_chunk_attn_bwd_workspace_bytes", "tasp_chunk_attn_bwd", "tasp_chunk_attn_bwd_profile",
-    "tasp_chunk_attn_bwd_flops", "tasp_chunk_attn_static",
+    "tasp_chunk_attn_bwd_flops", "tasp_chunk_attn_static", "tasp_chunk_attn_best_workspace_bytes",
 ]
 STATIC_SCRATCH_BYTES = 64 << 20
 
@@ -102,6 +102,8 @@ def _load():
                                        C.POINTER(C.c_int64), p32, C.c_int32, p32]
     lib.tasp_chunk_attn_workspace_bytes.argtypes = [C.c_void_p, C.POINTER(AttnArgs)]
     lib.tasp_chunk_attn_workspace_bytes.restype = C.c_size_t
+    lib.tasp_chunk_attn_best_workspace_bytes.argtypes = [C.c_void_p, C.POINTER(AttnArgs)]
+    lib.tasp_chunk_attn_best_workspace_bytes.restype = C.c_size_t
     lib.tasp_chunk_attn.argtypes = [C.c_void_p, C.POINTER(AttnArgs), C.c_void_p]
     lib.tasp_chunk_attn_static.argtypes = [C.c_void_p, C.POINTER(AttnArgs), C.c_void_p]
     lib.tasp_chunk_attn_profile.argtypes = [C.c_void_p, C.POINTER(AttnArgs), C.c_void_p, C.POINTER(Profile)]
@@ -230,7 +232,7 @@ class ChunkAttnPlan:
             raise ValueError("q must hold S / N local rows")
         self.out = torch.empty_like(q)
         self.lse = torch.empty(q.shape[:-1], dtype=torch.float32, device=q.device)
-        nbytes = lib.tasp_chunk_attn_workspace_bytes(schedule.handle, C.byref(self.args))
+        nbytes = lib.tasp_chunk_attn_best_workspace_bytes(schedule.handle, C.byref(self.args))
         self.workspace = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=q.device)
         self.args.out, self.args.lse = self.out.data_ptr(), self.lse.data_ptr()
         self.args.workspace, self.args.workspace_bytes = self.workspace.data_ptr(), nbytes

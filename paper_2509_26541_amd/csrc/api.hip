@@ -82,7 +82,9 @@ int build_step(const tasp_schedule_t* s, const tasp_attn_args* a, int step, Attn
   lp->o_bstride = L * a->Hq * a->d;
   lp->lse_bstride = L * a->Hq;
   lp->n_tasks = 0;
+  lp->n_split[0] = lp->n_split[1] = 1;
   int64_t keys[tasp::kMaxTasks] = {0, 0};
+  int32_t n_pool = 0;
   std::vector<tasp::Segment> segs;
   for (int qb = 0; qb < tasp::n_query_blocks(a->mask_mode); ++qb) {
     tasp::QueryBlock blk;
@@ -97,11 +99,13 @@ int build_step(const tasp_schedule_t* s, const tasp_attn_args* a, int step, Attn
     t.n_q = static_cast<int32_t>(blk.rows);
     t.q_pos0 = static_cast<int32_t>(blk.pos0);
     t.n_seg = static_cast<int32_t>(segs.size());
+    t.seg0 = n_pool;
     int64_t total = 0;
-    for (size_t i = 0; i < segs.size(); ++i) {
-      t.seg_start[i] = static_cast<int32_t>(segs[i].start);
-      t.seg_end[i] = static_cast<int32_t>(segs[i].end);
-      total += segs[i].end - segs[i].start;
+    for (const tasp::Segment& g : segs) {
+      lp->pool[2 * n_pool] = static_cast<int32_t>(g.start);
+      lp->pool[2 * n_pool + 1] = static_cast<int32_t>(g.end);
+      ++n_pool;
+      total += g.end - g.start;
     }
     keys[lp->n_tasks++] = total;
   }
@@ -110,14 +114,16 @@ int build_step(const tasp_schedule_t* s, const tasp_attn_args* a, int step, Attn
   return TASP_OK;
 }
 
-// Single-launch mode: the tasks of all steps joined per query block, in arrival order.  The segment
-// lists go to `dev_table` (kMaxTasks x 2 kMaxSegAll integers of device memory, written by small
-// kernels on `stream`); the descriptor points at them.
-int build_all_steps(const tasp_schedule_t* s, const tasp_attn_args* a, int32_t* dev_table, hipStream_t stream,
-                    AttnLaunch* all) {
-  std::vector<int32_t> table[tasp::kMaxTasks];
+// The tasks of all steps joined per query block, in arrival order, for one launch over them.
+struct JoinedSteps {
+  AttnLaunch all;
+  std::vector<int32_t> table[tasp::kMaxTasks];   // per task of `all`: (start, end) pairs
+  int64_t keys[tasp::kMaxTasks] = {0, 0};        // keys the last row of the block sees
+  size_t segments() const { return (table[0].size() + table[1].size()) / 2; }
+};
+
+int join_steps(const tasp_schedule_t* s, const tasp_attn_args* a, JoinedSteps* js) {
   std::vector<tasp::QueryBlock> empty;
-  int64_t keys[tasp::kMaxTasks] = {0, 0};
   for (int step = 0; step < s->n; ++step) {
     AttnLaunch lp{};
     empty.clear();
@@ -126,36 +132,99 @@ int build_all_steps(const tasp_schedule_t* s, const tasp_attn_args* a, int32_t* 
     if (step == 0) {
       // every query block sees its own diagonal at step 0, so step 0 defines the blocks
       if (!empty.empty()) return TASP_EUNSUPPORTED_SHAPE;
-      *all = lp;
-      for (int t = 0; t < all->n_tasks; ++t) all->task[t].n_seg = 0;
+      js->all = lp;
     }
     for (int t = 0; t < lp.n_tasks; ++t) {
       int dst = -1;
-      for (int u = 0; u < all->n_tasks; ++u)
-        if (all->task[u].q_row0 == lp.task[t].q_row0) dst = u;
+      for (int u = 0; u < js->all.n_tasks; ++u)
+        if (js->all.task[u].q_row0 == lp.task[t].q_row0) dst = u;
       if (dst < 0) return TASP_EUNSUPPORTED_SHAPE;
-      for (int i = 0; i < lp.task[t].n_seg; ++i) {
-        table[dst].push_back(lp.task[t].seg_start[i]);
-        table[dst].push_back(lp.task[t].seg_end[i]);
-        keys[dst] += lp.task[t].seg_end[i] - lp.task[t].seg_start[i];
-      }
+      const int32_t* g = lp.pool + 2 * lp.task[t].seg0;
+      for (int i = 0; i < lp.task[t].n_seg; ++i) js->keys[dst] += g[2 * i + 1] - g[2 * i];
+      js->table[dst].insert(js->table[dst].end(), g, g + 2 * lp.task[t].n_seg);
     }
   }
-  for (int t = 0; t < all->n_tasks; ++t) {
-    const size_t n_seg = table[t].size() / 2;
+  for (int t = 0; t < js->all.n_tasks; ++t) {
+    const size_t n_seg = js->table[t].size() / 2;
     if (n_seg > static_cast<size_t>(tasp::kMaxSegAll)) return TASP_EUNSUPPORTED_SHAPE;
-    all->task[t].n_seg = static_cast<int32_t>(n_seg);
-    all->seg_ext[t] = dev_table + static_cast<size_t>(t) * 2 * tasp::kMaxSegAll;
-    if (tasp::launch_write_i32(dev_table + static_cast<size_t>(t) * 2 * tasp::kMaxSegAll, table[t].data(),
-                               static_cast<int64_t>(table[t].size()), stream) != hipSuccess)
-      return TASP_EHIP;
+    js->all.task[t].n_seg = static_cast<int32_t>(n_seg);
   }
   // the block with more keys goes first so that its workgroups are not the tail of the launch
-  if (all->n_tasks == 2 && keys[1] > keys[0]) {
-    std::swap(all->task[0], all->task[1]);
-    std::swap(all->seg_ext[0], all->seg_ext[1]);
+  if (js->all.n_tasks == 2 && js->keys[1] > js->keys[0]) {
+    std::swap(js->all.task[0], js->all.task[1]);
+    std::swap(js->table[0], js->table[1]);
+    std::swap(js->keys[0], js->keys[1]);
   }
+  js->all.all_steps = 1;
   return TASP_OK;
+}
+
+// Puts the joined lists where the launch finds them: in its descriptor, or, where they do not fit,
+// one behind the other in `dev_table` (kFusedTableBytes of device memory, written by small kernels).
+int place_lists(JoinedSteps* js, bool in_descriptor, int32_t* dev_table, hipStream_t stream) {
+  std::vector<int32_t> flat(js->table[0]);
+  flat.insert(flat.end(), js->table[1].begin(), js->table[1].end());
+  js->all.task[0].seg0 = 0;
+  js->all.task[1].seg0 = static_cast<int32_t>(js->table[0].size() / 2);
+  if (in_descriptor) {
+    std::copy(flat.begin(), flat.end(), js->all.pool);
+    return TASP_OK;
+  }
+  for (int t = 0; t < js->all.n_tasks; ++t) js->all.seg_ext[t] = dev_table + 2 * js->all.task[t].seg0;
+  return tasp::launch_write_i32(dev_table, flat.data(), static_cast<int64_t>(flat.size()), stream) == hipSuccess ? TASP_OK : TASP_EHIP;
+}
+
+// How a forward call runs: step by step, or all steps in one launch, in that case possibly with the
+// keys of a query tile dealt to several workgroups.
+struct FwdPlan {
+  bool joined = false;
+  bool tile = false;                  // attn_tile_kernel
+  int32_t n_split[tasp::kMaxTasks] = {1, 1};
+  size_t table_bytes = 0;             // device memory for the segment lists, in front of the partial pairs
+  int32_t parts = 1;                  // partial pairs (the larger n_split)
+  size_t bytes(const Shape& sh) const {
+    return table_bytes + (parts > 1 ? static_cast<size_t>(parts) * (align_up(sh.o_bytes) + align_up(sh.lse_bytes)) : 0);
+  }
+};
+
+// Local rows up to which the steps of a call are joined although the caller did not ask for it.  A
+// step's launch costs its set-up, the read and write of the running output (or of a partial pair) and
+// the tail of its last workgroups; with L = S / N rows a query tile walks at most L keys a step, and
+// up to here those costs are a fifth of the call and more.  The results differ in rounding only.
+constexpr int64_t kJoinRows = 4096;
+// Workgroups of attn_tile_kernel that keep the chip busy (two per CU), and the fewest keys worth one.
+constexpr int64_t kTileTarget = 512;
+constexpr int64_t kMaxSplit = 32;
+
+// Decides from shapes alone (`js` holds the joined lists), within `ws_bytes` of workspace.
+FwdPlan plan_forward(const tasp_attn_args* a, const Shape& sh, const JoinedSteps& js, size_t ws_bytes) {
+  FwdPlan pl;
+  const bool fp32 = a->dtype == TASP_DTYPE_FP32;
+  pl.joined = true;
+  if (js.segments() > static_cast<size_t>(tasp::kPoolSeg)) pl.table_bytes = kFusedTableBytes;
+  if (pl.table_bytes > ws_bytes) { pl.joined = false; return pl; }
+  // A batch of a few sequences is split like one of them, so that its results are those of separate calls.
+  const int64_t B = sh.B <= 4 ? 1 : sh.B;
+  const int64_t G = a->Hq / a->Hkv;
+  int64_t big = 0, work = 0;          // workgroups of the large kernel; keys walked by all query tiles here
+  for (int t = 0; t < js.all.n_tasks; ++t) {
+    const int64_t tiles = (js.all.task[t].n_q * G + tasp::kTileRows - 1) / tasp::kTileRows * a->Hkv * B;
+    big += static_cast<int64_t>((js.all.task[t].n_q + 255) / 256) * a->Hq * B;
+    work += tiles * js.keys[t];
+  }
+  pl.tile = fp32 || big < 192;
+  if (!pl.tile) return pl;
+  const int64_t least = fp32 ? 64 : 128;
+  const int64_t per_wg = std::max(least, (work + kTileTarget - 1) / kTileTarget);
+  const size_t pair = align_up(sh.o_bytes) + align_up(sh.lse_bytes);
+  const int64_t room = pair > 0 ? static_cast<int64_t>((ws_bytes - pl.table_bytes) / pair) : 1;
+  for (int t = 0; t < js.all.n_tasks; ++t) {
+    int64_t n = (js.keys[t] + per_wg - 1) / per_wg;
+    n = std::min(std::min(n, kMaxSplit), room);
+    pl.n_split[t] = static_cast<int32_t>(std::max<int64_t>(n, 1));
+    pl.parts = std::max(pl.parts, pl.n_split[t]);
+  }
+  return pl;
 }
 
 // Optional per-launch timing with HIP events on the caller's stream (tasp_chunk_attn_profile).
@@ -190,10 +259,10 @@ struct Scope {
   ~Scope() { if (p) p->end(); }
 };
 
-hipError_t launch_attn(const AttnLaunch& lp, const tasp_attn_args* a, hipStream_t stream) {
+hipError_t launch_attn(const AttnLaunch& lp, const tasp_attn_args* a, hipStream_t stream, bool tile = false) {
   if (lp.n_tasks == 0) return hipSuccess;
-  return a->dtype == TASP_DTYPE_BF16 ? tasp::launch_attn_bf16(lp, a->d, stream)
-                                     : tasp::launch_attn_fp32(lp, a->d, stream);
+  return a->dtype == TASP_DTYPE_BF16 && !tile ? tasp::launch_attn_bf16(lp, a->d, stream)
+                                              : tasp::launch_attn_tile(lp, a->d, a->dtype == TASP_DTYPE_FP32, stream);
 }
 
 // ---- backward pass
@@ -299,6 +368,21 @@ size_t tasp_chunk_attn_workspace_bytes(const tasp_schedule_t* s, const tasp_attn
   return total;
 }
 
+size_t tasp_chunk_attn_best_workspace_bytes(const tasp_schedule_t* s, const tasp_attn_args* a) {
+  const size_t need = tasp_chunk_attn_workspace_bytes(s, a);
+  Shape sh;
+  if (validate(s, a, &sh) != TASP_OK || !(a->fuse_steps || sh.L <= kJoinRows)) return need;
+  try {
+    JoinedSteps js{};
+    if (join_steps(s, a, &js) != TASP_OK) return need;
+    // the same limit for every caller, so that the results do not depend on where the workspace comes from
+    const FwdPlan pl = plan_forward(a, sh, js, std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES));
+    return pl.joined ? std::max(need, pl.bytes(sh)) : need;
+  } catch (...) {
+    return need;
+  }
+}
+
 double tasp_chunk_attn_flops(const tasp_schedule_t* s, const tasp_attn_args* a) {
   if (s == nullptr || a == nullptr) return 0.0;
   if (tasp::check_sequence(*s, a->S, a->mask_mode) != TASP_OK) return 0.0;
@@ -362,21 +446,41 @@ static int run_chunk_attn(const tasp_schedule_t* s, const tasp_attn_args* a, voi
   }
 
   try {
-    std::vector<tasp::QueryBlock> empty;
-    if (a->fuse_steps) {
-      AttnLaunch all{};
-      {
-        Scope sc(prof, Profiler::kOther);
-        st = build_all_steps(s, a, reinterpret_cast<int32_t*>(ws), stream, &all);
-        if (st != TASP_OK) return st;
-      }
-      all.o_dst = o_run; all.lse_dst = a->lse; all.merge = 0;
-      {
-        Scope sc(prof, Profiler::kAttn);
-        if (launch_attn(all, a, stream) != hipSuccess) return TASP_EHIP;
+    if (a->fuse_steps || sh.L <= kJoinRows) {
+      JoinedSteps js{};
+      st = join_steps(s, a, &js);
+      if (st != TASP_OK && a->fuse_steps) return st;
+      FwdPlan pl;
+      if (st == TASP_OK) pl = plan_forward(a, sh, js, a->workspace != nullptr ? std::min<size_t>(a->workspace_bytes, std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES)) : 0);
+      if (pl.joined) {
+        {
+          Scope sc(pl.table_bytes > 0 ? prof : nullptr, Profiler::kOther);
+          st = place_lists(&js, pl.table_bytes == 0, reinterpret_cast<int32_t*>(a->workspace), stream);
+          if (st != TASP_OK) return st;
+        }
+        AttnLaunch& all = js.all;
+        all.out_final = a->out; all.lse_dst = a->lse; all.merge = 0;
+        for (int t = 0; t < all.n_tasks; ++t) all.n_split[t] = pl.n_split[t];
+        if (pl.parts > 1) {
+          unsigned char* parts = static_cast<unsigned char*>(a->workspace) + pl.table_bytes;
+          all.part_stride_o = static_cast<int64_t>(align_up(sh.o_bytes) / sizeof(float));
+          all.part_stride_lse = static_cast<int64_t>(align_up(sh.lse_bytes) / sizeof(float));
+          all.o_dst = reinterpret_cast<float*>(parts);
+          all.lse_dst = reinterpret_cast<float*>(parts + pl.parts * align_up(sh.o_bytes));
+        }
+        {
+          Scope sc(prof, Profiler::kAttn);
+          if (launch_attn(all, a, stream, pl.tile) != hipSuccess) return TASP_EHIP;
+        }
+        if (pl.parts > 1) {
+          Scope sc(prof, Profiler::kOther);
+          if (tasp::launch_combine(all, a->d, a->dtype == TASP_DTYPE_FP32, sh.L, a->lse, stream) != hipSuccess) return TASP_EHIP;
+        }
+        return TASP_OK;
       }
     }
-    for (int step = 0; step < s->n && !a->fuse_steps; ++step) {
+    std::vector<tasp::QueryBlock> empty;
+    for (int step = 0; step < s->n; ++step) {
       AttnLaunch lp{};
       empty.clear();
       st = build_step(s, a, step, &lp, &empty);
@@ -535,6 +639,7 @@ static int run_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args
       bp.q_bstride = lp.q_bstride; bp.kv_bstride = lp.kv_bstride; bp.lse_bstride = lp.lse_bstride;
       bp.n_tasks = lp.n_tasks;
       for (int t = 0; t < lp.n_tasks; ++t) { bp.task[t] = lp.task[t]; bp.seg_ext[t] = lp.seg_ext[t]; }
+      if (!lp.all_steps) std::copy(lp.pool, lp.pool + 2 * tasp::kMaxTasks * tasp::kMaxSeg, bp.pool);   // one step's lists
       bp.n_blk = tasp::n_query_blocks(b->mask_mode);
       for (int qb = 0; qb < bp.n_blk; ++qb) {
         tasp::QueryBlock blk;
@@ -600,11 +705,12 @@ static int run_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args
       std::vector<tasp::QueryBlock> empty;
       std::vector<tasp::Segment> ranges, step_ranges;
       if (b->fuse_steps) {
-        AttnLaunch all{};
-        int32_t* dev_table = reinterpret_cast<int32_t*>(after_rows);
+        JoinedSteps js{};
+        st = join_steps(s, &a, &js);
+        if (st != TASP_OK) return st;
         {
           Scope sc(prof, BwdSpans::kOther);
-          st = build_all_steps(s, &a, dev_table, stream, &all);
+          st = place_lists(&js, false, reinterpret_cast<int32_t*>(after_rows), stream);
           if (st != TASP_OK) return st;
         }
         for (int step = 0; step < s->n; ++step) {
@@ -612,7 +718,7 @@ static int run_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args
           if (st != TASP_OK) return st;
           ranges.insert(ranges.end(), step_ranges.begin(), step_ranges.end());
         }
-        st = launch_unit(all, ranges);
+        st = launch_unit(js.all, ranges);
         if (st != TASP_OK) return st;
       }
       for (int step = 0; step < s->n && !b->fuse_steps; ++step) {

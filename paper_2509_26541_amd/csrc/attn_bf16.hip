@@ -244,9 +244,8 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void attn_bf16_kernel(const AttnLa
   int* seg_raw = reinterpret_cast<int*>(smem);
   if (seg_ext != nullptr) {
     for (int i = tid; i < 2 * T.n_seg; i += C::NTHREADS) seg_raw[i] = seg_ext[i];
-  } else if (tid < T.n_seg) {
-    seg_raw[2 * tid] = T.seg_start[tid];
-    seg_raw[2 * tid + 1] = T.seg_end[tid];
+  } else {
+    for (int i = tid; i < 2 * T.n_seg; i += C::NTHREADS) seg_raw[i] = p.pool[2 * T.seg0 + i];
   }
   __syncthreads();
   // The first wavefront builds the list, 64 segments per round: every lane classifies one segment
@@ -862,6 +861,11 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void attn_bf16_kernel(const AttnLa
   // ---- epilogue: normalise and store.  A lane owns one query row per strip; per (db, i4) it holds
   // 4 consecutive output columns, and its partner lane (+32) the next 4, so a wavefront writes
   // 32-byte pieces of 32 rows per store and the 16 stores of a lane complete its 512-byte row.
+  // (The lane number is formed anew: kept across the loop it and what follows from it are registers
+  // that the d = 64 kernel of twelve wavefronts does not have.)
+  int zero_e = 0;
+  asm volatile("" : "+v"(zero_e));
+  const int lane_e = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero_e)), h_e = lane_e >> 5;
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
     const float l_mine = l_run[s] + l_lo[s];
@@ -869,9 +873,25 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void attn_bf16_kernel(const AttnLa
     const bool seen = l_tot > 0.f;
     const float inv = seen && r_tot > 0.f ? 1.f / r_tot : 0.f;
     float lse_new = seen ? (m_run[s] + __builtin_amdgcn_logf(l_tot)) * kLn2 : -__builtin_inff();
-    if (q_valid[s]) {
-      const int64_t grow = T.q_row0 + my_q[s];
-      float* od = p.o_dst + bi * p.o_bstride + (grow * p.Hq + hq) * D + 4 * h;
+    const int row_e = q_tile_row0 + wave_u * (32 * NS) + 32 * s + (lane_e & 31);
+    if (row_e < T.n_q) {
+      const int64_t grow = T.q_row0 + row_e;
+      if (p.out_final != nullptr) {
+        // nothing is folded in later: the row goes out rounded to its final type
+        __bf16* fd = static_cast<__bf16*>(p.out_final) + (bi * p.o_bstride + (grow * p.Hq + hq) * D + 4 * h_e);
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int i4 = 0; i4 < 4; ++i4) {
+            bf16x4 val;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) val[e] = static_cast<__bf16>(o[s][db][4 * i4 + e] * inv);
+            *reinterpret_cast<bf16x4*>(fd + 32 * db + 8 * i4) = val;
+          }
+        if (h_e == 0) p.lse_dst[bi * p.lse_bstride + grow * p.Hq + hq] = lse_new;
+        continue;
+      }
+      float* od = p.o_dst + bi * p.o_bstride + (grow * p.Hq + hq) * D + 4 * h_e;
       float* ld = p.lse_dst + bi * p.lse_bstride + grow * p.Hq + hq;
       float wa = 0.f, wb = inv;
       if (p.merge) {
@@ -910,7 +930,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void attn_bf16_kernel(const AttnLa
           }
           *reinterpret_cast<f32x4*>(od + 32 * db + 8 * i4) = val;
         }
-      if (h == 0) *ld = lse_new;
+      if (h_e == 0) *ld = lse_new;
     }
   }
   }  // next work item (PERSIST)
@@ -925,7 +945,7 @@ hipError_t launch_variant(const AttnLaunch& p0, hipStream_t stream) {
   if (items == 0) return hipSuccess;
   if (items > INT_MAX) return hipErrorInvalidValue;
   if constexpr (D == 64 && NW == 8) {          // (twelve wavefronts leave no registers for the outer loop)
-    if (p0.seg_ext[0] != nullptr) {            // all steps in one launch: persistent workgroups, one per CU
+    if (p0.all_steps) {                        // all steps in one launch: persistent workgroups, one per CU
       int dev = 0, cus = 0;
       if (note_hip(hipGetDevice(&dev)) != hipSuccess ||
           note_hip(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)

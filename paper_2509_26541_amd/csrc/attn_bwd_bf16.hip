@@ -151,9 +151,8 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_kernel(const BwdL
   int* seg_raw = reinterpret_cast<int*>(smem);
   if (seg_ext != nullptr) {
     for (int i = tid; i < 2 * T.n_seg; i += NTHREADS) seg_raw[i] = seg_ext[i];
-  } else if (tid < T.n_seg) {
-    seg_raw[2 * tid] = T.seg_start[tid];
-    seg_raw[2 * tid + 1] = T.seg_end[tid];
+  } else {
+    for (int i = tid; i < 2 * T.n_seg; i += NTHREADS) seg_raw[i] = p.pool[2 * T.seg0 + i];
   }
   __syncthreads();
   if (wave == 0) {

@@ -53,8 +53,8 @@ __global__ __launch_bounds__(WAVES * 64) void bwd_dq_fp32_kernel(const BwdLaunch
     acc[c] = 0.f;
   }
   for (int s = 0; s < T.n_seg; ++s) {
-    const int a = T.seg_start[s];
-    int b = T.seg_end[s];
+    const int a = p.pool[2 * (T.seg0 + s)];
+    int b = p.pool[2 * (T.seg0 + s) + 1];
     if (p.causal) b = min(b, q_pos + 1);             // key t is visible iff t <= q_pos
     for (int t = a; t < b; ++t) {
       float kx[CPL], sk = 0.f, sv = 0.f;

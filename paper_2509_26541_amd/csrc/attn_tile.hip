@@ -1,0 +1,484 @@
+// Blockwise attention for fp32 inputs of any size and for short bf16 calls: 128 query rows per
+// workgroup, the keys of a query tile dealt to as many workgroups as it takes to fill the chip.
+//
+// The large bf16 kernel (attn_bf16.hip) gives a workgroup 256 rows of one head and all its keys; a
+// call with a few hundred local rows then runs on a few dozen of the 256 CUs and a workgroup's chain
+// of key tiles is the length of the call.  Here the rows of a query tile are (local row, query head
+// of the group) pairs, so that grouped heads fill tiles and share K/V, and n_split workgroups each
+// take an equal run of the tile's visible keys; launch_combine adds the partial pairs up.
+//
+// Per wavefront 32 of the tile's rows, S^T = K Q^T and O^T = V^T P^T: one query per lane column, so
+// the softmax is in-lane but for one exchange, and the score registers are the B operand of the second
+// product as they stand.  bf16: v_mfma_f32_32x32x16_bf16, V through the transposing LDS read.  fp32:
+// v_mfma_f32_32x32x2_f32 (full fp32 products and sums); the 16 bytes a lane reads of a K row feed
+// four of them, and so do the 16 bytes (d = 64: two, from 8) it reads of a V row, because block c of
+// O^T takes the columns 4 i + c (2 i + c) instead of 32 neighbouring ones.  K and V tiles come through
+// direct global->LDS loads into two stages.
+//
+// What bounds it: fp32 the matrix pipe (a fp32 matrix instruction holds it for 64 cycles, which
+// leaves room for everything else a SIMD has to issue); short bf16 calls the launch, the set-up and
+// the latency of the first tiles.  Measured, whole calls: fp32, 16 heads of 128, 2 048 of 16 384 tokens,
+// causal, 1.20 ms (114 TFLOP/s of the 152 a large fp32 product reaches) against 20.1 ms with a
+// wavefront per query row; fp32, 4 heads of 64, 256 of 1 024 tokens, 20 us against 309; bf16, 8 heads
+// of 128, 512 of 4 096 tokens, 36 us against 117 with the large kernel on 16 CUs.
+#include <hip/hip_runtime.h>
+
+#include <climits>
+
+#include "gfx950.hpp"
+#include "internal.hpp"
+
+namespace tasp {
+namespace {
+
+constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kLn2 = 0.6931471805599453f;
+constexpr float kRescaleGap = 8.0f;      // the running max is only raised when it grew by more than 2^8
+constexpr float kNegBig = -1.0e30f;
+constexpr int BM = kTileRows;            // rows per workgroup: four wavefronts of 32
+constexpr int NTHREADS = 256;
+
+template <typename T, int D>
+struct TCfg {
+  static constexpr bool F32 = sizeof(T) == 4;
+  static constexpr int BT = F32 ? 32 : 64;              // keys per tile
+  static constexpr int NKB = BT / 32;                   // 32-key blocks
+  static constexpr int RB = D * static_cast<int>(sizeof(T));   // bytes of a row
+  static constexpr int UNITS = RB / 16;                 // 16-byte units per row
+  static constexpr int RPP = NTHREADS / UNITS;          // rows filled per pass
+  static constexpr int PASSES = BT / RPP;
+  static constexpr int TILE_BYTES = BT * RB;
+  static constexpr int STAGE_BYTES = 2 * TILE_BYTES;    // K tile, V tile
+  static constexpr int RPL = UNITS >= 16 ? 1 : 16 / UNITS;   // rows per 256-byte bank line
+  static constexpr int NDB = D / 32;                    // 32-column blocks of O^T
+  // Physical unit of logical unit u of row r.  K is read row-wise (32 lanes, one row each, the same
+  // unit): neighbouring bank lines differ.  V: fp32 rows are read whole; bf16 through the transposing
+  // read (4 rows, 2 units).
+  __device__ static int swz_k(int r, int u) { return u ^ ((r / RPL) % (UNITS < 16 ? UNITS : 16)); }
+  __device__ static int swz_v(int r, int u) { return F32 ? u : u ^ (4 * ((r / RPL) % (UNITS / 4))); }
+};
+
+__device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+__device__ inline f32x16 zero16() {
+  f32x16 z;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) z[i] = 0.f;
+  return z;
+}
+__device__ inline bf16x8 lds_tr8(const unsigned char* lo, const unsigned char* hi) {
+  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lds_void_ptr)const_cast<unsigned char*>(lo));
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lds_void_ptr)const_cast<unsigned char*>(hi));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(const AttnLaunch p) {
+  using C = TCfg<T, D>;
+  constexpr bool F32 = C::F32;
+  constexpr int BT = C::BT, NKB = C::NKB, NDB = C::NDB, NJ = C::UNITS / 2;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * C::STAGE_BYTES];
+  __shared__ __attribute__((aligned(16))) int s_tok[2][BT];   // global position of every key row (INT_MAX: none)
+  __shared__ __attribute__((aligned(16))) int s_msk[2][4];    // per wavefront: it fetched a key some row of the tile must not see
+  // Effective segments of this workgroup's share of the keys.
+  __shared__ int e_vbeg[kMaxSegAll + 1];   // start in the share
+  __shared__ int e_goff[kMaxSegAll];       //   global position minus that
+  __shared__ int e_n;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, lq = lane & 31;
+
+  // ---- which (sequence, KV head, task, row tile, share of the keys)
+  const int G = p.Hq / p.Hkv;
+  const int m0 = p.task[0].n_q * G, m1 = p.n_tasks > 1 ? p.task[1].n_q * G : 0;
+  const int tiles0 = (m0 + BM - 1) / BM, tiles1 = (m1 + BM - 1) / BM;
+  const int items0 = tiles0 * p.n_split[0], per_g = items0 + tiles1 * p.n_split[1];
+  const int w_all = xcd_balanced(blockIdx.x, p.batch * p.Hkv, per_g);
+  if (w_all < 0) return;
+  const int bg = w_all / per_g;
+  int rem = w_all - bg * per_g;
+  const int bi = bg / p.Hkv, g = bg - bi * p.Hkv;
+  const int tsk = rem >= items0 ? 1 : 0;
+  if (tsk) rem -= items0;
+  const int ns = p.n_split[tsk];
+  const int share = rem % ns;
+  // under the causal mask the later tiles of a block see more keys: they start first
+  const int tile = p.causal ? (tsk ? tiles1 : tiles0) - 1 - rem / ns : rem / ns;
+  const AttnTask& T_ = p.task[tsk];
+  const int m_all = tsk ? m1 : m0;
+  const int m = tile * BM + wave * 32 + lq;                  // row of the tile: (local row, head of the group)
+  const bool q_valid = m < m_all;
+  const int mc = q_valid ? m : m_all - 1;
+  const int row = mc / G, hq = g * G + mc - row * G;
+  const int q_pos = p.causal ? T_.q_pos0 + row : INT_MAX - 1;
+  const int q_last = T_.q_pos0 + (min(tile * BM + BM, m_all) - 1) / G;
+  const int q_first = p.causal ? T_.q_pos0 + tile * BM / G : INT_MAX - 1;   // a key at or before it is seen by every row
+
+  // ---- Q fragments (B operand): 16-byte units 2 j + h of the lane's row
+  const int64_t qoff = bi * p.q_bstride + (static_cast<int64_t>(T_.q_row0 + row) * p.Hq + hq) * D;
+  u32x4 qf[NJ];
+  {
+    const u32x4* src = reinterpret_cast<const u32x4*>(static_cast<const T*>(p.q) + qoff) + h;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) qf[j] = src[2 * j];
+  }
+
+  // ---- effective segments: what the mask leaves of every segment for this tile, then the share of it
+  // that is this workgroup's.  The first wavefront works through the list, 64 segments per round.
+  const int32_t* seg_ext = p.seg_ext[tsk];
+  int* list = reinterpret_cast<int*>(smem);      // staged in the still unused tile stages
+  for (int i = tid; i < 2 * T_.n_seg; i += NTHREADS) list[i] = seg_ext != nullptr ? seg_ext[i] : p.pool[2 * T_.seg0 + i];
+  __syncthreads();
+  if (wave == 0) {
+    auto visible = [&](int s, int& a) __attribute__((always_inline)) {
+      a = 0;
+      if (s >= T_.n_seg) return 0;
+      a = list[2 * s];
+      const int e = list[2 * s + 1];
+      return max(0, (p.causal ? min(e, q_last + 1) : e) - a);
+    };
+    int lo = 0, hi = INT_MAX;                     // this workgroup's share of the tile's visible keys
+    if (ns > 1) {
+      int total = 0, a;
+      for (int s0 = 0; s0 < T_.n_seg; s0 += 64) total += visible(s0 + lane, a);
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) total += __shfl_xor(total, o);
+      const int chunk = ((total + ns - 1) / ns + BT - 1) / BT * BT;
+      lo = share * chunk;
+      hi = lo + chunk;
+    }
+    int n_base = 0, v_base = 0, o_base = 0;
+    for (int s0 = 0; s0 < T_.n_seg; s0 += 64) {
+      int a;
+      const int len = visible(s0 + lane, a);
+      int sl = len;                               // inclusive scan of the lengths
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) { const int t = __shfl_up(sl, o); if (lane >= o) sl += t; }
+      const int beg = v_base + sl - len;          // position in the tile's visible keys
+      const int cb = max(beg, lo), ce = min(beg + len, hi), clen = max(0, ce - cb);
+      const unsigned long long has = __builtin_amdgcn_ballot_w64(clen > 0);
+      if (clen > 0) {
+        const int idx = n_base + __builtin_popcountll(has & ((1ull << lane) - 1));
+        e_vbeg[idx] = cb - lo;
+        e_goff[idx] = a + (cb - beg) - (cb - lo);
+        o_base = ce - lo;                         // (the last one of the round is taken below)
+      }
+      if (has != 0) o_base = __shfl(o_base, 63 - __builtin_clzll(has));
+      n_base += __builtin_popcountll(has);
+      v_base += __shfl(sl, 63);
+    }
+    if (lane == 0) { e_vbeg[n_base] = o_base; e_n = n_base; }
+  }
+  __syncthreads();
+  const int n_eff = e_n, n_keys = e_vbeg[n_eff];
+  const int n_tiles = (n_keys + BT - 1) / BT;
+
+  // ---- loader: this thread fills rows fr + RPP i, physical unit fu of the K and the V tile
+  const int fr = tid / C::UNITS, fu = tid % C::UNITS;
+  const int64_t row_bytes = static_cast<int64_t>(p.Hkv) * C::RB;
+  const int64_t head0 = (bi * p.kv_bstride + static_cast<int64_t>(g) * D) * static_cast<int64_t>(sizeof(T));
+  const unsigned char* Kg = static_cast<const unsigned char*>(p.k) + head0;
+  const unsigned char* Vg = static_cast<const unsigned char*>(p.v) + head0;
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  int seg_j[C::PASSES], seg_end[C::PASSES], seg_off[C::PASSES];     // the segment the thread's row of the pass was in last
+#pragma unroll
+  for (int i = 0; i < C::PASSES; ++i) { seg_j[i] = -1; seg_end[i] = 0; seg_off[i] = 0; }
+  auto fetch = [&](int t, int stage) __attribute__((always_inline)) {
+    unsigned char* dst = smem + stage * C::STAGE_BYTES + wave_u * 1024;
+    bool hidden = false;
+#pragma unroll
+    for (int i = 0; i < C::PASSES; ++i) {
+      const int r = fr + C::RPP * i, v = t * BT + r;
+      if (v >= seg_end[i]) {                                        // rows only move forward
+        int j = seg_j[i];
+        while (j < n_eff && v >= seg_end[i]) { ++j; seg_end[i] = j < n_eff ? e_vbeg[j + 1] : INT_MAX; }
+        seg_j[i] = j;
+        seg_off[i] = j < n_eff ? e_goff[j] : 0;
+      }
+      const int tok = seg_j[i] < n_eff ? v + seg_off[i] : INT_MAX;
+      hidden |= tok > q_first;
+      if (fu == 0) s_tok[stage][r] = tok;
+      const int64_t src = (tok == INT_MAX ? 0 : tok) * row_bytes;   // rows past the end fetch key 0 and are masked
+      global_to_lds_16_far(Kg + src + C::swz_k(r, fu) * 16, dst + i * NTHREADS * 16);
+      global_to_lds_16_far(Vg + src + C::swz_v(r, fu) * 16, dst + C::TILE_BYTES + i * NTHREADS * 16);
+    }
+    const bool any = __builtin_amdgcn_ballot_w64(hidden) != 0;
+    if (lane == 0) s_msk[stage][wave] = any ? 1 : 0;
+  };
+
+  // ---- LDS read addresses inside a stage
+  const int k_row = lq * C::RB, k_sw = C::swz_k(lq, h) * 16;        // unit 2 j + h sits at k_sw ^ 32 j
+  int v_adr[NDB];                                                   // bf16: as in the large kernel
+  if constexpr (F32) {
+    v_adr[0] = C::TILE_BYTES + 4 * h * C::RB + lq * (C::RB / 32);   // key 4 h (+ 8 (r / 4) + r % 4), 32 equal pieces of the row
+  } else {
+    const int ga = lane >> 4, jj = lane & 15;
+    const int vrow = 4 * (ga >> 1) + (jj >> 2);
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+      v_adr[db] = C::TILE_BYTES + (vrow * C::UNITS + C::swz_v(vrow, 4 * db + 2 * (ga & 1) + ((jj & 3) >> 1))) * 16 + 8 * (jj & 1);
+  }
+
+  f32x16 o[NDB];
+#pragma unroll
+  for (int db = 0; db < NDB; ++db) o[db] = zero16();
+  // running max (exp2 domain), sum in two levels (the last 64 tiles, everything before: one fp32
+  // accumulator would swallow the many small terms behind a few large ones), and what rounding added
+  // to the largest probabilities (bf16), as in the large kernel
+  float m_run = kNegBig, l_run = 0.f, l_lo = 0.f, r_fix = 0.f;
+  const float c = p.scale * kLog2e;
+
+  if (n_tiles > 0) fetch(0, 0);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) asm volatile("" : "+v"(qf[j]));      // landed before the loop: its only wait on vector memory is the one on the tile
+  for (int t = 0; t < n_tiles; ++t) {
+    const int stage = t & 1;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();                 // tile t is complete; nobody reads the other stage any more
+    if (t + 1 < n_tiles) fetch(t + 1, stage ^ 1);
+    const unsigned char* st = smem + stage * C::STAGE_BYTES;
+
+    f32x16 S[NKB];
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb) {
+      S[kb] = zero16();
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const u32x4 a = *reinterpret_cast<const u32x4*>(st + k_row + kb * 32 * C::RB + (k_sw ^ (32 * j)));
+        if constexpr (F32) {
+          const f32x4 af = __builtin_bit_cast(f32x4, a), bf = __builtin_bit_cast(f32x4, qf[j]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) S[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[e], bf[e], S[kb], 0, 0, 0);
+        } else {
+          S[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, qf[j]), S[kb], 0, 0, 0);
+        }
+      }
+    }
+    const i32x4 mk = *reinterpret_cast<const i32x4*>(&s_msk[stage][0]);
+    if (__builtin_amdgcn_readfirstlane(mk[0] | mk[1] | mk[2] | mk[3]) != 0) {
+#pragma unroll
+      for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const i32x4 tk = *reinterpret_cast<const i32x4*>(&s_tok[stage][32 * kb + 8 * i4 + 4 * h]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (tk[e] > q_pos) S[kb][4 * i4 + e] = -__builtin_inff();
+        }
+    }
+    float mx = S[0][0];
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) mx = fmaxf(mx, S[kb][i]);
+    if (__builtin_amdgcn_ballot_w64(mx * c > m_run + kRescaleGap) != 0) {
+      const float m_new = fmaxf(m_run, fmaxf(mx, __shfl_xor(mx, 32)) * c);     // both halves of a row agree
+      const float alpha = fast_exp2(m_run - m_new);
+      m_run = m_new;
+      l_run *= alpha; l_lo *= alpha; r_fix *= alpha;
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
+    }
+    if constexpr (!F32) {
+      const float p_top = fast_exp2(__builtin_fmaf(mx, c, -m_run));
+      r_fix += static_cast<float>(static_cast<__bf16>(p_top)) - p_top;
+    }
+    float sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        S[kb][i] = fast_exp2(__builtin_fmaf(S[kb][i], c, -m_run));
+        sum[i & 3] += S[kb][i];
+      }
+    l_lo += (sum[0] + sum[1]) + (sum[2] + sum[3]);
+    if ((t & 63) == 63) { l_run += l_lo; l_lo = 0.f; }
+
+    if constexpr (F32) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {             // keys 8 (r / 4) + r % 4 and four further on (the lane halves)
+        const unsigned char* va = st + v_adr[0] + (8 * (r / 4) + r % 4) * C::RB;
+        float vv[NDB];
+        if constexpr (NDB == 4) {
+          const f32x4 x = *reinterpret_cast<const f32x4*>(va);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) vv[e] = x[e];
+        } else {
+          const f32x2 x = *reinterpret_cast<const f32x2*>(va);
+          vv[0] = x[0]; vv[1] = x[1];
+        }
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv[db], S[0][r], o[db], 0, 0, 0);
+      }
+    } else {
+#pragma unroll
+      for (int gg = 0; gg < 2 * NKB; ++gg) {
+        bf16x8 pf;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pf[e] = static_cast<__bf16>(S[gg / 2][8 * (gg % 2) + e]);
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) {
+          const unsigned char* va = st + v_adr[db] + gg * 16 * C::RB;
+          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_tr8(va, va + 8 * C::RB), pf, o[db], 0, 0, 0);
+        }
+      }
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // no fetch may still be writing LDS when the workgroup ends
+
+  // ---- epilogue: normalise and store, 4 consecutive columns a lane and turn
+  const float l_mine = l_run + l_lo;
+  const float l_tot = l_mine + __shfl_xor(l_mine, 32), r_tot = l_tot + (r_fix + __shfl_xor(r_fix, 32));
+  const bool seen = l_tot > 0.f;
+  float wb = seen && r_tot > 0.f ? 1.f / r_tot : 0.f;
+  float lse_new = seen ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -__builtin_inff();
+  if (!q_valid) return;
+  const int64_t ooff = bi * p.o_bstride + (static_cast<int64_t>(T_.q_row0 + row) * p.Hq + hq) * D;
+  const int64_t loff = bi * p.lse_bstride + static_cast<int64_t>(T_.q_row0 + row) * p.Hq + hq;
+  // columns of register quad q of the lane: bf16 block q / 4, 32 (q / 4) + 8 (q % 4) + 4 h; fp32 d = 128
+  // row i of the blocks, 4 i; d = 64 rows i, i + 1, 2 i, where i = 8 (r / 4) + 4 h + r % 4
+  auto quad = [&](auto qq, f32x4& x) __attribute__((always_inline)) {
+    constexpr int Q = decltype(qq)::value;
+    if constexpr (!F32) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = o[Q / 4][4 * (Q % 4) + e];
+      return 32 * (Q / 4) + 8 * (Q % 4) + 4 * h;
+    } else if constexpr (NDB == 4) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = o[e][Q];
+      return 4 * (8 * (Q / 4) + 4 * h + Q % 4);
+    } else {
+      x = f32x4{o[0][2 * Q], o[1][2 * Q], o[0][2 * Q + 1], o[1][2 * Q + 1]};
+      return 2 * (8 * (2 * Q / 4) + 4 * h + (2 * Q) % 4);
+    }
+  };
+  if (p.merge == 0 && (p.part_stride_o != 0 || p.out_final == nullptr)) {
+    float* od = p.o_dst + share * p.part_stride_o + ooff;       // (stride 0: one share)
+    static_for<D / 8>([&](auto qq) __attribute__((always_inline)) {
+      f32x4 x;
+      const int col = quad(qq, x);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] *= wb;
+      *reinterpret_cast<f32x4*>(od + col) = x;
+    });
+    if (h == 0) p.lse_dst[share * p.part_stride_lse + loff] = lse_new;
+  } else if (p.merge == 0) {
+    T* od = static_cast<T*>(p.out_final) + ooff;
+    static_for<D / 8>([&](auto qq) __attribute__((always_inline)) {
+      f32x4 x;
+      const int col = quad(qq, x);
+      if constexpr (F32) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] *= wb;
+        *reinterpret_cast<f32x4*>(od + col) = x;
+      } else {
+        bf16x4 y;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = static_cast<__bf16>(x[e] * wb);
+        *reinterpret_cast<bf16x4*>(od + col) = y;
+      }
+    });
+    if (h == 0) p.lse_dst[loff] = lse_new;
+  } else {
+    // update_out_lse of Algorithm 3 folded into the store
+    float wa = 0.f;
+    const float lse_old = p.lse_dst[loff], mxl = fmaxf(lse_old, lse_new);
+    if (mxl == -__builtin_inff()) {
+      wb = 0.f;
+    } else {
+      const float ea = __expf(lse_old - mxl), eb = __expf(lse_new - mxl), rden = 1.f / (ea + eb);
+      wa = ea * rden;
+      wb *= eb * rden;
+      lse_new = mxl + __logf(ea + eb);
+    }
+    float* od = p.o_dst + ooff;
+    static_for<D / 8>([&](auto qq) __attribute__((always_inline)) {
+      f32x4 x;
+      const int col = quad(qq, x);
+      const f32x4 old = *reinterpret_cast<const f32x4*>(od + col);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = __builtin_fmaf(wa, old[e], x[e] * wb);
+      *reinterpret_cast<f32x4*>(od + col) = x;
+    });
+    if (h == 0) p.lse_dst[loff] = lse_new;      // (the lane of the other half has read the old one: same wavefront)
+  }
+}
+
+template <typename T, int D>
+hipError_t launch_tile_variant(const AttnLaunch& p, hipStream_t stream) {
+  const int64_t G = p.Hq / p.Hkv;
+  int64_t per_g = 0;
+  for (int t = 0; t < p.n_tasks; ++t) {
+    if (p.task[t].n_q * G > INT_MAX - BM || p.n_split[t] < 1) return hipErrorInvalidValue;
+    per_g += (p.task[t].n_q * G + BM - 1) / BM * p.n_split[t];
+  }
+  const int64_t units = static_cast<int64_t>(p.batch) * p.Hkv;
+  if (per_g == 0 || units == 0) return hipSuccess;
+  if (per_g * units > INT_MAX) return hipErrorInvalidValue;
+  const int64_t blocks = xcd_balanced_blocks(units, per_g);
+  if (blocks > INT_MAX) return hipErrorInvalidValue;
+  return TASP_LAUNCH((attn_tile_kernel<T, D>), dim3(static_cast<unsigned>(blocks)), dim3(NTHREADS), stream, p);
+}
+
+// One thread per 4 columns of one (row, head): the pairs of the row's shares added up as in
+// tasp_lse_merge_many.  Rows [0, row1) belong to the first query block (n0 shares), the rest to the second.
+template <typename T>
+__global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ o_part, const float* __restrict__ lse_part,
+                                                      T* __restrict__ out, float* __restrict__ lse_out, int64_t n4, int pieces,
+                                                      int heads, int L, int row1, int n0, int n1, int64_t stride_o, int64_t stride_lse) {
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (i >= n4) return;
+  const int64_t rh = i / pieces;
+  const int n = static_cast<int>(rh / heads % L) < row1 ? n0 : n1;
+  float mx = -__builtin_inff();
+  for (int s = 0; s < n; ++s) mx = fmaxf(mx, lse_part[s * stride_lse + rh]);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  float den = 0.f;
+  if (mx != -__builtin_inff()) {
+#pragma unroll 4
+    for (int s = 0; s < n; ++s) {
+      const float w = __expf(lse_part[s * stride_lse + rh] - mx);
+      const f32x4 x = *reinterpret_cast<const f32x4*>(o_part + s * stride_o + 4 * i);
+      den += w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(w, x[e], acc[e]);
+    }
+    const float r = 1.f / den;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] *= r;
+  }
+  if constexpr (sizeof(T) == 4) {
+    *reinterpret_cast<f32x4*>(out + 4 * i) = acc;
+  } else {
+    bf16x4 y;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] = static_cast<__bf16>(acc[e]);
+    *reinterpret_cast<bf16x4*>(out + 4 * i) = y;
+  }
+  if (i - rh * pieces == 0) lse_out[rh] = mx != -__builtin_inff() ? mx + __logf(den) : mx;
+}
+
+}  // namespace
+
+hipError_t launch_attn_tile(const AttnLaunch& p, int d, bool fp32, hipStream_t stream) {
+  if (d == 64) return fp32 ? launch_tile_variant<float, 64>(p, stream) : launch_tile_variant<__bf16, 64>(p, stream);
+  if (d == 128) return fp32 ? launch_tile_variant<float, 128>(p, stream) : launch_tile_variant<__bf16, 128>(p, stream);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_combine(const AttnLaunch& p, int d, bool fp32, int64_t L, float* lse_out, hipStream_t stream) {
+  // the tasks come heaviest first; the rows of the earlier one are those of the first query block
+  const int a = p.n_tasks > 1 && p.task[1].q_row0 < p.task[0].q_row0 ? 1 : 0;
+  const int n0 = p.n_split[a], n1 = p.n_tasks > 1 ? p.n_split[1 - a] : n0;
+  const int64_t row1 = p.task[a].n_q;
+  const int64_t n4 = p.batch * L * p.Hq * (d / 4), blocks = (n4 + 255) / 256;
+  if (blocks > INT_MAX) return hipErrorInvalidValue;
+  const dim3 grid(static_cast<unsigned>(blocks)), block(256);
+  if (fp32)
+    return TASP_LAUNCH((combine_kernel<float>), grid, block, stream, p.o_dst, p.lse_dst, static_cast<float*>(p.out_final), lse_out, n4,
+                       d / 4, p.Hq, static_cast<int>(L), static_cast<int>(row1), n0, n1, p.part_stride_o, p.part_stride_lse);
+  return TASP_LAUNCH((combine_kernel<__bf16>), grid, block, stream, p.o_dst, p.lse_dst, static_cast<__bf16*>(p.out_final), lse_out, n4,
+                     d / 4, p.Hq, static_cast<int>(L), static_cast<int>(row1), n0, n1, p.part_stride_o, p.part_stride_lse);
+}
+
+}  // namespace tasp

@@ -48,6 +48,13 @@ __device__ inline void global_to_lds_16(const unsigned char* base, unsigned off,
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(off), "s"(base));
 }
 
+// The 16-byte load with a 64-bit address per lane, for tensors a 32-bit offset does not reach.  With
+// the compiler-level fence.
+__device__ inline void global_to_lds_16_far(const unsigned char* src, unsigned char* lds_base) {
+  const unsigned lds_addr = static_cast<unsigned>(reinterpret_cast<size_t>((lds_void_ptr)lds_base));
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_addr), "v"(src) : "memory");
+}
+
 // Four bytes per lane: lane l's dword lands at lds_base + 4 l (a gather of 64 scalars into one
 // 256-byte row of LDS, with no register in between).
 template <bool FENCE>

@@ -8,17 +8,23 @@ namespace tasp {
 
 constexpr int kMaxSeg = 64;      // KV segments one query block can see in one step (2(N-1) for zig-zag)
 constexpr int kMaxTasks = 2;     // query blocks per step (the two half-chunks of the zig-zag layout)
-constexpr int kMaxSegAll = 1024; // segments of one query block over ALL steps (single-launch mode)
+constexpr int kTileRows = 128;   // rows (local row, head of the group) of a query tile of attn_tile_kernel
+constexpr int kMaxSegAll = 1024; // segments of one query block over ALL steps (steps joined in one launch)
+// Segments a launch descriptor holds, all its query blocks together.  A launch of all steps of eight
+// ranks fits (at most 112 + 56) and so do most of twelve; longer lists go through device memory, which
+// costs a launch of their own.  The descriptor travels as kernel arguments: below 4 KiB.
+constexpr int kPoolSeg = 384;
+static_assert(kPoolSeg >= kMaxTasks * kMaxSeg, "one step always fits");
 
-// One query block of one step: rows [q_row0, q_row0 + n_q) of the local Q, contiguous in the
-// sequence from q_pos0, attending to the concatenation of seg[0..n_seg).
+// One query block of one launch: rows [q_row0, q_row0 + n_q) of the local Q, contiguous in the
+// sequence from q_pos0, attending to the concatenation of its n_seg segments: (start, end) pairs of
+// the descriptor's pool from index seg0 on.
 struct AttnTask {
   int32_t q_row0;
   int32_t n_q;
   int32_t q_pos0;
   int32_t n_seg;
-  int32_t seg_start[kMaxSeg];
-  int32_t seg_end[kMaxSeg];
+  int32_t seg0;
 };
 
 struct AttnLaunch {
@@ -35,11 +41,20 @@ struct AttnLaunch {
   int64_t q_bstride, kv_bstride, o_bstride, lse_bstride;
   int32_t n_tasks;
   AttnTask task[kMaxTasks];
-  // Single-launch mode: the segment list of task t does not fit the descriptor and lives in device
-  // memory as task[t].n_seg (start, end) pairs; task[t].seg_start / seg_end are then unused.
+  // With many steps in one launch the segment lists may not fit the pool: they then live in device
+  // memory, task[t].n_seg (start, end) pairs at seg_ext[t], and the pool is unused.
   const int32_t* seg_ext[kMaxTasks];
   int32_t n_items;    // work items of the launch, for persistent workgroups; filled in by the launcher
+  void* out_final;    // not null: the rows are final and go here in the inputs' type, not to o_dst (merge = 0)
+  // attn_tile_kernel: task t's keys are dealt to n_split[t] workgroups per query tile.  Where that is
+  // more than one, split i leaves its normalised pair in o_dst + i part_stride_o and lse_dst + i
+  // part_stride_lse for launch_combine.
+  int32_t n_split[kMaxTasks];
+  int64_t part_stride_o, part_stride_lse;
+  int32_t all_steps;  // the steps of the call are joined in this launch
+  int32_t pool[2 * kPoolSeg];
 };
+static_assert(sizeof(AttnLaunch) <= 4096, "kernel arguments");
 
 // One contiguous run of local query rows (a half-chunk of the zig-zag layout, or all rows).
 struct BwdBlock {
@@ -69,6 +84,7 @@ struct BwdLaunch {
   int32_t n_tasks;
   AttnTask task[kMaxTasks];
   const int32_t* seg_ext[kMaxTasks];   // as in AttnLaunch (all steps in one launch)
+  int32_t pool[2 * kMaxTasks * kMaxSeg];
   int32_t n_blk;
   BwdBlock blk[kMaxTasks];
   int32_t n_rng;
@@ -82,6 +98,7 @@ struct BwdLaunch {
   float* part_dk;
   float* part_dv;
 };
+static_assert(sizeof(BwdLaunch) <= 4096, "kernel arguments");
 
 // Last HIP error this thread saw inside the library (hipSuccess if none); see tasp_last_hip_error().
 extern thread_local hipError_t g_last_hip_error;
@@ -99,9 +116,11 @@ inline hipError_t note_hip(hipError_t e) {
     ::tasp::note_hip(hipGetLastError());                                      \
   })
 
-// Implemented in attn_bf16.hip / attn_fp32.hip / merge.hip.  Each returns a hipError_t from the launch.
+// Implemented in attn_bf16.hip / attn_tile.hip / merge.hip.  Each returns a hipError_t from the launch.
 hipError_t launch_attn_bf16(const AttnLaunch& p, int d, hipStream_t stream);
-hipError_t launch_attn_fp32(const AttnLaunch& p, int d, hipStream_t stream);
+hipError_t launch_attn_tile(const AttnLaunch& p, int d, bool fp32, hipStream_t stream);
+// After a launch_attn_tile with several shares: out_final and lse_out from the pairs of the shares.
+hipError_t launch_combine(const AttnLaunch& p, int d, bool fp32, int64_t L, float* lse_out, hipStream_t stream);
 // rows [row0, row0 + rows) of every one of `batch` sequences of L rows each
 hipError_t launch_merge(float* o_acc, float* lse_acc, const float* o_part, const float* lse_part,
                         int64_t row0, int64_t rows, int32_t heads, int32_t d, int32_t batch, int64_t L,

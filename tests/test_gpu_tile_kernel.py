@@ -1,0 +1,58 @@
+"""Short calls on the GPU (query tiles of 128 (row, head) pairs, their keys dealt to several workgroups, steps
+joined in one launch) against the oracle, at the sizes where tiles, shares and segment lists end."""
+import ctypes as C
+
+import pytest
+import torch
+
+from paper_2509_26541_amd import workloads as wl
+from tests.helpers import max_abs, oracle_rows
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tb():
+    assert torch.cuda.is_available(), "GPU tests need an MI355X"
+    from paper_2509_26541_amd import binding
+    return binding
+
+
+# name, N, rank, S, Hq, Hkv, d, dtype, mask
+EDGES = [
+    ("one_row_g3", 4, 3, 4, 3, 1, 128, "fp32", wl.FULL),                      # L = 1, three heads to a KV head
+    ("tile_minus_1", 4, 1, 4 * 127, 1, 1, 64, "fp32", wl.FULL),
+    ("tile", 8, 2, 16 * 128, 2, 2, 128, "fp32", wl.ZIGZAG_CAUSAL),
+    ("tile_plus_1_g3", 8, 5, 16 * 43, 6, 2, 64, "fp32", wl.ZIGZAG_CAUSAL),   # 43 x 3 = 129 pairs
+    ("tile_bf16_g8", 8, 0, 16 * 16, 8, 1, 128, "bf16", wl.ZIGZAG_CAUSAL),    # 16 x 8 = 128 pairs, the fewest keys
+    ("tile_plus_bf16", 8, 7, 16 * 129, 2, 2, 64, "bf16", wl.ZIGZAG_CAUSAL),
+    ("many_shares", 4, 2, 4 * 1031, 1, 1, 128, "bf16", wl.FULL),             # 32 shares of a prime number of keys
+    ("many_shares_fp32", 8, 6, 16 * 257, 1, 1, 64, "fp32", wl.ZIGZAG_CAUSAL),
+    ("lists_in_memory", 16, 11, 32 * 64, 4, 2, 64, "bf16", wl.ZIGZAG_CAUSAL),  # more segments than a descriptor holds
+    ("lists_in_memory_fp32", 16, 15, 32 * 31, 2, 1, 128, "fp32", wl.ZIGZAG_CAUSAL),
+    ("not_joined", 32, 17, 64 * 33, 2, 1, 64, "fp32", wl.ZIGZAG_CAUSAL),     # too many segments to join: step by step
+]
+
+
+@pytest.mark.parametrize("case", EDGES, ids=[c[0] for c in EDGES])
+def test_short_calls_all_rows(tb, case):
+    name, n, rank, S, Hq, Hkv, d, dtype, mode = case
+    w = wl.Workload(name, n, rank, S, Hq, Hkv, d, dtype, mode, seed=wl.BASE_SEED + 8000 + S)
+    q, k, v = wl.make_qkv(w)
+    qd, kd, vd = q.cuda(), k.cuda(), v.cuda()
+    s = tb.tasp_schedule(n, rank)
+    rows = list(range(w.L))
+    ref_o, ref_l = oracle_rows(w, q, k, v, rows)
+    tol_o, tol_l = (2e-2, 1e-3) if dtype == "bf16" else (1e-4, 1e-4)
+    for fuse in (False, True):
+        plan = tb.ChunkAttnPlan(s, qd, kd, vd, mode, fuse_merge=fuse)
+        least = tb.lib.tasp_chunk_attn_workspace_bytes(s.handle, C.byref(plan.args))
+        assert least <= plan.args.workspace_bytes <= max(least, tb.STATIC_SCRATCH_BYTES)
+        # with room for every share, and with the least workspace the call takes
+        for nbytes in {plan.args.workspace_bytes, least}:
+            plan.args.workspace_bytes = nbytes
+            plan.out.fill_(float("nan"))
+            out, lse = plan.run()
+            torch.cuda.synchronize()
+            eo, el = max_abs(out.float().cpu().numpy(), ref_o), max_abs(lse.cpu().numpy(), ref_l)
+            assert eo <= tol_o and el <= tol_l, (name, fuse, nbytes, eo, el)
