@@ -285,9 +285,9 @@ double tasp_chunk_attn_flops(const tasp_schedule_t* s, const tasp_attn_args* a);
  *
  * All tensor pointers are DEVICE pointers, 16-byte aligned, dense row-major, laid out as for
  * tasp_chunk_attn: q, out, dout, dq [B, L, Hq, d]; k, v, dk, dv [B, S, Hkv, d]; lse [B, L, Hq] fp32
- * (out and lse as written by tasp_chunk_attn on the same inputs).  dtype is TASP_DTYPE_BF16 (matrix
- * instructions, the measured path) or TASP_DTYPE_FP32 (a plain small-shape path, all arithmetic
- * fp32); d is 64 or 128.  Every row of dq, dk and dv is written.
+ * (out and lse as written by tasp_chunk_attn on the same inputs).  dtype is TASP_DTYPE_BF16 (bf16
+ * matrix instructions) or TASP_DTYPE_FP32 (fp32 matrix instructions, all arithmetic fp32; with L <= 4096
+ * the steps are joined in one launch); d is 64 or 128.  Every row of dq, dk and dv is written.
  * workspace: device, 256-byte aligned, at least tasp_chunk_attn_bwd_workspace_bytes() (the delta
  * vector; for bf16 also lse scaled to base 2 in the same layout, both with one more entry behind the
  * last row, which is why B*L*Hq must stay below 2^30 there (TASP_EUNSUPPORTED_SHAPE otherwise), an
@@ -329,6 +329,9 @@ typedef struct tasp_attn_bwd_args {
 } tasp_attn_bwd_args;
 
 size_t tasp_chunk_attn_bwd_workspace_bytes(const tasp_schedule_t* s, const tasp_attn_bwd_args* a);
+/* As tasp_chunk_attn_best_workspace_bytes: room to deal the keys of a query tile to several workgroups
+ * (fp32; for bf16 the size above). */
+size_t tasp_chunk_attn_bwd_best_workspace_bytes(const tasp_schedule_t* s, const tasp_attn_bwd_args* a);
 int    tasp_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args* a, void* hip_stream);
 
 /* The same call with every launch bracketed by HIP events; synchronises the stream.  dq = the

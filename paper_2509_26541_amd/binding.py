@@ -28,6 +28,7 @@ EXPORTS = [
     "tasp_lse_merge_many", "tasp_calibration_mfma", "tasp_calibration_issue", "tasp_schedule_create_multinode",
     "tasp_chunk_attn_bwd_workspace_bytes", "tasp_chunk_attn_bwd", "tasp_chunk_attn_bwd_profile",
     "tasp_chunk_attn_bwd_flops", "tasp_chunk_attn_static", "tasp_chunk_attn_best_workspace_bytes",
+    "tasp_chunk_attn_bwd_best_workspace_bytes",
 ]
 STATIC_SCRATCH_BYTES = 64 << 20
 
@@ -119,6 +120,8 @@ def _load():
     lib.tasp_chunk_attn_flops.restype = C.c_double
     lib.tasp_chunk_attn_bwd_workspace_bytes.argtypes = [C.c_void_p, C.POINTER(AttnBwdArgs)]
     lib.tasp_chunk_attn_bwd_workspace_bytes.restype = C.c_size_t
+    lib.tasp_chunk_attn_bwd_best_workspace_bytes.argtypes = [C.c_void_p, C.POINTER(AttnBwdArgs)]
+    lib.tasp_chunk_attn_bwd_best_workspace_bytes.restype = C.c_size_t
     lib.tasp_chunk_attn_bwd.argtypes = [C.c_void_p, C.POINTER(AttnBwdArgs), C.c_void_p]
     lib.tasp_chunk_attn_bwd_profile.argtypes = [C.c_void_p, C.POINTER(AttnBwdArgs), C.c_void_p, C.POINTER(BwdProfile)]
     lib.tasp_chunk_attn_bwd_flops.argtypes = [C.c_void_p, C.POINTER(AttnBwdArgs)]
@@ -286,7 +289,7 @@ class ChunkAttnBwdPlan:
         a.fuse_steps = int(bool(fuse_steps))
         self.dq, self.dk, self.dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
         a.dq, a.dk, a.dv = self.dq.data_ptr(), self.dk.data_ptr(), self.dv.data_ptr()
-        nbytes = lib.tasp_chunk_attn_bwd_workspace_bytes(schedule.handle, C.byref(a))
+        nbytes = lib.tasp_chunk_attn_bwd_best_workspace_bytes(schedule.handle, C.byref(a))
         self.workspace = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=q.device)
         a.workspace, a.workspace_bytes = self.workspace.data_ptr(), nbytes
         a.aux_stream = aux_stream.cuda_stream if aux_stream is not None else None

@@ -296,6 +296,19 @@ int validate_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args* b, tasp_att
   return TASP_OK;
 }
 
+// fp32 backward with joined steps: workgroups the keys of a query tile are dealt to, so that about 512
+// dq workgroups stand beside the dk/dv ones, each with four 64-key tiles or more; within the workspace.
+int bwd_fp32_split(const tasp_attn_bwd_args* b, const Shape& sh, size_t ws_bytes) {
+  if (sh.L > kJoinRows) return 1;
+  const int64_t G = b->Hq / b->Hkv, B = sh.B <= 4 ? 1 : sh.B;
+  const int blocks = tasp::n_query_blocks(b->mask_mode);
+  const int64_t tiles = blocks * ((sh.L / blocks * G + 63) / 64) * b->Hkv * B;
+  const size_t front = align_up(sh.lse_bytes);
+  const int64_t room = ws_bytes > front && sh.o_bytes > 0 ? static_cast<int64_t>((ws_bytes - front) / sh.o_bytes) : 0;
+  const int64_t n = std::min(std::min((512 + tiles - 1) / tiles, b->S / 256), std::min(room, kMaxSplit));
+  return static_cast<int>(std::max<int64_t>(n, 1));
+}
+
 struct BwdSpans { enum Kind { kDq = 0, kDkv = 1, kOther = 2 }; };
 
 // Estimated duration of a dk/dv launch, in 64-row query tiles of one head, with one workgroup per
@@ -576,6 +589,15 @@ size_t tasp_chunk_attn_bwd_workspace_bytes(const tasp_schedule_t* s, const tasp_
   return dq_bytes + 2 * delta_bytes + table + parts;   // fp32 dq, delta, lse log2(e)
 }
 
+size_t tasp_chunk_attn_bwd_best_workspace_bytes(const tasp_schedule_t* s, const tasp_attn_bwd_args* b) {
+  const size_t need = tasp_chunk_attn_bwd_workspace_bytes(s, b);
+  tasp_attn_args a;
+  Shape sh;
+  if (validate_bwd(s, b, &a, &sh) != TASP_OK || b->dtype != TASP_DTYPE_FP32) return need;
+  const int n = bwd_fp32_split(b, sh, std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES));
+  return n > 1 ? std::max(need, align_up(sh.lse_bytes) + n * sh.o_bytes) : need;
+}
+
 double tasp_chunk_attn_bwd_flops(const tasp_schedule_t* s, const tasp_attn_bwd_args* b) {
   if (s == nullptr || b == nullptr) return 0.0;
   const tasp_attn_args a = as_forward(b);
@@ -594,7 +616,8 @@ static int run_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args
   // With a second stream from the caller the dk/dv kernels run beside the dq kernels: fork after
   // delta is on its way, join before returning.  The profiled run keeps one stream (its events
   // bracket launches on `stream`).
-  hipStream_t kv_stream = (b->aux_stream != nullptr && prof == nullptr) ? static_cast<hipStream_t>(b->aux_stream) : stream;
+  // The fp32 launch holds both kinds of workgroup and needs no second stream.
+  hipStream_t kv_stream = (b->aux_stream != nullptr && prof == nullptr && b->dtype == TASP_DTYPE_BF16) ? static_cast<hipStream_t>(b->aux_stream) : stream;
   struct Ev {
     hipEvent_t e = nullptr;
     ~Ev() { if (e) (void)hipEventDestroy(e); }
@@ -620,7 +643,7 @@ static int run_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args
       if ((bf16 ? tasp::launch_bwd_delta_bf16(b->out, b->dout, b->lse, delta, lse2, scale, n_rows, b->d, stream)
                 : tasp::launch_bwd_delta_fp32(b->out, b->dout, delta, n_rows, b->d, stream)) != hipSuccess)
         return TASP_EHIP;
-      if (tasp::launch_zero_f32(dq_acc, n_q_elems, stream) != hipSuccess) return TASP_EHIP;
+      if (bf16 && tasp::launch_zero_f32(dq_acc, n_q_elems, stream) != hipSuccess) return TASP_EHIP;
     }
     if (kv_stream != stream) {
       if (tasp::note_hip(hipEventCreateWithFlags(&fork.e, hipEventDisableTiming)) != hipSuccess ||
@@ -629,6 +652,8 @@ static int run_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args
           tasp::note_hip(hipStreamWaitEvent(kv_stream, fork.e, 0)) != hipSuccess)
         return TASP_EHIP;
     }
+    int n_split = 1;              // fp32: workgroups the keys of a query tile are dealt to
+    bool first_unit = true;
     // One unit = one dq launch and one dk/dv launch: a step, or all steps at once.
     auto launch_unit = [&](const AttnLaunch& lp, std::vector<tasp::Segment>& ranges) -> int {
       tasp::BwdLaunch bp{};
@@ -682,16 +707,32 @@ static int run_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args
         bp.part_dk = part;
         bp.part_dv = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(part) + align_up(sh.o_bytes));
       }
+      if (!bf16) {
+        // one launch for both kinds of workgroup, except where each is to be timed for itself
+        bp.n_split = n_split;
+        bp.part_dk = reinterpret_cast<float*>(static_cast<unsigned char*>(b->workspace) + align_up(sh.lse_bytes));
+        bp.part_stride = n_q_elems;
+        bp.accumulate = first_unit ? 0 : 1;           // every query row sees its own diagonal at step 0
+        first_unit = false;
+        if (prof == nullptr) {
+          if (tasp::launch_bwd_fp32(bp, b->d, true, true, stream) != hipSuccess) return TASP_EHIP;
+        } else {
+          { Scope sc(prof, BwdSpans::kDq); if (tasp::launch_bwd_fp32(bp, b->d, true, false, stream) != hipSuccess) return TASP_EHIP; }
+          { Scope sc(prof, BwdSpans::kDkv); if (tasp::launch_bwd_fp32(bp, b->d, false, true, stream) != hipSuccess) return TASP_EHIP; }
+        }
+        if (n_split > 1) {
+          Scope sc(prof, BwdSpans::kOther);
+          if (tasp::launch_bwd_sum_f32(bp.part_dk, bp.part_stride, n_split, dq_acc, n_q_elems, stream) != hipSuccess) return TASP_EHIP;
+        }
+        return TASP_OK;
+      }
       {
         Scope sc(prof, BwdSpans::kDq);
-        if ((bf16 ? tasp::launch_bwd_dq_bf16(bp, b->d, stream) : tasp::launch_bwd_dq_fp32(bp, b->d, stream)) != hipSuccess)
-          return TASP_EHIP;
+        if (tasp::launch_bwd_dq_bf16(bp, b->d, stream) != hipSuccess) return TASP_EHIP;
       }
       {
         Scope sc(prof, BwdSpans::kDkv);
-        if ((bf16 ? tasp::launch_bwd_dkv_bf16(bp, b->d, kv_stream) : tasp::launch_bwd_dkv_fp32(bp, b->d, kv_stream)) !=
-            hipSuccess)
-          return TASP_EHIP;
+        if (tasp::launch_bwd_dkv_bf16(bp, b->d, kv_stream) != hipSuccess) return TASP_EHIP;
       }
       if (bp.split_heads) {
         Scope sc(prof, BwdSpans::kOther);
@@ -720,6 +761,19 @@ static int run_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args
         }
         st = launch_unit(js.all, ranges);
         if (st != TASP_OK) return st;
+      }
+      if (!bf16 && sh.L <= kJoinRows) {
+        // All steps at once.  Over them every key of the sequence is met once, and what a query row or a
+        // key gets from one pair does not depend on the others: the lists are one segment, the sequence.
+        AttnLaunch lp{};
+        st = build_step(s, &a, 0, &lp, &empty);
+        if (st != TASP_OK) return st;
+        lp.pool[0] = 0;
+        lp.pool[1] = static_cast<int32_t>(b->S);
+        for (int t = 0; t < lp.n_tasks; ++t) { lp.task[t].seg0 = 0; lp.task[t].n_seg = 1; }
+        n_split = bwd_fp32_split(b, sh, b->workspace_bytes);
+        ranges.assign(1, tasp::Segment{0, b->S, 0});
+        return launch_unit(lp, ranges);
       }
       for (int step = 0; step < s->n && !b->fuse_steps; ++step) {
         AttnLaunch lp{};

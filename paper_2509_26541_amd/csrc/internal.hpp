@@ -65,12 +65,12 @@ struct BwdBlock {
 // segments it can see); the dk/dv kernel uses every key range that arrives at the step, laid end to
 // end (rng_vbeg = start of each range in that concatenation), and the query blocks.
 struct BwdLaunch {
-  const void* q;        // [B, L, Hq, d] bf16 (fp32 for the fp32 kernels, as k, v, dout, dk, dv)
+  const void* q;        // [B, L, Hq, d] bf16 (fp32 for the fp32 kernel, as k, v, dout, dk, dv)
   const void* k;        // [B, S, Hkv, d]
   const void* v;
   const void* dout;     // [B, L, Hq, d]
   const float* lse;     // [B, L, Hq] final lse of the forward pass
-  const float* delta;   // [B, L, Hq] sum_d dout * out (fp32 kernels)
+  const float* delta;   // [B, L, Hq] sum_d dout * out (fp32 kernel)
   const float* ndelta;  // [B, L, Hq] -delta, then one 0 (bf16 kernels)
   const float* nlse;    // [B, L, Hq] -lse / scale, -inf where lse is -inf (the row saw no key), then one -inf (bf16 kernels)
   float* dq_acc;        // [B, L, Hq, d] fp32, accumulated into
@@ -97,6 +97,10 @@ struct BwdLaunch {
   int32_t split_heads;
   float* part_dk;
   float* part_dv;
+  // fp32: the keys of a query tile are dealt to n_split workgroups; with more than one their dq sums go
+  // to part_dk + i part_stride for launch_bwd_sum_f32.  accumulate: dq_acc is added to, not written.
+  int32_t n_split, accumulate;
+  int64_t part_stride;
 };
 static_assert(sizeof(BwdLaunch) <= 4096, "kernel arguments");
 
@@ -144,9 +148,11 @@ int bwd_dkv_resident_workgroups(int d);
 hipError_t launch_bwd_delta_bf16(const void* out, const void* dout, const float* lse, float* ndelta, float* nlse,
                                  float scale, int64_t n_rows, int d, hipStream_t stream);
 hipError_t launch_zero_f32(float* dst, int64_t n, hipStream_t stream);   // n a multiple of 4, dst 16-byte aligned
-// Implemented in attn_bwd_fp32.hip (all tensors fp32; dq_acc is dq itself).
-hipError_t launch_bwd_dq_fp32(const BwdLaunch& p, int d, hipStream_t stream);
-hipError_t launch_bwd_dkv_fp32(const BwdLaunch& p, int d, hipStream_t stream);
+// Implemented in attn_bwd_fp32.hip (all tensors fp32; dq_acc is dq itself): the dq and the dk/dv
+// workgroups of a launch, in one grid where both are asked for.
+hipError_t launch_bwd_fp32(const BwdLaunch& p, int d, bool dq, bool dkv, hipStream_t stream);
+// dst = sum over i < n of the n_elems floats at parts + i stride, in order
+hipError_t launch_bwd_sum_f32(const float* parts, int64_t stride, int n, float* dst, int64_t n_elems, hipStream_t stream);
 hipError_t launch_bwd_delta_fp32(const void* out, const void* dout, float* delta, int64_t n_rows, int d,
                                  hipStream_t stream);
 

@@ -2,11 +2,12 @@
 joined in one launch) against the oracle, at the sizes where tiles, shares and segment lists end."""
 import ctypes as C
 
+import numpy as np
 import pytest
 import torch
 
 from paper_2509_26541_amd import workloads as wl
-from tests.helpers import max_abs, oracle_rows
+from tests.helpers import max_abs, oracle_grads, oracle_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -56,3 +57,37 @@ def test_short_calls_all_rows(tb, case):
             torch.cuda.synchronize()
             eo, el = max_abs(out.float().cpu().numpy(), ref_o), max_abs(lse.cpu().numpy(), ref_l)
             assert eo <= tol_o and el <= tol_l, (name, fuse, nbytes, eo, el)
+
+
+BWD_FP32 = [
+    # name, N, rank, S, Hq, Hkv, d, mask
+    ("one_row_g3", 4, 3, 4, 3, 1, 128, wl.FULL),
+    ("tile_minus_1", 4, 1, 4 * 63, 1, 1, 128, wl.FULL),
+    ("tile", 8, 2, 16 * 64, 2, 2, 64, wl.ZIGZAG_CAUSAL),
+    ("tile_plus_1_g5", 8, 7, 16 * 13, 5, 1, 128, wl.ZIGZAG_CAUSAL),          # 13 x 5 = 65 pairs
+    ("shares", 12, 4, 24 * 101, 6, 3, 64, wl.ZIGZAG_CAUSAL),                 # keys no multiple of anything
+    ("not_joined", 4, 0, 8 * 2056, 1, 1, 64, wl.ZIGZAG_CAUSAL),              # 4 112 local rows: step by step
+]
+
+
+@pytest.mark.parametrize("case", BWD_FP32, ids=[c[0] for c in BWD_FP32])
+def test_fp32_backward_every_element(tb, case):
+    name, n, rank, S, Hq, Hkv, d, mode = case
+    w = wl.Workload(name, n, rank, S, Hq, Hkv, d, "fp32", mode, seed=wl.BASE_SEED + 8500 + S)
+    q, k, v = wl.make_qkv(w)
+    do = wl.make_dout(w)
+    s = tb.tasp_schedule(n, rank)
+    qd, kd, vd, dod = q.cuda(), k.cuda(), v.cuda(), do.cuda()
+    out, lse = tb.tasp_chunk_attn(qd, kd, vd, s, mode)
+    ref = oracle_grads(w, q, k, v, do)
+    plan = tb.ChunkAttnBwdPlan(s, qd, kd, vd, out, lse, dod, mode)
+    least = tb.lib.tasp_chunk_attn_bwd_workspace_bytes(s.handle, C.byref(plan.args))
+    for nbytes in {plan.args.workspace_bytes, least}:
+        plan.args.workspace_bytes = nbytes
+        for t in (plan.dq, plan.dk, plan.dv):
+            t.fill_(float("nan"))
+        got = plan.run()
+        torch.cuda.synchronize()
+        for nm, g, r in zip(("dq", "dk", "dv"), got, ref):
+            err = float(np.abs(g.cpu().numpy().astype(np.float64) - r).max())
+            assert err <= 1e-4 * max(1.0, float(np.abs(r).max())), (name, nm, nbytes, err)
