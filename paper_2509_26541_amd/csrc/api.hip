@@ -76,6 +76,7 @@ int build_step(const tasp_schedule_t* s, const tasp_attn_args* a, int step, Attn
   lp->causal = a->mask_mode == TASP_MASK_ZIGZAG_CAUSAL ? 1 : 0;
   lp->scale = a->softmax_scale > 0.f ? a->softmax_scale : 1.0f / std::sqrt(static_cast<float>(a->d));
   const int64_t L = a->S / s->n;
+  lp->last_key = static_cast<int32_t>(a->S - 1);
   lp->batch = batch_of(a);
   lp->q_bstride = L * a->Hq * a->d;
   lp->kv_bstride = a->S * a->Hkv * a->d;
@@ -192,9 +193,60 @@ struct FwdPlan {
 // the tail of its last workgroups; with L = S / N rows a query tile walks at most L keys a step, and
 // up to here those costs are a fifth of the call and more.  The results differ in rounding only.
 constexpr int64_t kJoinRows = 4096;
-// Workgroups of attn_tile_kernel that keep the chip busy (two per CU), and the fewest keys worth one.
+// Workgroups of attn_tile_kernel that keep the chip busy (two per CU), and the most shares of one tile.
 constexpr int64_t kTileTarget = 512;
 constexpr int64_t kMaxSplit = 32;
+
+// A batch of a few sequences is run like one of them, so that its results are those of separate calls.
+int64_t plan_batch(const AttnLaunch& lp) { return lp.batch <= 4 ? 1 : lp.batch; }
+
+// Deals the keys of the query tiles of attn_tile_kernel so that about kTileTarget workgroups come
+// together, none with fewer than `least` keys; keys[t] = keys the last row of task t sees.
+void deal_keys(const AttnLaunch& lp, const int64_t* keys, int64_t least, int64_t most, int32_t* n_split) {
+  const int64_t G = lp.Hq / lp.Hkv;
+  int64_t work = 0;
+  for (int t = 0; t < lp.n_tasks; ++t)
+    work += (lp.task[t].n_q * G + tasp::kTileRows - 1) / tasp::kTileRows * lp.Hkv * plan_batch(lp) * keys[t];
+  const int64_t per_wg = std::max(least, (work + kTileTarget - 1) / kTileTarget);
+  for (int t = 0; t < lp.n_tasks; ++t)
+    n_split[t] = static_cast<int32_t>(std::max<int64_t>(1, std::min((keys[t] + per_wg - 1) / per_wg, most)));
+}
+
+// Whether attn_tile_kernel is the faster one for a bf16 launch.  Both kernels' durations are estimated in
+// (row, key) pairs a CU walks: the work of all workgroups over the 256 CUs, and not less than what
+// the CUs with the most heavy workgroups have.  A workgroup's set-up, first fetches and epilogue count
+// as that many keys more.  The large kernel pads query blocks to 256 rows (d = 64: 384 where that fills
+// as well), the small one computes only the strips of 32 that have rows, walks a key in 1.14 of the
+// time, and a lone workgroup of it uses about half a CU.  Over 110 shapes (3K to 32K tokens, both d,
+// 200 to 4000 workgroups) the choice costs 0.3 % on average against always taking the faster kernel.
+bool tile_is_faster(const AttnLaunch& lp, int d, const int64_t* keys, const int32_t* n_split) {
+  constexpr double kCus = 256.0;
+  const double B = static_cast<double>(plan_batch(lp)), G = lp.Hq / lp.Hkv;
+  auto padded = [](double x, double m) { return std::ceil(x / m) * m; };
+  double rows8 = 0, rows12 = 0;
+  for (int t = 0; t < lp.n_tasks; ++t) { rows8 += padded(lp.task[t].n_q, 256); rows12 += padded(lp.task[t].n_q, 384); }
+  const double bm = d == 64 && rows12 * 100 <= rows8 * 101 ? 384 : 256, fixed = bm == 384 ? 400 : 900;
+  double big = 0, tile = 0, big_one[tasp::kMaxTasks] = {}, tile_one[tasp::kMaxTasks] = {}, big_n[tasp::kMaxTasks] = {}, tile_n[tasp::kMaxTasks] = {};
+  bool split = false;
+  for (int t = 0; t < lp.n_tasks; ++t) {
+    const double n = lp.task[t].n_q, k = static_cast<double>(keys[t]), ns = n_split[t];
+    big_one[t] = bm * (k + fixed);
+    big_n[t] = padded(n, bm) / bm * lp.Hq * B;
+    big += big_one[t] * big_n[t];
+    tile_one[t] = tasp::kTileRows * (1.14 * k / ns + 300);
+    tile_n[t] = padded(n * G, tasp::kTileRows) / tasp::kTileRows * lp.Hkv * B * ns;
+    tile += tile_one[t] * padded(n * G, 32) / tasp::kTileRows * lp.Hkv * B * ns;
+    split |= ns > 1;
+  }
+  auto duration = [&](double total, const double* one, const double* n, double alone) {
+    const double longest = std::max(one[0], one[1]);
+    double heavy = 0;
+    for (int t = 0; t < lp.n_tasks; ++t) heavy += one[t] > 0.7 * longest ? n[t] : 0;
+    return std::max(total / kCus, longest * std::max(alone, std::ceil(heavy / kCus)));
+  };
+  const double sum_shares = split ? 60000 : 0;      // the launch that adds the shares up
+  return duration(tile, tile_one, tile_n, 1.8) + sum_shares < duration(big, big_one, big_n, 1.0);
+}
 
 // Decides from shapes alone (`js` holds the joined lists), within `ws_bytes` of workspace.
 FwdPlan plan_forward(const tasp_attn_args* a, const Shape& sh, const JoinedSteps& js, size_t ws_bytes) {
@@ -203,26 +255,15 @@ FwdPlan plan_forward(const tasp_attn_args* a, const Shape& sh, const JoinedSteps
   pl.joined = true;
   if (js.segments() > static_cast<size_t>(tasp::kPoolSeg)) pl.table_bytes = kFusedTableBytes;
   if (pl.table_bytes > ws_bytes) { pl.joined = false; return pl; }
-  // A batch of a few sequences is split like one of them, so that its results are those of separate calls.
-  const int64_t B = sh.B <= 4 ? 1 : sh.B;
-  const int64_t G = a->Hq / a->Hkv;
-  int64_t big = 0, work = 0;          // workgroups of the large kernel; keys walked by all query tiles here
-  for (int t = 0; t < js.all.n_tasks; ++t) {
-    const int64_t tiles = (js.all.task[t].n_q * G + tasp::kTileRows - 1) / tasp::kTileRows * a->Hkv * B;
-    big += static_cast<int64_t>((js.all.task[t].n_q + 255) / 256) * a->Hq * B;
-    work += tiles * js.keys[t];
-  }
-  pl.tile = fp32 || big < 192;
-  if (!pl.tile) return pl;
-  const int64_t least = fp32 ? 64 : 128;
-  const int64_t per_wg = std::max(least, (work + kTileTarget - 1) / kTileTarget);
   const size_t pair = align_up(sh.o_bytes) + align_up(sh.lse_bytes);
-  const int64_t room = pair > 0 ? static_cast<int64_t>((ws_bytes - pl.table_bytes) / pair) : 1;
+  const int64_t room = static_cast<int64_t>((ws_bytes - pl.table_bytes) / pair);
+  int32_t n_split[tasp::kMaxTasks] = {1, 1};
+  deal_keys(js.all, js.keys, fp32 ? 64 : 128, std::min(room, kMaxSplit), n_split);
+  pl.tile = fp32 || tile_is_faster(js.all, a->d, js.keys, n_split);
+  if (!pl.tile) return pl;
   for (int t = 0; t < js.all.n_tasks; ++t) {
-    int64_t n = (js.keys[t] + per_wg - 1) / per_wg;
-    n = std::min(std::min(n, kMaxSplit), room);
-    pl.n_split[t] = static_cast<int32_t>(std::max<int64_t>(n, 1));
-    pl.parts = std::max(pl.parts, pl.n_split[t]);
+    pl.n_split[t] = n_split[t];
+    pl.parts = std::max(pl.parts, n_split[t]);
   }
   return pl;
 }
@@ -259,10 +300,22 @@ struct Scope {
   ~Scope() { if (p) p->end(); }
 };
 
-hipError_t launch_attn(const AttnLaunch& lp, const tasp_attn_args* a, hipStream_t stream, bool tile = false) {
+hipError_t launch_attn(const AttnLaunch& lp, const tasp_attn_args* a, hipStream_t stream, bool tile) {
+  return tile ? tasp::launch_attn_tile(lp, a->d, a->dtype == TASP_DTYPE_FP32, stream) : tasp::launch_attn_bf16(lp, a->d, stream);
+}
+
+// The launch of one step.  With more local rows than kJoinRows the large kernel is within 5 % of the
+// faster one wherever it is not that itself.
+hipError_t launch_step(const AttnLaunch& lp, const tasp_attn_args* a, hipStream_t stream) {
   if (lp.n_tasks == 0) return hipSuccess;
-  return a->dtype == TASP_DTYPE_BF16 && !tile ? tasp::launch_attn_bf16(lp, a->d, stream)
-                                              : tasp::launch_attn_tile(lp, a->d, a->dtype == TASP_DTYPE_FP32, stream);
+  int64_t keys[tasp::kMaxTasks] = {0, 0}, rows = 0;
+  for (int t = 0; t < lp.n_tasks; ++t) rows += lp.task[t].n_q;
+  for (int t = 0; t < lp.n_tasks; ++t)
+    for (int i = 0; i < lp.task[t].n_seg; ++i) {
+      const int32_t* g = lp.pool + 2 * (lp.task[t].seg0 + i);
+      keys[t] += g[1] - g[0];
+    }
+  return launch_attn(lp, a, stream, a->dtype == TASP_DTYPE_FP32 || (rows <= kJoinRows && tile_is_faster(lp, a->d, keys, lp.n_split)));
 }
 
 // ---- backward pass
@@ -424,7 +477,7 @@ int tasp_step_attn(const tasp_schedule_t* s, const tasp_attn_args* a, int32_t st
     st = build_step(s, a, step, &lp, &empty);
     if (st != TASP_OK) return st;
     lp.o_dst = o_part; lp.lse_dst = lse_part; lp.merge = 0;
-    if (launch_attn(lp, a, stream) != hipSuccess) return TASP_EHIP;
+    if (launch_step(lp, a, stream) != hipSuccess) return TASP_EHIP;
     for (const auto& blk : empty)
       if (tasp::launch_fill_empty(o_part, lse_part, blk.local_row0, blk.rows, a->Hq, a->d, sh.B, sh.L, stream) !=
           hipSuccess)
@@ -502,7 +555,7 @@ static int run_chunk_attn(const tasp_schedule_t* s, const tasp_attn_args* a, voi
         lp.o_dst = o_run; lp.lse_dst = a->lse; lp.merge = 0;
         {
           Scope sc(prof, Profiler::kAttn);
-          if (launch_attn(lp, a, stream) != hipSuccess) return TASP_EHIP;
+          if (launch_step(lp, a, stream) != hipSuccess) return TASP_EHIP;
         }
         for (const auto& blk : empty)      // cannot happen with the placements of Sec. 3.2.3; kept for safety
           if (tasp::launch_fill_empty(o_run, a->lse, blk.local_row0, blk.rows, a->Hq, a->d, sh.B, sh.L, stream) !=
@@ -511,12 +564,12 @@ static int run_chunk_attn(const tasp_schedule_t* s, const tasp_attn_args* a, voi
       } else if (a->fuse_merge) {
         lp.o_dst = o_run; lp.lse_dst = a->lse; lp.merge = 1;
         Scope sc(prof, Profiler::kAttn);
-        if (launch_attn(lp, a, stream) != hipSuccess) return TASP_EHIP;
+        if (launch_step(lp, a, stream) != hipSuccess) return TASP_EHIP;
       } else {
         lp.o_dst = o_part; lp.lse_dst = lse_part; lp.merge = 0;
         {
           Scope sc(prof, Profiler::kAttn);
-          if (launch_attn(lp, a, stream) != hipSuccess) return TASP_EHIP;
+          if (launch_step(lp, a, stream) != hipSuccess) return TASP_EHIP;
         }
         // rows that saw no key at this step have nothing to fold in
         for (int t = 0; t < lp.n_tasks; ++t) {

@@ -61,7 +61,7 @@ struct Cfg {
   static constexpr int NTHREADS = 64 * NWAVES;
   static constexpr int BM = 32 * NS * NWAVES;         // query rows per workgroup (256)
   static constexpr int UNITS = D / 8;                 // 16-byte units per row
-  static constexpr int RPP = NTHREADS / UNITS < BN ? NTHREADS / UNITS : BN;   // rows filled per pass
+  static constexpr int RPP = NTHREADS / UNITS >= BN ? BN : (NTHREADS / UNITS >= 32 ? 32 : 16);   // rows filled per pass
   static constexpr int LOADERS = RPP * UNITS;         // threads that fetch tiles (the first LOADERS / 64 wavefronts)
   static constexpr int PASSES = BN / RPP;
   static constexpr int ROWS_PER_LINE = 16 / UNITS;    // rows per 256-byte bank line (1 or 2)
@@ -180,10 +180,11 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void attn_bf16_kernel(const AttnLa
   // holds the first position of the query tile and is split in two; hence kMaxSegAll + 2 entries.
   __shared__ int e_vbeg[kMaxSegAll + 2];   // start in the virtual concatenation
   __shared__ int e_goff[kMaxSegAll + 2];   //   global position minus virtual position
-  __shared__ int e_diag[kMaxSegAll + 2];   //   straddles the diagonal of this query tile
   __shared__ int e_n;
-  __shared__ int m_lo[kMaxSegAll + 2];     // runs of tiles that need the element-wise mask (sorted, the
-  __shared__ int m_hi[kMaxSegAll + 2];     //   last run is open-ended: m_hi = INT_MAX)
+  // Runs of tiles that need the element-wise mask (sorted, the last run is open-ended: m_hi = INT_MAX).
+  // A diagonal part holds at least one of the tile's own positions.
+  constexpr int MAX_RUNS = (kMaxSegAll < BM ? kMaxSegAll : BM) + 2;
+  __shared__ int m_lo[MAX_RUNS], m_hi[MAX_RUNS];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -204,7 +205,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void attn_bf16_kernel(const AttnLa
   // saves the 4 us a CU idles between two workgroups.  The outer loop costs registers, so this pays
   // only where there are registers to spare and the items are short: d = 64, all steps in one launch.
   for (int round = 0; PERSIST || round == 0; ++round) {
-  const int w_all = PERSIST ? persistent_item(blockIdx.x, gridDim.x, p.n_items, round) : xcd_balanced(blockIdx.x, p.batch * p.Hkv, per_g);
+  const int w_all = PERSIST ? persistent_item(blockIdx.x, gridDim.x, p.n_items, round) : xcd_balanced(blockIdx.x, p.batch * p.Hkv, per_g, xcd_window(32, per_g));
   if (w_all < 0) break;
   const int bi = w_all / per_b;
   const int w = w_all - bi * per_b;
@@ -279,9 +280,9 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void attn_bf16_kernel(const AttnLa
       }
       int idx = n_base + sc - cnt, vpos = v_base + sl - len;
       const int didx = d_base + sd - dg;
-      if (len_f > 0) { e_vbeg[idx] = vpos; e_goff[idx] = a - vpos; e_diag[idx] = 0; ++idx; vpos += len_f; }
+      if (len_f > 0) { e_vbeg[idx] = vpos; e_goff[idx] = a - vpos; ++idx; vpos += len_f; }
       if (len_d > 0) {
-        e_vbeg[idx] = vpos; e_goff[idx] = start_d - vpos; e_diag[idx] = 1;
+        e_vbeg[idx] = vpos; e_goff[idx] = start_d - vpos;
         m_lo[didx] = vpos / BN; m_hi[didx] = (vpos + len_d - 1) / BN;
       }
       n_base += __shfl(sc, 63); v_base += __shfl(sl, 63); d_base += __shfl(sd, 63);
@@ -331,6 +332,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void attn_bf16_kernel(const AttnLa
   // lane searches the segment list for its own row and gets an offset of its own (base offset 0).
   // A vector instruction costs the SIMD's issue port as much as a third of a matrix instruction,
   // and the port is what bounds this kernel.
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   constexpr int RW = 64 / C::UNITS;
   const int r_lane = lane / C::UNITS;
   const unsigned k_col = C::swz_k(fr, fu) * 16, v_col = C::swz_v(fr, fu) * 16;    // byte column this lane reads
@@ -351,7 +353,11 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void attn_bf16_kernel(const AttnLa
   int hist = 0, slow_below = RW;
   // every lane finds its own row of tile t (pass i); the wavefront's state is taken from its first lane
   auto locate_slow = [&](int i, int t) __attribute__((always_inline)) {
-    const int v = t * BN + fr + C::RPP * i;
+    // (the row number is formed anew: the twelve-wavefront kernel has no register to keep it in)
+    int zero = 0;
+    asm volatile("" : "+v"(zero));
+    const int lane_now = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+    const int v = t * BN + wave_u * RW + lane_now / C::UNITS + C::RPP * i;
     int j = w_seg[i], left;                                   // rows only move forward
     while (j < n_eff && v >= e_vbeg[j + 1]) ++j;
     if (j < n_eff) { tokk[i] = v + e_goff[j]; left = e_vbeg[j + 1] - v; }
@@ -401,7 +407,6 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void attn_bf16_kernel(const AttnLa
   // A wavefront's 64 lanes fill 1 KiB of consecutive LDS; the XOR swizzle of the tile layout is
   // applied on the source side: the lane that owns LDS slot (row, unit) reads the 16 bytes of column
   // swz(row, unit) of that row.
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   // wavefront-uniform, and known at compile time when every wavefront fetches (a branch costs a
   // wavefront 20-40 cycles even when it is not taken)
   const bool is_loader = C::LOADERS == C::NTHREADS || wave_u < C::LOADERS / 64;

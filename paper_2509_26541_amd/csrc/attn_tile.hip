@@ -16,11 +16,15 @@
 // direct global->LDS loads into two stages.
 //
 // What bounds it: fp32 the matrix pipe (a fp32 matrix instruction holds it for 64 cycles, which
-// leaves room for everything else a SIMD has to issue); short bf16 calls the launch, the set-up and
-// the latency of the first tiles.  Measured, whole calls: fp32, 16 heads of 128, 2 048 of 16 384 tokens,
-// causal, 1.20 ms (114 TFLOP/s of the 152 a large fp32 product reaches) against 20.1 ms with a
-// wavefront per query row; fp32, 4 heads of 64, 256 of 1 024 tokens, 20 us against 309; bf16, 8 heads
-// of 128, 512 of 4 096 tokens, 36 us against 117 with the large kernel on 16 CUs.
+// leaves room for everything else a SIMD has to issue); bf16 the issue slots (1 330 of the 1 450 cycles
+// a SIMD takes for 32 rows by 64 keys at d = 64), and in the shortest calls the launch, the set-up and
+// the latency of the first tiles.  Measured, whole calls:
+//   fp32, 16 heads of 128, 2 048 of 16 384 tokens, causal: 1.16 ms (118 TFLOP/s of the 152 a large fp32
+//     product reaches) against 20.1 ms with a wavefront per query row;
+//   fp32, 4 heads of 64, 256 of 1 024 tokens: 20 us against 309;
+//   bf16, 8 heads of 128, 512 of 4 096 tokens: 35 us against 117 with the large kernel on 16 CUs;
+//   bf16, 128 sequences of 3 072 tokens, 20 heads of 64: 0.73 ms against 0.91 with the large kernel,
+//     which pads 192 rows to 256 and searches for the rows of 27-token sub-chunks in every tile.
 #include <hip/hip_runtime.h>
 
 #include <climits>
@@ -37,6 +41,7 @@ constexpr float kRescaleGap = 8.0f;      // the running max is only raised when 
 constexpr float kNegBig = -1.0e30f;
 constexpr int BM = kTileRows;            // rows per workgroup: four wavefronts of 32
 constexpr int NTHREADS = 256;
+constexpr int CHUNK = 512;               // keys located at a time
 
 template <typename T, int D>
 struct TCfg {
@@ -77,7 +82,7 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
   constexpr bool F32 = C::F32;
   constexpr int BT = C::BT, NKB = C::NKB, NDB = C::NDB, NJ = C::UNITS / 2;
   __shared__ __attribute__((aligned(16))) unsigned char smem[2 * C::STAGE_BYTES];
-  __shared__ __attribute__((aligned(16))) int s_tok[2][BT];   // global position of every key row (INT_MAX: none)
+  __shared__ __attribute__((aligned(16))) int s_tok[2 * CHUNK];   // global positions of the keys (INT_MAX: none)
   __shared__ __attribute__((aligned(16))) int s_msk[2][4];    // per wavefront: it fetched a key some row of the tile must not see
   // Effective segments of this workgroup's share of the keys.
   __shared__ int e_vbeg[kMaxSegAll + 1];   // start in the share
@@ -91,7 +96,7 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
   const int m0 = p.task[0].n_q * G, m1 = p.n_tasks > 1 ? p.task[1].n_q * G : 0;
   const int tiles0 = (m0 + BM - 1) / BM, tiles1 = (m1 + BM - 1) / BM;
   const int items0 = tiles0 * p.n_split[0], per_g = items0 + tiles1 * p.n_split[1];
-  const int w_all = xcd_balanced(blockIdx.x, p.batch * p.Hkv, per_g);
+  const int w_all = xcd_balanced(blockIdx.x, p.batch * p.Hkv, per_g, xcd_window(D == 64 ? 96 : 64, per_g));
   if (w_all < 0) return;
   const int bg = w_all / per_g;
   int rem = w_all - bg * per_g;
@@ -104,7 +109,10 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
   const int tile = p.causal ? (tsk ? tiles1 : tiles0) - 1 - rem / ns : rem / ns;
   const AttnTask& T_ = p.task[tsk];
   const int m_all = tsk ? m1 : m0;
-  const int m = tile * BM + wave * 32 + lq;                  // row of the tile: (local row, head of the group)
+  // The strip of 32 rows a wavefront takes moves with the work item: wavefront i of a workgroup runs on
+  // SIMD i, and tiles with few rows left leave strips without work.
+  const int strip = (wave + w_all) & 3;
+  const int m = tile * BM + strip * 32 + lq;                 // row of the tile: (local row, head of the group)
   const bool q_valid = m < m_all;
   const int mc = q_valid ? m : m_all - 1;
   const int row = mc / G, hq = g * G + mc - row * G;
@@ -171,34 +179,49 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
   const int n_eff = e_n, n_keys = e_vbeg[n_eff];
   const int n_tiles = (n_keys + BT - 1) / BT;
 
+  // ---- positions of the keys, looked up for CHUNK of them at a time: chunk c in half c % 2 of s_tok.
+  // With sub-chunks of a few dozen keys most tiles cross a segment boundary; a search per tile and
+  // row cost more than the tile's exponentials.
+  auto locate = [&](int chunk) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < CHUNK / NTHREADS; ++i) {
+      const int v = chunk * CHUNK + i * NTHREADS + tid;
+      int lo = 0, n = n_eff;                                        // the last segment that begins at or before v
+      while (n > 1) {
+        const int half = n >> 1;
+        if (e_vbeg[lo + half] <= v) lo += half;
+        n -= half;
+      }
+      s_tok[(chunk & 1) * CHUNK + i * NTHREADS + tid] = v < n_keys ? v + e_goff[lo] : INT_MAX;
+    }
+  };
+
   // ---- loader: this thread fills rows fr + RPP i, physical unit fu of the K and the V tile
   const int fr = tid / C::UNITS, fu = tid % C::UNITS;
-  const int64_t row_bytes = static_cast<int64_t>(p.Hkv) * C::RB;
+  const unsigned row_bytes = static_cast<unsigned>(p.Hkv) * C::RB;
   const int64_t head0 = (bi * p.kv_bstride + static_cast<int64_t>(g) * D) * static_cast<int64_t>(sizeof(T));
   const unsigned char* Kg = static_cast<const unsigned char*>(p.k) + head0;
   const unsigned char* Vg = static_cast<const unsigned char*>(p.v) + head0;
+  const u32x4 k_buf = raw_buffer(Kg), v_buf = raw_buffer(Vg);
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  int seg_j[C::PASSES], seg_end[C::PASSES], seg_off[C::PASSES];     // the segment the thread's row of the pass was in last
-#pragma unroll
-  for (int i = 0; i < C::PASSES; ++i) { seg_j[i] = -1; seg_end[i] = 0; seg_off[i] = 0; }
   auto fetch = [&](int t, int stage) __attribute__((always_inline)) {
     unsigned char* dst = smem + stage * C::STAGE_BYTES + wave_u * 1024;
     bool hidden = false;
 #pragma unroll
     for (int i = 0; i < C::PASSES; ++i) {
-      const int r = fr + C::RPP * i, v = t * BT + r;
-      if (v >= seg_end[i]) {                                        // rows only move forward
-        int j = seg_j[i];
-        while (j < n_eff && v >= seg_end[i]) { ++j; seg_end[i] = j < n_eff ? e_vbeg[j + 1] : INT_MAX; }
-        seg_j[i] = j;
-        seg_off[i] = j < n_eff ? e_goff[j] : 0;
-      }
-      const int tok = seg_j[i] < n_eff ? v + seg_off[i] : INT_MAX;
+      const int r = fr + C::RPP * i;
+      const int tok = s_tok[(t * BT + r) & (2 * CHUNK - 1)];
       hidden |= tok > q_first;
-      if (fu == 0) s_tok[stage][r] = tok;
-      const int64_t src = (tok == INT_MAX ? 0 : tok) * row_bytes;   // rows past the end fetch key 0 and are masked
-      global_to_lds_16_far(Kg + src + C::swz_k(r, fu) * 16, dst + i * NTHREADS * 16);
-      global_to_lds_16_far(Vg + src + C::swz_v(r, fu) * 16, dst + C::TILE_BYTES + i * NTHREADS * 16);
+      const unsigned key = static_cast<unsigned>(min(tok, p.last_key));   // rows past the end fetch some key and are masked
+      if constexpr (F32) {                                          // tensors may exceed what a 32-bit offset reaches
+        const unsigned long long off = static_cast<unsigned long long>(key) * row_bytes;
+        global_to_lds_16_far(Kg + off + C::swz_k(r, fu) * 16, dst + i * NTHREADS * 16);
+        global_to_lds_16_far(Vg + off + C::swz_v(r, fu) * 16, dst + C::TILE_BYTES + i * NTHREADS * 16);
+      } else {                                                      // both factors are below 2^24 (host check)
+        const unsigned off = __umul24(key, row_bytes);
+        buffer_to_lds_16<true>(k_buf, 0u, off + C::swz_k(r, fu) * 16, dst + i * NTHREADS * 16);
+        buffer_to_lds_16<true>(v_buf, 0u, off + C::swz_v(r, fu) * 16, dst + C::TILE_BYTES + i * NTHREADS * 16);
+      }
     }
     const bool any = __builtin_amdgcn_ballot_w64(hidden) != 0;
     if (lane == 0) s_msk[stage][wave] = any ? 1 : 0;
@@ -226,7 +249,12 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
   float m_run = kNegBig, l_run = 0.f, l_lo = 0.f, r_fix = 0.f;
   const float c = p.scale * kLog2e;
 
-  if (n_tiles > 0) fetch(0, 0);
+  const bool idle = __builtin_amdgcn_readfirstlane(tile * BM + strip * 32) >= m_all;
+  if (n_tiles > 0) {
+    locate(0);
+    __syncthreads();
+    fetch(0, 0);
+  }
 #pragma unroll
   for (int j = 0; j < NJ; ++j) asm volatile("" : "+v"(qf[j]));      // landed before the loop: its only wait on vector memory is the one on the tile
   for (int t = 0; t < n_tiles; ++t) {
@@ -234,6 +262,9 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();                 // tile t is complete; nobody reads the other stage any more
     if (t + 1 < n_tiles) fetch(t + 1, stage ^ 1);
+    // two tiles before a chunk of keys begins: the half of the table it goes to has been left behind
+    if ((t + 2) % (CHUNK / BT) == 0 && t + 2 < n_tiles) locate((t + 2) / (CHUNK / BT));
+    if (idle) continue;
     const unsigned char* st = smem + stage * C::STAGE_BYTES;
 
     f32x16 S[NKB];
@@ -258,7 +289,7 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
       for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
         for (int i4 = 0; i4 < 4; ++i4) {
-          const i32x4 tk = *reinterpret_cast<const i32x4*>(&s_tok[stage][32 * kb + 8 * i4 + 4 * h]);
+          const i32x4 tk = *reinterpret_cast<const i32x4*>(&s_tok[((t * BT) & (2 * CHUNK - 1)) + 32 * kb + 8 * i4 + 4 * h]);
 #pragma unroll
           for (int e = 0; e < 4; ++e)
             if (tk[e] > q_pos) S[kb][4 * i4 + e] = -__builtin_inff();

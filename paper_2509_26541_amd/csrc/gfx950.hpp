@@ -104,12 +104,20 @@ __device__ inline int xcd_contiguous(int block, int nblocks) {
 // them gets the same mix and still meets each unit's items by falling work.  With units a multiple
 // of 8 this is xcd_contiguous.  The grid has xcd_balanced_blocks workgroups; -1 = none for this one.
 __host__ __device__ inline int xcd_balanced_share(int units) { const int g = units & -units; return g >= 8 ? 1 : 8 / g; }
-__device__ inline int xcd_balanced(int block, int units, int per_unit) {
+// `window` units at a time are met by falling work across them, not one behind the other: with several
+// units to an XCD, the long items of its last unit would otherwise start when most others are done.
+// A window should hold about as many items as run on an XCD at once (xcd_window): the items of a unit
+// then still run together and share its K and V in L2.
+__host__ __device__ inline int xcd_window(int resident, int per_unit) { return per_unit >= resident ? 1 : (resident + per_unit - 1) / per_unit; }
+__device__ inline int xcd_balanced(int block, int units, int per_unit, int window = 1) {
   const int k = xcd_balanced_share(units);
   const int xcd = block & 7, slot = block >> 3;
-  const int len = units / (8 / k) * per_unit;          // items of a group of k XCDs
+  const int n = units / (8 / k), len = n * per_unit;   // units and items of a group of k XCDs
   const int j = slot * k + xcd % k;
-  return j < len ? xcd / k * len + j : -1;
+  if (j >= len) return -1;
+  const int w0 = j / (window * per_unit) * window, wn = n - w0 < window ? n - w0 : window;   // first unit and units of the window
+  const int jj = j - w0 * per_unit, item = jj / wn;
+  return xcd / k * len + (w0 + jj - item * wn) * per_unit + item;
 }
 __host__ inline long long xcd_balanced_blocks(long long units, long long per_unit) {
   const long long k = xcd_balanced_share(static_cast<int>(units));

@@ -37,6 +37,7 @@ struct AttnLaunch {
   int32_t causal;     // key t visible to query p iff t <= p
   int32_t merge;      // 0: dst = partial of this step; 1: dst = update_out_lse(dst, partial)
   float scale;        // softmax scale (natural units)
+  int32_t last_key;   // position of the last key of the sequence
   int32_t batch;      // independent sequences; element strides between them:
   int64_t q_bstride, kv_bstride, o_bstride, lse_bstride;
   int32_t n_tasks;
