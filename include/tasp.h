@@ -288,6 +288,8 @@ double tasp_chunk_attn_flops(const tasp_schedule_t* s, const tasp_attn_args* a);
  * (out and lse as written by tasp_chunk_attn on the same inputs).  dtype is TASP_DTYPE_BF16 (bf16
  * matrix instructions) or TASP_DTYPE_FP32 (fp32 matrix instructions, all arithmetic fp32; with L <= 4096
  * the steps are joined in one launch); d is 64 or 128.  Every row of dq, dk and dv is written.
+ * With few local rows (L <= 4096) the steps are joined, one dq and one dk/dv launch for all of them, as with
+ * fuse_steps but with the keys taken by position: over the steps every key is met once.
  * workspace: device, 256-byte aligned, at least tasp_chunk_attn_bwd_workspace_bytes() (the delta
  * vector; for bf16 also lse scaled to base 2 in the same layout, both with one more entry behind the
  * last row, which is why B*L*Hq must stay below 2^30 there (TASP_EUNSUPPORTED_SHAPE otherwise), an
@@ -295,6 +297,9 @@ double tasp_chunk_attn_flops(const tasp_schedule_t* s, const tasp_attn_args* a);
  * one step's keys per query head of a group, twice the size of that copy: a step's dk/dv launch with
  * few, unequal key tiles is cut into one workgroup per key tile and query head, and the partial sums
  * are added in the order of the heads, so results do not depend on timing); contents are scratch.
+ * With joined steps a larger workspace (tasp_chunk_attn_bwd_best_workspace_bytes) lets launches that
+ * would leave the chip idle be cut finer: the keys of a query tile dealt to several workgroups, and the
+ * query heads and tiles a key tile needs, again added up in a fixed order.
  * Kernels are enqueued on hip_stream; the call returns without synchronising.  Errors as for
  * tasp_chunk_attn.
  * ---------------------------------------------------------------------------------------------- */
@@ -329,8 +334,8 @@ typedef struct tasp_attn_bwd_args {
 } tasp_attn_bwd_args;
 
 size_t tasp_chunk_attn_bwd_workspace_bytes(const tasp_schedule_t* s, const tasp_attn_bwd_args* a);
-/* As tasp_chunk_attn_best_workspace_bytes: room to deal the keys of a query tile to several workgroups
- * (fp32; for bf16 the size above). */
+/* The workspace with which the call runs fastest, at most the one above or TASP_STATIC_SCRATCH_BYTES,
+ * whichever is larger. */
 size_t tasp_chunk_attn_bwd_best_workspace_bytes(const tasp_schedule_t* s, const tasp_attn_bwd_args* a);
 int    tasp_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args* a, void* hip_stream);
 

@@ -349,29 +349,78 @@ int validate_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args* b, tasp_att
   return TASP_OK;
 }
 
-// fp32 backward with joined steps: workgroups the keys of a query tile are dealt to, so that about 512
-// dq workgroups stand beside the dk/dv ones, each with four 64-key tiles or more; within the workspace.
-int bwd_fp32_split(const tasp_attn_bwd_args* b, const Shape& sh, size_t ws_bytes) {
-  if (sh.L > kJoinRows) return 1;
-  const int64_t G = b->Hq / b->Hkv, B = sh.B <= 4 ? 1 : sh.B;
-  const int blocks = tasp::n_query_blocks(b->mask_mode);
-  const int64_t tiles = blocks * ((sh.L / blocks * G + 63) / 64) * b->Hkv * B;
-  const size_t front = align_up(sh.lse_bytes);
-  const int64_t room = ws_bytes > front && sh.o_bytes > 0 ? static_cast<int64_t>((ws_bytes - front) / sh.o_bytes) : 0;
-  const int64_t n = std::min(std::min((512 + tiles - 1) / tiles, b->S / 256), std::min(room, kMaxSplit));
+// Whether the steps of a backward call run in one launch of each kind, and how finely these are cut.
+struct BwdPlan {
+  bool joined = false;
+  size_t table_bytes = 0;      // device memory for the segment lists of fuse_steps
+  int32_t n_split = 1;         // workgroups the keys of a query tile are dealt to; their dq sums follow the lists
+  int32_t kv_split = 0;        // BwdLaunch::kv_split; the partial dk and dv follow the dq sums
+  size_t kv_bytes = 0;         // of one of the two
+};
+
+// Workgroups the keys of a query tile of a backward call are dealt to, so that `target` dq workgroups or
+// more come together, none with fewer than four 64-key tiles; `tiles` = dq workgroups without that.
+int dq_split(int64_t tiles, int64_t target, int64_t S, int64_t room) {
+  const int64_t n = std::min(std::min((target + tiles - 1) / tiles, S / 256), std::min(room, kMaxSplit));
   return static_cast<int>(std::max<int64_t>(n, 1));
+}
+
+// Device memory the arrays in front of the lists and partial sums take: bf16 -delta and -lse / scale, fp32 delta.
+size_t bwd_front_bytes(const tasp_attn_bwd_args* b, const Shape& sh) {
+  return b->dtype == TASP_DTYPE_BF16 ? 2 * align_up(sh.lse_bytes + sizeof(float)) : align_up(sh.lse_bytes);
 }
 
 struct BwdSpans { enum Kind { kDq = 0, kDkv = 1, kOther = 2 }; };
 
+// Everything of a backward launch that follows from the shapes and the caller's tensors; `ranges` = the keys
+// of the launch.
+int fill_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args* b, const AttnLaunch& lp, std::vector<tasp::Segment>& ranges,
+             tasp::BwdLaunch* bp) {
+  bp->q = b->q; bp->k = b->k; bp->v = b->v; bp->dout = b->dout; bp->lse = b->lse;
+  bp->dk = b->dk; bp->dv = b->dv;
+  bp->Hq = lp.Hq; bp->Hkv = lp.Hkv; bp->causal = lp.causal; bp->scale = lp.scale; bp->batch = lp.batch;
+  bp->q_bstride = lp.q_bstride; bp->kv_bstride = lp.kv_bstride; bp->lse_bstride = lp.lse_bstride;
+  bp->n_tasks = lp.n_tasks;
+  for (int t = 0; t < lp.n_tasks; ++t) { bp->task[t] = lp.task[t]; bp->seg_ext[t] = lp.seg_ext[t]; }
+  std::copy(lp.pool, lp.pool + 2 * tasp::kPoolSeg, bp->pool);
+  bp->n_split = 1;
+  bp->n_blk = tasp::n_query_blocks(b->mask_mode);
+  for (int qb = 0; qb < bp->n_blk; ++qb) {
+    tasp::QueryBlock blk;
+    const int st = tasp::query_block(*s, b->S, b->mask_mode, qb, &blk);
+    if (st != TASP_OK) return st;
+    bp->blk[qb] = {static_cast<int32_t>(blk.local_row0), static_cast<int32_t>(blk.rows), static_cast<int32_t>(blk.pos0)};
+  }
+  // The dk/dv kernel treats every key on its own, so the order of the ranges is free: by
+  // position, which under the causal mask is by falling work (early keys are seen by more
+  // queries), so that the workgroups with the most work start first.  Neighbours are joined.
+  std::sort(ranges.begin(), ranges.end(),
+            [](const tasp::Segment& x, const tasp::Segment& y) { return x.start < y.start; });
+  size_t n = 0;
+  for (size_t i = 0; i < ranges.size(); ++i) {
+    if (n > 0 && ranges[n - 1].end == ranges[i].start) ranges[n - 1].end = ranges[i].end;
+    else ranges[n++] = ranges[i];
+  }
+  if (n > static_cast<size_t>(tasp::kMaxSeg)) return TASP_EUNSUPPORTED_SHAPE;
+  bp->n_rng = static_cast<int32_t>(n);
+  int64_t vpos = 0;
+  for (size_t i = 0; i < n; ++i) {
+    bp->rng_start[i] = static_cast<int32_t>(ranges[i].start);
+    bp->rng_vbeg[i] = static_cast<int32_t>(vpos);
+    vpos += ranges[i].end - ranges[i].start;
+  }
+  bp->rng_vbeg[n] = static_cast<int32_t>(vpos);
+  return TASP_OK;
+}
+
 // Estimated duration of a dk/dv launch, in 64-row query tiles of one head, with one workgroup per
-// key tile (`per_tile` = 1, each serving all G query heads of its group) or per key tile and query
-// head (`per_tile` = G).  Mirrors what the kernel and the hardware do: the work list is (sequence,
-// KV head, head, key tile) in that order, every XCD gets one contiguous eighth of it (exactly so when
+// key tile (`kv_split` = 0, each serving all G query heads of its group) or per key tile, query head and
+// share of the query tiles.  Mirrors what the kernel and the hardware do: the work list is (sequence,
+// KV head, head, share, key tile) in that order, every XCD gets one contiguous eighth of it (exactly so when
 // the KV heads of the call are a multiple of 8; otherwise XCDs share heads, which this estimate
 // ignores), and each of its slots/8 workgroup slots takes the next workgroup when it is free.  A workgroup walks, for
 // each query block, the tiles from the first one that holds a row at or after its first key.
-int64_t dkv_makespan(const tasp::BwdLaunch& bp, int d, int per_tile, int slots) {
+int64_t dkv_makespan(const tasp::BwdLaunch& bp, int d, int kv_split, int64_t batch, int slots) {
   const int bs = d == 128 ? 256 : 128, bt = 64;
   const int64_t total = bp.rng_vbeg[bp.n_rng];
   const int64_t ktiles = (total + bs - 1) / bs;
@@ -390,7 +439,7 @@ int64_t dkv_makespan(const tasp::BwdLaunch& bp, int d, int per_tile, int slots) 
     }
     work[static_cast<size_t>(t)] = static_cast<int32_t>(w);
   }
-  const int64_t n = ktiles * bp.Hkv * bp.batch * per_tile;
+  const int64_t n = ktiles * bp.Hkv * batch * (kv_split > 0 ? G * kv_split : 1);
   const int xcd_slots = std::max(1, slots / 8);
   constexpr int64_t kFixed = 4;      // set-up and epilogue of a workgroup, in the same unit
   int64_t makespan = 0;
@@ -401,7 +450,8 @@ int64_t dkv_makespan(const tasp::BwdLaunch& bp, int d, int per_tile, int slots) 
     heap.assign(static_cast<size_t>(xcd_slots), 0);
     for (int64_t i = start; i < start + cnt; ++i) {
       const int64_t tile = i % ktiles;
-      const int64_t w = kFixed + static_cast<int64_t>(work[static_cast<size_t>(tile)]) * (per_tile == 1 ? G : 1);
+      const int64_t all = work[static_cast<size_t>(tile)];
+      const int64_t w = kFixed + (kv_split > 0 ? (all + kv_split - 1) / kv_split : all * G);
       std::pop_heap(heap.begin(), heap.end(), std::greater<int64_t>());
       heap.back() += w;
       std::push_heap(heap.begin(), heap.end(), std::greater<int64_t>());
@@ -409,6 +459,64 @@ int64_t dkv_makespan(const tasp::BwdLaunch& bp, int d, int per_tile, int slots) 
     makespan = std::max(makespan, *std::max_element(heap.begin(), heap.end()));
   }
   return makespan;
+}
+
+// Fills in what depends on shapes alone; `bp` is the joined launch, `ws_bytes` the workspace.
+BwdPlan plan_backward(const tasp_attn_bwd_args* b, const Shape& sh, const tasp::BwdLaunch& bp, size_t table_bytes, size_t ws_bytes) {
+  BwdPlan pl;
+  pl.joined = true;
+  pl.table_bytes = table_bytes;
+  const bool fp32 = b->dtype == TASP_DTYPE_FP32;
+  const int64_t B = sh.B <= 4 ? 1 : sh.B;       // as plan_batch
+  const int64_t G = b->Hq / b->Hkv;
+  size_t used = bwd_front_bytes(b, sh) + table_bytes;
+  auto room = [&](size_t each) { return each > 0 && ws_bytes > used ? static_cast<int64_t>((ws_bytes - used) / each) : 0; };
+  // dk/dv: finer than by key tile where the estimate says that wins by more than 4 %, the launch that
+  // adds the partial sums up (about one tile's time) and their way through memory included
+  if (!fp32 && G > 1) {
+    const int slots = tasp::bwd_dkv_resident_workgroups(b->d);
+    const int64_t wgs = tasp::bwd_dkv_workgroups(bp, b->d) / sh.B * B;
+    const size_t one = align_up(static_cast<size_t>(sh.B) * b->S * b->Hq * b->d * sizeof(float));
+    int64_t best = 0;
+    if (wgs < 8 * static_cast<int64_t>(slots))
+      for (const int c : {0, 1, 2, 4}) {
+        if (c > 0 && room(2 * one * c) < 1) break;
+        const double bytes = 4.0 * static_cast<double>(one) / sh.B * B * c;   // written and read, dk and dv
+        const int64_t t = dkv_makespan(bp, b->d, c, B, slots) + (c > 0 ? 1 + static_cast<int64_t>(bytes / 1.5e7) : 0);
+        if (c == 0 || t * 104 < best * 100) { best = t; pl.kv_split = c; pl.kv_bytes = one * c; }
+      }
+    used += 2 * pl.kv_bytes;
+  }
+  int64_t tiles = 0;
+  for (int t = 0; t < bp.n_tasks; ++t)
+    tiles += fp32 ? (bp.task[t].n_q * G + 63) / 64 * b->Hkv * B : static_cast<int64_t>((bp.task[t].n_q + 127) / 128) * b->Hq * B;
+  pl.n_split = dq_split(tiles, 512, b->S, room(align_up(sh.o_bytes)));
+  return pl;
+}
+size_t plan_bytes(const BwdPlan& pl, const tasp_attn_bwd_args* b, const Shape& sh) {
+  return bwd_front_bytes(b, sh) + pl.table_bytes + (pl.n_split > 1 ? pl.n_split * align_up(sh.o_bytes) : 0) + 2 * pl.kv_bytes;
+}
+
+// The joined steps as one launch.  Without fuse_steps the key lists are one segment, the sequence: over
+// the steps every key is met once, and what a query row or a key gets from one pair does not depend on the
+// others.  With it the lists of the steps follow each other (js: to be placed by the caller).
+int build_bwd_joined(const tasp_schedule_t* s, const tasp_attn_bwd_args* b, const tasp_attn_args* a, tasp::BwdLaunch* bp, JoinedSteps* js) {
+  AttnLaunch lp{};
+  if (b->fuse_steps) {
+    const int st = join_steps(s, a, js);
+    if (st != TASP_OK) return st;
+    lp = js->all;
+  } else {
+    std::vector<tasp::QueryBlock> empty;
+    const int st = build_step(s, a, 0, &lp, &empty);        // every query block sees its own diagonal at step 0
+    if (st != TASP_OK) return st;
+    if (!empty.empty()) return TASP_EUNSUPPORTED_SHAPE;
+    lp.pool[0] = 0;
+    lp.pool[1] = static_cast<int32_t>(b->S);
+    for (int t = 0; t < lp.n_tasks; ++t) { lp.task[t].seg0 = 0; lp.task[t].n_seg = 1; }
+  }
+  std::vector<tasp::Segment> all(1, tasp::Segment{0, b->S, 0});
+  return fill_bwd(s, b, lp, all, bp);
 }
 
 }  // namespace
@@ -646,9 +754,17 @@ size_t tasp_chunk_attn_bwd_best_workspace_bytes(const tasp_schedule_t* s, const 
   const size_t need = tasp_chunk_attn_bwd_workspace_bytes(s, b);
   tasp_attn_args a;
   Shape sh;
-  if (validate_bwd(s, b, &a, &sh) != TASP_OK || b->dtype != TASP_DTYPE_FP32) return need;
-  const int n = bwd_fp32_split(b, sh, std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES));
-  return n > 1 ? std::max(need, align_up(sh.lse_bytes) + n * sh.o_bytes) : need;
+  if (validate_bwd(s, b, &a, &sh) != TASP_OK || !(b->fuse_steps || sh.L <= kJoinRows)) return need;
+  try {
+    tasp::BwdLaunch bp{};
+    JoinedSteps js{};
+    if (build_bwd_joined(s, b, &a, &bp, &js) != TASP_OK) return need;
+    const BwdPlan pl = plan_backward(b, sh, bp, js.segments() > static_cast<size_t>(tasp::kPoolSeg) ? kFusedTableBytes : 0,
+                                     std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES));
+    return std::max(need, plan_bytes(pl, b, sh));
+  } catch (...) {
+    return need;
+  }
 }
 
 double tasp_chunk_attn_bwd_flops(const tasp_schedule_t* s, const tasp_attn_bwd_args* b) {
@@ -676,18 +792,24 @@ static int run_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args
     ~Ev() { if (e) (void)hipEventDestroy(e); }
   } fork, join;
   const bool bf16 = b->dtype == TASP_DTYPE_BF16;
-  float* dq_acc = bf16 ? static_cast<float*>(b->workspace) : static_cast<float*>(b->dq);
-  float* delta = bf16 ? reinterpret_cast<float*>(static_cast<unsigned char*>(b->workspace) + align_up(sh.o_bytes))
-                      : static_cast<float*>(b->workspace);
   const int64_t n_q_elems = static_cast<int64_t>(sh.B) * sh.L * b->Hq * b->d;
   const int64_t n_rows = static_cast<int64_t>(sh.B) * sh.L * b->Hq;
   // the dk/dv kernel addresses delta and lse2 with 32-bit byte offsets
   if (bf16 && n_rows >= (int64_t{1} << 30)) return TASP_EUNSUPPORTED_SHAPE;
+  // Workspace: the row arrays (bwd_front_bytes), then with joined steps what BwdPlan says; step by step for
+  // bf16 the fp32 dq and the partial dk and dv of a split launch, room for L keys each.
   const size_t row_block = align_up(sh.lse_bytes + sizeof(float));
-  float* lse2 = bf16 ? reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(delta) + row_block) : nullptr;
-  unsigned char* after_rows = static_cast<unsigned char*>(b->workspace) + align_up(sh.o_bytes) + 2 * row_block;
-  // partial dk / dv of a dk/dv launch split by query head (see launch_unit): room for L keys a launch
-  float* part = (bf16 && !b->fuse_steps && b->Hq > b->Hkv) ? reinterpret_cast<float*>(after_rows) : nullptr;
+  unsigned char* ws = static_cast<unsigned char*>(b->workspace);
+  unsigned char* after_rows = ws + bwd_front_bytes(b, sh);
+  float* delta = reinterpret_cast<float*>(ws);
+  float* lse2 = bf16 ? reinterpret_cast<float*>(ws + row_block) : nullptr;
+  float* dq_acc = bf16 ? reinterpret_cast<float*>(after_rows) : static_cast<float*>(b->dq);
+  float* part = (bf16 && !b->fuse_steps && b->Hq > b->Hkv) ? reinterpret_cast<float*>(after_rows + align_up(sh.o_bytes)) : nullptr;
+  auto set_buffers = [&](tasp::BwdLaunch* bp) {
+    if (bf16) { bp->ndelta = delta; bp->nlse = lse2; } else { bp->delta = delta; }
+    bp->dq_acc = dq_acc;
+  };
+  const bool joined = b->fuse_steps || sh.L <= kJoinRows;
 
   try {
     {
@@ -696,7 +818,7 @@ static int run_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args
       if ((bf16 ? tasp::launch_bwd_delta_bf16(b->out, b->dout, b->lse, delta, lse2, scale, n_rows, b->d, stream)
                 : tasp::launch_bwd_delta_fp32(b->out, b->dout, delta, n_rows, b->d, stream)) != hipSuccess)
         return TASP_EHIP;
-      if (bf16 && tasp::launch_zero_f32(dq_acc, n_q_elems, stream) != hipSuccess) return TASP_EHIP;
+      if (bf16 && !joined && tasp::launch_zero_f32(dq_acc, n_q_elems, stream) != hipSuccess) return TASP_EHIP;
     }
     if (kv_stream != stream) {
       if (tasp::note_hip(hipEventCreateWithFlags(&fork.e, hipEventDisableTiming)) != hipSuccess ||
@@ -705,78 +827,14 @@ static int run_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args
           tasp::note_hip(hipStreamWaitEvent(kv_stream, fork.e, 0)) != hipSuccess)
         return TASP_EHIP;
     }
-    int n_split = 1;              // fp32: workgroups the keys of a query tile are dealt to
     bool first_unit = true;
-    // One unit = one dq launch and one dk/dv launch: a step, or all steps at once.
-    auto launch_unit = [&](const AttnLaunch& lp, std::vector<tasp::Segment>& ranges) -> int {
-      tasp::BwdLaunch bp{};
-      bp.q = b->q; bp.k = b->k; bp.v = b->v; bp.dout = b->dout; bp.lse = b->lse;
-      if (bf16) { bp.ndelta = delta; bp.nlse = lse2; } else { bp.delta = delta; }
-      bp.dq_acc = dq_acc; bp.dk = b->dk; bp.dv = b->dv;
-      bp.Hq = lp.Hq; bp.Hkv = lp.Hkv; bp.causal = lp.causal; bp.scale = lp.scale; bp.batch = lp.batch;
-      bp.q_bstride = lp.q_bstride; bp.kv_bstride = lp.kv_bstride; bp.lse_bstride = lp.lse_bstride;
-      bp.n_tasks = lp.n_tasks;
-      for (int t = 0; t < lp.n_tasks; ++t) { bp.task[t] = lp.task[t]; bp.seg_ext[t] = lp.seg_ext[t]; }
-      if (!lp.all_steps) std::copy(lp.pool, lp.pool + 2 * tasp::kMaxTasks * tasp::kMaxSeg, bp.pool);   // one step's lists
-      bp.n_blk = tasp::n_query_blocks(b->mask_mode);
-      for (int qb = 0; qb < bp.n_blk; ++qb) {
-        tasp::QueryBlock blk;
-        const int st2 = tasp::query_block(*s, b->S, b->mask_mode, qb, &blk);
-        if (st2 != TASP_OK) return st2;
-        bp.blk[qb] = {static_cast<int32_t>(blk.local_row0), static_cast<int32_t>(blk.rows), static_cast<int32_t>(blk.pos0)};
-      }
-      // The dk/dv kernel treats every key on its own, so the order of the ranges is free: by
-      // position, which under the causal mask is by falling work (early keys are seen by more
-      // queries), so that the workgroups with the most work start first.  Neighbours are joined.
-      std::sort(ranges.begin(), ranges.end(),
-                [](const tasp::Segment& x, const tasp::Segment& y) { return x.start < y.start; });
-      size_t n = 0;
-      for (size_t i = 0; i < ranges.size(); ++i) {
-        if (n > 0 && ranges[n - 1].end == ranges[i].start) ranges[n - 1].end = ranges[i].end;
-        else ranges[n++] = ranges[i];
-      }
-      if (n > static_cast<size_t>(tasp::kMaxSeg)) return TASP_EUNSUPPORTED_SHAPE;
-      bp.n_rng = static_cast<int32_t>(n);
-      int64_t vpos = 0;
-      for (size_t i = 0; i < n; ++i) {
-        bp.rng_start[i] = static_cast<int32_t>(ranges[i].start);
-        bp.rng_vbeg[i] = static_cast<int32_t>(vpos);
-        vpos += ranges[i].end - ranges[i].start;
-      }
-      bp.rng_vbeg[n] = static_cast<int32_t>(vpos);
-      // A step's key tiles are few (S / N keys) and under the causal mask their work differs by
-      // whole multiples (a tile is seen by both local half-chunks, by one, or by none), so the
-      // launch ends with most CUs idle while a few finish a second tile.  Such a launch is cut
-      // finer, one workgroup per key tile and query head; the partial sums are added up afterwards.
-      // The finer launch costs a little where the coarse one is already even (partial sums written
-      // and read back, more workgroup set-ups), so it is used where the estimate says it wins by more
-      // than 4 %.
-      bp.split_heads = 0;
-      const int64_t wgs = tasp::bwd_dkv_workgroups(bp, b->d);
-      const int slots = tasp::bwd_dkv_resident_workgroups(b->d);
-      if (part != nullptr && vpos <= sh.L && wgs > 0 && wgs < 8 * static_cast<int64_t>(slots) &&
-          dkv_makespan(bp, b->d, bp.Hq / bp.Hkv, slots) * 104 < dkv_makespan(bp, b->d, 1, slots) * 100) {
-        bp.split_heads = 1;
-        bp.part_dk = part;
-        bp.part_dv = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(part) + align_up(sh.o_bytes));
-      }
+    // The launches of one step, or of all steps at once.
+    auto enqueue = [&](const tasp::BwdLaunch& bp) -> int {
       if (!bf16) {
         // one launch for both kinds of workgroup, except where each is to be timed for itself
-        bp.n_split = n_split;
-        bp.part_dk = reinterpret_cast<float*>(static_cast<unsigned char*>(b->workspace) + align_up(sh.lse_bytes));
-        bp.part_stride = n_q_elems;
-        bp.accumulate = first_unit ? 0 : 1;           // every query row sees its own diagonal at step 0
-        first_unit = false;
-        if (prof == nullptr) {
-          if (tasp::launch_bwd_fp32(bp, b->d, true, true, stream) != hipSuccess) return TASP_EHIP;
-        } else {
-          { Scope sc(prof, BwdSpans::kDq); if (tasp::launch_bwd_fp32(bp, b->d, true, false, stream) != hipSuccess) return TASP_EHIP; }
-          { Scope sc(prof, BwdSpans::kDkv); if (tasp::launch_bwd_fp32(bp, b->d, false, true, stream) != hipSuccess) return TASP_EHIP; }
-        }
-        if (n_split > 1) {
-          Scope sc(prof, BwdSpans::kOther);
-          if (tasp::launch_bwd_sum_f32(bp.part_dk, bp.part_stride, n_split, dq_acc, n_q_elems, stream) != hipSuccess) return TASP_EHIP;
-        }
+        if (prof == nullptr) return tasp::launch_bwd_fp32(bp, b->d, true, true, stream) == hipSuccess ? TASP_OK : TASP_EHIP;
+        { Scope sc(prof, BwdSpans::kDq); if (tasp::launch_bwd_fp32(bp, b->d, true, false, stream) != hipSuccess) return TASP_EHIP; }
+        { Scope sc(prof, BwdSpans::kDkv); if (tasp::launch_bwd_fp32(bp, b->d, false, true, stream) != hipSuccess) return TASP_EHIP; }
         return TASP_OK;
       }
       {
@@ -787,48 +845,76 @@ static int run_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args
         Scope sc(prof, BwdSpans::kDkv);
         if (tasp::launch_bwd_dkv_bf16(bp, b->d, kv_stream) != hipSuccess) return TASP_EHIP;
       }
-      if (bp.split_heads) {
+      if (bp.kv_split > 0) {
         Scope sc(prof, BwdSpans::kOther);
         if (tasp::launch_bwd_dkv_reduce(bp, b->d, kv_stream) != hipSuccess) return TASP_EHIP;
       }
       return TASP_OK;
     };
+    // One unit = one dq launch and one dk/dv launch: a step.
+    auto launch_unit = [&](const AttnLaunch& lp, std::vector<tasp::Segment>& ranges) -> int {
+      tasp::BwdLaunch bp{};
+      const int st2 = fill_bwd(s, b, lp, ranges, &bp);
+      if (st2 != TASP_OK) return st2;
+      set_buffers(&bp);
+      // A step's key tiles are few (S / N keys) and under the causal mask their work differs by
+      // whole multiples (a tile is seen by both local half-chunks, by one, or by none), so the
+      // launch ends with most CUs idle while a few finish a second tile.  Such a launch is cut
+      // finer, one workgroup per key tile and query head; the partial sums are added up afterwards.
+      // The finer launch costs a little where the coarse one is already even (partial sums written
+      // and read back, more workgroup set-ups), so it is used where the estimate says it wins by more
+      // than 4 %.
+      const int64_t wgs = tasp::bwd_dkv_workgroups(bp, b->d);
+      const int slots = tasp::bwd_dkv_resident_workgroups(b->d);
+      if (part != nullptr && bp.rng_vbeg[bp.n_rng] <= sh.L && wgs > 0 && wgs < 8 * static_cast<int64_t>(slots) &&
+          dkv_makespan(bp, b->d, 1, sh.B, slots) * 104 < dkv_makespan(bp, b->d, 0, sh.B, slots) * 100) {
+        bp.kv_split = 1;
+        bp.part_dk = part;
+        bp.part_dv = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(part) + align_up(sh.o_bytes));
+      }
+      bp.accumulate = bf16 || !first_unit ? 1 : 0;      // fp32: every query row sees its own diagonal at step 0
+      first_unit = false;
+      return enqueue(bp);
+    };
+    // All steps in one launch of each kind.
+    auto launch_joined = [&]() -> int {
+      tasp::BwdLaunch bp{};
+      JoinedSteps js{};
+      int st2 = build_bwd_joined(s, b, &a, &bp, &js);
+      if (st2 != TASP_OK) return st2;
+      set_buffers(&bp);
+      const bool listed = js.segments() > static_cast<size_t>(tasp::kPoolSeg);
+      const BwdPlan pl = plan_backward(b, sh, bp, listed ? kFusedTableBytes : 0, std::min(b->workspace_bytes, std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES)));
+      if (b->fuse_steps) {
+        Scope sc(listed ? prof : nullptr, BwdSpans::kOther);
+        st2 = place_lists(&js, !listed, reinterpret_cast<int32_t*>(after_rows), stream);
+        if (st2 != TASP_OK) return st2;
+        for (int t = 0; t < bp.n_tasks; ++t) { bp.task[t] = js.all.task[t]; bp.seg_ext[t] = js.all.seg_ext[t]; }
+        std::copy(js.all.pool, js.all.pool + 2 * tasp::kPoolSeg, bp.pool);
+      }
+      unsigned char* at = after_rows + pl.table_bytes;
+      bp.n_split = pl.n_split;
+      bp.dq_final = bf16 && pl.n_split == 1 ? b->dq : nullptr;
+      bp.part_dq = reinterpret_cast<float*>(at);
+      bp.part_stride = static_cast<int64_t>(align_up(sh.o_bytes) / sizeof(float));
+      if (pl.n_split > 1) at += pl.n_split * align_up(sh.o_bytes);
+      bp.kv_split = pl.kv_split;
+      bp.part_dk = reinterpret_cast<float*>(at);
+      bp.part_dv = reinterpret_cast<float*>(at + pl.kv_bytes);
+      st2 = enqueue(bp);
+      if (st2 == TASP_OK && pl.n_split > 1) {
+        Scope sc(prof, BwdSpans::kOther);
+        if (tasp::launch_bwd_sum(bp.part_dq, bp.part_stride, pl.n_split, b->dq, bf16, n_q_elems, stream) != hipSuccess) return TASP_EHIP;
+      }
+      return st2;
+    };
     // All units; returns at the first failure, and the join below runs either way so that the
     // caller's second stream is never left forked (which would also break a stream capture).
     auto walk = [&]() -> int {
       std::vector<tasp::QueryBlock> empty;
-      std::vector<tasp::Segment> ranges, step_ranges;
-      if (b->fuse_steps) {
-        JoinedSteps js{};
-        st = join_steps(s, &a, &js);
-        if (st != TASP_OK) return st;
-        {
-          Scope sc(prof, BwdSpans::kOther);
-          st = place_lists(&js, false, reinterpret_cast<int32_t*>(after_rows), stream);
-          if (st != TASP_OK) return st;
-        }
-        for (int step = 0; step < s->n; ++step) {
-          st = tasp::step_key_ranges(*s, b->S, b->mask_mode, b->order, step, &step_ranges);
-          if (st != TASP_OK) return st;
-          ranges.insert(ranges.end(), step_ranges.begin(), step_ranges.end());
-        }
-        st = launch_unit(js.all, ranges);
-        if (st != TASP_OK) return st;
-      }
-      if (!bf16 && sh.L <= kJoinRows) {
-        // All steps at once.  Over them every key of the sequence is met once, and what a query row or a
-        // key gets from one pair does not depend on the others: the lists are one segment, the sequence.
-        AttnLaunch lp{};
-        st = build_step(s, &a, 0, &lp, &empty);
-        if (st != TASP_OK) return st;
-        lp.pool[0] = 0;
-        lp.pool[1] = static_cast<int32_t>(b->S);
-        for (int t = 0; t < lp.n_tasks; ++t) { lp.task[t].seg0 = 0; lp.task[t].n_seg = 1; }
-        n_split = bwd_fp32_split(b, sh, b->workspace_bytes);
-        ranges.assign(1, tasp::Segment{0, b->S, 0});
-        return launch_unit(lp, ranges);
-      }
-      for (int step = 0; step < s->n && !b->fuse_steps; ++step) {
+      std::vector<tasp::Segment> ranges;
+      if (joined) return launch_joined();
+      for (int step = 0; step < s->n; ++step) {
         AttnLaunch lp{};
         empty.clear();
         st = build_step(s, &a, step, &lp, &empty);
@@ -847,7 +933,7 @@ static int run_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args
         return st != TASP_OK ? st : TASP_EHIP;
     }
     if (st != TASP_OK) return st;
-    if (bf16) {
+    if (bf16 && !joined) {
       Scope sc(prof, BwdSpans::kOther);
       if (tasp::launch_cast_bf16(dq_acc, b->dq, n_q_elems, stream) != hipSuccess) return TASP_EHIP;
     }

@@ -125,13 +125,15 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_kernel(const BwdL
   const int G = p.Hq / p.Hkv;
   const int tiles0 = (p.task[0].n_q + BS - 1) / BS;
   const int tiles1 = p.n_tasks > 1 ? (p.task[1].n_q + BS - 1) / BS : 0;
-  const int per_g = (tiles0 + tiles1) * G, per_b = per_g * p.Hkv;
-  const int w_all = xcd_balanced(blockIdx.x, p.batch * p.Hkv, per_g);
+  const int per_g = (tiles0 + tiles1) * G * p.n_split, per_b = per_g * p.Hkv;
+  const int w_all = xcd_balanced(blockIdx.x, p.batch * p.Hkv, per_g, xcd_window(D == 64 ? 96 : 64, per_g));
   if (w_all < 0) return;
   const int bi = w_all / per_b;
   const int w = w_all - bi * per_b;
   const int g = w / per_g;
   int rem = w - g * per_g;
+  const int share = rem % p.n_split;            // of the tile's keys
+  rem /= p.n_split;
   const int tsk = rem >= tiles0 * G ? 1 : 0;
   if (tsk) rem -= tiles0 * G;
   // under the causal mask the later query tiles of a block see more keys: they start first
@@ -156,29 +158,44 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_kernel(const BwdL
   }
   __syncthreads();
   if (wave == 0) {
-    int n_base = 0, v_base = 0;
+    auto visible = [&](int s, int& a) __attribute__((always_inline)) {
+      a = 0;
+      if (s >= T.n_seg) return 0;
+      a = seg_raw[2 * s];
+      const int e = seg_raw[2 * s + 1];
+      return max(0, (p.causal ? min(e, q_last + 1) : e) - a);
+    };
+    int lo = 0, hi = INT_MAX;                      // this workgroup's share of the tile's visible keys
+    if (p.n_split > 1) {
+      int total = 0, a;
+      for (int s0 = 0; s0 < T.n_seg; s0 += 64) total += visible(s0 + lane, a);
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) total += __shfl_xor(total, o);
+      const int chunk = ((total + p.n_split - 1) / p.n_split + BT - 1) / BT * BT;
+      lo = share * chunk;
+      hi = lo + chunk;
+    }
+    int n_base = 0, v_base = 0, end = 0;
     for (int s0 = 0; s0 < T.n_seg; s0 += 64) {
-      const int s = s0 + lane;
-      int a = 0, len = 0;
-      if (s < T.n_seg) {
-        a = seg_raw[2 * s];
-        const int e = seg_raw[2 * s + 1];
-        len = max(0, (p.causal ? min(e, q_last + 1) : e) - a);
-      }
-      const int cnt = len > 0 ? 1 : 0;
-      int sc = cnt, sl = len;                      // inclusive scans
+      int a;
+      const int len = visible(s0 + lane, a);
+      int sl = len;                                // inclusive scan
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
-        const int t1 = __shfl_up(sc, o), t2 = __shfl_up(sl, o);
-        if (lane >= o) { sc += t1; sl += t2; }
+        const int t2 = __shfl_up(sl, o);
+        if (lane >= o) sl += t2;
       }
-      if (len > 0) {
-        const int idx = n_base + sc - 1, vpos = v_base + sl - len;
-        e_vbeg[idx] = vpos; e_goff[idx] = a - vpos;
+      const int beg = v_base + sl - len, cb = max(beg, lo), ce = min(beg + len, hi);
+      const unsigned long long has = __builtin_amdgcn_ballot_w64(ce > cb);
+      if (ce > cb) {
+        const int idx = n_base + __builtin_popcountll(has & ((1ull << lane) - 1));
+        e_vbeg[idx] = cb - lo; e_goff[idx] = a + (cb - beg) - (cb - lo);
       }
-      n_base += __shfl(sc, 63); v_base += __shfl(sl, 63);
+      if (has != 0) end = __shfl(ce, 63 - __builtin_clzll(has)) - lo;
+      n_base += __builtin_popcountll(has);
+      v_base += __shfl(sl, 63);
     }
-    if (lane == 0) { e_vbeg[n_base] = v_base; e_n = n_base; }
+    if (lane == 0) { e_vbeg[n_base] = end; e_n = n_base; }
   }
   __syncthreads();
   const int n_eff = e_n;
@@ -363,16 +380,30 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_kernel(const BwdL
   }
   wait_all_loads();
 
-  // ---- epilogue: dq_acc += scale dq.  A lane owns one query row; per (db, i4) it holds 4
-  // consecutive columns and its partner lane (+32) the next 4.
+  // ---- epilogue.  A lane owns one query row; per (db, i4) it holds 4 consecutive columns and its
+  // partner lane (+32) the next 4.
   if (q_valid) {
-    float* dst0 = p.dq_acc + qoff + 4 * h;
+    if (p.dq_final != nullptr) {
+      __bf16* fd = static_cast<__bf16*>(p.dq_final) + qoff + 4 * h;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          bf16x4 val;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) val[e] = static_cast<__bf16>(dq[db][4 * i4 + e] * p.scale);
+          *reinterpret_cast<bf16x4*>(fd + 32 * db + 8 * i4) = val;
+        }
+      return;
+    }
+    float* dst0 = (p.n_split > 1 ? p.part_dq + share * p.part_stride : p.dq_acc) + qoff + 4 * h;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4) {
         f32x4* dst = reinterpret_cast<f32x4*>(dst0 + 32 * db + 8 * i4);
-        f32x4 val = *dst;
+        f32x4 val = {0.f, 0.f, 0.f, 0.f};
+        if (p.accumulate) val = *dst;
 #pragma unroll
         for (int e = 0; e < 4; ++e) val[e] = __builtin_fmaf(dq[db][4 * i4 + e], p.scale, val[e]);
         *dst = val;
@@ -387,7 +418,8 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_kernel(const BwdL
 // V rows stay in LDS instead (read as B operand when needed), which is what lets a wavefront with
 // two 32 x D accumulators fit the 256 registers of two wavefronts per SIMD at D = 128.  At D = 64
 // the kernel fits 168 registers, i.e. three workgroups of four wavefronts per CU (-6 % against two).
-// With SPLIT a workgroup serves one query head of the group only and leaves fp32 partial sums.
+// With SPLIT a workgroup serves one query head of the group and a share of the query tiles and leaves
+// fp32 partial sums.
 // -lse / scale and -delta of a tile's queries come from the arrays the delta kernel left (p.nlse,
 // p.ndelta), gathered straight into LDS like the tile itself (no wavefront ever waits on them);
 // they are what the score and dout.v accumulators start from.
@@ -407,18 +439,20 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 3) void bwd_dkv_kernel(const
   const int G = p.Hq / p.Hkv;
   const int total_keys = p.rng_vbeg[p.n_rng];
   const int ktiles = (total_keys + BS - 1) / BS;
-  const int w_all = xcd_balanced(blockIdx.x, p.batch * p.Hkv, ktiles * (SPLIT ? G : 1));
+  const int per_tile = SPLIT ? G * p.kv_split : 1;          // workgroups per key tile
+  const int w_all = xcd_balanced(blockIdx.x, p.batch * p.Hkv, ktiles * per_tile, xcd_window(NW == 8 ? 32 : 96, ktiles * per_tile));
   if (w_all < 0) return;
   // Split by head, the work list of a KV head is head-major: the workgroups an XCD runs at one time
   // then stream the query tiles of the same head through its L2, as they do without the split
   // (tile-major measured 9 % slower), and each head's tiles still come by falling work.
-  const int per_tile = SPLIT ? G : 1;          // workgroups per key tile
   const int bi = w_all / (ktiles * p.Hkv * per_tile);
   const int w = w_all - bi * (ktiles * p.Hkv * per_tile);
   const int g = w / (ktiles * per_tile);
   const int wt = w - g * (ktiles * per_tile);
   const int v0 = (wt % ktiles) * BS;           // first key of the tile in the virtual concatenation
-  const int hh_beg = SPLIT ? wt / ktiles : 0, hh_end = SPLIT ? hh_beg + 1 : G;   // query heads of the group served here
+  const int part = wt / ktiles;
+  const int q_step = SPLIT ? p.kv_split : 1, q_share = SPLIT ? part % q_step : 0;      // every q_step-th query tile is served here, the
+  const int hh_beg = SPLIT ? part / q_step : 0, hh_end = SPLIT ? hh_beg + 1 : G;       //   last but q_share one first, for these query heads of the group
 
   // smallest global position among the keys of the tile: queries before it see none of them
   if (tid == 0) {
@@ -483,11 +517,11 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 3) void bwd_dkv_kernel(const
   struct It { int hh, blk, qt; };
   // the first state at or after (hh, blk, qt) in walking order that has work; blk < 0 means done
   auto settle = [&](It it) __attribute__((always_inline)) {
-    if (it.hh >= hh_end) { it.hh = hh_beg; --it.qt; }
+    if (it.hh >= hh_end) { it.hh = hh_beg; it.qt -= q_step; }
     while (it.blk >= 0) {
       if (it.qt >= first_tile(it.blk)) return it;
       --it.blk;
-      if (it.blk >= 0) it.qt = tiles_of(it.blk) - 1;
+      if (it.blk >= 0) it.qt = tiles_of(it.blk) - 1 - q_share;
     }
     return it;
   };
@@ -588,7 +622,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 3) void bwd_dkv_kernel(const
       asm volatile("" : "+v"(a_row), "+v"(a_tr0), "+v"(a_tr1), "+v"(av_));
   };
 
-  It cur = settle(It{hh_beg, p.n_blk - 1, tiles_of(p.n_blk - 1) - 1});
+  It cur = settle(It{hh_beg, p.n_blk - 1, tiles_of(p.n_blk - 1) - 1 - q_share});
   if (cur.blk >= 0) fetch(cur, 0);
   int stage = 0;
   while (cur.blk >= 0) {
@@ -685,7 +719,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 3) void bwd_dkv_kernel(const
   if constexpr (SPLIT) {
     if (key_valid) {
       const int64_t vi = v0 + wave * 32 + lq;
-      const int64_t poff = (((static_cast<int64_t>(bi) * G + hh_beg) * total_keys + vi) * p.Hkv + g) * D + 4 * h;
+      const int64_t poff = (((static_cast<int64_t>(bi) * per_tile + part) * total_keys + vi) * p.Hkv + g) * D + 4 * h;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -751,13 +785,13 @@ __global__ __launch_bounds__(256) void bwd_delta_kernel(const __bf16* __restrict
   }
 }
 
-// dk, dv of a launch split by query head: one thread per (sequence, key, KV head, 4 columns) adds the
-// G partial sums in the order of the heads, so the result does not depend on how the launch ran.
+// dk, dv of a split launch: one thread per (sequence, key, KV head, 4 columns) adds the
+// partial sums in the order of the heads and shares, so the result does not depend on how the launch ran.
 template <int D>
 __global__ __launch_bounds__(256) void bwd_dkv_reduce_kernel(const BwdLaunch p) {
   constexpr int C4 = D / 4;
   const int total_keys = p.rng_vbeg[p.n_rng];
-  const int G = p.Hq / p.Hkv;
+  const int n_parts = p.Hq / p.Hkv * p.kv_split;
   const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   const int64_t per_b = static_cast<int64_t>(total_keys) * p.Hkv * C4;
   if (idx >= per_b * p.batch) return;
@@ -770,8 +804,8 @@ __global__ __launch_bounds__(256) void bwd_dkv_reduce_kernel(const BwdLaunch p) 
   for (int j = 0; j < p.n_rng; ++j)
     if (vi >= p.rng_vbeg[j] && vi < p.rng_vbeg[j + 1]) tok = p.rng_start[j] + (vi - p.rng_vbeg[j]);
   f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
-  for (int hh = 0; hh < G; ++hh) {
-    const int64_t poff = ((((bi * G + hh) * total_keys + vi) * p.Hkv + g) * C4 + c4) * 4;
+  for (int part = 0; part < n_parts; ++part) {
+    const int64_t poff = ((((bi * n_parts + part) * total_keys + vi) * p.Hkv + g) * C4 + c4) * 4;
     const f32x4 x = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p.part_dk + poff));
     const f32x4 y = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p.part_dv + poff));
 #pragma unroll
@@ -799,7 +833,7 @@ hipError_t launch_bwd_dq_bf16(const BwdLaunch& p, int d, hipStream_t stream) {
   int64_t tiles = 0;
   constexpr int BS = 128;
   for (int t = 0; t < p.n_tasks; ++t) tiles += (p.task[t].n_q + BS - 1) / BS;
-  const int64_t items = tiles * p.Hq * p.batch;
+  const int64_t items = tiles * p.Hq * p.batch * p.n_split;
   if (items == 0) return hipSuccess;
   if (items > INT_MAX) return hipErrorInvalidValue;
   const int64_t units = static_cast<int64_t>(p.batch) * p.Hkv;
@@ -814,14 +848,14 @@ template <int D, int NW, bool VLDS>
 hipError_t launch_dkv_variant(const BwdLaunch& p, hipStream_t stream) {
   constexpr int BS = 32 * NW;
   const int64_t total = p.rng_vbeg[p.n_rng];
-  const int64_t items = (total + BS - 1) / BS * p.Hkv * p.batch * (p.split_heads ? p.Hq / p.Hkv : 1);
+  const int64_t items = (total + BS - 1) / BS * p.Hkv * p.batch * (p.kv_split > 0 ? p.Hq / p.Hkv * p.kv_split : 1);
   if (items == 0) return hipSuccess;
   if (items > INT_MAX) return hipErrorInvalidValue;
   const int64_t units = static_cast<int64_t>(p.batch) * p.Hkv;
   const int64_t blocks = xcd_balanced_blocks(units, items / units);
   if (blocks > INT_MAX) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(blocks)), block(64 * NW);
-  if (p.split_heads) return TASP_LAUNCH((bwd_dkv_kernel<D, NW, VLDS, true>), grid, block, stream, p);
+  if (p.kv_split > 0) return TASP_LAUNCH((bwd_dkv_kernel<D, NW, VLDS, true>), grid, block, stream, p);
   return TASP_LAUNCH((bwd_dkv_kernel<D, NW, VLDS, false>), grid, block, stream, p);
 }
 

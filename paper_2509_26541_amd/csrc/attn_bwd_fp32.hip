@@ -348,7 +348,7 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
       *reinterpret_cast<f32x4*>(dv + col) = b;
     });
   } else {
-    float* dq = (p.n_split > 1 ? p.part_dk + share * p.part_stride : p.dq_acc) + x_off / 4;
+    float* dq = (p.n_split > 1 ? p.part_dq + share * p.part_stride : p.dq_acc) + x_off / 4;
     static_for<D / 8>([&](auto qq) __attribute__((always_inline)) {
       f32x4 a;
       const int col = quad<NDB, decltype(qq)::value>(acc[0], h, a);
@@ -387,7 +387,8 @@ __global__ __launch_bounds__(256) void bwd_delta_fp32_kernel(const float* __rest
 }
 
 // dst = sum of the n arrays of n4 x 4 floats, one behind the other, in order
-__global__ __launch_bounds__(256) void bwd_sum_kernel(const float* __restrict__ parts, int64_t stride, int n, float* __restrict__ dst, int64_t n4) {
+template <typename T>
+__global__ __launch_bounds__(256) void bwd_sum_kernel(const float* __restrict__ parts, int64_t stride, int n, T* __restrict__ dst, int64_t n4) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   if (i >= n4) return;
   f32x4 s = *reinterpret_cast<const f32x4*>(parts + 4 * i);
@@ -397,7 +398,14 @@ __global__ __launch_bounds__(256) void bwd_sum_kernel(const float* __restrict__ 
 #pragma unroll
     for (int e = 0; e < 4; ++e) s[e] += x[e];
   }
-  *reinterpret_cast<f32x4*>(dst + 4 * i) = s;
+  if constexpr (sizeof(T) == 4) {
+    *reinterpret_cast<f32x4*>(dst + 4 * i) = s;
+  } else {
+    bf16x4 r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = static_cast<__bf16>(s[e]);
+    *reinterpret_cast<bf16x4*>(dst + 4 * i) = r;
+  }
 }
 
 }  // namespace
@@ -429,11 +437,13 @@ hipError_t launch_bwd_fp32(const BwdLaunch& p, int d, bool dq, bool dkv, hipStre
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_bwd_sum_f32(const float* parts, int64_t stride, int n, float* dst, int64_t n_elems, hipStream_t stream) {
+hipError_t launch_bwd_sum(const float* parts, int64_t stride, int n, void* dst, bool bf16, int64_t n_elems, hipStream_t stream) {
   const int64_t blocks = (n_elems / 4 + 255) / 256;
   if (blocks == 0) return hipSuccess;
   if (blocks > INT_MAX) return hipErrorInvalidValue;
-  return TASP_LAUNCH(bwd_sum_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), stream, parts, stride, n, dst, n_elems / 4);
+  const dim3 grid(static_cast<unsigned>(blocks));
+  if (bf16) return TASP_LAUNCH((bwd_sum_kernel<__bf16>), grid, dim3(256), stream, parts, stride, n, static_cast<__bf16*>(dst), n_elems / 4);
+  return TASP_LAUNCH((bwd_sum_kernel<float>), grid, dim3(256), stream, parts, stride, n, static_cast<float*>(dst), n_elems / 4);
 }
 
 hipError_t launch_bwd_delta_fp32(const void* out, const void* dout, float* delta, int64_t n_rows, int d,

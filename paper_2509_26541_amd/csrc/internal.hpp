@@ -85,23 +85,27 @@ struct BwdLaunch {
   int32_t n_tasks;
   AttnTask task[kMaxTasks];
   const int32_t* seg_ext[kMaxTasks];   // as in AttnLaunch (all steps in one launch)
-  int32_t pool[2 * kMaxTasks * kMaxSeg];
+  int32_t pool[2 * kPoolSeg];
   int32_t n_blk;
   BwdBlock blk[kMaxTasks];
   int32_t n_rng;
   int32_t rng_start[kMaxSeg];
   int32_t rng_vbeg[kMaxSeg + 1];
-  // dk/dv launch split by query head (a workgroup per key tile AND query head of the group, for
-  // launches whose key tiles alone are too few and too unequal to fill the chip): the workgroups
-  // write fp32 partial sums [B, Hq / Hkv, keys of the launch, Hkv, d] (unscaled, keys in the order of
-  // the concatenated ranges) and launch_bwd_dkv_reduce adds them up in a fixed order.
-  int32_t split_heads;
+  // dk/dv launch split finer than by key tile, for launches whose key tiles alone are too few and too
+  // unequal to fill the chip: a workgroup per key tile, query head of the group and share of the query
+  // tiles (kv_split > 0 shares: share i takes every kv_split-th tile).  The workgroups write fp32 partial sums
+  // [B, Hq / Hkv, kv_split, keys of the launch, Hkv, d] (unscaled, keys in the order of the concatenated
+  // ranges) and launch_bwd_dkv_reduce adds them up in a fixed order.  0: not split.
+  int32_t kv_split;
   float* part_dk;
   float* part_dv;
-  // fp32: the keys of a query tile are dealt to n_split workgroups; with more than one their dq sums go
-  // to part_dk + i part_stride for launch_bwd_sum_f32.  accumulate: dq_acc is added to, not written.
+  // The keys of a query tile are dealt to n_split workgroups; with more than one their dq sums go
+  // to part_dq + i part_stride for launch_bwd_sum.  With one, dq_final (not null) takes the rows as bf16,
+  // otherwise dq_acc is added to (accumulate) or written.
   int32_t n_split, accumulate;
+  float* part_dq;
   int64_t part_stride;
+  void* dq_final;
 };
 static_assert(sizeof(BwdLaunch) <= 4096, "kernel arguments");
 
@@ -139,7 +143,7 @@ hipError_t launch_write_i32(int32_t* dst, const int32_t* host_vals, int64_t n, h
 // Implemented in attn_bwd_bf16.hip.
 hipError_t launch_bwd_dq_bf16(const BwdLaunch& p, int d, hipStream_t stream);
 hipError_t launch_bwd_dkv_bf16(const BwdLaunch& p, int d, hipStream_t stream);
-// after a launch with split_heads: dk, dv = sum over the query heads of the partial sums, as bf16
+// after a launch with kv_split: dk, dv = sum over the query heads of the partial sums, as bf16
 hipError_t launch_bwd_dkv_reduce(const BwdLaunch& p, int d, hipStream_t stream);
 // workgroups of the dk/dv launch without the split, and how many of them the chip holds at once
 int64_t bwd_dkv_workgroups(const BwdLaunch& p, int d);
@@ -152,8 +156,8 @@ hipError_t launch_zero_f32(float* dst, int64_t n, hipStream_t stream);   // n a 
 // Implemented in attn_bwd_fp32.hip (all tensors fp32; dq_acc is dq itself): the dq and the dk/dv
 // workgroups of a launch, in one grid where both are asked for.
 hipError_t launch_bwd_fp32(const BwdLaunch& p, int d, bool dq, bool dkv, hipStream_t stream);
-// dst = sum over i < n of the n_elems floats at parts + i stride, in order
-hipError_t launch_bwd_sum_f32(const float* parts, int64_t stride, int n, float* dst, int64_t n_elems, hipStream_t stream);
+// dst (fp32, or bf16) = sum over i < n of the n_elems floats at parts + i stride, in order
+hipError_t launch_bwd_sum(const float* parts, int64_t stride, int n, void* dst, bool bf16, int64_t n_elems, hipStream_t stream);
 hipError_t launch_bwd_delta_fp32(const void* out, const void* dout, float* delta, int64_t n_rows, int d,
                                  hipStream_t stream);
 

@@ -91,3 +91,42 @@ def test_fp32_backward_every_element(tb, case):
         for nm, g, r in zip(("dq", "dk", "dv"), got, ref):
             err = float(np.abs(g.cpu().numpy().astype(np.float64) - r).max())
             assert err <= 1e-4 * max(1.0, float(np.abs(r).max())), (name, nm, nbytes, err)
+
+
+BWD_BF16 = [
+    # name, N, rank, S, Hq, Hkv, d, mask, fuse_steps
+    ("one_row", 4, 2, 4, 2, 1, 128, wl.FULL, False),
+    ("tile_minus_1", 4, 1, 4 * 127, 2, 1, 64, wl.FULL, True),
+    ("shares_and_heads", 8, 3, 16 * 129, 4, 1, 128, wl.ZIGZAG_CAUSAL, False),       # dq keys and dk/dv query tiles dealt out
+    ("shares_and_heads_listed", 16, 9, 32 * 65, 4, 2, 64, wl.ZIGZAG_CAUSAL, True),  # the lists of the steps in device memory
+    ("joined_edge", 4, 0, 4 * 4096, 2, 1, 64, wl.FULL, False),                      # the most local rows whose steps are joined
+    ("not_joined", 4, 3, 4 * 4097, 2, 1, 64, wl.FULL, False),
+]
+
+
+@pytest.mark.parametrize("case", BWD_BF16, ids=[c[0] for c in BWD_BF16])
+def test_bf16_backward_every_element(tb, case):
+    name, n, rank, S, Hq, Hkv, d, mode, fuse_steps = case
+    w = wl.Workload(name, n, rank, S, Hq, Hkv, d, "bf16", mode, seed=wl.BASE_SEED + 8700 + S)
+    q, k, v = wl.make_qkv(w)
+    do = wl.make_dout(w)
+    s = tb.tasp_schedule(n, rank)
+    qd, kd, vd, dod = q.cuda(), k.cuda(), v.cuda(), do.cuda()
+    out, lse = tb.tasp_chunk_attn(qd, kd, vd, s, mode)
+    keep = list(range(w.L)) if w.L <= 512 else wl.sample_rows(w, 64)          # rows with an upstream gradient
+    sparse = torch.zeros_like(do)
+    sparse[keep] = do[keep]
+    ref = oracle_grads(w, q, k, v, do, rows=keep, out=out.cpu())
+    plan = tb.ChunkAttnBwdPlan(s, qd, kd, vd, out, lse, sparse.cuda(), mode, fuse_steps=fuse_steps)
+    least = tb.lib.tasp_chunk_attn_bwd_workspace_bytes(s.handle, C.byref(plan.args))
+    for nbytes in {plan.args.workspace_bytes, least}:
+        plan.args.workspace_bytes = nbytes
+        for t in (plan.dq, plan.dk, plan.dv):
+            t.fill_(float("nan"))
+        dq, dk, dv = plan.run()
+        torch.cuda.synchronize()
+        assert bool(torch.isfinite(dq.float()).all())
+        for nm, g, r in zip(("dq", "dk", "dv"), (dq[keep], dk, dv), ref):
+            err = np.abs(g.float().cpu().numpy().astype(np.float64) - r)
+            worst = float((err / (np.abs(r) / 128 + np.abs(r).max() / 256 + 1e-30)).max())
+            assert worst <= 1.0, (name, nm, nbytes, worst)
