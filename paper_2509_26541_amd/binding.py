@@ -8,6 +8,10 @@ import ctypes as C
 import os
 
 import numpy as np
+# PyTorch's ROCm wheel ships its own HIP runtime.  Importing torch first makes libtasp.so bind to
+# that same runtime; loaded the other way round the process ends up with two runtimes and the
+# library's launches fail with "no ROCm-capable device is detected".
+import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libtasp.so")
@@ -75,10 +79,6 @@ def _load():
     if not os.path.exists(LIB_PATH):
         raise ImportError("libtasp.so is not built: run `python paper_2509_26541_amd/build.py` "
                           "(there is no CPU fallback)")
-    # PyTorch's ROCm wheel ships its own HIP runtime.  Importing torch first makes libtasp.so bind to
-    # that same runtime; loaded the other way round the process ends up with two runtimes and the
-    # library's launches fail with "no ROCm-capable device is detected".
-    import torch  # noqa: F401
     lib = C.CDLL(LIB_PATH)
     p32 = C.POINTER(C.c_int32)
     lib.tasp_strerror.restype = C.c_char_p
@@ -196,13 +196,13 @@ def tasp_schedule_multinode(ranks_per_node, n_nodes, rank):
     return Schedule(ranks_per_node * n_nodes, rank, ranks_per_node=ranks_per_node)
 
 
-def _torch():
-    import torch
-    return torch
+def _stream():
+    """The current stream of the current device, as torch.cuda.current_stream().cuda_stream without building the
+    stream object: a tenth of the host time of a short call."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _args(q, k, v, mask_mode, order, fuse_merge, softmax_scale, fuse_steps=False):
-    torch = _torch()
     if not (q.is_cuda and k.is_cuda and v.is_cuda):
         raise ValueError("q, k, v must be device tensors")
     if not (q.is_contiguous() and k.is_contiguous() and v.is_contiguous()):
@@ -228,7 +228,6 @@ class ChunkAttnPlan:
 
     def __init__(self, schedule, q, k, v, mask_mode, order=ORDER_TASP, fuse_merge=False, softmax_scale=0.0,
                  fuse_steps=False):
-        torch = _torch()
         self.schedule = schedule
         self.args = _args(q, k, v, mask_mode, order, fuse_merge, softmax_scale, fuse_steps)
         if q.shape[-3] * schedule.n_ranks != k.shape[-3]:
@@ -242,15 +241,13 @@ class ChunkAttnPlan:
         self._keep = (q, k, v)
 
     def run(self, stream=None):
-        torch = _torch()
-        s = torch.cuda.current_stream().cuda_stream if stream is None else stream
+        s = _stream() if stream is None else stream
         _check(lib.tasp_chunk_attn(self.schedule.handle, C.byref(self.args), C.c_void_p(s)), "tasp_chunk_attn")
         return self.out, self.lse
 
     def profile(self, stream=None):
         """Runs the call once with per-launch HIP-event timing; returns a Profile (milliseconds)."""
-        torch = _torch()
-        s = torch.cuda.current_stream().cuda_stream if stream is None else stream
+        s = _stream() if stream is None else stream
         prof = Profile()
         _check(lib.tasp_chunk_attn_profile(self.schedule.handle, C.byref(self.args), C.c_void_p(s), C.byref(prof)),
                "tasp_chunk_attn_profile")
@@ -272,7 +269,6 @@ class ChunkAttnBwdPlan:
     def __init__(self, schedule, q, k, v, out, lse, dout, mask_mode, order=ORDER_TASP, softmax_scale=0.0,
                  aux_stream=None, fuse_steps=False):
         """aux_stream: a torch.cuda.Stream for the dk/dv kernels (None: everything on one stream)."""
-        torch = _torch()
         fa = _args(q, k, v, mask_mode, order, True, softmax_scale)
         if q.shape[-3] * schedule.n_ranks != k.shape[-3]:
             raise ValueError("q must hold S / N local rows")
@@ -297,14 +293,12 @@ class ChunkAttnBwdPlan:
         self._keep = (q, k, v, out, lse, dout, aux_stream)
 
     def run(self, stream=None):
-        torch = _torch()
-        s = torch.cuda.current_stream().cuda_stream if stream is None else stream
+        s = _stream() if stream is None else stream
         _check(lib.tasp_chunk_attn_bwd(self.schedule.handle, C.byref(self.args), C.c_void_p(s)), "tasp_chunk_attn_bwd")
         return self.dq, self.dk, self.dv
 
     def profile(self, stream=None):
-        torch = _torch()
-        s = torch.cuda.current_stream().cuda_stream if stream is None else stream
+        s = _stream() if stream is None else stream
         prof = BwdProfile()
         _check(lib.tasp_chunk_attn_bwd_profile(self.schedule.handle, C.byref(self.args), C.c_void_p(s), C.byref(prof)),
                "tasp_chunk_attn_bwd_profile")
@@ -318,14 +312,13 @@ def tasp_chunk_attn_static(q, k, v, out, lse, schedule, mask_mode, order=ORDER_T
                            softmax_scale=0.0, fuse_steps=False):
     """tasp_chunk_attn into the caller's out / lse with the library's own fixed scratch as workspace:
     nothing is allocated, here or in the library.  Raises TaspError(EWORKSPACE) beyond STATIC_SCRATCH_BYTES."""
-    torch = _torch()
     a = _args(q, k, v, mask_mode, order, fuse_merge, softmax_scale, fuse_steps)
     if not (out.is_cuda and out.is_contiguous() and out.dtype == q.dtype and out.shape == q.shape):
         raise ValueError("out must be a contiguous device tensor shaped and typed like q")
     if not (lse.is_cuda and lse.is_contiguous() and lse.dtype == torch.float32 and lse.shape == q.shape[:-1]):
         raise ValueError("lse must be a contiguous fp32 device tensor [.., L, Hq]")
     a.out, a.lse = out.data_ptr(), lse.data_ptr()
-    s = torch.cuda.current_stream().cuda_stream
+    s = _stream()
     _check(lib.tasp_chunk_attn_static(schedule.handle, C.byref(a), C.c_void_p(s)), "tasp_chunk_attn_static")
     return out, lse
 
@@ -340,11 +333,10 @@ def tasp_chunk_attn_bwd(q, k, v, out, lse, dout, schedule, mask_mode, order=ORDE
 
 def tasp_step_attn(q, k, v, schedule, mask_mode, step, order=ORDER_TASP, softmax_scale=0.0):
     """Partial (out_s fp32, lse_s fp32) of one step, before any merge."""
-    torch = _torch()
     a = _args(q, k, v, mask_mode, order, False, softmax_scale)
     o = torch.empty(q.shape, dtype=torch.float32, device=q.device)
     lse = torch.empty(q.shape[:-1], dtype=torch.float32, device=q.device)
-    s = torch.cuda.current_stream().cuda_stream
+    s = _stream()
     _check(lib.tasp_step_attn(schedule.handle, C.byref(a), step, o.data_ptr(), lse.data_ptr(), C.c_void_p(s)),
            "tasp_step_attn")
     return o, lse
@@ -352,20 +344,18 @@ def tasp_step_attn(q, k, v, schedule, mask_mode, step, order=ORDER_TASP, softmax
 
 def tasp_calibration_copy(dst, src):
     """Streams src into dst (same-size contiguous device tensors) with the library's copy kernel."""
-    torch = _torch()
     nbytes = src.numel() * src.element_size()
     if dst.numel() * dst.element_size() != nbytes or not (src.is_cuda and dst.is_cuda):
         raise ValueError("device tensors of equal byte size expected")
-    s = torch.cuda.current_stream().cuda_stream
+    s = _stream()
     _check(lib.tasp_calibration_copy(dst.data_ptr(), src.data_ptr(), nbytes, C.c_void_p(s)), "tasp_calibration_copy")
     return dst
 
 
 def tasp_calibration_mfma(iters):
     """Launches the matrix-pipe calibration kernel on the current stream; returns its flop count."""
-    torch = _torch()
     flops = C.c_double(0.0)
-    s = torch.cuda.current_stream().cuda_stream
+    s = _stream()
     _check(lib.tasp_calibration_mfma(int(iters), C.byref(flops), C.c_void_p(s)), "tasp_calibration_mfma")
     return flops.value
 
@@ -374,9 +364,8 @@ def tasp_calibration_issue(kind, per_slot, iters=2000):
     """Shader-clock cycles per slot of the issue-cost calibration (kind 0: per_slot fma, 1: per_slot
     exp, 2: eight fma + per_slot ds_read_b128, each behind one matrix instruction): the slowest
     wavefront of each of the 256 workgroups, averaged over the workgroups."""
-    torch = _torch()
     out = torch.zeros((256, 8), dtype=torch.int64, device="cuda")
-    s = torch.cuda.current_stream().cuda_stream
+    s = _stream()
     _check(lib.tasp_calibration_issue(int(kind), int(per_slot), int(iters), out.data_ptr(), C.c_void_p(s)),
            "tasp_calibration_issue")
     torch.cuda.synchronize()
@@ -386,7 +375,6 @@ def tasp_calibration_issue(kind, per_slot, iters=2000):
 def tasp_lse_merge_many(o_parts, lse_parts, o_out=None, lse_out=None):
     """All partial pairs merged in one pass.  o_parts: list of fp32 device tensors [rows, heads, d],
     lse_parts: list of [rows, heads]; returns (o_out, lse_out) (allocated if not given)."""
-    torch = _torch()
     n = len(o_parts)
     if n == 0 or n != len(lse_parts):
         raise ValueError("equally many out and lse partials, at least one")
@@ -403,7 +391,7 @@ def tasp_lse_merge_many(o_parts, lse_parts, o_out=None, lse_out=None):
         lse_out = torch.empty_like(lse_parts[0])
     op = (C.c_void_p * n)(*[t.data_ptr() for t in o_parts])
     lp = (C.c_void_p * n)(*[t.data_ptr() for t in lse_parts])
-    s = torch.cuda.current_stream().cuda_stream
+    s = _stream()
     _check(lib.tasp_lse_merge_many(o_out.data_ptr(), lse_out.data_ptr(), op, lp, n, rows, heads, d, C.c_void_p(s)),
            "tasp_lse_merge_many")
     return o_out, lse_out
@@ -411,14 +399,13 @@ def tasp_lse_merge_many(o_parts, lse_parts, o_out=None, lse_out=None):
 
 def tasp_lse_merge(o_acc, lse_acc, o_part, lse_part):
     """update_out_lse in place on (o_acc, lse_acc); all fp32 device tensors [rows, heads, d] / [rows, heads]."""
-    torch = _torch()
     for t in (o_acc, lse_acc, o_part, lse_part):
         if not (t.is_cuda and t.is_contiguous() and t.dtype == torch.float32):
             raise ValueError("fp32 contiguous device tensors expected")
     rows, heads, d = o_acc.shape
     if o_part.shape != o_acc.shape or lse_acc.shape != (rows, heads) or lse_part.shape != (rows, heads):
         raise ValueError("shape mismatch")
-    s = torch.cuda.current_stream().cuda_stream
+    s = _stream()
     _check(lib.tasp_lse_merge(o_acc.data_ptr(), lse_acc.data_ptr(), o_part.data_ptr(), lse_part.data_ptr(),
                               rows, heads, d, C.c_void_p(s)), "tasp_lse_merge")
     return o_acc, lse_acc

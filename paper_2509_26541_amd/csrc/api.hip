@@ -68,9 +68,8 @@ int validate(const tasp_schedule_t* s, const tasp_attn_args* a, Shape* sh) {
   return TASP_OK;
 }
 
-// Builds the launch descriptor of one step; `empty` receives the query blocks that see no key.
-int build_step(const tasp_schedule_t* s, const tasp_attn_args* a, int step, AttnLaunch* lp,
-               std::vector<tasp::QueryBlock>* empty) {
+// What every launch of a forward call has in common.
+void init_launch(const tasp_schedule_t* s, const tasp_attn_args* a, AttnLaunch* lp) {
   lp->q = a->q; lp->k = a->k; lp->v = a->v;
   lp->Hq = a->Hq; lp->Hkv = a->Hkv;
   lp->causal = a->mask_mode == TASP_MASK_ZIGZAG_CAUSAL ? 1 : 0;
@@ -84,6 +83,12 @@ int build_step(const tasp_schedule_t* s, const tasp_attn_args* a, int step, Attn
   lp->lse_bstride = L * a->Hq;
   lp->n_tasks = 0;
   lp->n_split[0] = lp->n_split[1] = 1;
+}
+
+// Builds the launch descriptor of one step; `empty` receives the query blocks that see no key.
+int build_step(const tasp_schedule_t* s, const tasp_attn_args* a, int step, AttnLaunch* lp,
+               std::vector<tasp::QueryBlock>* empty) {
+  init_launch(s, a, lp);
   int64_t keys[tasp::kMaxTasks] = {0, 0};
   int32_t n_pool = 0;
   std::vector<tasp::Segment> segs;
@@ -124,31 +129,21 @@ struct JoinedSteps {
 };
 
 int join_steps(const tasp_schedule_t* s, const tasp_attn_args* a, JoinedSteps* js) {
-  std::vector<tasp::QueryBlock> empty;
-  for (int step = 0; step < s->n; ++step) {
-    AttnLaunch lp{};
-    empty.clear();
-    const int st = build_step(s, a, step, &lp, &empty);
+  init_launch(s, a, &js->all);
+  for (int qb = 0; qb < tasp::n_query_blocks(a->mask_mode); ++qb) {
+    tasp::QueryBlock blk;
+    int st = tasp::query_block(*s, a->S, a->mask_mode, qb, &blk);
     if (st != TASP_OK) return st;
-    if (step == 0) {
-      // every query block sees its own diagonal at step 0, so step 0 defines the blocks
-      if (!empty.empty()) return TASP_EUNSUPPORTED_SHAPE;
-      js->all = lp;
-    }
-    for (int t = 0; t < lp.n_tasks; ++t) {
-      int dst = -1;
-      for (int u = 0; u < js->all.n_tasks; ++u)
-        if (js->all.task[u].q_row0 == lp.task[t].q_row0) dst = u;
-      if (dst < 0) return TASP_EUNSUPPORTED_SHAPE;
-      const int32_t* g = lp.pool + 2 * lp.task[t].seg0;
-      for (int i = 0; i < lp.task[t].n_seg; ++i) js->keys[dst] += g[2 * i + 1] - g[2 * i];
-      js->table[dst].insert(js->table[dst].end(), g, g + 2 * lp.task[t].n_seg);
-    }
-  }
-  for (int t = 0; t < js->all.n_tasks; ++t) {
-    const size_t n_seg = js->table[t].size() / 2;
-    if (n_seg > static_cast<size_t>(tasp::kMaxSegAll)) return TASP_EUNSUPPORTED_SHAPE;
-    js->all.task[t].n_seg = static_cast<int32_t>(n_seg);
+    st = tasp::all_step_segments(*s, a->S, a->mask_mode, a->order, qb, &js->table[qb]);
+    if (st != TASP_OK) return st;
+    const std::vector<int32_t>& g = js->table[qb];
+    if (g.empty() || g.size() / 2 > static_cast<size_t>(tasp::kMaxSegAll)) return TASP_EUNSUPPORTED_SHAPE;
+    for (size_t i = 0; i < g.size(); i += 2) js->keys[qb] += g[i + 1] - g[i];
+    AttnTask& t = js->all.task[js->all.n_tasks++];
+    t.q_row0 = static_cast<int32_t>(blk.local_row0);
+    t.n_q = static_cast<int32_t>(blk.rows);
+    t.q_pos0 = static_cast<int32_t>(blk.pos0);
+    t.n_seg = static_cast<int32_t>(g.size() / 2);
   }
   // the block with more keys goes first so that its workgroups are not the tail of the launch
   if (js->all.n_tasks == 2 && js->keys[1] > js->keys[0]) {
@@ -163,14 +158,14 @@ int join_steps(const tasp_schedule_t* s, const tasp_attn_args* a, JoinedSteps* j
 // Puts the joined lists where the launch finds them: in its descriptor, or, where they do not fit,
 // one behind the other in `dev_table` (kFusedTableBytes of device memory, written by small kernels).
 int place_lists(JoinedSteps* js, bool in_descriptor, int32_t* dev_table, hipStream_t stream) {
-  std::vector<int32_t> flat(js->table[0]);
-  flat.insert(flat.end(), js->table[1].begin(), js->table[1].end());
   js->all.task[0].seg0 = 0;
   js->all.task[1].seg0 = static_cast<int32_t>(js->table[0].size() / 2);
   if (in_descriptor) {
-    std::copy(flat.begin(), flat.end(), js->all.pool);
+    std::copy(js->table[1].begin(), js->table[1].end(), std::copy(js->table[0].begin(), js->table[0].end(), js->all.pool));
     return TASP_OK;
   }
+  std::vector<int32_t> flat(js->table[0]);
+  flat.insert(flat.end(), js->table[1].begin(), js->table[1].end());
   for (int t = 0; t < js->all.n_tasks; ++t) js->all.seg_ext[t] = dev_table + 2 * js->all.task[t].seg0;
   return tasp::launch_write_i32(dev_table, flat.data(), static_cast<int64_t>(flat.size()), stream) == hipSuccess ? TASP_OK : TASP_EHIP;
 }
@@ -193,23 +188,56 @@ struct FwdPlan {
 // the tail of its last workgroups; with L = S / N rows a query tile walks at most L keys a step, and
 // up to here those costs are a fifth of the call and more.  The results differ in rounding only.
 constexpr int64_t kJoinRows = 4096;
-// Workgroups of attn_tile_kernel that keep the chip busy (two per CU), and the most shares of one tile.
-constexpr int64_t kTileTarget = 512;
-constexpr int64_t kMaxSplit = 32;
+constexpr int64_t kMaxSplit = 32;    // shares of one tile
 
 // A batch of a few sequences is run like one of them, so that its results are those of separate calls.
 int64_t plan_batch(const AttnLaunch& lp) { return lp.batch <= 4 ? 1 : lp.batch; }
 
-// Deals the keys of the query tiles of attn_tile_kernel so that about kTileTarget workgroups come
-// together, none with fewer than `least` keys; keys[t] = keys the last row of task t sees.
-void deal_keys(const AttnLaunch& lp, const int64_t* keys, int64_t least, int64_t most, int32_t* n_split) {
-  const int64_t G = lp.Hq / lp.Hkv;
-  int64_t work = 0;
-  for (int t = 0; t < lp.n_tasks; ++t)
-    work += (lp.task[t].n_q * G + tasp::kTileRows - 1) / tasp::kTileRows * lp.Hkv * plan_batch(lp) * keys[t];
-  const int64_t per_wg = std::max(least, (work + kTileTarget - 1) / kTileTarget);
-  for (int t = 0; t < lp.n_tasks; ++t)
-    n_split[t] = static_cast<int32_t>(std::max<int64_t>(1, std::min((keys[t] + per_wg - 1) / per_wg, most)));
+// Deals the keys of the query tiles of attn_tile_kernel to n_split[t] workgroups each; keys[t] = keys the
+// last row of task t sees.  A lone workgroup of the kernel uses about half a CU and several share one, so
+// what counts is the length of the longest share times the workgroups of the fullest CU: shares as long as
+// 256, 512, ... workgroups in all make them, each against its fixed cost (set-up, first fetches, epilogue: 4 us)
+// and the way of the partial pairs through memory.  (With as many shares as the work asks for, without
+// regard to whole rounds of the CUs, 4 heads of 128 over 4 096 of 32 768 tokens took 211 us against 179.)
+void deal_keys(const AttnLaunch& lp, int d, bool fp32, const int64_t* keys, int64_t most, int32_t* n_split) {
+  const double per_us = (fp32 ? 7.0 : 72.0) * (d == 64 ? (fp32 ? 2.0 : 1.5) : 1.0);     // keys of a tile that a CU walks in a microsecond
+  const int64_t step = fp32 ? 32 : 64, least = fp32 ? 64 : 128;
+  const int64_t G = lp.Hq / lp.Hkv, B = plan_batch(lp);
+  int64_t tiles[tasp::kMaxTasks] = {0, 0}, longest = 0;
+  for (int t = 0; t < lp.n_tasks; ++t) {
+    tiles[t] = (lp.task[t].n_q * G + tasp::kTileRows - 1) / tasp::kTileRows * lp.Hkv * B;
+    longest = std::max(longest, keys[t]);
+  }
+  auto shares = [&](int64_t per_wg, int64_t (&n)[tasp::kMaxTasks]) {
+    int64_t total = 0;
+    for (int t = 0; t < lp.n_tasks; ++t) {
+      n[t] = std::max<int64_t>(1, std::min((keys[t] + per_wg - 1) / per_wg, most));
+      total += tiles[t] * n[t];
+    }
+    return total;
+  };
+  double best = -1;
+  for (int k = 0; k <= 6; ++k) {                  // k = 0: every tile in one share
+    int64_t lo = least / step, hi = std::max(lo, (longest + step - 1) / step), n[tasp::kMaxTasks] = {1, 1};
+    if (k == 0) lo = hi;
+    else if (shares(hi * step, n) > 256 * k) continue;
+    while (lo < hi) {                             // the shortest shares with at most 256 k workgroups
+      const int64_t mid = (lo + hi) / 2;
+      if (shares(mid * step, n) <= 256 * k) hi = mid; else lo = mid + 1;
+    }
+    const int64_t total = shares(hi * step, n);
+    double one = 0, bytes = 0;
+    for (int t = 0; t < lp.n_tasks; ++t) {
+      one = std::max(one, static_cast<double>(keys[t]) / n[t]);
+      bytes += 8.0 * n[t] * lp.task[t].n_q * lp.Hq * B * d;
+    }
+    const double rounds = std::max(1.8, std::ceil(total / 256.0));
+    const double cost = (one + 4 * per_us) * rounds + (n[0] > 1 || n[1] > 1 ? (4 + bytes / 8e6) * per_us : 0);
+    if (best < 0 || cost < best) {
+      best = cost;
+      for (int t = 0; t < lp.n_tasks; ++t) n_split[t] = static_cast<int32_t>(n[t]);
+    }
+  }
 }
 
 // Whether attn_tile_kernel is the faster one for a bf16 launch.  Both kernels' durations are estimated in
@@ -258,7 +286,7 @@ FwdPlan plan_forward(const tasp_attn_args* a, const Shape& sh, const JoinedSteps
   const size_t pair = align_up(sh.o_bytes) + align_up(sh.lse_bytes);
   const int64_t room = static_cast<int64_t>((ws_bytes - pl.table_bytes) / pair);
   int32_t n_split[tasp::kMaxTasks] = {1, 1};
-  deal_keys(js.all, js.keys, fp32 ? 64 : 128, std::min(room, kMaxSplit), n_split);
+  deal_keys(js.all, a->d, fp32, js.keys, std::min(room, kMaxSplit), n_split);
   pl.tile = fp32 || tile_is_faster(js.all, a->d, js.keys, n_split);
   if (!pl.tile) return pl;
   for (int t = 0; t < js.all.n_tasks; ++t) {

@@ -21,12 +21,14 @@
 // the latency of the first tiles.  Measured, whole calls:
 //   fp32, 16 heads of 128, 2 048 of 16 384 tokens, causal: 1.16 ms (118 TFLOP/s of the 152 a large fp32
 //     product reaches) against 20.1 ms with a wavefront per query row;
-//   fp32, 4 heads of 64, 256 of 1 024 tokens: 20 us against 309;
-//   bf16, 8 heads of 128, 512 of 4 096 tokens: 35 us against 117 with the large kernel on 16 CUs;
-//   bf16, 128 sequences of 3 072 tokens, 20 heads of 64: 0.73 ms against 0.91 with the large kernel,
+//   fp32, 4 heads of 64, 256 of 1 024 tokens: 17 us against 309;
+//   bf16, 8 heads of 128, 512 of 4 096 tokens: 24 us against 117 with the large kernel on 16 CUs (a workgroup of
+//     it: set-up 2.8 us, first tile 1.3, four tiles 8.4, epilogue 2.3);
+//   bf16, 128 sequences of 3 072 tokens, 20 heads of 64: 0.71 ms against 0.91 with the large kernel,
 //     which pads 192 rows to 256 and searches for the rows of 27-token sub-chunks in every tile.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
 
 #include "gfx950.hpp"
@@ -91,9 +93,20 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, lq = lane & 31;
 
+  // What the set-up needs of the kernel arguments is asked for here, in one go and at fixed places: they
+  // come from far (a first dependent read of them costs about as much as a tile).
+  const AttnTask t0 = p.task[0], t1 = p.task[1];
+  const int32_t* const seg_ext0 = p.seg_ext[0];
+  const int32_t* const seg_ext1 = p.seg_ext[1];
+  int* const s_pool = reinterpret_cast<int*>(smem);           // in the still unused tile stages
+  static_assert(2 * kPoolSeg * 4 <= C::STAGE_BYTES, "");
+  int pooled[2 * kPoolSeg / NTHREADS];
+#pragma unroll
+  for (int i = 0; i < 2 * kPoolSeg / NTHREADS; ++i) pooled[i] = p.pool[NTHREADS * i + tid];
+
   // ---- which (sequence, KV head, task, row tile, share of the keys)
   const int G = p.Hq / p.Hkv;
-  const int m0 = p.task[0].n_q * G, m1 = p.n_tasks > 1 ? p.task[1].n_q * G : 0;
+  const int m0 = t0.n_q * G, m1 = p.n_tasks > 1 ? t1.n_q * G : 0;
   const int tiles0 = (m0 + BM - 1) / BM, tiles1 = (m1 + BM - 1) / BM;
   const int items0 = tiles0 * p.n_split[0], per_g = items0 + tiles1 * p.n_split[1];
   const int w_all = xcd_balanced(blockIdx.x, p.batch * p.Hkv, per_g, xcd_window(D == 64 ? 96 : 64, per_g));
@@ -101,14 +114,16 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
   const int bg = w_all / per_g;
   int rem = w_all - bg * per_g;
   const int bi = bg / p.Hkv, g = bg - bi * p.Hkv;
-  const int tsk = rem >= items0 ? 1 : 0;
-  if (tsk) rem -= items0;
-  const int ns = p.n_split[tsk];
+  const bool second = rem >= items0;
+  if (second) rem -= items0;
+  const int ns = second ? p.n_split[1] : p.n_split[0];
   const int share = rem % ns;
   // under the causal mask the later tiles of a block see more keys: they start first
-  const int tile = p.causal ? (tsk ? tiles1 : tiles0) - 1 - rem / ns : rem / ns;
-  const AttnTask& T_ = p.task[tsk];
-  const int m_all = tsk ? m1 : m0;
+  const int tile = p.causal ? (second ? tiles1 : tiles0) - 1 - rem / ns : rem / ns;
+  const int q_row0 = second ? t1.q_row0 : t0.q_row0, q_pos0 = second ? t1.q_pos0 : t0.q_pos0;
+  const int n_seg = second ? t1.n_seg : t0.n_seg, seg0 = second ? t1.seg0 : t0.seg0;
+  const int32_t* const seg_ext = second ? seg_ext1 : seg_ext0;
+  const int m_all = second ? m1 : m0;
   // The strip of 32 rows a wavefront takes moves with the work item: wavefront i of a workgroup runs on
   // SIMD i, and tiles with few rows left leave strips without work.
   const int strip = (wave + w_all) & 3;
@@ -116,12 +131,12 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
   const bool q_valid = m < m_all;
   const int mc = q_valid ? m : m_all - 1;
   const int row = mc / G, hq = g * G + mc - row * G;
-  const int q_pos = p.causal ? T_.q_pos0 + row : INT_MAX - 1;
-  const int q_last = T_.q_pos0 + (min(tile * BM + BM, m_all) - 1) / G;
-  const int q_first = p.causal ? T_.q_pos0 + tile * BM / G : INT_MAX - 1;   // a key at or before it is seen by every row
+  const int q_pos = p.causal ? q_pos0 + row : INT_MAX - 1;
+  const int q_last = q_pos0 + (min(tile * BM + BM, m_all) - 1) / G;
+  const int q_first = p.causal ? q_pos0 + tile * BM / G : INT_MAX - 1;   // a key at or before it is seen by every row
 
   // ---- Q fragments (B operand): 16-byte units 2 j + h of the lane's row
-  const int64_t qoff = bi * p.q_bstride + (static_cast<int64_t>(T_.q_row0 + row) * p.Hq + hq) * D;
+  const int64_t qoff = bi * p.q_bstride + (static_cast<int64_t>(q_row0 + row) * p.Hq + hq) * D;
   u32x4 qf[NJ];
   {
     const u32x4* src = reinterpret_cast<const u32x4*>(static_cast<const T*>(p.q) + qoff) + h;
@@ -131,30 +146,29 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
 
   // ---- effective segments: what the mask leaves of every segment for this tile, then the share of it
   // that is this workgroup's.  The first wavefront works through the list, 64 segments per round.
-  const int32_t* seg_ext = p.seg_ext[tsk];
-  int* list = reinterpret_cast<int*>(smem);      // staged in the still unused tile stages
-  for (int i = tid; i < 2 * T_.n_seg; i += NTHREADS) list[i] = seg_ext != nullptr ? seg_ext[i] : p.pool[2 * T_.seg0 + i];
+  if (seg_ext == nullptr) {
+#pragma unroll
+    for (int i = 0; i < 2 * kPoolSeg / NTHREADS; ++i) s_pool[NTHREADS * i + tid] = pooled[i];
+  }
   __syncthreads();
   if (wave == 0) {
     auto visible = [&](int s, int& a) __attribute__((always_inline)) {
       a = 0;
-      if (s >= T_.n_seg) return 0;
-      a = list[2 * s];
-      const int e = list[2 * s + 1];
+      if (s >= n_seg) return 0;
+      int e;
+      if (seg_ext != nullptr) { a = seg_ext[2 * s]; e = seg_ext[2 * s + 1]; }
+      else { a = s_pool[2 * (seg0 + s)]; e = s_pool[2 * (seg0 + s) + 1]; }
       return max(0, (p.causal ? min(e, q_last + 1) : e) - a);
     };
     int lo = 0, hi = INT_MAX;                     // this workgroup's share of the tile's visible keys
-    if (ns > 1) {
-      int total = 0, a;
-      for (int s0 = 0; s0 < T_.n_seg; s0 += 64) total += visible(s0 + lane, a);
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) total += __shfl_xor(total, o);
+    if (ns > 1) {                                 // only with joined steps: over them every key of the sequence comes once
+      const int total = p.causal ? q_last + 1 : p.last_key + 1;
       const int chunk = ((total + ns - 1) / ns + BT - 1) / BT * BT;
       lo = share * chunk;
       hi = lo + chunk;
     }
     int n_base = 0, v_base = 0, o_base = 0;
-    for (int s0 = 0; s0 < T_.n_seg; s0 += 64) {
+    for (int s0 = 0; s0 < n_seg; s0 += 64) {
       int a;
       const int len = visible(s0 + lane, a);
       int sl = len;                               // inclusive scan of the lengths
@@ -206,13 +220,14 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   auto fetch = [&](int t, int stage) __attribute__((always_inline)) {
     unsigned char* dst = smem + stage * C::STAGE_BYTES + wave_u * 1024;
-    bool hidden = false;
+    int tok[C::PASSES], last = -1;
+#pragma unroll
+    for (int i = 0; i < C::PASSES; ++i) tok[i] = s_tok[(t * BT + fr + C::RPP * i) & (2 * CHUNK - 1)];     // one round trip for all passes
 #pragma unroll
     for (int i = 0; i < C::PASSES; ++i) {
       const int r = fr + C::RPP * i;
-      const int tok = s_tok[(t * BT + r) & (2 * CHUNK - 1)];
-      hidden |= tok > q_first;
-      const unsigned key = static_cast<unsigned>(min(tok, p.last_key));   // rows past the end fetch some key and are masked
+      last = max(last, tok[i]);
+      const unsigned key = static_cast<unsigned>(min(tok[i], p.last_key));   // rows past the end fetch some key and are masked
       if constexpr (F32) {                                          // tensors may exceed what a 32-bit offset reaches
         const unsigned long long off = static_cast<unsigned long long>(key) * row_bytes;
         global_to_lds_16_far(Kg + off + C::swz_k(r, fu) * 16, dst + i * NTHREADS * 16);
@@ -223,7 +238,7 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
         buffer_to_lds_16<true>(v_buf, 0u, off + C::swz_v(r, fu) * 16, dst + C::TILE_BYTES + i * NTHREADS * 16);
       }
     }
-    const bool any = __builtin_amdgcn_ballot_w64(hidden) != 0;
+    const bool any = __builtin_amdgcn_ballot_w64(last > q_first) != 0;
     if (lane == 0) s_msk[stage][wave] = any ? 1 : 0;
   };
 
@@ -267,22 +282,43 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
     if (idle) continue;
     const unsigned char* st = smem + stage * C::STAGE_BYTES;
 
+    // The matrix instructions of both products take their A operands as streams of fragments read ahead, so
+    // that a wavefront alone on its SIMD does not wait for LDS at each of them (one fp32 K fragment feeds four
+    // long instructions: the compiler's order does).
     f32x16 S[NKB];
-#pragma unroll
-    for (int kb = 0; kb < NKB; ++kb) {
-      S[kb] = zero16();
+    if constexpr (F32) {
+      S[0] = zero16();
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
-        const u32x4 a = *reinterpret_cast<const u32x4*>(st + k_row + kb * 32 * C::RB + (k_sw ^ (32 * j)));
-        if constexpr (F32) {
-          const f32x4 af = __builtin_bit_cast(f32x4, a), bf = __builtin_bit_cast(f32x4, qf[j]);
+        const f32x4 af = *reinterpret_cast<const f32x4*>(st + k_row + (k_sw ^ (32 * j))), bf = __builtin_bit_cast(f32x4, qf[j]);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) S[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[e], bf[e], S[kb], 0, 0, 0);
-        } else {
-          S[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, qf[j]), S[kb], 0, 0, 0);
-        }
+        for (int e = 0; e < 4; ++e) S[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[e], bf[e], S[0], 0, 0, 0);
       }
+    } else {
+      constexpr int NF = NKB * NJ, PD = 6;
+      bf16x8 ring[PD];
+      auto read_k = [&](auto ff) __attribute__((always_inline)) {
+        constexpr int F = decltype(ff)::value;
+        ring[F % PD] = *reinterpret_cast<const bf16x8*>(st + k_row + F / NJ * 32 * C::RB + (k_sw ^ (32 * (F % NJ))));
+      };
+      static_for<PD>(read_k);
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<NF>([&](auto ff) __attribute__((always_inline)) {
+        constexpr int F = decltype(ff)::value, kb = F / NJ, j = F % NJ;
+        if constexpr (j == 0) S[kb] = zero16();
+        S[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[F % PD], __builtin_bit_cast(bf16x8, qf[j]), S[kb], 0, 0, 0);
+        if constexpr (F + PD < NF) read_k(std::integral_constant<int, F + PD>{});
+        __builtin_amdgcn_sched_barrier(0);
+      });
     }
+    constexpr int NV = F32 ? 1 : 2 * NKB * NDB, PV = 4;       // bf16 V^T fragments: 16-key group f / NDB, block f % NDB of O^T
+    bf16x8 vring[PV];
+    auto read_v = [&](auto ff) __attribute__((always_inline)) {
+      constexpr int F = decltype(ff)::value;
+      const unsigned char* va = st + v_adr[F % NDB] + F / NDB * 16 * C::RB;
+      vring[F % PV] = lds_tr8(va, va + 8 * C::RB);
+    };
+    if constexpr (!F32) static_for<PV>(read_v);               // on their way during the maxima
     const i32x4 mk = *reinterpret_cast<const i32x4*>(&s_msk[stage][0]);
     if (__builtin_amdgcn_readfirstlane(mk[0] | mk[1] | mk[2] | mk[3]) != 0) {
 #pragma unroll
@@ -315,17 +351,15 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
       r_fix += static_cast<float>(static_cast<__bf16>(p_top)) - p_top;
     }
     float sum[4] = {0.f, 0.f, 0.f, 0.f};
+    auto exps = [&](auto first, auto count) __attribute__((always_inline)) {      // of scores first .. first + count of the 16 NKB a lane holds
 #pragma unroll
-    for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        S[kb][i] = fast_exp2(__builtin_fmaf(S[kb][i], c, -m_run));
-        sum[i & 3] += S[kb][i];
+      for (int i = decltype(first)::value; i < decltype(first)::value + decltype(count)::value; ++i) {
+        S[i / 16][i % 16] = fast_exp2(__builtin_fmaf(S[i / 16][i % 16], c, -m_run));
+        sum[i & 3] += S[i / 16][i % 16];
       }
-    l_lo += (sum[0] + sum[1]) + (sum[2] + sum[3]);
-    if ((t & 63) == 63) { l_run += l_lo; l_lo = 0.f; }
-
+    };
     if constexpr (F32) {
+      exps(std::integral_constant<int, 0>{}, std::integral_constant<int, 16>{});
 #pragma unroll
       for (int r = 0; r < 16; ++r) {             // keys 8 (r / 4) + r % 4 and four further on (the lane halves)
         const unsigned char* va = st + v_adr[0] + (8 * (r / 4) + r % 4) * C::RB;
@@ -342,18 +376,24 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
         for (int db = 0; db < NDB; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv[db], S[0][r], o[db], 0, 0, 0);
       }
     } else {
+      // the exponentials of a 16-key group ride beside the matrix instructions of the group before
+      constexpr int PER = 8 / NDB;
+      exps(std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{});
+      bf16x8 pf;
+      static_for<NV>([&](auto ff) __attribute__((always_inline)) {
+        constexpr int F = decltype(ff)::value, gg = F / NDB, db = F % NDB;
+        if constexpr (db == 0) {
 #pragma unroll
-      for (int gg = 0; gg < 2 * NKB; ++gg) {
-        bf16x8 pf;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) pf[e] = static_cast<__bf16>(S[gg / 2][8 * (gg % 2) + e]);
-#pragma unroll
-        for (int db = 0; db < NDB; ++db) {
-          const unsigned char* va = st + v_adr[db] + gg * 16 * C::RB;
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_tr8(va, va + 8 * C::RB), pf, o[db], 0, 0, 0);
+          for (int e = 0; e < 8; ++e) pf[e] = static_cast<__bf16>(S[gg / 2][8 * (gg % 2) + e]);
         }
-      }
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vring[F % PV], pf, o[db], 0, 0, 0);
+        if constexpr (F + PV < NV) read_v(std::integral_constant<int, F + PV>{});
+        if constexpr (gg + 1 < 2 * NKB) exps(std::integral_constant<int, 8 * (gg + 1) + PER * db>{}, std::integral_constant<int, PER>{});
+        __builtin_amdgcn_sched_barrier(0);
+      });
     }
+    l_lo += (sum[0] + sum[1]) + (sum[2] + sum[3]);
+    if ((t & 63) == 63) { l_run += l_lo; l_lo = 0.f; }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // no fetch may still be writing LDS when the workgroup ends
 
@@ -364,8 +404,8 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
   float wb = seen && r_tot > 0.f ? 1.f / r_tot : 0.f;
   float lse_new = seen ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -__builtin_inff();
   if (!q_valid) return;
-  const int64_t ooff = bi * p.o_bstride + (static_cast<int64_t>(T_.q_row0 + row) * p.Hq + hq) * D;
-  const int64_t loff = bi * p.lse_bstride + static_cast<int64_t>(T_.q_row0 + row) * p.Hq + hq;
+  const int64_t ooff = bi * p.o_bstride + (static_cast<int64_t>(q_row0 + row) * p.Hq + hq) * D;
+  const int64_t loff = bi * p.lse_bstride + static_cast<int64_t>(q_row0 + row) * p.Hq + hq;
   // columns of register quad q of the lane: bf16 block q / 4, 32 (q / 4) + 8 (q % 4) + 4 h; fp32 d = 128
   // row i of the blocks, 4 i; d = 64 rows i, i + 1, 2 i, where i = 8 (r / 4) + 4 h + r % 4
   auto quad = [&](auto qq, f32x4& x) __attribute__((always_inline)) {
@@ -451,42 +491,96 @@ hipError_t launch_tile_variant(const AttnLaunch& p, hipStream_t stream) {
   return TASP_LAUNCH((attn_tile_kernel<T, D>), dim3(static_cast<unsigned>(blocks)), dim3(NTHREADS), stream, p);
 }
 
-// One thread per 4 columns of one (row, head): the pairs of the row's shares added up as in
-// tasp_lse_merge_many.  Rows [0, row1) belong to the first query block (n0 shares), the rest to the second.
-template <typename T>
+// The pairs of a row's shares added up as in tasp_lse_merge_many, D / 4 lanes of 4 columns to a (row, head).
+// SPREAD, for more than four shares: a wavefront per (row, head), the shares dealt to its 256 / D groups of
+// lanes, eight of a lane's shares requested at once, so that a row costs one or two trips to memory (a share
+// at a time, 16 shares of 1 024 rows took 7 us; now 4).  Otherwise a lane takes all shares of its columns.
+// Rows [0, row1) belong to the first query block (n0 shares), the rest to the second.
+template <typename T, int D, bool SPREAD>
 __global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ o_part, const float* __restrict__ lse_part,
-                                                      T* __restrict__ out, float* __restrict__ lse_out, int64_t n4, int pieces,
+                                                      T* __restrict__ out, float* __restrict__ lse_out, int64_t n_rh,
                                                       int heads, int L, int row1, int n0, int n1, int64_t stride_o, int64_t stride_lse) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= n4) return;
-  const int64_t rh = i / pieces;
+  constexpr int PIECES = D / 4, GROUPS = SPREAD ? 64 / PIECES : 1, AT_ONCE = SPREAD ? 8 : 4;
+  const int lane = threadIdx.x & 63, c = lane % PIECES, grp = SPREAD ? lane / PIECES : 0;
+  const int64_t rh = SPREAD ? static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6)
+                            : (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) / PIECES;
+  if (rh >= n_rh) return;
   const int n = static_cast<int>(rh / heads % L) < row1 ? n0 : n1;
-  float mx = -__builtin_inff();
-  for (int s = 0; s < n; ++s) mx = fmaxf(mx, lse_part[s * stride_lse + rh]);
+  const float* op = o_part + rh * D + 4 * c;
+  const float* lp = lse_part + rh;
+  float mx = -__builtin_inff(), den = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  float den = 0.f;
-  if (mx != -__builtin_inff()) {
-#pragma unroll 4
-    for (int s = 0; s < n; ++s) {
-      const float w = __expf(lse_part[s * stride_lse + rh] - mx);
-      const f32x4 x = *reinterpret_cast<const f32x4*>(o_part + s * stride_o + 4 * i);
-      den += w;
+  for (int s0 = grp; s0 < n; s0 += GROUPS * AT_ONCE) {
+    float l[AT_ONCE];
+    f32x4 x[AT_ONCE];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(w, x[e], acc[e]);
+    for (int k = 0; k < AT_ONCE; ++k) {
+      const int s = s0 + GROUPS * k;
+      l[k] = -__builtin_inff();
+      x[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (s < n) {
+        l[k] = lp[s * stride_lse];
+        x[k] = *reinterpret_cast<const f32x4*>(op + s * stride_o);
+      }
     }
-    const float r = 1.f / den;
+    float m = mx;
+#pragma unroll
+    for (int k = 0; k < AT_ONCE; ++k) m = fmaxf(m, l[k]);
+    if (m == -__builtin_inff()) continue;
+    const float r = __expf(mx - m);
+    den *= r;
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[e] *= r;
+#pragma unroll
+    for (int k = 0; k < AT_ONCE; ++k) {
+      const float w = __expf(l[k] - m);
+      den += w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(w, x[k][e], acc[e]);
+    }
+    mx = m;
   }
+  float m = mx;
+#pragma unroll
+  for (int o = PIECES; o < PIECES * GROUPS; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+  const float r = m > -__builtin_inff() ? __expf(mx - m) : 0.f;
+  den *= r;
+#pragma unroll
+  for (int o = PIECES; o < PIECES * GROUPS; o <<= 1) den += __shfl_xor(den, o);
+  const float w = den > 0.f ? r / den : 0.f;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    acc[e] *= w;
+#pragma unroll
+    for (int o = PIECES; o < PIECES * GROUPS; o <<= 1) acc[e] += __shfl_xor(acc[e], o);
+  }
+  if (grp != 0) return;
   if constexpr (sizeof(T) == 4) {
-    *reinterpret_cast<f32x4*>(out + 4 * i) = acc;
+    *reinterpret_cast<f32x4*>(out + rh * D + 4 * c) = acc;
   } else {
     bf16x4 y;
 #pragma unroll
     for (int e = 0; e < 4; ++e) y[e] = static_cast<__bf16>(acc[e]);
-    *reinterpret_cast<bf16x4*>(out + 4 * i) = y;
+    *reinterpret_cast<bf16x4*>(out + rh * D + 4 * c) = y;
   }
-  if (i - rh * pieces == 0) lse_out[rh] = mx != -__builtin_inff() ? mx + __logf(den) : mx;
+  if (c == 0) lse_out[rh] = den > 0.f ? m + __logf(den) : -__builtin_inff();
+}
+
+template <typename T, int D>
+hipError_t launch_combine_variant(const AttnLaunch& p, int64_t L, float* lse_out, hipStream_t stream) {
+  // the tasks come heaviest first; the rows of the earlier one are those of the first query block
+  const int a = p.n_tasks > 1 && p.task[1].q_row0 < p.task[0].q_row0 ? 1 : 0;
+  const int n0 = p.n_split[a], n1 = p.n_tasks > 1 ? p.n_split[1 - a] : n0;
+  const bool spread = std::max(n0, n1) > 4;
+  const int64_t n_rh = p.batch * L * p.Hq, per_block = spread ? 4 : 1024 / D, blocks = (n_rh + per_block - 1) / per_block;
+  if (blocks > INT_MAX) return hipErrorInvalidValue;
+  if (!spread)
+    return TASP_LAUNCH((combine_kernel<T, D, false>), dim3(static_cast<unsigned>(blocks)), dim3(256), stream, p.o_dst, p.lse_dst,
+                       static_cast<T*>(p.out_final), lse_out, n_rh, p.Hq, static_cast<int>(L), p.task[a].n_q, n0, n1, p.part_stride_o,
+                       p.part_stride_lse);
+  return TASP_LAUNCH((combine_kernel<T, D, true>), dim3(static_cast<unsigned>(blocks)), dim3(256), stream, p.o_dst, p.lse_dst,
+                     static_cast<T*>(p.out_final), lse_out, n_rh, p.Hq, static_cast<int>(L), p.task[a].n_q, n0, n1, p.part_stride_o,
+                     p.part_stride_lse);
 }
 
 }  // namespace
@@ -498,18 +592,9 @@ hipError_t launch_attn_tile(const AttnLaunch& p, int d, bool fp32, hipStream_t s
 }
 
 hipError_t launch_combine(const AttnLaunch& p, int d, bool fp32, int64_t L, float* lse_out, hipStream_t stream) {
-  // the tasks come heaviest first; the rows of the earlier one are those of the first query block
-  const int a = p.n_tasks > 1 && p.task[1].q_row0 < p.task[0].q_row0 ? 1 : 0;
-  const int n0 = p.n_split[a], n1 = p.n_tasks > 1 ? p.n_split[1 - a] : n0;
-  const int64_t row1 = p.task[a].n_q;
-  const int64_t n4 = p.batch * L * p.Hq * (d / 4), blocks = (n4 + 255) / 256;
-  if (blocks > INT_MAX) return hipErrorInvalidValue;
-  const dim3 grid(static_cast<unsigned>(blocks)), block(256);
-  if (fp32)
-    return TASP_LAUNCH((combine_kernel<float>), grid, block, stream, p.o_dst, p.lse_dst, static_cast<float*>(p.out_final), lse_out, n4,
-                       d / 4, p.Hq, static_cast<int>(L), static_cast<int>(row1), n0, n1, p.part_stride_o, p.part_stride_lse);
-  return TASP_LAUNCH((combine_kernel<__bf16>), grid, block, stream, p.o_dst, p.lse_dst, static_cast<__bf16*>(p.out_final), lse_out, n4,
-                     d / 4, p.Hq, static_cast<int>(L), static_cast<int>(row1), n0, n1, p.part_stride_o, p.part_stride_lse);
+  if (d == 64) return fp32 ? launch_combine_variant<float, 64>(p, L, lse_out, stream) : launch_combine_variant<__bf16, 64>(p, L, lse_out, stream);
+  if (d == 128) return fp32 ? launch_combine_variant<float, 128>(p, L, lse_out, stream) : launch_combine_variant<__bf16, 128>(p, L, lse_out, stream);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace tasp

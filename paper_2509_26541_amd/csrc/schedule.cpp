@@ -174,6 +174,39 @@ int step_segments(const tasp_schedule& s, int64_t S, int32_t mask_mode, int32_t 
   return arriving_ranges(s, S, mask_mode, order, step, q_block, out);
 }
 
+int all_step_segments(const tasp_schedule& s, int64_t S, int32_t mask_mode, int32_t order, int32_t q_block,
+                      std::vector<int32_t>* out) {
+  QueryBlock qb;
+  const int st = query_block(s, S, mask_mode, q_block, &qb);
+  if (st != TASP_OK) return st;
+  const bool causal = mask_mode == TASP_MASK_ZIGZAG_CAUSAL, ring_order = order == TASP_ORDER_RING;
+  const int64_t q_first = qb.pos0, q_last = qb.pos0 + qb.rows - 1;
+  const int64_t len = causal ? S / (2 * static_cast<int64_t>(s.n)) : S / s.n;   // of the block a piece is cut from
+  const int32_t m = ring_order ? 1 : s.n_rings;
+  std::vector<int64_t> bound(static_cast<size_t>(m) + 1);
+  for (int32_t i = 0; i <= m; ++i) bound[static_cast<size_t>(i)] = static_cast<int64_t>(i) * len / m;
+  out->reserve(static_cast<size_t>(s.n) * m * (causal ? 4 : 2));
+  for (int32_t step = 0; step < s.n; ++step) {
+    const size_t step_beg = out->size();
+    bool last_diag = false;
+    auto push = [&](int64_t a, int64_t b) {
+      if (a >= b || (causal && a > q_last)) return;       // empty, or hidden from every row of the block
+      const bool diag = causal && b - 1 > q_first;
+      if (out->size() > step_beg && out->back() == a && diag == last_diag) { out->back() = static_cast<int32_t>(b); return; }
+      out->push_back(static_cast<int32_t>(a));
+      out->push_back(static_cast<int32_t>(b));
+      last_diag = diag;
+    };
+    for (int32_t ring = 0; ring < m; ++ring) {
+      const int64_t src = ring_order ? ((s.rank - step) % s.n + s.n) % s.n : s.arrival[static_cast<size_t>(step) * m + ring];
+      const int64_t a = bound[static_cast<size_t>(ring)], b = bound[static_cast<size_t>(ring) + 1];
+      push(src * len + a, src * len + b);
+      if (causal) push(S - src * len - b, S - src * len - a);
+    }
+  }
+  return TASP_OK;
+}
+
 int step_key_ranges(const tasp_schedule& s, int64_t S, int32_t mask_mode, int32_t order, int32_t step,
                     std::vector<Segment>* out) {
   return arriving_ranges(s, S, mask_mode, order, step, -1, out);
