@@ -69,13 +69,15 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
   __shared__ int e_vbeg[kMaxSeg + 1], e_goff[kMaxSeg], e_n;      // dq: effective segments of this share of the keys
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, lq = lane & 31;
-  const int xs = wave & 1, yg = wave >> 1;
+  // strip of X rows and half of the Y tile, dealt differently in neighbouring workgroups: wavefront i runs on
+  // SIMD i, and strips and halves without rows are left out
+  const int xs = (wave ^ block) & 1, yg = (wave >> 1 ^ block >> 1) & 1;
   const int G = p.Hq / p.Hkv;
   const int64_t q_pitch = static_cast<int64_t>(p.Hq) * C::RB, k_pitch = static_cast<int64_t>(p.Hkv) * C::RB;
 
   // ---- the workgroup's X rows
   int bi, g, tsk = 0, share = 0, x_pos, x_lo = 0, x_hi = 0;      // position of the lane's X row, of the first and the last one
-  bool x_valid;
+  bool x_valid, idle;                                            // idle: no X row of the strip exists
   int64_t x_off;                                                 // byte offset of the lane's X row
   int64_t row_idx = 0;                                           // dq: (row, head) index of it
   if constexpr (!DKV) {
@@ -93,6 +95,7 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
     const int tile = p.causal ? (tsk ? tiles1 : tiles0) - 1 - rem / p.n_split : rem / p.n_split;   // more keys first
     const int m_all = tsk ? m1 : m0, m = tile * BX + xs * 32 + lq;
     x_valid = m < m_all;
+    idle = tile * BX + xs * 32 >= m_all;
     const int mc = x_valid ? m : m_all - 1, row = mc / G, hq = g * G + mc - row * G;
     const int pos0 = p.task[tsk].q_pos0;
     x_pos = p.causal ? pos0 + row : INT_MAX - 1;
@@ -114,6 +117,7 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
     };
     const int v = v0 + xs * 32 + lq;
     x_valid = v < total;
+    idle = v0 + xs * 32 >= total;
     x_pos = token_of(x_valid ? v : total - 1);
     x_lo = token_of(v0);
     x_hi = token_of(min(v0 + BX, total) - 1);
@@ -177,14 +181,22 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
   const unsigned char* Y1 = static_cast<const unsigned char*>(DKV ? p.q : p.k) + (DKV ? bi * p.q_bstride : bi * p.kv_bstride + static_cast<int64_t>(g) * D) * 4;
   const unsigned char* Y2 = static_cast<const unsigned char*>(DKV ? p.dout : p.v) + (DKV ? bi * p.q_bstride : bi * p.kv_bstride + static_cast<int64_t>(g) * D) * 4;
   int seg_j = -1, seg_end = 0, seg_off = 0;                      // dq: the segment of the thread's last row
+  // (in registers: a choice between two kernel arguments would become a load, and the wait for it would be one
+  // for the tile fetch in flight)
+  int row0_a = p.blk[0].row0, row0_b = p.blk[1].row0, pos0_a = p.blk[0].pos0, pos0_b = p.blk[1].pos0;
+  asm volatile("" : "+s"(row0_a), "+s"(row0_b), "+s"(pos0_a), "+s"(pos0_b));
   // dkv: pair v of the stream -> local row, head (v >= n_y: row 0 and position -1)
+  const float inv_g = 1.f / static_cast<float>(G);
   auto y_row = [&](int v, int& pos, int& hh) __attribute__((always_inline)) {
     const bool second = v >= y_cnt0;
-    const int m = second ? y_first[1] + v - y_cnt0 : y_first[0] + v, r = m / G;
+    const int m = second ? y_first[1] + v - y_cnt0 : y_first[0] + v;
+    int r = static_cast<int>(static_cast<float>(m) * inv_g);                   // m / G, exact after one correction either way
     hh = m - r * G;
+    if (hh < 0) { hh += G; --r; }
+    if (hh >= G) { hh -= G; ++r; }
     if (v >= n_y) { pos = -1; hh = 0; return 0; }
-    pos = p.causal ? (second ? p.blk[1].pos0 : p.blk[0].pos0) + r : INT_MAX - 1;
-    return (second ? p.blk[1].row0 : p.blk[0].row0) + r;
+    pos = p.causal ? (second ? pos0_b : pos0_a) + r : INT_MAX - 1;
+    return (second ? row0_b : row0_a) + r;
   };
   auto fetch = [&](int t, int stage) __attribute__((always_inline)) {
     unsigned char* dst = smem + stage * C::STAGE_BYTES + wave_u * 1024;
@@ -247,68 +259,94 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
     const int stage = t & 1;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();                 // tile t is complete; nobody reads the other stage any more
-    if (t + 1 < n_tiles) fetch(t + 1, stage ^ 1);
+    if (t + 1 < n_tiles) fetch(t + 1, stage ^ 1);    // (dealt out between the matrix instructions it spills at d = 128)
+    if (idle || t * BT + 32 * yg >= n_y) continue;
     const unsigned char* st1 = smem + stage * C::STAGE_BYTES;
     const unsigned char* st2 = st1 + C::TILE_BYTES;
+    // formed where they are used: held across the loop the fragment addresses are registers too many at d = 64
+    int rw = r_adr, wc = w_col;
+    asm volatile("" : "+v"(rw), "+v"(wc));
+    // The matrix instructions as four streams, their A operands read from LDS one or two steps ahead, and the
+    // vector work in the shadow of the ones that do not need it: p beside T2, ds beside acc2 (dq: beside acc1,
+    // one row ahead).  Left to itself it stood between the streams, where a lone wavefront's matrix pipe is idle
+    // (71 % busy at d = 128; this order: see the head of the file).
     f32x16 P = zero16(), E = zero16();
+    f32x4 fr_[2];
+    auto read_row = [&](auto jj) __attribute__((always_inline)) {              // stream of T1, then of T2
+      constexpr int J = decltype(jj)::value;
+      fr_[J % 2] = *reinterpret_cast<const f32x4*>((J < NJ ? st1 : st2) + (rw ^ (32 * (J % NJ))));
+    };
+    f32x4 nl = {0.f, 0.f, 0.f, 0.f};
+    static_for<2>(read_row);
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<2 * NJ>([&](auto jj) __attribute__((always_inline)) {
+      constexpr int J = decltype(jj)::value, j = J % NJ;
+      const f32x4 a = fr_[J % 2], x = __builtin_bit_cast(f32x4, J < NJ ? x1[j] : x2[j]);
+      if constexpr (J < NJ) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const f32x4 a = *reinterpret_cast<const f32x4*>(st1 + (r_adr ^ (32 * j)));
-      const f32x4 b = __builtin_bit_cast(f32x4, x1[j]);
+        for (int e = 0; e < 4; ++e) P = mfma(a[e], x[e], P);
+      } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) P = mfma(a[e], b[e], P);
-    }
+        for (int e = 0; e < 4; ++e) E = mfma(a[e], x[e], E);
+      }
+      if constexpr (J + 2 < 2 * NJ) read_row(std::integral_constant<int, J + 2>{});
+      if constexpr (J > NJ) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const f32x4 a = *reinterpret_cast<const f32x4*>(st2 + (r_adr ^ (32 * j)));
-      const f32x4 b = __builtin_bit_cast(f32x4, x2[j]);
+        for (int r = (J - NJ - 1) * (16 / NJ); r < (J - NJ) * (16 / NJ); ++r) P[r] = __builtin_amdgcn_exp2f(P[r]);
+      }
+      if constexpr (J >= NJ) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) E = mfma(a[e], b[e], E);
-    }
+        for (int r = (J - NJ) * (16 / NJ); r < (J - NJ + 1) * (16 / NJ); ++r) P[r] = __builtin_fmaf(P[r], c, DKV ? neg_lse2(nl[r % 4]) : x_nl);
+      }
+      if constexpr (DKV && J >= NJ - 1 && (J + 1 - NJ) * (16 / NJ) % 4 == 0 && J + 1 < 2 * NJ)     // lse of the four rows that come next
+        nl = *reinterpret_cast<const f32x4*>(&s_lse[stage][32 * yg + 8 * ((J + 1 - NJ) * (16 / NJ) / 4) + 4 * h]);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+#pragma unroll
+    for (int r = 16 - 16 / NJ; r < 16; ++r) P[r] = __builtin_amdgcn_exp2f(P[r]);
     const i32x4 mk = *reinterpret_cast<const i32x4*>(&s_msk[stage][0]);
-    const bool need_mask = __builtin_amdgcn_readfirstlane(mk[0] | mk[1] | mk[2] | mk[3]) != 0;
+    if (__builtin_amdgcn_readfirstlane(mk[0] | mk[1] | mk[2] | mk[3]) != 0) {
 #pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4) {
-      const int r0 = 32 * yg + 8 * i4 + 4 * h;
-      f32x4 nl, dl;
-      if constexpr (DKV) {
-        nl = *reinterpret_cast<const f32x4*>(&s_lse[stage][r0]);
-        dl = *reinterpret_cast<const f32x4*>(&s_del[stage][r0]);
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = 4 * i4 + e;
-        P[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(P[r], c, DKV ? neg_lse2(nl[e]) : x_nl));
-      }
-      if (need_mask) {
-        const i32x4 ps = *reinterpret_cast<const i32x4*>(&s_pos[stage][r0]);
+      for (int i4 = 0; i4 < 4; ++i4) {
+        const i32x4 ps = *reinterpret_cast<const i32x4*>(&s_pos[stage][32 * yg + 8 * i4 + 4 * h]);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           if (DKV ? x_pos > ps[e] : ps[e] > x_pos) P[4 * i4 + e] = 0.f;
       }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) E[4 * i4 + e] = P[4 * i4 + e] * (E[4 * i4 + e] - (DKV ? dl[e] : x_del));
     }
+    struct Piece { float v[NDB]; };
+    Piece piece[2];
+    auto read_piece = [&](auto kk) __attribute__((always_inline)) {            // stream of acc2 (dkv), then of acc1
+      constexpr int K = decltype(kk)::value, r = K % 16;
+      const unsigned char* at = (DKV && K < 16 ? st2 : st1) + w_row + (8 * (r / 4) + r % 4) * C::RB + (wc ^ ((8 * (r / 4 % 2) + r % 4) * 16));
+      if constexpr (NDB == 4) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(at);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      constexpr int kX = 16;
-      const int adr = w_row + (8 * (r / 4) + r % 4) * C::RB + (w_col ^ ((8 * (r / 4 % 2) + r % 4) * kX));
-#pragma unroll
-      for (int a = 0; a < NACC; ++a) {
-        const unsigned char* st = a == 0 ? st1 : st2;
-        float y[NDB];
-        if constexpr (NDB == 4) {
-          const f32x4 v = *reinterpret_cast<const f32x4*>(st + adr);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] = v[e];
-        } else {
-          const f32x2 v = *reinterpret_cast<const f32x2*>(st + adr);
-          y[0] = v[0]; y[1] = v[1];
-        }
-#pragma unroll
-        for (int db = 0; db < NDB; ++db) acc[a][db] = mfma(y[db], a == 0 ? E[r] : P[r], acc[a][db]);
+        for (int e = 0; e < 4; ++e) piece[K % 2].v[e] = v[e];
+      } else {
+        const f32x2 v = *reinterpret_cast<const f32x2*>(at);
+        piece[K % 2].v[0] = v[0]; piece[K % 2].v[1] = v[1];
       }
-    }
+    };
+    f32x4 dl = {0.f, 0.f, 0.f, 0.f};
+    static_for<2>(read_piece);
+    if constexpr (DKV) dl = *reinterpret_cast<const f32x4*>(&s_del[stage][32 * yg + 4 * h]);
+    else E[0] = P[0] * (E[0] - x_del);
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<16 * NACC>([&](auto kk) __attribute__((always_inline)) {
+      constexpr int K = decltype(kk)::value, r = K % 16, A = DKV && K < 16 ? 1 : 0;
+      const Piece y = piece[K % 2];
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) acc[A * (NACC - 1)][db] = mfma(y.v[db], A ? P[r] : E[r], acc[A * (NACC - 1)][db]);
+      if constexpr (K + 2 < 16 * NACC) read_piece(std::integral_constant<int, K + 2>{});
+      if constexpr (DKV) {
+        if constexpr (K < 16) E[r] = P[r] * (E[r] - dl[r % 4]);
+        if constexpr (K < 15 && r % 4 == 3) dl = *reinterpret_cast<const f32x4*>(&s_del[stage][32 * yg + 8 * ((r + 1) / 4) + 4 * h]);
+      } else if constexpr (K < 15) {
+        E[r + 1] = P[r + 1] * (E[r + 1] - x_del);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();                   // the stages are free: the second half of the Y rows hands its sums over
