@@ -313,6 +313,9 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_kernel(const BwdL
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]), "+v"(dof[ks]));
   asm volatile("" : "+v"(nl2), "+v"(nd));
+  f32x16 nd16;                       // what the dout.v accumulator starts from
+#pragma unroll
+  for (int i = 0; i < 16; ++i) nd16[i] = nd;
   for (int t = 0; t < n_tiles; ++t) {
     const int stage = t & 1;
     wait_all_loads();
@@ -343,11 +346,8 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_kernel(const BwdL
         S = mfma(ring[slot], qf[f], S);
       } else if constexpr (f < 2 * KS) {
         constexpr int ks = f - KS;
-        if constexpr (ks == 0) {
-#pragma unroll
-          for (int i = 0; i < 16; ++i) dP[i] = 0.f;
-        }
-        dP = mfma(ring[slot], dof[ks], dP);
+        if constexpr (ks == 0) dP = mfma(ring[slot], dof[0], nd16);     // (starts from -delta: an addition per value less)
+        else dP = mfma(ring[slot], dof[ks], dP);
         constexpr int per = 16 / KS;
 #pragma unroll
         for (int i = ks * per; i < (ks + 1) * per; ++i) S[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(S[i], c, nl2));
@@ -367,7 +367,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_kernel(const BwdL
         if constexpr (db == 0) {          // ds^T of the 16 keys of group j (registers 8 j .. 8 j + 7), packed to bf16
           float ds[8];
 #pragma unroll
-          for (int e = 0; e < 8; ++e) ds[e] = S[8 * j + e] * (dP[8 * j + e] + nd);
+          for (int e = 0; e < 8; ++e) ds[e] = S[8 * j + e] * dP[8 * j + e];
           ef[j] = u32x4{pack2(ds[0], ds[1]), pack2(ds[2], ds[3]), pack2(ds[4], ds[5]), pack2(ds[6], ds[7])};
         }
         dq[db] = mfma(ring[slot], __builtin_bit_cast(bf16x8, ef[j]), dq[db]);
