@@ -190,8 +190,14 @@ struct FwdPlan {
 constexpr int64_t kJoinRows = 4096;
 constexpr int64_t kMaxSplit = 32;    // shares of one tile
 
-// A batch of a few sequences is run like one of them, so that its results are those of separate calls.
-int64_t plan_batch(const AttnLaunch& lp) { return lp.batch <= 4 ? 1 : lp.batch; }
+// Sequences a call is planned for: one, where a few of them leave the chip idle together, so that the results
+// of such a batch are those of separate calls.
+int64_t plan_batch(int64_t batch, int64_t tiles_of_one) { return batch <= 4 && batch * tiles_of_one <= 128 ? 1 : batch; }
+int64_t plan_batch(const AttnLaunch& lp) {
+  int64_t tiles = 0;
+  for (int t = 0; t < lp.n_tasks; ++t) tiles += (static_cast<int64_t>(lp.task[t].n_q) * (lp.Hq / lp.Hkv) + tasp::kTileRows - 1) / tasp::kTileRows * lp.Hkv;
+  return plan_batch(lp.batch, tiles);
+}
 
 // Deals the keys of the query tiles of attn_tile_kernel to n_split[t] workgroups each; keys[t] = keys the
 // last row of task t sees.  A lone workgroup of the kernel uses about half a CU and several share one, so
@@ -217,7 +223,7 @@ void deal_keys(const AttnLaunch& lp, int d, bool fp32, const int64_t* keys, int6
     return total;
   };
   double best = -1;
-  for (int k = 0; k <= 6; ++k) {                  // k = 0: every tile in one share
+  for (int k = 0; k <= 8; ++k) {                  // k = 0: every tile in one share
     int64_t lo = least / step, hi = std::max(lo, (longest + step - 1) / step), n[tasp::kMaxTasks] = {1, 1};
     if (k == 0) lo = hi;
     else if (shares(hi * step, n) > 256 * k) continue;
@@ -495,8 +501,11 @@ BwdPlan plan_backward(const tasp_attn_bwd_args* b, const Shape& sh, const tasp::
   pl.joined = true;
   pl.table_bytes = table_bytes;
   const bool fp32 = b->dtype == TASP_DTYPE_FP32;
-  const int64_t B = sh.B <= 4 ? 1 : sh.B;       // as plan_batch
   const int64_t G = b->Hq / b->Hkv;
+  int64_t tiles_of_one = 0;
+  for (int t = 0; t < bp.n_tasks; ++t)
+    tiles_of_one += fp32 ? (bp.task[t].n_q * G + 63) / 64 * b->Hkv : static_cast<int64_t>((bp.task[t].n_q + 127) / 128) * b->Hq;
+  const int64_t B = plan_batch(sh.B, tiles_of_one);
   size_t used = bwd_front_bytes(b, sh) + table_bytes;
   auto room = [&](size_t each) { return each > 0 && ws_bytes > used ? static_cast<int64_t>((ws_bytes - used) / each) : 0; };
   // dk/dv: finer than by key tile where the estimate says that wins by more than 4 %, the launch that
@@ -515,10 +524,7 @@ BwdPlan plan_backward(const tasp_attn_bwd_args* b, const Shape& sh, const tasp::
       }
     used += 2 * pl.kv_bytes;
   }
-  int64_t tiles = 0;
-  for (int t = 0; t < bp.n_tasks; ++t)
-    tiles += fp32 ? (bp.task[t].n_q * G + 63) / 64 * b->Hkv * B : static_cast<int64_t>((bp.task[t].n_q + 127) / 128) * b->Hq * B;
-  pl.n_split = dq_split(tiles, 512, b->S, room(align_up(sh.o_bytes)));
+  pl.n_split = dq_split(tiles_of_one * B, 512, b->S, room(align_up(sh.o_bytes)));
   return pl;
 }
 size_t plan_bytes(const BwdPlan& pl, const tasp_attn_bwd_args* b, const Shape& sh) {
