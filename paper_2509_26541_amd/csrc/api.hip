@@ -177,11 +177,19 @@ struct FwdPlan {
   bool tile = false;                  // attn_tile_kernel
   int32_t n_split[tasp::kMaxTasks] = {1, 1};
   size_t table_bytes = 0;             // device memory for the segment lists, in front of the partial pairs
-  int32_t parts = 1;                  // partial pairs (the larger n_split)
-  size_t bytes(const Shape& sh) const {
-    return table_bytes + (parts > 1 ? static_cast<size_t>(parts) * (align_up(sh.o_bytes) + align_up(sh.lse_bytes)) : 0);
-  }
+  size_t part_bytes = 0;              // of the shares' pairs
 };
+
+// Bytes of one share's partial pairs of a task.
+size_t share_bytes(const AttnLaunch& lp, int t, int d) {
+  return static_cast<size_t>(lp.batch) * lp.task[t].n_q * lp.Hq * (d + 1) * sizeof(float);
+}
+// Bytes of all of them: per task with shares the outputs, then the lse, each part on its own 256 bytes.
+size_t all_share_bytes(const AttnLaunch& lp, int d, const int32_t* n) {
+  size_t sum = 0;
+  for (int t = 0; t < lp.n_tasks; ++t) sum += n[t] > 1 ? n[t] * share_bytes(lp, t, d) + 2 * kAlign : 0;
+  return sum;
+}
 
 // Local rows up to which the steps of a call are joined although the caller did not ask for it.  A
 // step's launch costs its set-up, the read and write of the running output (or of a partial pair) and
@@ -205,7 +213,7 @@ int64_t plan_batch(const AttnLaunch& lp) {
 // 256, 512, ... workgroups in all make them, each against its fixed cost (set-up, first fetches, epilogue: 4 us)
 // and the way of the partial pairs through memory.  (With as many shares as the work asks for, without
 // regard to whole rounds of the CUs, 4 heads of 128 over 4 096 of 32 768 tokens took 211 us against 179.)
-void deal_keys(const AttnLaunch& lp, int d, bool fp32, const int64_t* keys, int64_t most, int32_t* n_split) {
+void deal_keys(const AttnLaunch& lp, int d, bool fp32, const int64_t* keys, size_t room, int32_t* n_split) {
   const double per_us = (fp32 ? 7.0 : 72.0) * (d == 64 ? (fp32 ? 2.0 : 1.5) : 1.0);     // keys of a tile that a CU walks in a microsecond
   const int64_t step = fp32 ? 32 : 64, least = fp32 ? 64 : 128;
   const int64_t G = lp.Hq / lp.Hkv, B = plan_batch(lp);
@@ -217,7 +225,7 @@ void deal_keys(const AttnLaunch& lp, int d, bool fp32, const int64_t* keys, int6
   auto shares = [&](int64_t per_wg, int64_t (&n)[tasp::kMaxTasks]) {
     int64_t total = 0;
     for (int t = 0; t < lp.n_tasks; ++t) {
-      n[t] = std::max<int64_t>(1, std::min((keys[t] + per_wg - 1) / per_wg, most));
+      n[t] = std::max<int64_t>(1, std::min((keys[t] + per_wg - 1) / per_wg, kMaxSplit));
       total += tiles[t] * n[t];
     }
     return total;
@@ -232,10 +240,12 @@ void deal_keys(const AttnLaunch& lp, int d, bool fp32, const int64_t* keys, int6
       if (shares(mid * step, n) <= 256 * k) hi = mid; else lo = mid + 1;
     }
     const int64_t total = shares(hi * step, n);
+    const int32_t n32[tasp::kMaxTasks] = {static_cast<int32_t>(n[0]), static_cast<int32_t>(n[1])};
+    if (all_share_bytes(lp, d, n32) > room) continue;
     double one = 0, bytes = 0;
     for (int t = 0; t < lp.n_tasks; ++t) {
       one = std::max(one, static_cast<double>(keys[t]) / n[t]);
-      bytes += 8.0 * n[t] * lp.task[t].n_q * lp.Hq * B * d;
+      bytes += n[t] > 1 ? 8.0 * n[t] * lp.task[t].n_q * lp.Hq * B * d : 0;
     }
     const double rounds = std::max(1.8, std::ceil(total / 256.0));
     const double cost = (one + 4 * per_us) * rounds + (n[0] > 1 || n[1] > 1 ? (4 + bytes / 8e6) * per_us : 0);
@@ -283,22 +293,18 @@ bool tile_is_faster(const AttnLaunch& lp, int d, const int64_t* keys, const int3
 }
 
 // Decides from shapes alone (`js` holds the joined lists), within `ws_bytes` of workspace.
-FwdPlan plan_forward(const tasp_attn_args* a, const Shape& sh, const JoinedSteps& js, size_t ws_bytes) {
+FwdPlan plan_forward(const tasp_attn_args* a, const JoinedSteps& js, size_t ws_bytes) {
   FwdPlan pl;
   const bool fp32 = a->dtype == TASP_DTYPE_FP32;
   pl.joined = true;
   if (js.segments() > static_cast<size_t>(tasp::kPoolSeg)) pl.table_bytes = kFusedTableBytes;
   if (pl.table_bytes > ws_bytes) { pl.joined = false; return pl; }
-  const size_t pair = align_up(sh.o_bytes) + align_up(sh.lse_bytes);
-  const int64_t room = static_cast<int64_t>((ws_bytes - pl.table_bytes) / pair);
   int32_t n_split[tasp::kMaxTasks] = {1, 1};
-  deal_keys(js.all, a->d, fp32, js.keys, std::min(room, kMaxSplit), n_split);
+  deal_keys(js.all, a->d, fp32, js.keys, ws_bytes - pl.table_bytes, n_split);
   pl.tile = fp32 || tile_is_faster(js.all, a->d, js.keys, n_split);
   if (!pl.tile) return pl;
-  for (int t = 0; t < js.all.n_tasks; ++t) {
-    pl.n_split[t] = n_split[t];
-    pl.parts = std::max(pl.parts, n_split[t]);
-  }
+  for (int t = 0; t < js.all.n_tasks; ++t) pl.n_split[t] = n_split[t];
+  pl.part_bytes = all_share_bytes(js.all, a->d, n_split);
   return pl;
 }
 
@@ -584,8 +590,8 @@ size_t tasp_chunk_attn_best_workspace_bytes(const tasp_schedule_t* s, const tasp
     JoinedSteps js{};
     if (join_steps(s, a, &js) != TASP_OK) return need;
     // the same limit for every caller, so that the results do not depend on where the workspace comes from
-    const FwdPlan pl = plan_forward(a, sh, js, std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES));
-    return pl.joined ? std::max(need, pl.bytes(sh)) : need;
+    const FwdPlan pl = plan_forward(a, js, std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES));
+    return pl.joined ? std::max(need, pl.table_bytes + pl.part_bytes) : need;
   } catch (...) {
     return need;
   }
@@ -659,7 +665,7 @@ static int run_chunk_attn(const tasp_schedule_t* s, const tasp_attn_args* a, voi
       st = join_steps(s, a, &js);
       if (st != TASP_OK && a->fuse_steps) return st;
       FwdPlan pl;
-      if (st == TASP_OK) pl = plan_forward(a, sh, js, a->workspace != nullptr ? std::min<size_t>(a->workspace_bytes, std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES)) : 0);
+      if (st == TASP_OK) pl = plan_forward(a, js, a->workspace != nullptr ? std::min<size_t>(a->workspace_bytes, std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES)) : 0);
       if (pl.joined) {
         {
           Scope sc(pl.table_bytes > 0 ? prof : nullptr, Profiler::kOther);
@@ -668,21 +674,23 @@ static int run_chunk_attn(const tasp_schedule_t* s, const tasp_attn_args* a, voi
         }
         AttnLaunch& all = js.all;
         all.out_final = a->out; all.lse_dst = a->lse; all.merge = 0;
-        for (int t = 0; t < all.n_tasks; ++t) all.n_split[t] = pl.n_split[t];
-        if (pl.parts > 1) {
-          unsigned char* parts = static_cast<unsigned char*>(a->workspace) + pl.table_bytes;
-          all.part_stride_o = static_cast<int64_t>(align_up(sh.o_bytes) / sizeof(float));
-          all.part_stride_lse = static_cast<int64_t>(align_up(sh.lse_bytes) / sizeof(float));
-          all.o_dst = reinterpret_cast<float*>(parts);
-          all.lse_dst = reinterpret_cast<float*>(parts + pl.parts * align_up(sh.o_bytes));
+        size_t at = pl.table_bytes;
+        for (int t = 0; t < all.n_tasks; ++t) {
+          all.n_split[t] = pl.n_split[t];
+          if (pl.n_split[t] < 2) continue;
+          const size_t lse = pl.n_split[t] * share_bytes(all, t, a->d) / (a->d + 1);
+          all.part_o[t] = reinterpret_cast<float*>(static_cast<unsigned char*>(a->workspace) + at);
+          at += align_up(lse * a->d);
+          all.part_lse[t] = reinterpret_cast<float*>(static_cast<unsigned char*>(a->workspace) + at);
+          at += align_up(lse);
         }
         {
           Scope sc(prof, Profiler::kAttn);
           if (launch_attn(all, a, stream, pl.tile) != hipSuccess) return TASP_EHIP;
         }
-        if (pl.parts > 1) {
+        if (pl.part_bytes > 0) {
           Scope sc(prof, Profiler::kOther);
-          if (tasp::launch_combine(all, a->d, a->dtype == TASP_DTYPE_FP32, sh.L, a->lse, stream) != hipSuccess) return TASP_EHIP;
+          if (tasp::launch_combine(all, a->d, a->dtype == TASP_DTYPE_FP32, stream) != hipSuccess) return TASP_EHIP;
         }
         return TASP_OK;
       }

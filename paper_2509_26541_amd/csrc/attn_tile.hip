@@ -423,8 +423,12 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
       return 2 * (8 * (2 * Q / 4) + 4 * h + (2 * Q) % 4);
     }
   };
-  if (p.merge == 0 && (p.part_stride_o != 0 || p.out_final == nullptr)) {
-    float* od = p.o_dst + share * p.part_stride_o + ooff;       // (stride 0: one share)
+  if (p.merge == 0 && (ns > 1 || p.out_final == nullptr)) {
+    // a share's pair, or the partial pair of a step
+    const int64_t n_q = second ? t1.n_q : t0.n_q;
+    const int64_t rh = ns > 1 ? ((static_cast<int64_t>(share) * p.batch + bi) * n_q + row) * p.Hq + hq : 0;
+    float* od = ns > 1 ? (second ? p.part_o[1] : p.part_o[0]) + rh * D : p.o_dst + ooff;
+    float* ld = ns > 1 ? (second ? p.part_lse[1] : p.part_lse[0]) + rh : p.lse_dst + loff;
     static_for<D / 8>([&](auto qq) __attribute__((always_inline)) {
       f32x4 x;
       const int col = quad(qq, x);
@@ -432,7 +436,7 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
       for (int e = 0; e < 4; ++e) x[e] *= wb;
       *reinterpret_cast<f32x4*>(od + col) = x;
     });
-    if (h == 0) p.lse_dst[share * p.part_stride_lse + loff] = lse_new;
+    if (h == 0) *ld = lse_new;
   } else if (p.merge == 0) {
     T* od = static_cast<T*>(p.out_final) + ooff;
     static_for<D / 8>([&](auto qq) __attribute__((always_inline)) {
@@ -495,19 +499,31 @@ hipError_t launch_tile_variant(const AttnLaunch& p, hipStream_t stream) {
 // SPREAD, for more than four shares: a wavefront per (row, head), the shares dealt to its 256 / D groups of
 // lanes, eight of a lane's shares requested at once, so that a row costs one or two trips to memory (a share
 // at a time, 16 shares of 1 024 rows took 7 us; now 4).  Otherwise a lane takes all shares of its columns.
-// Rows [0, row1) belong to the first query block (n0 shares), the rest to the second.
+// The rows of every task with shares, one task behind the other.
+struct CombineTask {
+  const float* o;          // [n, B, n_q, heads, D]
+  const float* lse;
+  int32_t n, n_q, row0;
+  int64_t n_rh;            // B n_q heads
+};
+struct CombineTasks { CombineTask t[kMaxTasks]; };
+
 template <typename T, int D, bool SPREAD>
-__global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ o_part, const float* __restrict__ lse_part,
-                                                      T* __restrict__ out, float* __restrict__ lse_out, int64_t n_rh,
-                                                      int heads, int L, int row1, int n0, int n1, int64_t stride_o, int64_t stride_lse) {
+__global__ __launch_bounds__(256) void combine_kernel(const CombineTasks tasks, T* __restrict__ out, float* __restrict__ lse_out, int heads, int L) {
   constexpr int PIECES = D / 4, GROUPS = SPREAD ? 64 / PIECES : 1, AT_ONCE = SPREAD ? 8 : 4;
   const int lane = threadIdx.x & 63, c = lane % PIECES, grp = SPREAD ? lane / PIECES : 0;
-  const int64_t rh = SPREAD ? static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6)
-                            : (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) / PIECES;
-  if (rh >= n_rh) return;
-  const int n = static_cast<int>(rh / heads % L) < row1 ? n0 : n1;
-  const float* op = o_part + rh * D + 4 * c;
-  const float* lp = lse_part + rh;
+  int64_t i = SPREAD ? static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6)
+                     : (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) / PIECES;
+  const bool second = i >= tasks.t[0].n_rh;
+  if (second) i -= tasks.t[0].n_rh;
+  const int64_t n_rh = second ? tasks.t[1].n_rh : tasks.t[0].n_rh;
+  if (i >= n_rh) return;
+  const int n = second ? tasks.t[1].n : tasks.t[0].n, n_q = second ? tasks.t[1].n_q : tasks.t[0].n_q, row0 = second ? tasks.t[1].row0 : tasks.t[0].row0;
+  const int64_t stride_lse = n_rh, stride_o = n_rh * D;
+  const int64_t bi = i / (static_cast<int64_t>(n_q) * heads);
+  const int64_t rh = i + (bi * (L - n_q) + row0) * heads;              // among the call's (row, head) pairs
+  const float* op = (second ? tasks.t[1].o : tasks.t[0].o) + i * D + 4 * c;
+  const float* lp = (second ? tasks.t[1].lse : tasks.t[0].lse) + i;
   float mx = -__builtin_inff(), den = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   for (int s0 = grp; s0 < n; s0 += GROUPS * AT_ONCE) {
@@ -567,20 +583,23 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ 
 }
 
 template <typename T, int D>
-hipError_t launch_combine_variant(const AttnLaunch& p, int64_t L, float* lse_out, hipStream_t stream) {
-  // the tasks come heaviest first; the rows of the earlier one are those of the first query block
-  const int a = p.n_tasks > 1 && p.task[1].q_row0 < p.task[0].q_row0 ? 1 : 0;
-  const int n0 = p.n_split[a], n1 = p.n_tasks > 1 ? p.n_split[1 - a] : n0;
-  const bool spread = std::max(n0, n1) > 4;
-  const int64_t n_rh = p.batch * L * p.Hq, per_block = spread ? 4 : 1024 / D, blocks = (n_rh + per_block - 1) / per_block;
+hipError_t launch_combine_variant(const AttnLaunch& p, hipStream_t stream) {
+  CombineTasks tasks{};
+  int k = 0, most = 0;
+  int64_t n_rh = 0;
+  for (int t = 0; t < p.n_tasks; ++t) {
+    if (p.n_split[t] < 2) continue;
+    CombineTask& c = tasks.t[k++];
+    c = {p.part_o[t], p.part_lse[t], p.n_split[t], p.task[t].n_q, p.task[t].q_row0, static_cast<int64_t>(p.batch) * p.task[t].n_q * p.Hq};
+    n_rh += c.n_rh;
+    most = std::max(most, c.n);
+  }
+  if (n_rh == 0) return hipSuccess;
+  const int64_t L = p.lse_bstride / p.Hq, per_block = most > 4 ? 4 : 1024 / D, blocks = (n_rh + per_block - 1) / per_block;
   if (blocks > INT_MAX) return hipErrorInvalidValue;
-  if (!spread)
-    return TASP_LAUNCH((combine_kernel<T, D, false>), dim3(static_cast<unsigned>(blocks)), dim3(256), stream, p.o_dst, p.lse_dst,
-                       static_cast<T*>(p.out_final), lse_out, n_rh, p.Hq, static_cast<int>(L), p.task[a].n_q, n0, n1, p.part_stride_o,
-                       p.part_stride_lse);
-  return TASP_LAUNCH((combine_kernel<T, D, true>), dim3(static_cast<unsigned>(blocks)), dim3(256), stream, p.o_dst, p.lse_dst,
-                     static_cast<T*>(p.out_final), lse_out, n_rh, p.Hq, static_cast<int>(L), p.task[a].n_q, n0, n1, p.part_stride_o,
-                     p.part_stride_lse);
+  const dim3 grid(static_cast<unsigned>(blocks));
+  if (most > 4) return TASP_LAUNCH((combine_kernel<T, D, true>), grid, dim3(256), stream, tasks, static_cast<T*>(p.out_final), p.lse_dst, p.Hq, static_cast<int>(L));
+  return TASP_LAUNCH((combine_kernel<T, D, false>), grid, dim3(256), stream, tasks, static_cast<T*>(p.out_final), p.lse_dst, p.Hq, static_cast<int>(L));
 }
 
 }  // namespace
@@ -591,9 +610,9 @@ hipError_t launch_attn_tile(const AttnLaunch& p, int d, bool fp32, hipStream_t s
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_combine(const AttnLaunch& p, int d, bool fp32, int64_t L, float* lse_out, hipStream_t stream) {
-  if (d == 64) return fp32 ? launch_combine_variant<float, 64>(p, L, lse_out, stream) : launch_combine_variant<__bf16, 64>(p, L, lse_out, stream);
-  if (d == 128) return fp32 ? launch_combine_variant<float, 128>(p, L, lse_out, stream) : launch_combine_variant<__bf16, 128>(p, L, lse_out, stream);
+hipError_t launch_combine(const AttnLaunch& p, int d, bool fp32, hipStream_t stream) {
+  if (d == 64) return fp32 ? launch_combine_variant<float, 64>(p, stream) : launch_combine_variant<__bf16, 64>(p, stream);
+  if (d == 128) return fp32 ? launch_combine_variant<float, 128>(p, stream) : launch_combine_variant<__bf16, 128>(p, stream);
   return hipErrorInvalidValue;
 }
 

@@ -48,10 +48,11 @@ struct AttnLaunch {
   int32_t n_items;    // work items of the launch, for persistent workgroups; filled in by the launcher
   void* out_final;    // not null: the rows are final and go here in the inputs' type, not to o_dst (merge = 0)
   // attn_tile_kernel: task t's keys are dealt to n_split[t] workgroups per query tile.  Where that is
-  // more than one, split i leaves its normalised pair in o_dst + i part_stride_o and lse_dst + i
-  // part_stride_lse for launch_combine.
+  // more than one, share i leaves its normalised pair in part_o[t], part_lse[t] ([n_split, B, n_q, Hq(, d)],
+  // the task's rows only) for launch_combine; tasks with one share write their rows themselves.
   int32_t n_split[kMaxTasks];
-  int64_t part_stride_o, part_stride_lse;
+  float* part_o[kMaxTasks];
+  float* part_lse[kMaxTasks];
   int32_t all_steps;  // the steps of the call are joined in this launch
   int32_t pool[2 * kPoolSeg];
 };
@@ -128,8 +129,8 @@ inline hipError_t note_hip(hipError_t e) {
 // Implemented in attn_bf16.hip / attn_tile.hip / merge.hip.  Each returns a hipError_t from the launch.
 hipError_t launch_attn_bf16(const AttnLaunch& p, int d, hipStream_t stream);
 hipError_t launch_attn_tile(const AttnLaunch& p, int d, bool fp32, hipStream_t stream);
-// After a launch_attn_tile with several shares: out_final and lse_out from the pairs of the shares.
-hipError_t launch_combine(const AttnLaunch& p, int d, bool fp32, int64_t L, float* lse_out, hipStream_t stream);
+// After a launch_attn_tile with several shares: the rows of out_final and lse_dst from the pairs of the shares.
+hipError_t launch_combine(const AttnLaunch& p, int d, bool fp32, hipStream_t stream);
 // rows [row0, row0 + rows) of every one of `batch` sequences of L rows each
 hipError_t launch_merge(float* o_acc, float* lse_acc, const float* o_part, const float* lse_part,
                         int64_t row0, int64_t rows, int32_t heads, int32_t d, int32_t batch, int64_t L,
