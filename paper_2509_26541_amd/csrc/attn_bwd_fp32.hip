@@ -46,6 +46,12 @@ __device__ inline f32x16 zero16() {
 }
 __device__ inline f32x16 mfma(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
 
+__device__ inline float wave_sum(float x) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
+  return x;
+}
+
 // Columns of register quad Q of an accumulator set (block c, row i of block = column NDB i + c).
 template <int NDB, int Q>
 __device__ inline int quad(const f32x16 (&o)[NDB], int h, f32x4& x) {
@@ -362,7 +368,10 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
           hand[((a * NDB + db) * 4 + i4) * 64] = f32x4{acc[a][db][4 * i4], acc[a][db][4 * i4 + 1], acc[a][db][4 * i4 + 2], acc[a][db][4 * i4 + 3]};
   }
   __syncthreads();
-  if (yg == 1 || !x_valid) return;
+  if (yg == 1) return;
+  // An infinity or NaN of a pair that the mask leaves out, or of a row that saw no key, comes to an X row as 0 times
+  // that.  Rows whose sums are not finite are left out here and walked for themselves below, over the pairs they have.
+  float z = 0.f;
 #pragma unroll
   for (int a = 0; a < NACC; ++a)
 #pragma unroll
@@ -371,9 +380,16 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
       for (int i4 = 0; i4 < 4; ++i4) {
         const f32x4 o = hand[((a * NDB + db) * 4 + i4) * 64];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[a][db][4 * i4 + e] += o[e];
+        for (int e = 0; e < 4; ++e) {
+          acc[a][db][4 * i4 + e] += o[e];
+          z = __builtin_fmaf(acc[a][db][4 * i4 + e], 0.f, z);
+        }
       }
-  if constexpr (DKV) {
+  const unsigned long long odd = __builtin_amdgcn_ballot_w64(x_valid && !(z == 0.f));
+  unsigned again = static_cast<unsigned>(odd) | static_cast<unsigned>(odd >> 32);          // bit i: row i of the strip
+  if (!x_valid || (again >> lq & 1)) {
+    // nothing, or below
+  } else if constexpr (DKV) {
     float* dk = reinterpret_cast<float*>(static_cast<unsigned char*>(p.dk) + x_off);
     float* dv = reinterpret_cast<float*>(static_cast<unsigned char*>(p.dv) + x_off);
     static_for<D / 8>([&](auto qq) __attribute__((always_inline)) {
@@ -396,6 +412,57 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
       for (int e = 0; e < 4; ++e) a[e] = __builtin_fmaf(a[e], p.scale, old[e]);
       *reinterpret_cast<f32x4*>(dq + col) = a;
     });
+  }
+  constexpr int CPL = D / 64;
+  while (again != 0) {               // a wavefront per row, a pair at a time: as slow as it is rare
+    const int src = __builtin_ctz(again);
+    again &= again - 1;
+    const int pos_a = __shfl(x_pos, src);
+    const int64_t at = (static_cast<int64_t>(__shfl(static_cast<int>(x_off >> 32), src)) << 32 | static_cast<unsigned>(__shfl(static_cast<int>(x_off), src))) / 4 + lane;
+    float xa[CPL], xb[CPL], sa[CPL], sb[CPL];
+#pragma unroll
+    for (int e = 0; e < CPL; ++e) {
+      xa[e] = static_cast<const float*>(DKV ? p.k : p.q)[at + 64 * e];
+      xb[e] = static_cast<const float*>(DKV ? p.v : p.dout)[at + 64 * e];
+      sa[e] = sb[e] = 0.f;
+    }
+    auto pair = [&](int64_t y, float nl, float del) __attribute__((always_inline)) {       // y: of the Y row, in floats
+      float ya[CPL], yb[CPL], s1 = 0.f, s2 = 0.f;
+#pragma unroll
+      for (int e = 0; e < CPL; ++e) {
+        ya[e] = reinterpret_cast<const float*>(Y1)[y + lane + 64 * e];
+        yb[e] = reinterpret_cast<const float*>(Y2)[y + lane + 64 * e];
+        s1 = __builtin_fmaf(xa[e], ya[e], s1);
+        s2 = __builtin_fmaf(xb[e], yb[e], s2);
+      }
+      const float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(wave_sum(s1), c, nl)), ds = pr * (wave_sum(s2) - del);
+#pragma unroll
+      for (int e = 0; e < CPL; ++e) {
+        sa[e] = __builtin_fmaf(ds, ya[e], sa[e]);
+        sb[e] = __builtin_fmaf(pr, yb[e], sb[e]);
+      }
+    };
+    if constexpr (!DKV) {
+      const float nl = __shfl(x_nl, src), del = __shfl(x_del, src);
+      for (int j = 0; j < e_n && nl > -__builtin_inff(); ++j)
+        for (int v = e_vbeg[j]; v < e_vbeg[j + 1] && v + e_goff[j] <= pos_a; ++v) pair((v + e_goff[j]) * (k_pitch / 4), nl, del);
+      float* dq = (p.n_split > 1 ? p.part_dq + share * p.part_stride : p.dq_acc) + at;
+#pragma unroll
+      for (int e = 0; e < CPL; ++e) dq[64 * e] = __builtin_fmaf(sa[e], p.scale, p.accumulate ? dq[64 * e] : 0.f);
+    } else {
+      for (int b = 0; b < p.n_blk; ++b)
+        for (int r = p.causal ? max(0, pos_a - p.blk[b].pos0) : 0; r < p.blk[b].n; ++r)
+          for (int hh = 0; hh < G; ++hh) {
+            const int64_t rh = static_cast<int64_t>(p.blk[b].row0 + r) * p.Hq + g * G + hh;
+            const float nl = neg_lse2(p.lse[bi * p.lse_bstride + rh]);
+            if (nl > -__builtin_inff()) pair(rh * D, nl, p.delta[bi * p.lse_bstride + rh]);
+          }
+#pragma unroll
+      for (int e = 0; e < CPL; ++e) {
+        static_cast<float*>(p.dk)[at + 64 * e] = sa[e] * p.scale;
+        static_cast<float*>(p.dv)[at + 64 * e] = sb[e];
+      }
+    }
   }
 }
 

@@ -227,7 +227,9 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
     for (int i = 0; i < C::PASSES; ++i) {
       const int r = fr + C::RPP * i;
       last = max(last, tok[i]);
-      const unsigned key = static_cast<unsigned>(min(tok[i], p.last_key));   // rows past the end fetch some key and are masked
+      // rows past the end fetch the first key and are masked; every row sees that one, so nothing it holds reaches
+      // a row that it should not (0 times infinity)
+      const unsigned key = tok[i] == INT_MAX ? 0u : static_cast<unsigned>(tok[i]);
       if constexpr (F32) {                                          // tensors may exceed what a 32-bit offset reaches
         const unsigned long long off = static_cast<unsigned long long>(key) * row_bytes;
         global_to_lds_16_far(Kg + off + C::swz_k(r, fu) * 16, dst + i * NTHREADS * 16);
@@ -403,7 +405,19 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
   const bool seen = l_tot > 0.f;
   float wb = seen && r_tot > 0.f ? 1.f / r_tot : 0.f;
   float lse_new = seen ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -__builtin_inff();
-  if (!q_valid) return;
+  // fp32: an infinity or NaN of a key that a row of the tile does not see comes to it as 0 times that.  Rows whose
+  // sums are not finite are left out here and walked for themselves below, over the keys they see.
+  unsigned again = 0;                              // bit i: row i of the strip
+  if constexpr (F32) {
+    float z = 0.f;
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) z = __builtin_fmaf(o[db][i], 0.f, z);
+    const unsigned long long odd = __builtin_amdgcn_ballot_w64(q_valid && !(z == 0.f));
+    again = static_cast<unsigned>(odd) | static_cast<unsigned>(odd >> 32);
+  }
+  const bool store = q_valid && !(again >> lq & 1);
   const int64_t ooff = bi * p.o_bstride + (static_cast<int64_t>(q_row0 + row) * p.Hq + hq) * D;
   const int64_t loff = bi * p.lse_bstride + static_cast<int64_t>(q_row0 + row) * p.Hq + hq;
   // columns of register quad q of the lane: bf16 block q / 4, 32 (q / 4) + 8 (q % 4) + 4 h; fp32 d = 128
@@ -423,7 +437,9 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
       return 2 * (8 * (2 * Q / 4) + 4 * h + (2 * Q) % 4);
     }
   };
-  if (p.merge == 0 && (ns > 1 || p.out_final == nullptr)) {
+  if (!store) {
+    // nothing, or below
+  } else if (p.merge == 0 && (ns > 1 || p.out_final == nullptr)) {
     // a share's pair, or the partial pair of a step
     const int64_t n_q = second ? t1.n_q : t0.n_q;
     const int64_t rh = ns > 1 ? ((static_cast<int64_t>(share) * p.batch + bi) * n_q + row) * p.Hq + hq : 0;
@@ -476,6 +492,75 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
       *reinterpret_cast<f32x4*>(od + col) = x;
     });
     if (h == 0) p.lse_dst[loff] = lse_new;      // (the lane of the other half has read the old one: same wavefront)
+  }
+  if constexpr (F32) {
+    while (again != 0) {                           // a wavefront per row, a key per lane: as slow as it is rare
+      const int src = __builtin_ctz(again);
+      again &= again - 1;
+      const int row_a = __shfl(row, src), hq_a = __shfl(hq, src), pos_a = __shfl(q_pos, src);
+      const int64_t rh_a = static_cast<int64_t>(q_row0 + row_a) * p.Hq + hq_a;
+      const float* qa = static_cast<const float*>(p.q) + bi * p.q_bstride + rh_a * D;
+      float m_a = -__builtin_inff(), l_a = 0.f, acc[D / 64];
+#pragma unroll
+      for (int e = 0; e < D / 64; ++e) acc[e] = 0.f;
+      for (int v0 = 0; v0 < n_keys; v0 += 64) {
+        const int v = v0 + lane;
+        int lo = 0, n = n_eff;                     // as in locate
+        while (n > 1) {
+          const int half = n >> 1;
+          if (e_vbeg[lo + half] <= v) lo += half;
+          n -= half;
+        }
+        const int tok = v < n_keys ? v + e_goff[lo] : INT_MAX;
+        const bool sees = tok <= pos_a;
+        unsigned long long todo = __builtin_amdgcn_ballot_w64(sees);
+        if (todo == 0) continue;
+        float sc = -__builtin_inff();
+        if (sees) {
+          const float* kr = reinterpret_cast<const float*>(Kg + static_cast<unsigned long long>(tok) * row_bytes);
+          float dot = 0.f;
+          for (int e = 0; e < D; ++e) dot = __builtin_fmaf(qa[e], kr[e], dot);
+          sc = dot * c;
+        }
+        float m_new = fmaxf(m_a, sc);
+#pragma unroll
+        for (int s = 32; s >= 1; s >>= 1) m_new = fmaxf(m_new, __shfl_xor(m_new, s));
+        const float alpha = fast_exp2(m_a - m_new), pr = sees ? fast_exp2(sc - m_new) : 0.f;
+        float sum = pr;
+#pragma unroll
+        for (int s = 32; s >= 1; s >>= 1) sum += __shfl_xor(sum, s);
+        m_a = m_new;
+        l_a = l_a * alpha + sum;
+#pragma unroll
+        for (int e = 0; e < D / 64; ++e) acc[e] *= alpha;
+        for (; todo != 0; todo &= todo - 1) {
+          const int j = __builtin_ctzll(todo);
+          const float pj = __shfl(pr, j);
+          const float* vr = reinterpret_cast<const float*>(Vg + static_cast<unsigned long long>(__shfl(tok, j)) * row_bytes);
+#pragma unroll
+          for (int e = 0; e < D / 64; ++e) acc[e] = __builtin_fmaf(pj, vr[lane + 64 * e], acc[e]);
+        }
+      }
+      float wn = l_a > 0.f ? 1.f / l_a : 0.f, wo = 0.f, lse_a = l_a > 0.f ? (m_a + __builtin_amdgcn_logf(l_a)) * kLn2 : -__builtin_inff();
+      const int64_t part = ns > 1 ? (static_cast<int64_t>(share) * p.batch + bi) * (second ? t1.n_q : t0.n_q) * p.Hq + static_cast<int64_t>(row_a) * p.Hq + hq_a : 0;
+      float* od = ns > 1 ? (second ? p.part_o[1] : p.part_o[0]) + part * D
+                         : (p.out_final != nullptr ? static_cast<float*>(p.out_final) : p.o_dst) + bi * p.o_bstride + rh_a * D;
+      float* ld = ns > 1 ? (second ? p.part_lse[1] : p.part_lse[0]) + part : p.lse_dst + bi * p.lse_bstride + rh_a;
+      if (p.merge != 0) {
+        const float lse_old = *ld, mxl = fmaxf(lse_old, lse_a);
+        const bool some = mxl > -__builtin_inff();
+        const float ea = some ? __expf(lse_old - mxl) : 0.f, eb = some ? __expf(lse_a - mxl) : 0.f, rden = some ? 1.f / (ea + eb) : 0.f;
+        wo = ea * rden;
+        wn *= eb * rden;
+        lse_a = some ? mxl + __logf(ea + eb) : lse_a;
+      }
+#pragma unroll
+      for (int e = 0; e < D / 64; ++e) {
+        const float mine = acc[e] * wn;
+        od[lane + 64 * e] = p.merge != 0 ? __builtin_fmaf(wo, od[lane + 64 * e], mine) : mine;
+      }
+      if (lane == 0) *ld = lse_a;
+    }
   }
 }
 

@@ -130,3 +130,57 @@ def test_bf16_backward_every_element(tb, case):
             err = np.abs(g.float().cpu().numpy().astype(np.float64) - r)
             worst = float((err / (np.abs(r) / 128 + np.abs(r).max() / 256 + 1e-30)).max())
             assert worst <= 1.0, (name, nm, nbytes, worst)
+
+
+NOT_FINITE = [
+    # name, N, rank, S, Hq, Hkv, d
+    ("shares", 8, 3, 16 * 75, 4, 2, 64),
+    ("tile_edges", 4, 1, 8 * 97, 3, 1, 128),
+    ("not_joined", 32, 17, 64 * 33, 2, 1, 64),                               # step by step, folded into the running pair
+]
+
+
+@pytest.mark.parametrize("case", NOT_FINITE, ids=[c[0] for c in NOT_FINITE])
+def test_fp32_what_is_not_seen_has_no_part(tb, case):
+    """Infinities and NaN reach only the rows and keys of the pairs that the mask leaves."""
+    from oracle import schedule as sch
+    name, n, rank, S, Hq, Hkv, d = case
+    w = wl.Workload(name, n, rank, S, Hq, Hkv, d, "fp32", wl.ZIGZAG_CAUSAL, seed=wl.BASE_SEED + 9100 + S)
+    q, k, v = wl.make_qkv(w)
+    do = wl.make_dout(w)
+    pos = np.asarray(sch.local_positions(n, rank, S, wl.ZIGZAG_CAUSAL))
+    s = tb.tasp_schedule(n, rank)
+    half = S // (2 * n)
+    t1, t2 = int(pos[half + half // 3]), int(pos[half // 2])                 # in a diagonal tile of each query block
+    kp, vp = k.clone(), v.clone()
+    vp[t1], vp[t2, :, 1] = float("nan"), float("inf")
+    kp[S - 1, :, 0] = float("nan")                                           # seen by the last row of all only, if by one here
+    ref_o, ref_l = oracle_rows(w, q, k, v, range(w.L))
+    seen_v = pos >= min(t1, t2)
+    seen_k = pos >= S - 1
+    for fuse in (False, True):
+        out, lse = tb.tasp_chunk_attn(q.cuda(), kp.cuda(), vp.cuda(), s, w.mask_mode, fuse_merge=fuse)
+        out, lse = out.cpu().numpy(), lse.cpu().numpy()
+        assert max_abs(out[~seen_v], ref_o[~seen_v]) <= 1e-4, (name, fuse)
+        assert max_abs(lse[~seen_k], ref_l[~seen_k]) <= 1e-4, (name, fuse)
+        assert not np.isfinite(out[seen_v]).all(axis=-1).any()
+        assert np.isposinf(out[(pos >= t2) & (pos < t1)][..., 1]).all()
+
+    # backward: the same keys, an upstream gradient that overflowed, and a row that saw no key
+    out, lse = tb.tasp_chunk_attn(q.cuda(), k.cuda(), v.cuda(), s, w.mask_mode)
+    r_inf, r_dead = half // 4, half + half // 2
+    clean = do.clone()
+    clean[[r_inf, r_dead]] = 0.0
+    ref = oracle_grads(w, q, k, v, clean)
+    do[r_inf] = float("inf")
+    out[r_dead], lse[r_dead] = float("nan"), float("-inf")
+    kp[t2] = float("nan")
+    dq, dk, dv = (g.cpu().numpy() for g in tb.tasp_chunk_attn_bwd(q.cuda(), kp.cuda(), vp.cuda(), out, lse, do.cuda(), s, w.mask_mode))
+    keys = np.arange(S)
+    rows = (pos < min(t1, t2)) & (np.arange(w.L) != r_inf)
+    rows[r_dead] = True
+    cols = (keys > pos[r_inf]) & ~np.isin(keys, (t1, t2, S - 1))
+    for nm, g, r, at in (("dq", dq, ref[0], rows), ("dk", dk, ref[1], cols), ("dv", dv, ref[2], cols)):
+        err = float(np.abs(g[at].astype(np.float64) - r[at]).max())
+        assert err <= 1e-4 * max(1.0, float(np.abs(r).max())), (name, nm, err)
+    assert not np.isfinite(dv[: pos[r_inf] + 1]).any()
