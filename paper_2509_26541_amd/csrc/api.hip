@@ -375,7 +375,7 @@ int validate_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args* b, tasp_att
   *a = as_forward(b);
   int st = validate(s, a, sh);
   if (st != TASP_OK) return st;
-  if (b->fuse_steps && b->dtype != TASP_DTYPE_BF16) return TASP_EUNSUPPORTED_SHAPE;   // the plain fp32 backward path walks step by step
+  if (b->fuse_steps && b->dtype != TASP_DTYPE_BF16) return TASP_EUNSUPPORTED_SHAPE;   // refused; with few local rows its steps are joined anyway
   if (b->out == nullptr || b->lse == nullptr || b->dout == nullptr || b->dq == nullptr || b->dk == nullptr ||
       b->dv == nullptr)
     return TASP_EINVAL;

@@ -15,7 +15,7 @@
 //
 // What bounds it: the matrix pipe, 64 cycles an instruction, which leaves the issue slots for the rest,
 // and in short calls the unequal work of the dk/dv workgroups under the causal mask.  Measured, whole
-// call: 8 heads of 64, 514 of 6 168 tokens, causal, 161 us against 4 980 with a wavefront per row.
+// call: 8 heads of 64, 514 of 6 168 tokens, causal, 144 us against 5 010 with a wavefront per row.
 #include <hip/hip_runtime.h>
 
 #include <climits>

@@ -19,10 +19,10 @@
 // leaves room for everything else a SIMD has to issue); bf16 the issue slots (1 330 of the 1 450 cycles
 // a SIMD takes for 32 rows by 64 keys at d = 64), and in the shortest calls the launch, the set-up and
 // the latency of the first tiles.  Measured, whole calls:
-//   fp32, 16 heads of 128, 2 048 of 16 384 tokens, causal: 1.16 ms (118 TFLOP/s of the 152 a large fp32
+//   fp32, 16 heads of 128, 2 048 of 16 384 tokens, causal: 1.11 ms (124 TFLOP/s of the 152 a large fp32
 //     product reaches) against 20.1 ms with a wavefront per query row;
-//   fp32, 4 heads of 64, 256 of 1 024 tokens: 17 us against 309;
-//   bf16, 8 heads of 128, 512 of 4 096 tokens: 24 us against 117 with the large kernel on 16 CUs (a workgroup of
+//   fp32, 4 heads of 64, 256 of 1 024 tokens: 16 us against 308;
+//   bf16, 8 heads of 128, 512 of 4 096 tokens: 25 us against 117 with the large kernel on 16 CUs (a workgroup of
 //     it: set-up 2.8 us, first tile 1.3, four tiles 8.4, epilogue 2.3);
 //   bf16, 128 sequences of 3 072 tokens, 20 heads of 64: 0.71 ms against 0.91 with the large kernel,
 //     which pads 192 rows to 256 and searches for the rows of 27-token sub-chunks in every tile.
