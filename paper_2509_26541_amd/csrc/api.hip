@@ -665,7 +665,9 @@ static int run_chunk_attn(const tasp_schedule_t* s, const tasp_attn_args* a, voi
       st = join_steps(s, a, &js);
       if (st != TASP_OK && a->fuse_steps) return st;
       FwdPlan pl;
-      if (st == TASP_OK) pl = plan_forward(a, js, a->workspace != nullptr ? std::min<size_t>(a->workspace_bytes, std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES)) : 0);
+      // a call that needs no workspace (need = 0) takes any pointer; one that is not aligned is left alone
+      const bool usable = a->workspace != nullptr && (reinterpret_cast<uintptr_t>(a->workspace) & (kAlign - 1)) == 0;
+      if (st == TASP_OK) pl = plan_forward(a, js, usable ? std::min<size_t>(a->workspace_bytes, std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES)) : 0);
       if (pl.joined) {
         {
           Scope sc(pl.table_bytes > 0 ? prof : nullptr, Profiler::kOther);

@@ -59,6 +59,25 @@ def test_short_calls_all_rows(tb, case):
             assert eo <= tol_o and el <= tol_l, (name, fuse, nbytes, eo, el)
 
 
+def test_fp32_fused_merge_leaves_an_unaligned_workspace_alone(tb):
+    """fp32 with the merge folded in needs no workspace, so its pointer is not checked: shares of the keys, which
+    would use it, are only planned where it is aligned."""
+    w = wl.Workload("unaligned", 4, 1, 1024, 4, 4, 64, "fp32", wl.FULL, seed=wl.BASE_SEED + 8400)
+    q, k, v = wl.make_qkv(w)
+    plan = tb.ChunkAttnPlan(tb.tasp_schedule(4, 1), q.cuda(), k.cuda(), v.cuda(), w.mask_mode, fuse_merge=True)
+    assert tb.lib.tasp_chunk_attn_workspace_bytes(plan.schedule.handle, C.byref(plan.args)) == 0
+    assert plan.args.workspace_bytes > 256
+    plan.workspace.fill_(77)
+    plan.args.workspace += 4
+    plan.args.workspace_bytes -= 4
+    out, lse = plan.run()
+    torch.cuda.synchronize()
+    rows = list(range(w.L))
+    ref_o, ref_l = oracle_rows(w, q, k, v, rows)
+    assert max_abs(out.cpu().numpy(), ref_o) <= 1e-4 and max_abs(lse.cpu().numpy(), ref_l) <= 1e-4
+    assert bool((plan.workspace == 77).all())
+
+
 BWD_FP32 = [
     # name, N, rank, S, Hq, Hkv, d, mask
     ("one_row_g3", 4, 3, 4, 3, 1, 128, wl.FULL),
