@@ -27,6 +27,7 @@ namespace tasp {
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kLn2 = 0.6931471805599453f;
 constexpr int BX = 64, BT = 64;          // X rows of a workgroup, Y rows of a tile
 constexpr int NTHREADS = 256;
 
@@ -138,8 +139,10 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
   }
   // a row that saw no key (lse = -inf) contributes nothing: exp2(-inf) = 0
   auto neg_lse2 = [](float l) __attribute__((always_inline)) { return l > -__builtin_inff() ? -l * kLog2e : -__builtin_inff(); };
-  float x_nl = 0.f, x_del = 0.f;
-  if constexpr (!DKV) { x_nl = neg_lse2(p.lse[row_idx]); x_del = p.delta[row_idx]; }
+  // exp2 of what rounding took from -lse log2(e), the same for every p of a row, less one
+  auto lse2_rest = [](float l, float nl2) __attribute__((always_inline)) { return l > -__builtin_inff() ? __builtin_fmaf(-l, kLog2e, -nl2) * kLn2 : 0.f; };
+  float x_nl = 0.f, x_del = 0.f, x_rest = 0.f;
+  if constexpr (!DKV) { x_nl = neg_lse2(p.lse[row_idx]); x_rest = lse2_rest(p.lse[row_idx], x_nl); x_del = p.delta[row_idx]; }
 
   // ---- the Y rows: dq a share of the visible keys, dkv the pairs (row, head) of both query blocks from
   // the first row that sees the first key on
@@ -276,7 +279,19 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
     // vector work in the shadow of the ones that do not need it: p beside T2, ds beside acc2 (dq: beside acc1,
     // one row ahead).  Left to itself it stood between the streams, where a lone wavefront's matrix pipe is idle
     // (71 % busy at d = 128; this order: see the head of the file).
-    f32x16 P = zero16(), E = zero16();
+    // Scores as NP, dout.v as NE chains (more spill), added up where they are used: the error of one
+    // long chain was larger than that of sums over a wavefront's lanes (8 heads of 128, 600 of 4 800 tokens: dk 1.29e-6
+    // against 1.15e-6; so 1.08e-6, with the rest of lse below; 2 to 4 % of the time).
+    constexpr int NP = D / 32, NE = 2;
+    f32x16 P = zero16(), E = zero16(), Pc[NP - 1], Ec[NE - 1];
+#pragma unroll
+    for (int i = 0; i < NP - 1; ++i) Pc[i] = zero16();
+#pragma unroll
+    for (int i = 0; i < NE - 1; ++i) Ec[i] = zero16();
+    auto sum_of = [](const f32x16& x, const auto& more, int r) __attribute__((always_inline)) {
+      if constexpr (sizeof(more) == sizeof(x)) return x[r] + more[0][r];
+      else return (x[r] + more[0][r]) + (more[1][r] + more[2][r]);
+    };
     f32x4 fr_[2];
     auto read_row = [&](auto jj) __attribute__((always_inline)) {              // stream of T1, then of T2
       constexpr int J = decltype(jj)::value;
@@ -290,26 +305,36 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
       const f32x4 a = fr_[J % 2], x = __builtin_bit_cast(f32x4, J < NJ ? x1[j] : x2[j]);
       if constexpr (J < NJ) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) P = mfma(a[e], x[e], P);
+        for (int e = 0; e < 4; ++e) { f32x16& to = e % NP ? Pc[e % NP - 1] : P; to = mfma(a[e], x[e], to); }
       } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) E = mfma(a[e], x[e], E);
+        for (int e = 0; e < 4; ++e) { f32x16& to = e % NE ? Ec[e % NE - 1] : E; to = mfma(a[e], x[e], to); }
       }
       if constexpr (J + 2 < 2 * NJ) read_row(std::integral_constant<int, J + 2>{});
       if constexpr (J > NJ) {
 #pragma unroll
-        for (int r = (J - NJ - 1) * (16 / NJ); r < (J - NJ) * (16 / NJ); ++r) P[r] = __builtin_amdgcn_exp2f(P[r]);
+        for (int r = (J - NJ - 1) * (16 / NJ); r < (J - NJ) * (16 / NJ); ++r) {
+          P[r] = __builtin_amdgcn_exp2f(P[r]);
+          if constexpr (DKV) P[r] = __builtin_fmaf(P[r], Pc[0][r], P[r]);
+        }
       }
       if constexpr (J >= NJ) {
 #pragma unroll
-        for (int r = (J - NJ) * (16 / NJ); r < (J - NJ + 1) * (16 / NJ); ++r) P[r] = __builtin_fmaf(P[r], c, DKV ? neg_lse2(nl[r % 4]) : x_nl);
+        for (int r = (J - NJ) * (16 / NJ); r < (J - NJ + 1) * (16 / NJ); ++r) {
+          const float nl2 = DKV ? neg_lse2(nl[r % 4]) : x_nl;
+          P[r] = __builtin_fmaf(sum_of(P, Pc, r), c, nl2);
+          if constexpr (DKV) Pc[0][r] = lse2_rest(nl[r % 4], nl2);
+        }
       }
       if constexpr (DKV && J >= NJ - 1 && (J + 1 - NJ) * (16 / NJ) % 4 == 0 && J + 1 < 2 * NJ)     // lse of the four rows that come next
         nl = *reinterpret_cast<const f32x4*>(&s_lse[stage][32 * yg + 8 * ((J + 1 - NJ) * (16 / NJ) / 4) + 4 * h]);
       __builtin_amdgcn_sched_barrier(0);
     });
 #pragma unroll
-    for (int r = 16 - 16 / NJ; r < 16; ++r) P[r] = __builtin_amdgcn_exp2f(P[r]);
+    for (int r = 16 - 16 / NJ; r < 16; ++r) {
+      P[r] = __builtin_amdgcn_exp2f(P[r]);
+      if constexpr (DKV) P[r] = __builtin_fmaf(P[r], Pc[0][r], P[r]);
+    }
     const i32x4 mk = *reinterpret_cast<const i32x4*>(&s_msk[stage][0]);
     if (__builtin_amdgcn_readfirstlane(mk[0] | mk[1] | mk[2] | mk[3]) != 0) {
 #pragma unroll
@@ -337,7 +362,7 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
     f32x4 dl = {0.f, 0.f, 0.f, 0.f};
     static_for<2>(read_piece);
     if constexpr (DKV) dl = *reinterpret_cast<const f32x4*>(&s_del[stage][32 * yg + 4 * h]);
-    else E[0] = P[0] * (E[0] - x_del);
+    else E[0] = P[0] * (sum_of(E, Ec, 0) - x_del);
     __builtin_amdgcn_sched_barrier(0);
     static_for<16 * NACC>([&](auto kk) __attribute__((always_inline)) {
       constexpr int K = decltype(kk)::value, r = K % 16, A = DKV && K < 16 ? 1 : 0;
@@ -346,10 +371,10 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
       for (int db = 0; db < NDB; ++db) acc[A * (NACC - 1)][db] = mfma(y.v[db], A ? P[r] : E[r], acc[A * (NACC - 1)][db]);
       if constexpr (K + 2 < 16 * NACC) read_piece(std::integral_constant<int, K + 2>{});
       if constexpr (DKV) {
-        if constexpr (K < 16) E[r] = P[r] * (E[r] - dl[r % 4]);
+        if constexpr (K < 16) E[r] = P[r] * (sum_of(E, Ec, r) - dl[r % 4]);
         if constexpr (K < 15 && r % 4 == 3) dl = *reinterpret_cast<const f32x4*>(&s_del[stage][32 * yg + 8 * ((r + 1) / 4) + 4 * h]);
       } else if constexpr (K < 15) {
-        E[r + 1] = P[r + 1] * (E[r + 1] - x_del);
+        E[r + 1] = P[r + 1] * (sum_of(E, Ec, r + 1) - x_del);
       }
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -409,7 +434,7 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
       f32x4 old = {0.f, 0.f, 0.f, 0.f};
       if (p.accumulate) old = *reinterpret_cast<const f32x4*>(dq + col);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) a[e] = __builtin_fmaf(a[e], p.scale, old[e]);
+      for (int e = 0; e < 4; ++e) a[e] = __builtin_fmaf(__builtin_fmaf(a[e], x_rest, a[e]), p.scale, old[e]);
       *reinterpret_cast<f32x4*>(dq + col) = a;
     });
   }
