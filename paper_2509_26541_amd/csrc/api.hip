@@ -418,7 +418,7 @@ int fill_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args* b, const AttnLa
              tasp::BwdLaunch* bp) {
   bp->q = b->q; bp->k = b->k; bp->v = b->v; bp->dout = b->dout; bp->lse = b->lse;
   bp->dk = b->dk; bp->dv = b->dv;
-  bp->Hq = lp.Hq; bp->Hkv = lp.Hkv; bp->causal = lp.causal; bp->scale = lp.scale; bp->batch = lp.batch;
+  bp->Hq = lp.Hq; bp->Hkv = lp.Hkv; bp->group = tasp::make_divider(static_cast<uint32_t>(lp.Hq / lp.Hkv)); bp->causal = lp.causal; bp->scale = lp.scale; bp->batch = lp.batch;
   bp->q_bstride = lp.q_bstride; bp->kv_bstride = lp.kv_bstride; bp->lse_bstride = lp.lse_bstride;
   bp->n_tasks = lp.n_tasks;
   for (int t = 0; t < lp.n_tasks; ++t) { bp->task[t] = lp.task[t]; bp->seg_ext[t] = lp.seg_ext[t]; }

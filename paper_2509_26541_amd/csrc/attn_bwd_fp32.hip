@@ -80,6 +80,7 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
   // SIMD i, and strips and halves without rows are left out
   const int xs = (wave ^ block) & 1, yg = (wave >> 1 ^ block >> 1) & 1;
   const int G = p.Hq / p.Hkv;
+  const Divider group = p.group;
   const int64_t q_pitch = static_cast<int64_t>(p.Hq) * C::RB, k_pitch = static_cast<int64_t>(p.Hkv) * C::RB;
 
   // ---- the workgroup's X rows
@@ -195,14 +196,11 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
   int row0_a = p.blk[0].row0, row0_b = p.blk[1].row0, pos0_a = p.blk[0].pos0, pos0_b = p.blk[1].pos0;
   asm volatile("" : "+s"(row0_a), "+s"(row0_b), "+s"(pos0_a), "+s"(pos0_b));
   // dkv: pair v of the stream -> local row, head (v >= n_y: row 0 and position -1)
-  const float inv_g = 1.f / static_cast<float>(G);
   auto y_row = [&](int v, int& pos, int& hh) __attribute__((always_inline)) {
     const bool second = v >= y_cnt0;
     const int m = second ? y_first[1] + v - y_cnt0 : y_first[0] + v;
-    int r = static_cast<int>(static_cast<float>(m) * inv_g);                   // m / G, exact after one correction either way
+    const int r = static_cast<int>(divide(static_cast<uint32_t>(m), group));   // exact up to INT_MAX (a float estimate with one correction is not)
     hh = m - r * G;
-    if (hh < 0) { hh += G; --r; }
-    if (hh >= G) { hh -= G; ++r; }
     if (v >= n_y) { pos = -1; hh = 0; return 0; }
     pos = p.causal ? (second ? pos0_b : pos0_a) + r : INT_MAX - 1;
     return (second ? row0_b : row0_a) + r;

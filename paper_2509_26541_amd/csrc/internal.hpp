@@ -4,6 +4,8 @@
 
 #include <cstdint>
 
+#include "divider.hpp"
+
 namespace tasp {
 
 constexpr int kMaxSeg = 64;      // KV segments one query block can see in one step (2(N-1) for zig-zag)
@@ -79,6 +81,7 @@ struct BwdLaunch {
   void* dk;             // [B, S, Hkv, d] bf16; the rows of this step's keys are written
   void* dv;
   int32_t Hq, Hkv;
+  Divider group;        // by Hq / Hkv
   int32_t causal;
   float scale;
   int32_t batch;
