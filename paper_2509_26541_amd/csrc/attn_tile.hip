@@ -646,14 +646,16 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineTasks tasks, 
     float m = mx;
 #pragma unroll
     for (int k = 0; k < AT_ONCE; ++k) m = fmaxf(m, l[k]);
-    if (m == -__builtin_inff()) continue;
-    const float r = __expf(mx - m);
+    // no share so far saw a key: all weights are 0, and so are the outputs unless they are NaN (a row of NaN scores
+    // has lse = -inf and NaN outputs), which 0 times them keeps
+    const float ref = m == -__builtin_inff() ? 0.f : m;
+    const float r = __expf(mx - ref);
     den *= r;
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[e] *= r;
 #pragma unroll
     for (int k = 0; k < AT_ONCE; ++k) {
-      const float w = __expf(l[k] - m);
+      const float w = __expf(l[k] - ref);
       den += w;
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(w, x[k][e], acc[e]);

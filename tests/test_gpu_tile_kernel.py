@@ -78,6 +78,28 @@ def test_fp32_fused_merge_leaves_an_unaligned_workspace_alone(tb):
     assert bool((plan.workspace == 77).all())
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("heads", [(4, 4, 64), (8, 2, 128)], ids=["4x64", "8/2x128"])
+def test_a_row_of_nan_scores_stays_nan(tb, dtype, heads):
+    """NaN in a query row makes its output NaN, also where the pairs of several shares are added up; other rows
+    are what they are without it, but for the rounding behind their running maximum, which 32 rows raise together."""
+    Hq, Hkv, d = heads
+    w = wl.Workload("nan_row", 4, 1, 4096, Hq, Hkv, d, dtype, wl.FULL, seed=wl.BASE_SEED + 8450 + d)
+    q, k, v = (t.cuda() for t in wl.make_qkv(w))
+    bad = q.clone()
+    bad[5, 1] = float("nan")
+    for fuse_steps in (False, True):
+        plan = tb.ChunkAttnPlan(tb.tasp_schedule(4, 1), q, k, v, w.mask_mode, fuse_merge=True, fuse_steps=fuse_steps)
+        clean = [t.clone() for t in plan.run()]
+        prof = plan.profile()
+        assert prof.attn_launches == 1 and prof.other_launches >= 1          # joined steps, and a launch that adds shares up
+        out, lse = tb.tasp_chunk_attn(bad, k, v, plan.schedule, w.mask_mode, fuse_merge=True, fuse_steps=fuse_steps)
+        assert bool(out[5, 1].isnan().all())
+        out[5, 1], lse[5, 1] = clean[0][5, 1], clean[1][5, 1]
+        assert float((out.float() - clean[0].float()).abs().max()) <= (2e-2 if dtype == "bf16" else 1e-5)
+        assert float((lse - clean[1]).abs().max()) <= 1e-5
+
+
 BWD_FP32 = [
     # name, N, rank, S, Hq, Hkv, d, mask
     ("one_row_g3", 4, 3, 4, 3, 1, 128, wl.FULL),
