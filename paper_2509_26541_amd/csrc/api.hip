@@ -198,8 +198,9 @@ size_t all_share_bytes(const AttnLaunch& lp, int d, const int32_t* n) {
 constexpr int64_t kJoinRows = 4096;
 constexpr int64_t kMaxSplit = 32;    // shares of one tile
 
-// Sequences a call is planned for: one, where a few of them leave the chip idle together, so that the results
-// of such a batch are those of separate calls.
+// Sequences a call is planned for: one, where a few of them leave the chip idle together.  Where there is room for
+// the shares that one of them would get alone, the results of such a batch are bit for bit those of separate
+// calls; they are not where the partial pairs of all take more than the workspace that is planned for.
 int64_t plan_batch(int64_t batch, int64_t tiles_of_one) { return batch <= 4 && batch * tiles_of_one <= 128 ? 1 : batch; }
 int64_t plan_batch(const AttnLaunch& lp) {
   int64_t tiles = 0;
@@ -292,20 +293,28 @@ bool tile_is_faster(const AttnLaunch& lp, int d, const int64_t* keys, const int3
   return duration(tile, tile_one, tile_n, 1.8) + sum_shares < duration(big, big_one, big_n, 1.0);
 }
 
-// Decides from shapes alone (`js` holds the joined lists), within `ws_bytes` of workspace.
-FwdPlan plan_forward(const tasp_attn_args* a, const JoinedSteps& js, size_t ws_bytes) {
+// Decides from shapes alone (`js` holds the joined lists).  Kernel and shares are those for the largest workspace
+// that tasp_chunk_attn_best_workspace_bytes could report, wherever the `ws_bytes` of the call hold these shares
+// (none do with the large kernel): the results do not depend on who brings the workspace, if it is the reported
+// one or larger.  With less the shares are dealt anew, and the kernel is chosen for them.
+FwdPlan plan_forward(const tasp_attn_args* a, const JoinedSteps& js, size_t need, size_t ws_bytes) {
   FwdPlan pl;
   const bool fp32 = a->dtype == TASP_DTYPE_FP32;
   pl.joined = true;
   if (js.segments() > static_cast<size_t>(tasp::kPoolSeg)) pl.table_bytes = kFusedTableBytes;
   if (pl.table_bytes > ws_bytes) { pl.joined = false; return pl; }
-  int32_t n_split[tasp::kMaxTasks] = {1, 1};
-  deal_keys(js.all, a->d, fp32, js.keys, ws_bytes - pl.table_bytes, n_split);
-  pl.tile = fp32 || tile_is_faster(js.all, a->d, js.keys, n_split);
-  if (!pl.tile) return pl;
-  for (int t = 0; t < js.all.n_tasks; ++t) pl.n_split[t] = n_split[t];
-  pl.part_bytes = all_share_bytes(js.all, a->d, n_split);
-  return pl;
+  size_t room = std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES) - pl.table_bytes;
+  for (;;) {
+    int32_t n_split[tasp::kMaxTasks] = {1, 1};
+    deal_keys(js.all, a->d, fp32, js.keys, room, n_split);
+    pl.tile = fp32 || tile_is_faster(js.all, a->d, js.keys, n_split);
+    if (!pl.tile) return pl;
+    pl.part_bytes = all_share_bytes(js.all, a->d, n_split);
+    for (int t = 0; t < js.all.n_tasks; ++t) pl.n_split[t] = n_split[t];
+    if (pl.part_bytes <= ws_bytes - pl.table_bytes) return pl;
+    room = ws_bytes - pl.table_bytes;                 // what is dealt for this much fits
+    pl = FwdPlan{true, false, {1, 1}, pl.table_bytes, 0};
+  }
 }
 
 // Optional per-launch timing with HIP events on the caller's stream (tasp_chunk_attn_profile).
@@ -589,8 +598,7 @@ size_t tasp_chunk_attn_best_workspace_bytes(const tasp_schedule_t* s, const tasp
   try {
     JoinedSteps js{};
     if (join_steps(s, a, &js) != TASP_OK) return need;
-    // the same limit for every caller, so that the results do not depend on where the workspace comes from
-    const FwdPlan pl = plan_forward(a, js, std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES));
+    const FwdPlan pl = plan_forward(a, js, need, std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES));
     return pl.joined ? std::max(need, pl.table_bytes + pl.part_bytes) : need;
   } catch (...) {
     return need;
@@ -667,7 +675,7 @@ static int run_chunk_attn(const tasp_schedule_t* s, const tasp_attn_args* a, voi
       FwdPlan pl;
       // a call that needs no workspace (need = 0) takes any pointer; one that is not aligned is left alone
       const bool usable = a->workspace != nullptr && (reinterpret_cast<uintptr_t>(a->workspace) & (kAlign - 1)) == 0;
-      if (st == TASP_OK) pl = plan_forward(a, js, usable ? std::min<size_t>(a->workspace_bytes, std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES)) : 0);
+      if (st == TASP_OK) pl = plan_forward(a, js, need, usable ? a->workspace_bytes : 0);
       if (pl.joined) {
         {
           Scope sc(pl.table_bytes > 0 ? prof : nullptr, Profiler::kOther);

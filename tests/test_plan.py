@@ -1,0 +1,128 @@
+"""How a call is cut follows from its shape: kernel, shares and partial sums are the same with the workspace that the
+library reports for it and with a larger one, such as the array of the static call.  The planner of csrc/api.hip, compiled for the host.  CPU only."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from tests import asm_checks
+
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+pytestmark = pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
+
+PROGRAM = r"""
+#include "api.hip"
+#include <cstdio>
+#include <random>
+
+namespace tasp {   // launches: none is made here
+hipError_t launch_attn_bf16(const AttnLaunch&, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_attn_tile(const AttnLaunch&, int, bool, hipStream_t) { return hipSuccess; }
+hipError_t launch_combine(const AttnLaunch&, int, bool, hipStream_t) { return hipSuccess; }
+hipError_t launch_merge(float*, float*, const float*, const float*, int64_t, int64_t, int32_t, int32_t, int32_t, int64_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_fill_empty(float*, float*, int64_t, int64_t, int32_t, int32_t, int32_t, int64_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_cast_bf16(const float*, void*, int64_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_write_i32(int32_t*, const int32_t*, int64_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_bwd_dq_bf16(const BwdLaunch&, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_bwd_dkv_bf16(const BwdLaunch&, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_bwd_dkv_reduce(const BwdLaunch&, int, hipStream_t) { return hipSuccess; }
+int64_t bwd_dkv_workgroups(const BwdLaunch& p, int d) {
+  const int bs = d == 128 ? 256 : 128;
+  return (static_cast<int64_t>(p.rng_vbeg[p.n_rng]) + bs - 1) / bs * p.Hkv * p.batch;
+}
+int bwd_dkv_resident_workgroups(int d) { return d == 128 ? 256 : 768; }
+hipError_t launch_bwd_delta_bf16(const void*, const void*, const float*, float*, float*, float, int64_t, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_zero_f32(float*, int64_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_bwd_fp32(const BwdLaunch&, int, bool, bool, hipStream_t) { return hipSuccess; }
+hipError_t launch_bwd_sum(const float*, int64_t, int, void*, bool, int64_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_bwd_delta_fp32(const void*, const void*, float*, int64_t, int, hipStream_t) { return hipSuccess; }
+}
+
+struct Plan { bool ok, tile; int n0, n1, kv; size_t bytes; };
+
+static Plan forward(const tasp_schedule_t* s, tasp_attn_args a, size_t ws) {     // ws = 0: as much as is reported for the call
+  JoinedSteps js{};
+  Shape sh;
+  if (validate(s, &a, &sh) != TASP_OK || join_steps(s, &a, &js) != TASP_OK) return {};
+  const FwdPlan p = plan_forward(&a, js, tasp_chunk_attn_workspace_bytes(s, &a), ws ? ws : tasp_chunk_attn_best_workspace_bytes(s, &a));
+  return {p.joined, p.tile, p.n_split[0], p.n_split[1], 0, p.table_bytes + p.part_bytes};
+}
+static Plan backward(const tasp_schedule_t* s, tasp_attn_bwd_args b, size_t ws) {
+  JoinedSteps js{};
+  tasp_attn_args a;
+  Shape sh;
+  tasp::BwdLaunch bp{};
+  if (validate_bwd(s, &b, &a, &sh) != TASP_OK || build_bwd_joined(s, &b, &a, &bp, &js) != TASP_OK) return {};
+  const size_t used = ws ? ws : tasp_chunk_attn_bwd_best_workspace_bytes(s, &b);
+  const BwdPlan p = plan_backward(&b, sh, bp, js.segments() > static_cast<size_t>(tasp::kPoolSeg) ? kFusedTableBytes : 0, used);
+  if (plan_bytes(p, &b, sh) > used) std::printf("backward plan of %zu bytes in %zu\n", plan_bytes(p, &b, sh), used);
+  return {plan_bytes(p, &b, sh) <= used, false, p.n_split, 0, p.kv_split, plan_bytes(p, &b, sh)};
+}
+static bool same(const Plan& x, const Plan& y) { return x.ok == y.ok && x.tile == y.tile && x.n0 == y.n0 && x.n1 == y.n1 && x.kv == y.kv; }
+
+int main() {
+  std::mt19937 rng(5);
+  auto pick = [&](std::initializer_list<int> l) { return l.begin()[rng() % l.size()]; };
+  const size_t fixed = TASP_STATIC_SCRATCH_BYTES;
+  int bad = 0, fwd = 0, bwd = 0, shared = 0;
+  auto report = [&](const char* what, const tasp_attn_args& a, int n, const Plan& x, const Plan& y) {
+    if (bad++ < 10)
+      std::printf("%s: n=%d S=%lld %d/%d d=%d dtype=%d mask=%d batch=%d fuse_steps=%d: tile %d shares %d %d kv %d, not %d %d %d %d\n", what, n, (long long)a.S, a.Hq, a.Hkv,
+                  a.d, a.dtype, a.mask_mode, a.batch, a.fuse_steps, x.tile, x.n0, x.n1, x.kv, y.tile, y.n0, y.n1, y.kv);
+  };
+  for (int i = 0; i < 12000; ++i) {
+    const int n = pick({4, 8, 8, 12, 16}), r = static_cast<int>(rng() % n);
+    tasp_schedule_t* s = nullptr;
+    if (tasp_schedule_create(n, r, &s) != TASP_OK) return 2;
+    tasp_attn_args a{};
+    a.q = a.k = a.v = a.out = reinterpret_cast<void*>(256);
+    a.d = pick({64, 128});
+    a.Hkv = pick({1, 1, 2, 3, 4, 8, 12, 20});
+    a.Hq = a.Hkv * pick({1, 1, 2, 3, 4, 8});
+    a.dtype = pick({TASP_DTYPE_FP32, TASP_DTYPE_BF16, TASP_DTYPE_BF16});
+    a.mask_mode = pick({TASP_MASK_FULL, TASP_MASK_ZIGZAG_CAUSAL, TASP_MASK_ZIGZAG_CAUSAL});
+    a.fuse_merge = pick({0, 1});
+    a.fuse_steps = pick({0, 1});
+    a.batch = pick({1, 1, 2, 3, 4, 16});
+    const int64_t rows = 2 << (rng() % 11);                            // up to 4096 local rows
+    a.S = n * (rows + 2 * (rng() % (rows / 2 + 1)));
+    if (a.S > n * kJoinRows) a.S = n * kJoinRows;
+    const size_t need = tasp_chunk_attn_workspace_bytes(s, &a);
+    const Plan best = forward(s, a, 0);
+    if (best.ok && need <= fixed) {
+      ++fwd;
+      shared += best.n0 > 1 || best.n1 > 1;
+      const Plan st = forward(s, a, fixed);
+      if (!same(best, st)) report("forward, static", a, n, best, st);
+      const Plan least = forward(s, a, std::max<size_t>(need, 1));
+      if (least.ok && least.bytes > std::max<size_t>(need, 1)) report("forward, least", a, n, least, least);
+      if (best.bytes > std::max(tasp_chunk_attn_best_workspace_bytes(s, &a), need)) report("forward, bytes", a, n, best, best);
+    }
+    tasp_attn_bwd_args b{};
+    b.q = b.k = b.v = b.out = b.dout = b.dq = b.dk = b.dv = reinterpret_cast<void*>(256);
+    b.lse = reinterpret_cast<float*>(256);
+    b.S = a.S; b.Hq = a.Hq; b.Hkv = a.Hkv; b.d = a.d; b.dtype = a.dtype; b.mask_mode = a.mask_mode; b.batch = a.batch;
+    b.fuse_steps = a.dtype == TASP_DTYPE_BF16 ? a.fuse_steps : 0;
+    const Plan bb = backward(s, b, 0);
+    if (bb.ok) {
+      ++bwd;
+      const Plan more = backward(s, b, std::max(fixed, tasp_chunk_attn_bwd_workspace_bytes(s, &b)));
+      if (!same(bb, more)) report("backward, room", a, n, bb, more);
+      backward(s, b, tasp_chunk_attn_bwd_workspace_bytes(s, &b));      // the least: within it
+    }
+    tasp_schedule_destroy(s);
+  }
+  std::printf("%d forward (%d with shares), %d backward, %d differ\n", fwd, shared, bwd, bad);
+  return bad != 0 || fwd < 8000 || shared < 2000 || bwd < 8000;
+}
+"""
+
+
+def test_plan_follows_from_the_shape(tmp_path):
+    src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
+    src.write_text(PROGRAM)
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I" + os.path.join(asm_checks.ROOT, "include"), "-I" + asm_checks.CSRC,
+                    "-x", "hip", str(src), os.path.join(asm_checks.CSRC, "schedule.cpp"), "-o", str(exe)], check=True, capture_output=True, text=True)
+    res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stdout
