@@ -264,7 +264,13 @@ void deal_keys(const AttnLaunch& lp, int d, bool fp32, const int64_t* keys, size
 // as well), the small one computes only the strips of 32 that have rows, walks a key in 1.14 of the
 // time, and a lone workgroup of it uses about half a CU.  Over 110 shapes (3K to 32K tokens, both d,
 // 200 to 4000 workgroups) the choice costs 0.3 % on average against always taking the faster kernel.
-bool tile_is_faster(const AttnLaunch& lp, int d, const int64_t* keys, const int32_t* n_split) {
+// A step by itself (`step`) is another thing than joined steps: its partial pairs go out in fp32, its short lists
+// leave the small kernel more set-up per key, and there are no shares.  Over 78 shapes of it (256 to 4 700 rows a
+// step, both d) the small kernel took 0.53 to 1.01 of the large one's time where its estimate was below kStepMargin
+// of the other, and 1.03 to 1.21 above (16 heads over 2, 3 320 rows, no mask: 113.7 us a step against 94.3).
+// At d = 64 a second workgroup on a CU lengthened it by 1.4 (4 and 12 heads, 3 072 rows: 48.8 and 68.2 us).
+constexpr double kStepMargin = 0.89;
+bool tile_is_faster(const AttnLaunch& lp, int d, const int64_t* keys, const int32_t* n_split, bool step = false) {
   constexpr double kCus = 256.0;
   const double B = static_cast<double>(plan_batch(lp)), G = lp.Hq / lp.Hkv;
   auto padded = [](double x, double m) { return std::ceil(x / m) * m; };
@@ -283,14 +289,16 @@ bool tile_is_faster(const AttnLaunch& lp, int d, const int64_t* keys, const int3
     tile += tile_one[t] * padded(n * G, 32) / tasp::kTileRows * lp.Hkv * B * ns;
     split |= ns > 1;
   }
-  auto duration = [&](double total, const double* one, const double* n, double alone) {
+  auto duration = [&](double total, const double* one, const double* n, double alone, double pair) {
     const double longest = std::max(one[0], one[1]);
     double heavy = 0;
     for (int t = 0; t < lp.n_tasks; ++t) heavy += one[t] > 0.7 * longest ? n[t] : 0;
-    return std::max(total / kCus, longest * std::max(alone, std::ceil(heavy / kCus)));
+    const double on_one = std::ceil(heavy / kCus);
+    return std::max(total / kCus, longest * std::max(on_one > 1 ? pair : alone, on_one));
   };
   const double sum_shares = split ? 60000 : 0;      // the launch that adds the shares up
-  return duration(tile, tile_one, tile_n, 1.8) + sum_shares < duration(big, big_one, big_n, 1.0);
+  const double small = duration(tile, tile_one, tile_n, 1.8, step && d == 64 ? 2.5 : 1.8) + sum_shares;
+  return small < (step ? kStepMargin : 1.0) * duration(big, big_one, big_n, 1.0, 1.0);
 }
 
 // Decides from shapes alone (`js` holds the joined lists).  Kernel and shares are those for the largest workspace
@@ -364,7 +372,7 @@ hipError_t launch_step(const AttnLaunch& lp, const tasp_attn_args* a, hipStream_
       const int32_t* g = lp.pool + 2 * (lp.task[t].seg0 + i);
       keys[t] += g[1] - g[0];
     }
-  return launch_attn(lp, a, stream, a->dtype == TASP_DTYPE_FP32 || (rows <= kJoinRows && tile_is_faster(lp, a->d, keys, lp.n_split)));
+  return launch_attn(lp, a, stream, a->dtype == TASP_DTYPE_FP32 || (rows <= kJoinRows && tile_is_faster(lp, a->d, keys, lp.n_split, true)));
 }
 
 // ---- backward pass

@@ -1,5 +1,6 @@
 """How a call is cut follows from its shape: kernel, shares and partial sums are the same with the workspace that the
-library reports for it and with a larger one, such as the array of the static call.  The planner of csrc/api.hip, compiled for the host.  CPU only."""
+library reports for it and with a larger one, such as the array of the static call; and which kernel a step takes.
+The planner of csrc/api.hip, compiled for the host.  CPU only."""
 import os
 import shutil
 import subprocess
@@ -11,15 +12,18 @@ from tests import asm_checks
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 pytestmark = pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
 
-PROGRAM = r"""
+STUBS = r"""
 #include "api.hip"
 #include <cstdio>
 #include <random>
 
+struct Launched { int large, tile, combine; tasp::AttnLaunch last; };
+static Launched g;                                // what the forward launches would have been
+
 namespace tasp {   // launches: none is made here
-hipError_t launch_attn_bf16(const AttnLaunch&, int, hipStream_t) { return hipSuccess; }
-hipError_t launch_attn_tile(const AttnLaunch&, int, bool, hipStream_t) { return hipSuccess; }
-hipError_t launch_combine(const AttnLaunch&, int, bool, hipStream_t) { return hipSuccess; }
+hipError_t launch_attn_bf16(const AttnLaunch& p, int, hipStream_t) { ++g.large; g.last = p; return hipSuccess; }
+hipError_t launch_attn_tile(const AttnLaunch& p, int, bool, hipStream_t) { ++g.tile; g.last = p; return hipSuccess; }
+hipError_t launch_combine(const AttnLaunch&, int, bool, hipStream_t) { ++g.combine; return hipSuccess; }
 hipError_t launch_merge(float*, float*, const float*, const float*, int64_t, int64_t, int32_t, int32_t, int32_t, int64_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_fill_empty(float*, float*, int64_t, int64_t, int32_t, int32_t, int32_t, int64_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_cast_bf16(const float*, void*, int64_t, hipStream_t) { return hipSuccess; }
@@ -38,6 +42,9 @@ hipError_t launch_bwd_fp32(const BwdLaunch&, int, bool, bool, hipStream_t) { ret
 hipError_t launch_bwd_sum(const float*, int64_t, int, void*, bool, int64_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_bwd_delta_fp32(const void*, const void*, float*, int64_t, int, hipStream_t) { return hipSuccess; }
 }
+"""
+
+PLAN = r"""
 
 struct Plan { bool ok, tile; int n0, n1, kv; size_t bytes; };
 
@@ -119,10 +126,50 @@ int main() {
 """
 
 
-def test_plan_follows_from_the_shape(tmp_path):
+STEPS = r"""
+// n, rank, rows, heads, KV heads, d, mask, us a step with the large and with the small kernel
+struct Case { int n, rank, rows, hq, hkv, d, mask; double large, small; };
+static const Case kCases[] = {
+  {8, 6, 3320, 16, 2, 128, 0, 94.3, 113.7}, {8, 0, 2974, 32, 4, 128, 1, 94.9, 104.9}, {4, 0, 3884, 32, 8, 128, 1, 138.1, 149.5},
+  {4, 1, 4096, 8, 8, 128, 0, 89.0, 92.0}, {4, 2, 3072, 12, 12, 64, 0, 65.7, 68.2},
+  {8, 1, 872, 12, 12, 64, 1, 26.9, 18.5}, {8, 2, 446, 16, 2, 128, 1, 26.9, 15.8}, {12, 7, 3248, 1, 1, 64, 1, 47.9, 40.0},
+  {8, 0, 1330, 64, 8, 128, 0, 96.9, 81.9}, {16, 4, 1970, 8, 1, 128, 1, 62.7, 43.9},
+};
+
+int main() {
+  int bad = 0;
+  for (const Case& c : kCases) {
+    tasp_schedule_t* s = nullptr;
+    if (tasp_schedule_create(c.n, c.rank, &s) != TASP_OK) return 2;
+    tasp_attn_args a{};
+    a.q = a.k = a.v = reinterpret_cast<void*>(256);
+    a.S = static_cast<int64_t>(c.rows) * c.n; a.Hq = c.hq; a.Hkv = c.hkv; a.d = c.d;
+    a.dtype = TASP_DTYPE_BF16; a.mask_mode = c.mask ? TASP_MASK_ZIGZAG_CAUSAL : TASP_MASK_FULL;
+    g = {};
+    for (int i = 1; i < c.n; ++i)       // (step 0, with the diagonal, is another launch than the others)
+      if (tasp_step_attn(s, &a, i, reinterpret_cast<float*>(256), reinterpret_cast<float*>(256), nullptr) != TASP_OK) return 3;
+    std::printf("%d rows, %d/%d heads of %d: large %d, small %d\n", c.rows, c.hq, c.hkv, c.d, g.large, g.tile);
+    bad += (c.large < c.small ? g.tile : g.large) != 0;
+    tasp_schedule_destroy(s);
+  }
+  return bad;
+}
+"""
+
+
+def _run(tmp_path, program):
     src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
-    src.write_text(PROGRAM)
+    src.write_text(STUBS + program)
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I" + os.path.join(asm_checks.ROOT, "include"), "-I" + asm_checks.CSRC,
                     "-x", "hip", str(src), os.path.join(asm_checks.CSRC, "schedule.cpp"), "-o", str(exe)], check=True, capture_output=True, text=True)
     res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
     assert res.returncode == 0, res.stdout
+
+
+def test_plan_follows_from_the_shape(tmp_path):
+    _run(tmp_path, PLAN)
+
+
+def test_a_step_takes_the_faster_kernel(tmp_path):
+    """Shapes timed with either kernel, per step."""
+    _run(tmp_path, STEPS)
