@@ -256,6 +256,13 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
   for (int a = 0; a < NACC; ++a)
 #pragma unroll
     for (int db = 0; db < NDB; ++db) acc[a][db] = zero16();
+  // dq: what FLUSH tiles have added goes to a second set of sums, so that the error of the chain of additions does not
+  // grow with the number of keys.  Relative error of dq, 12 heads of 64, 16 384 tokens of 16 ranks, no mask: 1.05e-6
+  // with one set, 5.2e-7 with 8 tiles, 4.7e-7 with 2 (sums over a wavefront's lanes: 7.5e-7); 8 heads, 6 168 tokens: 145 us with either.
+  constexpr int FLUSH = 2;
+  f32x16 q_sum[DKV ? 1 : NDB];
+#pragma unroll
+  for (int db = 0; db < (DKV ? 1 : NDB); ++db) q_sum[db] = zero16();
   const float c = p.scale * kLog2e;
 
   if (n_tiles > 0) fetch(0, 0);
@@ -376,6 +383,16 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
       }
       __builtin_amdgcn_sched_barrier(0);
     });
+    if constexpr (!DKV) {
+      if (t % FLUSH == FLUSH - 1) {
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) { q_sum[db] += acc[0][db]; acc[0][db] = zero16(); }
+      }
+    }
+  }
+  if constexpr (!DKV) {
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) acc[0][db] += q_sum[db];
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();                   // the stages are free: the second half of the Y rows hands its sums over

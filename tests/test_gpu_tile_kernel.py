@@ -134,6 +134,29 @@ def test_fp32_backward_every_element(tb, case):
             assert err <= 1e-4 * max(1.0, float(np.abs(r).max())), (name, nm, nbytes, err)
 
 
+@pytest.mark.parametrize("shape", [(16, 7, 16384, 12, 12, 64), (4, 0, 20480, 2, 1, 128)], ids=["16k_d64", "20k_d128"])
+def test_fp32_dq_error_does_not_grow_with_the_keys(tb, shape):
+    """dq of many keys against 64 bits, from out and lse that are exact but for their last rounding.  Bound: 7.5e-7, what
+    sums over the lanes of a wavefront reach on these inputs (d = 64; 1.4e-6 for d = 128); one chain of additions per
+    share of the keys has 1.0e-6 to 1.05e-6, the two levels of sums 4.7e-7."""
+    n, rank, S, Hq, Hkv, d = shape
+    w = wl.Workload("dq_error", n, rank, S, Hq, Hkv, d, "fp32", wl.FULL, seed=wl.BASE_SEED + 8600 + d)
+    q, k, v = (t.cuda() for t in wl.make_qkv(w))
+    do = wl.make_dout(w).cuda()
+    out, lse = torch.empty_like(q), torch.empty(q.shape[:-1], device="cuda")
+    ref = torch.empty(q.shape, dtype=torch.float64, device="cuda")
+    for h in range(Hq):
+        kh, vh, g = k[:, h * Hkv // Hq].double(), v[:, h * Hkv // Hq].double(), do[:, h].double()
+        s = q[:, h].double() @ kh.t() / d ** 0.5
+        l = torch.logsumexp(s, 1, keepdim=True)
+        p = torch.exp(s - l)
+        o = p @ vh
+        out[:, h], lse[:, h] = o, l[:, 0]
+        ref[:, h] = (p * (g @ vh.t() - (g * o).sum(1, keepdim=True))) @ kh / d ** 0.5
+    dq = tb.tasp_chunk_attn_bwd(q, k, v, out, lse, do, tb.tasp_schedule(n, rank), w.mask_mode)[0]
+    assert float((dq.double() - ref).norm() / ref.norm()) <= 7.5e-7
+
+
 BWD_BF16 = [
     # name, N, rank, S, Hq, Hkv, d, mask, fuse_steps
     ("one_row", 4, 2, 4, 2, 1, 128, wl.FULL, False),
