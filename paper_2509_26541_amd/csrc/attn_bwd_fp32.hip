@@ -73,6 +73,7 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
   __shared__ __attribute__((aligned(256))) float s_lse[2][BT];   // dkv: of the tile's rows
   __shared__ __attribute__((aligned(256))) float s_del[2][BT];
   __shared__ __attribute__((aligned(16))) int s_msk[2][4];       // per wavefront: it fetched a row that takes the element-wise mask
+  __shared__ int s_odd[4];                                       // per strip of X rows and half: it left tiles out
   __shared__ int e_vbeg[kMaxSeg + 1], e_goff[kMaxSeg], e_n;      // dq: effective segments of this share of the keys
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, lq = lane & 31;
@@ -263,6 +264,10 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
   f32x16 q_sum[DKV ? 1 : NDB];
 #pragma unroll
   for (int db = 0; db < (DKV ? 1 : NDB); ++db) q_sum[db] = zero16();
+  // Pairs that the mask leaves out, and in the dk/dv workgroups those of query rows that saw no key, have p = 0 and ds = 0.
+  // An infinity or NaN of such a Y row would come to the X row as 0 times that: half tiles with such pairs and such
+  // a row are left out (a wavefront decides for its own) and added to the stored rows at the end, row by row.
+  bool odd_tiles = false;
   const float c = p.scale * kLog2e;
 
   if (n_tiles > 0) fetch(0, 0);
@@ -277,9 +282,28 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
     if (idle || t * BT + 32 * yg >= n_y) continue;
     const unsigned char* st1 = smem + stage * C::STAGE_BYTES;
     const unsigned char* st2 = st1 + C::TILE_BYTES;
+    // some pair of the half tile has no part (the mask, or a query row that saw no key)
+    const i32x4 mk = *reinterpret_cast<const i32x4*>(&s_msk[stage][0]);
+    bool apart = __builtin_amdgcn_readfirstlane(mk[0] | mk[1] | mk[2] | mk[3]) != 0;
+    if constexpr (DKV) apart |= __builtin_amdgcn_ballot_w64(s_lse[stage][32 * yg + lq] == -__builtin_inff()) != 0;
     // formed where they are used: held across the loop the fragment addresses are registers too many at d = 64
     int rw = r_adr, wc = w_col;
     asm volatile("" : "+v"(rw), "+v"(wc));
+    if (apart) {                     // see odd_tiles (looked at here, where few registers are taken)
+      float z = DKV ? s_del[stage][32 * yg + lq] * 0.f : 0.f;
+#pragma unroll 4
+      for (int r = 0; r < 16; ++r) {
+        const int at = w_row + (8 * (r / 4) + r % 4) * C::RB + (wc ^ ((8 * (r / 4 % 2) + r % 4) * 16));
+        const float* y1 = reinterpret_cast<const float*>(st1 + at);
+        const float* y2 = reinterpret_cast<const float*>(st2 + at);
+#pragma unroll
+        for (int e = 0; e < NDB; ++e) {
+          z = __builtin_fmaf(y1[e], 0.f, z);
+          if constexpr (DKV) z = __builtin_fmaf(y2[e], 0.f, z);
+        }
+      }
+      if (__builtin_amdgcn_ballot_w64(!(z == 0.f)) != 0) { odd_tiles = true; continue; }
+    }
     // The matrix instructions as four streams, their A operands read from LDS one or two steps ahead, and the
     // vector work in the shadow of the ones that do not need it: p beside T2, ds beside acc2 (dq: beside acc1,
     // one row ahead).  Left to itself it stood between the streams, where a lone wavefront's matrix pipe is idle
@@ -340,14 +364,17 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
       P[r] = __builtin_amdgcn_exp2f(P[r]);
       if constexpr (DKV) P[r] = __builtin_fmaf(P[r], Pc[0][r], P[r]);
     }
-    const i32x4 mk = *reinterpret_cast<const i32x4*>(&s_msk[stage][0]);
-    if (__builtin_amdgcn_readfirstlane(mk[0] | mk[1] | mk[2] | mk[3]) != 0) {
+    if (apart) {
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4) {
         const i32x4 ps = *reinterpret_cast<const i32x4*>(&s_pos[stage][32 * yg + 8 * i4 + 4 * h]);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (DKV ? x_pos > ps[e] : ps[e] > x_pos) P[4 * i4 + e] = 0.f;
+          if (DKV ? x_pos > ps[e] : ps[e] > x_pos) {
+            P[4 * i4 + e] = 0.f;
+            E[4 * i4 + e] = 0.f;                 // (an infinity from finite factors as well)
+            for (f32x16& x : Ec) x[4 * i4 + e] = 0.f;
+          }
       }
     }
     struct Piece { float v[NDB]; };
@@ -398,6 +425,7 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
   __syncthreads();                   // the stages are free: the second half of the Y rows hands its sums over
 
   f32x4* hand = reinterpret_cast<f32x4*>(smem) + xs * (NACC * NDB * 4 * 64) + lane;
+  if (lane == 0) s_odd[2 * xs + yg] = odd_tiles ? 1 : 0;
   if (yg == 1) {
 #pragma unroll
     for (int a = 0; a < NACC; ++a)
@@ -409,9 +437,6 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
   }
   __syncthreads();
   if (yg == 1) return;
-  // An infinity or NaN of a pair that the mask leaves out, or of a row that saw no key, comes to an X row as 0 times
-  // that.  Rows whose sums are not finite are left out here and walked for themselves below, over the pairs they have.
-  float z = 0.f;
 #pragma unroll
   for (int a = 0; a < NACC; ++a)
 #pragma unroll
@@ -420,15 +445,10 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
       for (int i4 = 0; i4 < 4; ++i4) {
         const f32x4 o = hand[((a * NDB + db) * 4 + i4) * 64];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          acc[a][db][4 * i4 + e] += o[e];
-          z = __builtin_fmaf(acc[a][db][4 * i4 + e], 0.f, z);
-        }
+        for (int e = 0; e < 4; ++e) acc[a][db][4 * i4 + e] += o[e];
       }
-  const unsigned long long odd = __builtin_amdgcn_ballot_w64(x_valid && !(z == 0.f));
-  unsigned again = static_cast<unsigned>(odd) | static_cast<unsigned>(odd >> 32);          // bit i: row i of the strip
-  if (!x_valid || (again >> lq & 1)) {
-    // nothing, or below
+  if (!x_valid) {
+    // nothing
   } else if constexpr (DKV) {
     float* dk = reinterpret_cast<float*>(static_cast<unsigned char*>(p.dk) + x_off);
     float* dv = reinterpret_cast<float*>(static_cast<unsigned char*>(p.dv) + x_off);
@@ -449,58 +469,93 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
       f32x4 old = {0.f, 0.f, 0.f, 0.f};
       if (p.accumulate) old = *reinterpret_cast<const f32x4*>(dq + col);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) a[e] = __builtin_fmaf(__builtin_fmaf(a[e], x_rest, a[e]), p.scale, old[e]);
+      for (int e = 0; e < 4; ++e) a[e] = x_nl == -__builtin_inff() ? old[e] : __builtin_fmaf(__builtin_fmaf(a[e], x_rest, a[e]), p.scale, old[e]);     // (a row that saw no key: 0)
       *reinterpret_cast<f32x4*>(dq + col) = a;
     });
   }
+  if (__builtin_amdgcn_readfirstlane(s_odd[2 * xs] | s_odd[2 * xs + 1]) == 0) return;
+
+  // The half tiles that were left out: an X row after the other, a pair at a time, added to the rows stored above.  As
+  // slow as it is rare.
+  __threadfence_block();
+  const float* const f1 = reinterpret_cast<const float*>(Y1);
+  const float* const f2 = reinterpret_cast<const float*>(Y2);
   constexpr int CPL = D / 64;
-  while (again != 0) {               // a wavefront per row, a pair at a time: as slow as it is rare
-    const int src = __builtin_ctz(again);
-    again &= again - 1;
-    const int pos_a = __shfl(x_pos, src);
-    const int64_t at = (static_cast<int64_t>(__shfl(static_cast<int>(x_off >> 32), src)) << 32 | static_cast<unsigned>(__shfl(static_cast<int>(x_off), src))) / 4 + lane;
-    float xa[CPL], xb[CPL], sa[CPL], sb[CPL];
-#pragma unroll
-    for (int e = 0; e < CPL; ++e) {
-      xa[e] = static_cast<const float*>(DKV ? p.k : p.q)[at + 64 * e];
-      xb[e] = static_cast<const float*>(DKV ? p.v : p.dout)[at + 64 * e];
-      sa[e] = sb[e] = 0.f;
-    }
-    auto pair = [&](int64_t y, float nl, float del) __attribute__((always_inline)) {       // y: of the Y row, in floats
-      float ya[CPL], yb[CPL], s1 = 0.f, s2 = 0.f;
-#pragma unroll
-      for (int e = 0; e < CPL; ++e) {
-        ya[e] = reinterpret_cast<const float*>(Y1)[y + lane + 64 * e];
-        yb[e] = reinterpret_cast<const float*>(Y2)[y + lane + 64 * e];
-        s1 = __builtin_fmaf(xa[e], ya[e], s1);
-        s2 = __builtin_fmaf(xb[e], yb[e], s2);
-      }
-      const float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(wave_sum(s1), c, nl)), ds = pr * (wave_sum(s2) - del);
-#pragma unroll
-      for (int e = 0; e < CPL; ++e) {
-        sa[e] = __builtin_fmaf(ds, ya[e], sa[e]);
-        sb[e] = __builtin_fmaf(pr, yb[e], sb[e]);
-      }
-    };
+  // position, and offset in floats from Y1 and Y2, of row v of the stream; dkv: and of its lse and delta
+  auto y_at = [&](int v, int& pos, int64_t& at) __attribute__((always_inline)) {
+    at = 0;
     if constexpr (!DKV) {
-      const float nl = __shfl(x_nl, src), del = __shfl(x_del, src);
-      for (int j = 0; j < e_n && nl > -__builtin_inff(); ++j)
-        for (int v = e_vbeg[j]; v < e_vbeg[j + 1] && v + e_goff[j] <= pos_a; ++v) pair((v + e_goff[j]) * (k_pitch / 4), nl, del);
-      float* dq = (p.n_split > 1 ? p.part_dq + share * p.part_stride : p.dq_acc) + at;
-#pragma unroll
-      for (int e = 0; e < CPL; ++e) dq[64 * e] = __builtin_fmaf(sa[e], p.scale, p.accumulate ? dq[64 * e] : 0.f);
+      pos = INT_MAX;
+      for (int j = 0; j < e_n; ++j)
+        if (v >= e_vbeg[j] && v < e_vbeg[j + 1]) pos = v + e_goff[j];
+      return (pos == INT_MAX ? 0 : pos) * (k_pitch / 4);
     } else {
-      for (int b = 0; b < p.n_blk; ++b)
-        for (int r = p.causal ? max(0, pos_a - p.blk[b].pos0) : 0; r < p.blk[b].n; ++r)
-          for (int hh = 0; hh < G; ++hh) {
-            const int64_t rh = static_cast<int64_t>(p.blk[b].row0 + r) * p.Hq + g * G + hh;
-            const float nl = neg_lse2(p.lse[bi * p.lse_bstride + rh]);
-            if (nl > -__builtin_inff()) pair(rh * D, nl, p.delta[bi * p.lse_bstride + rh]);
-          }
+      int hh;
+      const int row = y_row(v, pos, hh);
+      at = bi * p.lse_bstride + static_cast<int64_t>(row) * p.Hq + g * G + hh;
+      return row * (q_pitch / 4) + static_cast<int64_t>(g * G + hh) * D;
+    }
+  };
+#pragma unroll 1
+  for (int t = 0; t < n_tiles; ++t) {
+    int pos;
+    int64_t at;
+    const int64_t mine = y_at(t * BT + lane, pos, at);
+    const bool masked = __builtin_amdgcn_ballot_w64(DKV ? pos < x_hi : pos > x_lo) != 0;
+    const unsigned long long no_key = __builtin_amdgcn_ballot_w64(DKV && p.lse[at] == -__builtin_inff());
+    if (!masked && no_key == 0) continue;
+    float z = DKV ? p.delta[at] * 0.f : 0.f;
+#pragma unroll 1
+    for (int e = 0; e < D; ++e) {
+      z = __builtin_fmaf(f1[mine + e], 0.f, z);
+      if constexpr (DKV) z = __builtin_fmaf(f2[mine + e], 0.f, z);
+    }
+    const unsigned long long odd = __builtin_amdgcn_ballot_w64(!(z == 0.f));
+#pragma unroll 1
+    for (int half = 0; half < 2; ++half) {
+      if (static_cast<unsigned>(odd >> 32 * half) == 0 || !(masked || static_cast<unsigned>(no_key >> 32 * half) != 0)) continue;
+      const int v_end = min(t * BT + 32 * half + 32, n_y);
+#pragma unroll 1
+      for (int src = 0; src < 32; ++src) {
+        if (__shfl(x_valid ? 1 : 0, src) == 0) break;
+        const int pos_a = __shfl(x_pos, src);
+        const int64_t xo = (static_cast<int64_t>(__shfl(static_cast<int>(x_off >> 32), src)) << 32 | static_cast<unsigned>(__shfl(static_cast<int>(x_off), src))) / 4 + lane;
+        const float nl_a = __shfl(x_nl, src), rest_a = __shfl(x_rest, src), del_a = __shfl(x_del, src);
+        float xa[CPL], xb[CPL], sa[CPL], sb[CPL];
 #pragma unroll
-      for (int e = 0; e < CPL; ++e) {
-        static_cast<float*>(p.dk)[at + 64 * e] = sa[e] * p.scale;
-        static_cast<float*>(p.dv)[at + 64 * e] = sb[e];
+        for (int e = 0; e < CPL; ++e) {
+          xa[e] = static_cast<const float*>(DKV ? p.k : p.q)[xo + 64 * e];
+          xb[e] = static_cast<const float*>(DKV ? p.v : p.dout)[xo + 64 * e];
+          sa[e] = sb[e] = 0.f;
+        }
+#pragma unroll 1
+        for (int v = t * BT + 32 * half; v < v_end; ++v) {
+          const int64_t y = y_at(v, pos, at) + lane;
+          const float l = DKV ? p.lse[at] : 0.f, nl = DKV ? neg_lse2(l) : nl_a;
+          if ((DKV ? pos_a > pos : pos > pos_a) || nl == -__builtin_inff()) continue;
+          float ya[CPL], yb[CPL], s1 = 0.f, s2 = 0.f;
+#pragma unroll
+          for (int e = 0; e < CPL; ++e) {
+            ya[e] = f1[y + 64 * e];
+            yb[e] = f2[y + 64 * e];
+            s1 = __builtin_fmaf(xa[e], ya[e], s1);
+            s2 = __builtin_fmaf(xb[e], yb[e], s2);
+          }
+          float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(wave_sum(s1), c, nl));
+          pr = __builtin_fmaf(pr, DKV ? lse2_rest(l, nl) : rest_a, pr);
+          const float ds = pr * (wave_sum(s2) - (DKV ? p.delta[at] : del_a));
+#pragma unroll
+          for (int e = 0; e < CPL; ++e) {
+            sa[e] = __builtin_fmaf(ds, ya[e], sa[e]);
+            sb[e] = __builtin_fmaf(pr, yb[e], sb[e]);
+          }
+        }
+        float* const d1 = (DKV ? static_cast<float*>(p.dk) : p.n_split > 1 ? p.part_dq + share * p.part_stride : p.dq_acc) + xo;
+#pragma unroll
+        for (int e = 0; e < CPL; ++e) {
+          d1[64 * e] = __builtin_fmaf(sa[e], p.scale, d1[64 * e]);
+          if constexpr (DKV) static_cast<float*>(p.dv)[xo + 64 * e] += sb[e];
+        }
       }
     }
   }

@@ -272,6 +272,9 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
   float m_run = kNegBig, l_run = 0.f, l_lo = 0.f, r_fix = 0.f;
   const float c = p.scale * kLog2e;
 
+  // fp32: an infinity or NaN in V of a key that a row does not see would come to it as 0 times that.  Only tiles with the
+  // element-wise mask hold such pairs; those of them with such a V are left out and added key by key after the others.
+  bool odd_tiles = false;
   const bool idle = __builtin_amdgcn_readfirstlane(tile * BM + strip * 32) >= m_all;
   if (n_tiles > 0) {
     locate(0);
@@ -290,6 +293,21 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
     if (idle) continue;
     const unsigned char* st = smem + stage * C::STAGE_BYTES;
 
+    bool masked = false;             // by element
+    if constexpr (F32) {             // (asked here, where few registers are taken; bf16: under way with the V fragments)
+      const i32x4 mk = *reinterpret_cast<const i32x4*>(&s_msk[stage][0]);
+      masked = __builtin_amdgcn_readfirstlane(mk[0] | mk[1] | mk[2] | mk[3]) != 0;
+      if (masked) {                              // see odd_tiles
+        float z = 0.f;
+#pragma unroll 4
+        for (int r = 0; r < 16; ++r) {
+          const float* va = reinterpret_cast<const float*>(st + v_adr[0] + (8 * (r / 4) + r % 4) * C::RB);
+#pragma unroll
+          for (int e = 0; e < NDB; ++e) z = __builtin_fmaf(va[e], 0.f, z);
+        }
+        if (__builtin_amdgcn_ballot_w64(!(z == 0.f)) != 0) { odd_tiles = true; continue; }
+      }
+    }
     // The matrix instructions of both products take their A operands as streams of fragments read ahead, so
     // that a wavefront alone on its SIMD does not wait for LDS at each of them (one fp32 K fragment feeds four
     // long instructions: the compiler's order does).
@@ -327,8 +345,11 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
       vring[F % PV] = lds_tr8(va, va + 8 * C::RB);
     };
     if constexpr (!F32) static_for<PV>(read_v);               // on their way during the maxima
-    const i32x4 mk = *reinterpret_cast<const i32x4*>(&s_msk[stage][0]);
-    if (__builtin_amdgcn_readfirstlane(mk[0] | mk[1] | mk[2] | mk[3]) != 0) {
+    if constexpr (!F32) {
+      const i32x4 mk = *reinterpret_cast<const i32x4*>(&s_msk[stage][0]);
+      masked = __builtin_amdgcn_readfirstlane(mk[0] | mk[1] | mk[2] | mk[3]) != 0;
+    }
+    if (masked) {
 #pragma unroll
       for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
@@ -415,6 +436,48 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
   if constexpr (F32) {
 #pragma unroll
     for (int db = 0; db < NDB; ++db) o[db] += o_sum[db];
+    if (odd_tiles) {
+#pragma unroll 1
+      for (int t = 0; t < n_tiles; ++t) {
+        const int v = t * BT + lq;
+        int lo = 0, n = n_eff;                     // as in locate
+        while (n > 1) {
+          const int half = n >> 1;
+          if (e_vbeg[lo + half] <= v) lo += half;
+          n -= half;
+        }
+        const int tok = v < n_keys ? v + e_goff[lo] : INT_MAX;
+        if (__builtin_amdgcn_ballot_w64(tok > q_first) == 0) continue;
+        const float* vr = reinterpret_cast<const float*>(Vg + static_cast<unsigned long long>(tok == INT_MAX ? 0 : tok) * row_bytes) + h * (D / 2);
+        float z = 0.f;
+        for (int e = 0; e < D / 2; ++e) z = __builtin_fmaf(vr[e], 0.f, z);
+        if (__builtin_amdgcn_ballot_w64(!(z == 0.f)) == 0) continue;
+#pragma unroll 1
+        for (int k = 0; k < BT; ++k) {
+          const int key = __builtin_amdgcn_readlane(tok, k);
+          if (key == INT_MAX) break;               // past the end, as all that follow
+          const u32x4* kr = reinterpret_cast<const u32x4*>(Kg + static_cast<unsigned long long>(key) * row_bytes) + h;
+          float dot = 0.f;
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) {
+            const f32x4 a = __builtin_bit_cast(f32x4, kr[2 * j]), b = __builtin_bit_cast(f32x4, qf[j]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dot = __builtin_fmaf(a[e], b[e], dot);
+          }
+          dot += __shfl_xor(dot, 32);
+          if (key > q_pos) continue;
+          const float m_new = fmaxf(m_run, dot * c), alpha = fast_exp2(m_run - m_new), pk = fast_exp2(__builtin_fmaf(dot, c, -m_new));
+          m_run = m_new;
+          l_run *= alpha;
+          l_lo = l_lo * alpha + (h == 0 ? pk : 0.f);
+          const float* vk = reinterpret_cast<const float*>(Vg + static_cast<unsigned long long>(key) * row_bytes);
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+#pragma unroll
+            for (int db = 0; db < NDB; ++db) o[db][i] = __builtin_fmaf(pk, vk[NDB * (8 * (i / 4) + 4 * h + i % 4) + db], o[db][i] * alpha);
+        }
+      }
+    }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // no fetch may still be writing LDS when the workgroup ends
 
@@ -424,19 +487,6 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
   const bool seen = l_tot > 0.f;
   float wb = seen && r_tot > 0.f ? 1.f / r_tot : 0.f;
   float lse_new = seen ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -__builtin_inff();
-  // fp32: an infinity or NaN of a key that a row of the tile does not see comes to it as 0 times that.  Rows whose
-  // sums are not finite are left out here and walked for themselves below, over the keys they see.
-  unsigned again = 0;                              // bit i: row i of the strip
-  if constexpr (F32) {
-    float z = 0.f;
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) z = __builtin_fmaf(o[db][i], 0.f, z);
-    const unsigned long long odd = __builtin_amdgcn_ballot_w64(q_valid && !(z == 0.f));
-    again = static_cast<unsigned>(odd) | static_cast<unsigned>(odd >> 32);
-  }
-  const bool store = q_valid && !(again >> lq & 1);
   const int64_t ooff = bi * p.o_bstride + (static_cast<int64_t>(q_row0 + row) * p.Hq + hq) * D;
   const int64_t loff = bi * p.lse_bstride + static_cast<int64_t>(q_row0 + row) * p.Hq + hq;
   // columns of register quad q of the lane: bf16 block q / 4, 32 (q / 4) + 8 (q % 4) + 4 h; fp32 d = 128
@@ -456,8 +506,8 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
       return 2 * (8 * (2 * Q / 4) + 4 * h + (2 * Q) % 4);
     }
   };
-  if (!store) {
-    // nothing, or below
+  if (!q_valid) {
+    // nothing
   } else if (p.merge == 0 && (ns > 1 || p.out_final == nullptr)) {
     // a share's pair, or the partial pair of a step
     const int64_t n_q = second ? t1.n_q : t0.n_q;
@@ -511,75 +561,6 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
       *reinterpret_cast<f32x4*>(od + col) = x;
     });
     if (h == 0) p.lse_dst[loff] = lse_new;      // (the lane of the other half has read the old one: same wavefront)
-  }
-  if constexpr (F32) {
-    while (again != 0) {                           // a wavefront per row, a key per lane: as slow as it is rare
-      const int src = __builtin_ctz(again);
-      again &= again - 1;
-      const int row_a = __shfl(row, src), hq_a = __shfl(hq, src), pos_a = __shfl(q_pos, src);
-      const int64_t rh_a = static_cast<int64_t>(q_row0 + row_a) * p.Hq + hq_a;
-      const float* qa = static_cast<const float*>(p.q) + bi * p.q_bstride + rh_a * D;
-      float m_a = -__builtin_inff(), l_a = 0.f, acc[D / 64];
-#pragma unroll
-      for (int e = 0; e < D / 64; ++e) acc[e] = 0.f;
-      for (int v0 = 0; v0 < n_keys; v0 += 64) {
-        const int v = v0 + lane;
-        int lo = 0, n = n_eff;                     // as in locate
-        while (n > 1) {
-          const int half = n >> 1;
-          if (e_vbeg[lo + half] <= v) lo += half;
-          n -= half;
-        }
-        const int tok = v < n_keys ? v + e_goff[lo] : INT_MAX;
-        const bool sees = tok <= pos_a;
-        unsigned long long todo = __builtin_amdgcn_ballot_w64(sees);
-        if (todo == 0) continue;
-        float sc = -__builtin_inff();
-        if (sees) {
-          const float* kr = reinterpret_cast<const float*>(Kg + static_cast<unsigned long long>(tok) * row_bytes);
-          float dot = 0.f;
-          for (int e = 0; e < D; ++e) dot = __builtin_fmaf(qa[e], kr[e], dot);
-          sc = dot * c;
-        }
-        float m_new = fmaxf(m_a, sc);
-#pragma unroll
-        for (int s = 32; s >= 1; s >>= 1) m_new = fmaxf(m_new, __shfl_xor(m_new, s));
-        const float alpha = fast_exp2(m_a - m_new), pr = sees ? fast_exp2(sc - m_new) : 0.f;
-        float sum = pr;
-#pragma unroll
-        for (int s = 32; s >= 1; s >>= 1) sum += __shfl_xor(sum, s);
-        m_a = m_new;
-        l_a = l_a * alpha + sum;
-#pragma unroll
-        for (int e = 0; e < D / 64; ++e) acc[e] *= alpha;
-        for (; todo != 0; todo &= todo - 1) {
-          const int j = __builtin_ctzll(todo);
-          const float pj = __shfl(pr, j);
-          const float* vr = reinterpret_cast<const float*>(Vg + static_cast<unsigned long long>(__shfl(tok, j)) * row_bytes);
-#pragma unroll
-          for (int e = 0; e < D / 64; ++e) acc[e] = __builtin_fmaf(pj, vr[lane + 64 * e], acc[e]);
-        }
-      }
-      float wn = l_a > 0.f ? 1.f / l_a : 0.f, wo = 0.f, lse_a = l_a > 0.f ? (m_a + __builtin_amdgcn_logf(l_a)) * kLn2 : -__builtin_inff();
-      const int64_t part = ns > 1 ? (static_cast<int64_t>(share) * p.batch + bi) * (second ? t1.n_q : t0.n_q) * p.Hq + static_cast<int64_t>(row_a) * p.Hq + hq_a : 0;
-      float* od = ns > 1 ? (second ? p.part_o[1] : p.part_o[0]) + part * D
-                         : (p.out_final != nullptr ? static_cast<float*>(p.out_final) : p.o_dst) + bi * p.o_bstride + rh_a * D;
-      float* ld = ns > 1 ? (second ? p.part_lse[1] : p.part_lse[0]) + part : p.lse_dst + bi * p.lse_bstride + rh_a;
-      if (p.merge != 0) {
-        const float lse_old = *ld, mxl = fmaxf(lse_old, lse_a);
-        const bool some = mxl > -__builtin_inff();
-        const float ea = some ? __expf(lse_old - mxl) : 0.f, eb = some ? __expf(lse_a - mxl) : 0.f, rden = some ? 1.f / (ea + eb) : 0.f;
-        wo = ea * rden;
-        wn *= eb * rden;
-        lse_a = some ? mxl + __logf(ea + eb) : lse_a;
-      }
-#pragma unroll
-      for (int e = 0; e < D / 64; ++e) {
-        const float mine = acc[e] * wn;
-        od[lane + 64 * e] = p.merge != 0 ? __builtin_fmaf(wo, od[lane + 64 * e], mine) : mine;
-      }
-      if (lane == 0) *ld = lse_a;
-    }
   }
 }
 

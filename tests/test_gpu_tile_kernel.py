@@ -248,3 +248,72 @@ def test_fp32_what_is_not_seen_has_no_part(tb, case):
         err = float(np.abs(g[at].astype(np.float64) - r[at]).max())
         assert err <= 1e-4 * max(1.0, float(np.abs(r).max())), (name, nm, err)
     assert not np.isfinite(dv[: pos[r_inf] + 1]).any()
+
+
+@pytest.mark.parametrize("heads", [(2, 2, 64), (6, 2, 128)], ids=["2x64", "6/2x128"])
+def test_fp32_one_nan_at_any_place_of_a_tile(tb, heads):
+    """A NaN in one V row, then in one upstream gradient, at places all over the tiles (diagonal or not, either half of
+    one): what does not see it is what it is without it, what sees it is NaN."""
+    from oracle import schedule as sch
+    Hq, Hkv, d = heads
+    w = wl.Workload("nan_place", 4, 2, 8 * 150, Hq, Hkv, d, "fp32", wl.ZIGZAG_CAUSAL, seed=wl.BASE_SEED + 9400 + d)
+    q, k, v = (t.cuda() for t in wl.make_qkv(w))
+    do = wl.make_dout(w).cuda()
+    s = tb.tasp_schedule(w.n_ranks, w.rank)
+    pos = torch.as_tensor(np.asarray(sch.local_positions(w.n_ranks, w.rank, w.S, w.mask_mode))).cuda()
+    out, lse = (t.clone() for t in tb.tasp_chunk_attn(q, k, v, s, w.mask_mode))
+    dq, dk, dv = (t.clone() for t in tb.tasp_chunk_attn_bwd(q, k, v, out, lse, do, s, w.mask_mode))
+    keys = torch.arange(w.S, device="cuda")
+    for row in range(3, w.L, 29):
+        t = int(pos[row])
+        bad = v.clone()
+        bad[t] = float("nan")
+        o, l = tb.tasp_chunk_attn(q, k, bad, s, w.mask_mode)
+        gq = tb.tasp_chunk_attn_bwd(q, k, bad, out, lse, do, s, w.mask_mode)[0]
+        sees = pos >= t
+        assert bool(o[sees].isnan().all()) and bool(gq[sees].isnan().all()), t
+        assert float((o[~sees] - out[~sees]).abs().max()) <= 1e-5 and float((gq[~sees] - dq[~sees]).abs().max()) <= 1e-4, t
+        assert float((l - lse).abs().max()) <= 1e-5, t
+        bad = do.clone()
+        bad[row] = float("nan")
+        _, gk, gv = tb.tasp_chunk_attn_bwd(q, k, v, out, lse, bad, s, w.mask_mode)
+        seen = keys <= t
+        assert bool(gk[seen].isnan().all()) and bool(gv[seen].isnan().all()), t
+        assert float((gk[~seen] - dk[~seen]).abs().max()) <= 1e-4 and float((gv[~seen] - dv[~seen]).abs().max()) <= 1e-4, t
+
+
+def test_fp32_values_that_are_not_finite_cost_little(tb):
+    """Nearly all rows that see a NaN or infinity take the ordinary way: a call with one in a key or row that every other one
+    meets, and one with nothing but NaN, take less than six times a clean one (each row by itself: hundreds of times)."""
+    w = wl.Workload("not_finite_time", 8, 3, 16384, 4, 4, 64, "fp32", wl.ZIGZAG_CAUSAL, seed=wl.BASE_SEED + 9500)
+    q, k, v = (t.cuda() for t in wl.make_qkv(w))
+    do = wl.make_dout(w).cuda()
+    s = tb.tasp_schedule(w.n_ranks, w.rank)
+    out, lse = (t.clone() for t in tb.tasp_chunk_attn(q, k, v, s, w.mask_mode))
+
+    def best_ms(f):
+        times = []
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            f()
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    def times(q, k, v, out, lse, do):
+        fwd = tb.ChunkAttnPlan(s, q, k, v, w.mask_mode)
+        bwd = tb.ChunkAttnBwdPlan(s, q, k, v, out, lse, do, w.mask_mode)
+        return best_ms(fwd.run), best_ms(bwd.run)
+
+    clean = times(q, k, v, out, lse, do)
+    first = v.clone()
+    first[0] = float("inf")
+    dead_o, dead_l, dead_q = out.clone(), lse.clone(), q.clone()
+    dead_q[-1], dead_o[-1], dead_l[-1] = float("nan"), float("nan"), float("-inf")           # the forward's result for a NaN row
+    every = [torch.full_like(t, float("nan")) for t in (q, k, v, out, lse, do)]
+    for name, args in (("first key", (q, k, first, out, lse, do)), ("last row", (dead_q, k, v, dead_o, dead_l, do)), ("all", every)):
+        got = times(*args)
+        print(name, clean, got, flush=True)
+        assert got[0] <= 6 * clean[0] and got[1] <= 6 * clean[1], (name, clean, got)
