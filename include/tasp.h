@@ -193,14 +193,17 @@ int    tasp_chunk_attn(const tasp_schedule_t* s, const tasp_attn_args* a, void* 
  * device and frees nothing; inputs and outputs are the caller's as before.
  *   - A call whose tasp_chunk_attn_workspace_bytes() exceeds TASP_STATIC_SCRATCH_BYTES returns
  *     TASP_EWORKSPACE and enqueues nothing (bf16: B*L*Hq*d <= 16 Mi elements with fuse_merge, half of
- *     that without; fp32 with fuse_merge needs no workspace at all).
+ *     that without; fp32 with fuse_merge and without fuse_steps needs none).
  *   - The device that is current when the call is made must be the device of hip_stream.  The first
  *     call on a device asks the HIP runtime for the array's address on that device (a symbol query;
  *     make that first call outside a stream capture).
  *   - All calls on one GPU share the one array, and it keeps the last call's contents: nothing in it
  *     has to start at zero (step 0 of every call overwrites what it uses), but two calls that overlap
- *     on one GPU (different streams, or different threads) race.  Serialise them.
- * Results are those of tasp_chunk_attn (the same kernels run). */
+ *     on one GPU (different streams, or different threads) race.  Serialise them.  A call whose
+ *     tasp_chunk_attn_workspace_bytes() is 0 does not touch the array and may overlap with any other.
+ * Results are those of tasp_chunk_attn (the same kernels run) bit for bit; a call that needs no workspace
+ * and whose lists of segments need device memory there (some hundred sub-chunks per query block) runs
+ * step by step and differs in rounding. */
 #define TASP_STATIC_SCRATCH_BYTES (64u << 20)
 int tasp_chunk_attn_static(const tasp_schedule_t* s, const tasp_attn_args* a, void* hip_stream);
 

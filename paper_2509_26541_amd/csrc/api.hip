@@ -175,6 +175,7 @@ int place_lists(JoinedSteps* js, bool in_descriptor, int32_t* dev_table, hipStre
 struct FwdPlan {
   bool joined = false;
   bool tile = false;                  // attn_tile_kernel
+  bool serial = false;                // a workgroup of it takes all shares of its tile: no partial pairs
   int32_t n_split[tasp::kMaxTasks] = {1, 1};
   size_t table_bytes = 0;             // device memory for the segment lists, in front of the partial pairs
   size_t part_bytes = 0;              // of the shares' pairs
@@ -304,7 +305,9 @@ bool tile_is_faster(const AttnLaunch& lp, int d, const int64_t* keys, const int3
 // Decides from shapes alone (`js` holds the joined lists).  Kernel and shares are those for the largest workspace
 // that tasp_chunk_attn_best_workspace_bytes could report, wherever the `ws_bytes` of the call hold these shares
 // (none do with the large kernel): the results do not depend on who brings the workspace, if it is the reported
-// one or larger.  With less the shares are dealt anew, and the kernel is chosen for them.
+// one or larger.  With less the shares are dealt anew, and the kernel is chosen for them.  A call without any workspace
+// (fp32 with the merge folded in needs none) has its workgroups take the shares in turn: the same results, without
+// the gain, and nothing that calls on other streams could write over.
 FwdPlan plan_forward(const tasp_attn_args* a, const JoinedSteps& js, size_t need, size_t ws_bytes) {
   FwdPlan pl;
   const bool fp32 = a->dtype == TASP_DTYPE_FP32;
@@ -320,8 +323,9 @@ FwdPlan plan_forward(const tasp_attn_args* a, const JoinedSteps& js, size_t need
     pl.part_bytes = all_share_bytes(js.all, a->d, n_split);
     for (int t = 0; t < js.all.n_tasks; ++t) pl.n_split[t] = n_split[t];
     if (pl.part_bytes <= ws_bytes - pl.table_bytes) return pl;
+    if (fp32 && ws_bytes == 0) { pl.serial = true; pl.part_bytes = 0; return pl; }
     room = ws_bytes - pl.table_bytes;                 // what is dealt for this much fits
-    pl = FwdPlan{true, false, {1, 1}, pl.table_bytes, 0};
+    pl = FwdPlan{true, false, false, {1, 1}, pl.table_bytes, 0};
   }
 }
 
@@ -357,8 +361,8 @@ struct Scope {
   ~Scope() { if (p) p->end(); }
 };
 
-hipError_t launch_attn(const AttnLaunch& lp, const tasp_attn_args* a, hipStream_t stream, bool tile) {
-  return tile ? tasp::launch_attn_tile(lp, a->d, a->dtype == TASP_DTYPE_FP32, stream) : tasp::launch_attn_bf16(lp, a->d, stream);
+hipError_t launch_attn(const AttnLaunch& lp, const tasp_attn_args* a, hipStream_t stream, bool tile, bool serial = false) {
+  return tile ? tasp::launch_attn_tile(lp, a->d, a->dtype == TASP_DTYPE_FP32, serial, stream) : tasp::launch_attn_bf16(lp, a->d, stream);
 }
 
 // The launch of one step.  With more local rows than kJoinRows the large kernel is within 5 % of the
@@ -695,7 +699,7 @@ static int run_chunk_attn(const tasp_schedule_t* s, const tasp_attn_args* a, voi
         size_t at = pl.table_bytes;
         for (int t = 0; t < all.n_tasks; ++t) {
           all.n_split[t] = pl.n_split[t];
-          if (pl.n_split[t] < 2) continue;
+          if (pl.n_split[t] < 2 || pl.serial) continue;
           const size_t lse = pl.n_split[t] * share_bytes(all, t, a->d) / (a->d + 1);
           all.part_o[t] = reinterpret_cast<float*>(static_cast<unsigned char*>(a->workspace) + at);
           at += align_up(lse * a->d);
@@ -704,7 +708,7 @@ static int run_chunk_attn(const tasp_schedule_t* s, const tasp_attn_args* a, voi
         }
         {
           Scope sc(prof, Profiler::kAttn);
-          if (launch_attn(all, a, stream, pl.tile) != hipSuccess) return TASP_EHIP;
+          if (launch_attn(all, a, stream, pl.tile, pl.serial) != hipSuccess) return TASP_EHIP;
         }
         if (pl.part_bytes > 0) {
           Scope sc(prof, Profiler::kOther);
@@ -787,13 +791,16 @@ int tasp_chunk_attn_static(const tasp_schedule_t* s, const tasp_attn_args* a, vo
   const int st = validate(s, a, &sh);
   if (st != TASP_OK) return st;
   // workspace_bytes() trusts its arguments; they have been validated above
-  if (tasp_chunk_attn_workspace_bytes(s, a) > static_cast<size_t>(TASP_STATIC_SCRATCH_BYTES)) return TASP_EWORKSPACE;
-  void* ws = nullptr;
-  const int sp = static_scratch(&ws);
-  if (sp != TASP_OK) return sp;
+  const size_t need = tasp_chunk_attn_workspace_bytes(s, a);
+  if (need > static_cast<size_t>(TASP_STATIC_SCRATCH_BYTES)) return TASP_EWORKSPACE;
   tasp_attn_args b = *a;
-  b.workspace = ws;
-  b.workspace_bytes = TASP_STATIC_SCRATCH_BYTES;
+  b.workspace = nullptr;
+  b.workspace_bytes = 0;
+  if (need > 0) {            // a call that needs no workspace leaves the array alone: such calls may overlap
+    const int sp = static_scratch(&b.workspace);
+    if (sp != TASP_OK) return sp;
+    b.workspace_bytes = TASP_STATIC_SCRATCH_BYTES;
+  }
   return run_chunk_attn(s, &b, hip_stream, nullptr);
 }
 

@@ -78,8 +78,21 @@ __device__ inline bf16x8 lds_tr8(const unsigned char* lo, const unsigned char* h
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(const AttnLaunch p) {
+// One more (normalised) pair into running sums that are kept unnormalised against their running maximum: the sums are
+// multiplied by r, the pair's outputs by w.  Where no share so far saw a key all weights are 0, and so are the outputs unless
+// they are NaN (a row of NaN scores has lse = -inf and NaN outputs), which 0 times them keeps.
+__device__ inline void fold(float lse, float& mx, float& den, float& r, float& w) {
+  const float m = fmaxf(mx, lse), ref = m == -__builtin_inff() ? 0.f : m;
+  r = __expf(mx - ref);
+  w = __expf(lse - ref);
+  den = __builtin_fmaf(den, r, w);
+  mx = m;
+}
+
+// SERIAL (fp32): a workgroup takes all shares of its tile one after the other and folds their pairs in the output
+// itself, as combine_kernel does from memory: the same bits without a workspace.
+template <typename T, int D, bool SERIAL>
+__global__ __launch_bounds__(NTHREADS, (D == 64 ? 3 : 2) - SERIAL) void attn_tile_kernel(const AttnLaunch p) {
   using C = TCfg<T, D>;
   constexpr bool F32 = C::F32;
   constexpr int BT = C::BT, NKB = C::NKB, NDB = C::NDB, NJ = C::UNITS / 2;
@@ -108,7 +121,7 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
   const int G = p.Hq / p.Hkv;
   const int m0 = t0.n_q * G, m1 = p.n_tasks > 1 ? t1.n_q * G : 0;
   const int tiles0 = (m0 + BM - 1) / BM, tiles1 = (m1 + BM - 1) / BM;
-  const int items0 = tiles0 * p.n_split[0], per_g = items0 + tiles1 * p.n_split[1];
+  const int items0 = tiles0 * (SERIAL ? 1 : p.n_split[0]), per_g = items0 + tiles1 * (SERIAL ? 1 : p.n_split[1]);
   const int w_all = xcd_balanced(blockIdx.x, p.batch * p.Hkv, per_g, xcd_window(D == 64 ? 96 : 64, per_g));
   if (w_all < 0) return;
   const int bg = w_all / per_g;
@@ -117,9 +130,10 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
   const bool second = rem >= items0;
   if (second) rem -= items0;
   const int ns = second ? p.n_split[1] : p.n_split[0];
-  const int share = rem % ns;
+  const int per_share = SERIAL ? 1 : ns;
+  int share = rem % per_share;
   // under the causal mask the later tiles of a block see more keys: they start first
-  const int tile = p.causal ? (second ? tiles1 : tiles0) - 1 - rem / ns : rem / ns;
+  const int tile = p.causal ? (second ? tiles1 : tiles0) - 1 - rem / per_share : rem / per_share;
   const int q_row0 = second ? t1.q_row0 : t0.q_row0, q_pos0 = second ? t1.q_pos0 : t0.q_pos0;
   const int n_seg = second ? t1.n_seg : t0.n_seg, seg0 = second ? t1.seg0 : t0.seg0;
   const int32_t* const seg_ext = second ? seg_ext1 : seg_ext0;
@@ -144,6 +158,16 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
     for (int j = 0; j < NJ; ++j) qf[j] = src[2 * j];
   }
 
+  float mx_all = -__builtin_inff(), den_all = 0.f;       // SERIAL: of the shares so far
+  for (int round = 0; SERIAL ? round < ns : round == 0; ++round) {
+  if constexpr (SERIAL) {
+    share = round;
+    if (round > 0) {
+#pragma unroll
+      for (int i = 0; i < 2 * kPoolSeg / NTHREADS; ++i) pooled[i] = p.pool[NTHREADS * i + tid];
+      __syncthreads();               // nobody reads the tiles and lists of the share before any more
+    }
+  }
   // ---- effective segments: what the mask leaves of every segment for this tile, then the share of it
   // that is this workgroup's.  The first wavefront works through the list, 64 segments per round.
   if (seg_ext == nullptr) {
@@ -506,7 +530,28 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
       return 2 * (8 * (2 * Q / 4) + 4 * h + (2 * Q) % 4);
     }
   };
-  if (!q_valid) {
+  if (SERIAL && ns > 1) {
+    float r, w;
+    fold(lse_new, mx_all, den_all, r, w);
+    const bool last = round == ns - 1;
+    const float inv = den_all > 0.f ? 1.f / den_all : 0.f;
+    float* od = static_cast<float*>(p.out_final) + ooff;
+    if (q_valid) {
+      static_for<D / 8>([&](auto qq) __attribute__((always_inline)) {
+        f32x4 x, sum = {0.f, 0.f, 0.f, 0.f};
+        const int col = quad(qq, x);
+        if (round > 0) sum = *reinterpret_cast<const f32x4*>(od + col);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          x[e] *= wb;
+          sum[e] = __builtin_fmaf(w, x[e], sum[e] * r);
+          if (last) sum[e] *= inv;
+        }
+        *reinterpret_cast<f32x4*>(od + col) = sum;
+      });
+      if (last && h == 0) p.lse_dst[loff] = den_all > 0.f ? mx_all + __logf(den_all) : -__builtin_inff();
+    }
+  } else if (!q_valid) {
     // nothing
   } else if (p.merge == 0 && (ns > 1 || p.out_final == nullptr)) {
     // a share's pair, or the partial pair of a step
@@ -562,28 +607,30 @@ __global__ __launch_bounds__(NTHREADS, D == 64 ? 3 : 2) void attn_tile_kernel(co
     });
     if (h == 0) p.lse_dst[loff] = lse_new;      // (the lane of the other half has read the old one: same wavefront)
   }
+  }  // next share (SERIAL)
 }
 
-template <typename T, int D>
+template <typename T, int D, bool SERIAL = false>
 hipError_t launch_tile_variant(const AttnLaunch& p, hipStream_t stream) {
   const int64_t G = p.Hq / p.Hkv;
   int64_t per_g = 0;
   for (int t = 0; t < p.n_tasks; ++t) {
     if (p.task[t].n_q * G > INT_MAX - BM || p.n_split[t] < 1) return hipErrorInvalidValue;
-    per_g += (p.task[t].n_q * G + BM - 1) / BM * p.n_split[t];
+    per_g += (p.task[t].n_q * G + BM - 1) / BM * (SERIAL ? 1 : p.n_split[t]);
   }
   const int64_t units = static_cast<int64_t>(p.batch) * p.Hkv;
   if (per_g == 0 || units == 0) return hipSuccess;
   if (per_g * units > INT_MAX) return hipErrorInvalidValue;
   const int64_t blocks = xcd_balanced_blocks(units, per_g);
   if (blocks > INT_MAX) return hipErrorInvalidValue;
-  return TASP_LAUNCH((attn_tile_kernel<T, D>), dim3(static_cast<unsigned>(blocks)), dim3(NTHREADS), stream, p);
+  return TASP_LAUNCH((attn_tile_kernel<T, D, SERIAL>), dim3(static_cast<unsigned>(blocks)), dim3(NTHREADS), stream, p);
 }
 
 // The pairs of a row's shares added up as in tasp_lse_merge_many, D / 4 lanes of 4 columns to a (row, head).
-// SPREAD, for more than four shares: a wavefront per (row, head), the shares dealt to its 256 / D groups of
+// bf16 with more than four shares (SPREAD): a wavefront per (row, head), the shares dealt to its 256 / D groups of
 // lanes, eight of a lane's shares requested at once, so that a row costs one or two trips to memory (a share
-// at a time, 16 shares of 1 024 rows took 7 us; now 4).  Otherwise a lane takes all shares of its columns.
+// at a time, 16 shares of 1 024 rows took 7 us; now 4).  Otherwise a lane takes all shares of its columns; fp32 always,
+// one after the other with sixteen requested at once, so that a workgroup that walks the shares itself gets the same sums.
 // The rows of every task with shares, one task behind the other.
 struct CombineTask {
   const float* o;          // [n, B, n_q, heads, D]
@@ -595,7 +642,7 @@ struct CombineTasks { CombineTask t[kMaxTasks]; };
 
 template <typename T, int D, bool SPREAD>
 __global__ __launch_bounds__(256) void combine_kernel(const CombineTasks tasks, T* __restrict__ out, float* __restrict__ lse_out, int heads, int L) {
-  constexpr int PIECES = D / 4, GROUPS = SPREAD ? 64 / PIECES : 1, AT_ONCE = SPREAD ? 8 : 4;
+  constexpr int PIECES = D / 4, GROUPS = SPREAD ? 64 / PIECES : 1, AT_ONCE = sizeof(T) == 4 ? 16 : SPREAD ? 8 : 4;
   const int lane = threadIdx.x & 63, c = lane % PIECES, grp = SPREAD ? lane / PIECES : 0;
   int64_t i = SPREAD ? static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6)
                      : (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) / PIECES;
@@ -624,49 +671,63 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineTasks tasks, 
         x[k] = *reinterpret_cast<const f32x4*>(op + s * stride_o);
       }
     }
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+      for (int k = 0; k < AT_ONCE; ++k) {
+        if (s0 + k < n) {
+          float r, w;
+          fold(l[k], mx, den, r, w);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(w, x[k][e], acc[e] * r);
+        }
+      }
+    } else {
+      float m = mx;
+#pragma unroll
+      for (int k = 0; k < AT_ONCE; ++k) m = fmaxf(m, l[k]);
+      const float ref = m == -__builtin_inff() ? 0.f : m;
+      const float r = __expf(mx - ref);
+      den *= r;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] *= r;
+#pragma unroll
+      for (int k = 0; k < AT_ONCE; ++k) {
+        const float w = __expf(l[k] - ref);
+        den += w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(w, x[k][e], acc[e]);
+      }
+      mx = m;
+    }
+  }
+  if constexpr (sizeof(T) == 4) {
+    const float inv = den > 0.f ? 1.f / den : 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] *= inv;
+    *reinterpret_cast<f32x4*>(out + rh * D + 4 * c) = acc;
+    if (c == 0) lse_out[rh] = den > 0.f ? mx + __logf(den) : -__builtin_inff();
+  } else {
     float m = mx;
 #pragma unroll
-    for (int k = 0; k < AT_ONCE; ++k) m = fmaxf(m, l[k]);
-    // no share so far saw a key: all weights are 0, and so are the outputs unless they are NaN (a row of NaN scores
-    // has lse = -inf and NaN outputs), which 0 times them keeps
-    const float ref = m == -__builtin_inff() ? 0.f : m;
-    const float r = __expf(mx - ref);
+    for (int o = PIECES; o < PIECES * GROUPS; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+    const float r = m > -__builtin_inff() ? __expf(mx - m) : 0.f;
     den *= r;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e] *= r;
+    for (int o = PIECES; o < PIECES * GROUPS; o <<= 1) den += __shfl_xor(den, o);
+    const float w = den > 0.f ? r / den : 0.f;
 #pragma unroll
-    for (int k = 0; k < AT_ONCE; ++k) {
-      const float w = __expf(l[k] - ref);
-      den += w;
+    for (int e = 0; e < 4; ++e) {
+      acc[e] *= w;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(w, x[k][e], acc[e]);
+      for (int o = PIECES; o < PIECES * GROUPS; o <<= 1) acc[e] += __shfl_xor(acc[e], o);
     }
-    mx = m;
-  }
-  float m = mx;
-#pragma unroll
-  for (int o = PIECES; o < PIECES * GROUPS; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
-  const float r = m > -__builtin_inff() ? __expf(mx - m) : 0.f;
-  den *= r;
-#pragma unroll
-  for (int o = PIECES; o < PIECES * GROUPS; o <<= 1) den += __shfl_xor(den, o);
-  const float w = den > 0.f ? r / den : 0.f;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    acc[e] *= w;
-#pragma unroll
-    for (int o = PIECES; o < PIECES * GROUPS; o <<= 1) acc[e] += __shfl_xor(acc[e], o);
-  }
-  if (grp != 0) return;
-  if constexpr (sizeof(T) == 4) {
-    *reinterpret_cast<f32x4*>(out + rh * D + 4 * c) = acc;
-  } else {
+    if (grp != 0) return;
     bf16x4 y;
 #pragma unroll
     for (int e = 0; e < 4; ++e) y[e] = static_cast<__bf16>(acc[e]);
     *reinterpret_cast<bf16x4*>(out + rh * D + 4 * c) = y;
+    if (c == 0) lse_out[rh] = den > 0.f ? m + __logf(den) : -__builtin_inff();
   }
-  if (c == 0) lse_out[rh] = den > 0.f ? m + __logf(den) : -__builtin_inff();
 }
 
 template <typename T, int D>
@@ -682,16 +743,21 @@ hipError_t launch_combine_variant(const AttnLaunch& p, hipStream_t stream) {
     most = std::max(most, c.n);
   }
   if (n_rh == 0) return hipSuccess;
-  const int64_t L = p.lse_bstride / p.Hq, per_block = most > 4 ? 4 : 1024 / D, blocks = (n_rh + per_block - 1) / per_block;
+  const bool spread = sizeof(T) == 2 && most > 4;
+  const int64_t L = p.lse_bstride / p.Hq, per_block = spread ? 4 : 1024 / D, blocks = (n_rh + per_block - 1) / per_block;
   if (blocks > INT_MAX) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(blocks));
-  if (most > 4) return TASP_LAUNCH((combine_kernel<T, D, true>), grid, dim3(256), stream, tasks, static_cast<T*>(p.out_final), p.lse_dst, p.Hq, static_cast<int>(L));
+  if constexpr (sizeof(T) == 2)
+    if (spread) return TASP_LAUNCH((combine_kernel<T, D, true>), grid, dim3(256), stream, tasks, static_cast<T*>(p.out_final), p.lse_dst, p.Hq, static_cast<int>(L));
   return TASP_LAUNCH((combine_kernel<T, D, false>), grid, dim3(256), stream, tasks, static_cast<T*>(p.out_final), p.lse_dst, p.Hq, static_cast<int>(L));
 }
 
 }  // namespace
 
-hipError_t launch_attn_tile(const AttnLaunch& p, int d, bool fp32, hipStream_t stream) {
+hipError_t launch_attn_tile(const AttnLaunch& p, int d, bool fp32, bool serial, hipStream_t stream) {
+  if (serial && fp32 && d == 64) return launch_tile_variant<float, 64, true>(p, stream);
+  if (serial && fp32 && d == 128) return launch_tile_variant<float, 128, true>(p, stream);
+  if (serial) return hipErrorInvalidValue;
   if (d == 64) return fp32 ? launch_tile_variant<float, 64>(p, stream) : launch_tile_variant<__bf16, 64>(p, stream);
   if (d == 128) return fp32 ? launch_tile_variant<float, 128>(p, stream) : launch_tile_variant<__bf16, 128>(p, stream);
   return hipErrorInvalidValue;

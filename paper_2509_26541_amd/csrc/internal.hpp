@@ -131,7 +131,8 @@ inline hipError_t note_hip(hipError_t e) {
 
 // Implemented in attn_bf16.hip / attn_tile.hip / merge.hip.  Each returns a hipError_t from the launch.
 hipError_t launch_attn_bf16(const AttnLaunch& p, int d, hipStream_t stream);
-hipError_t launch_attn_tile(const AttnLaunch& p, int d, bool fp32, hipStream_t stream);
+// `serial` (fp32, out_final): a workgroup takes all shares of its tile in turn, without part_o and part_lse.
+hipError_t launch_attn_tile(const AttnLaunch& p, int d, bool fp32, bool serial, hipStream_t stream);
 // After a launch_attn_tile with several shares: the rows of out_final and lse_dst from the pairs of the shares.
 hipError_t launch_combine(const AttnLaunch& p, int d, bool fp32, hipStream_t stream);
 // rows [row0, row0 + rows) of every one of `batch` sequences of L rows each

@@ -78,6 +78,28 @@ def test_fp32_fused_merge_leaves_an_unaligned_workspace_alone(tb):
     assert bool((plan.workspace == 77).all())
 
 
+@pytest.mark.parametrize("shape", [(4, 1, 4 * 256, 4, 4, 64, wl.FULL), (8, 3, 16 * 257, 4, 1, 128, wl.ZIGZAG_CAUSAL)], ids=["d64", "d128_ragged"])
+def test_fp32_static_calls_overlap(tb, shape):
+    """fp32 with the merge folded in needs no workspace: static calls of it leave the library's array alone and may run on
+    several streams at once, and they give the bits of the call whose shares go through a workspace."""
+    n, rank, S, Hq, Hkv, d, mask = shape
+    s = tb.tasp_schedule(n, rank)
+    w = [wl.Workload("static_overlap", n, rank, S, Hq, Hkv, d, "fp32", mask, seed=wl.BASE_SEED + 8900 + i) for i in range(2)]
+    x = [[t.cuda() for t in wl.make_qkv(i)] for i in w]
+    ref = [[t.clone() for t in tb.tasp_chunk_attn(*i, s, mask, fuse_merge=True)] for i in x]
+    assert tb.ChunkAttnPlan(s, *x[0], mask, fuse_merge=True).profile().other_launches == 1       # shares are dealt
+    got = [[torch.empty_like(i[0]), torch.empty(i[0].shape[:-1], device="cuda")] for i in x]
+    streams = [torch.cuda.Stream() for _ in x]
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for i in range(2):
+            with torch.cuda.stream(streams[i]):
+                tb.tasp_chunk_attn_static(*x[i], *got[i], s, mask, fuse_merge=True)
+        torch.cuda.synchronize()
+        for i in range(2):
+            assert torch.equal(got[i][0], ref[i][0]) and torch.equal(got[i][1], ref[i][1])
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("heads", [(4, 4, 64), (8, 2, 128)], ids=["4x64", "8/2x128"])
 def test_a_row_of_nan_scores_stays_nan(tb, dtype, heads):

@@ -17,12 +17,12 @@ STUBS = r"""
 #include <cstdio>
 #include <random>
 
-struct Launched { int large, tile, combine; tasp::AttnLaunch last; };
+struct Launched { int large, tile, serial, combine; tasp::AttnLaunch last; };
 static Launched g;                                // what the forward launches would have been
 
 namespace tasp {   // launches: none is made here
 hipError_t launch_attn_bf16(const AttnLaunch& p, int, hipStream_t) { ++g.large; g.last = p; return hipSuccess; }
-hipError_t launch_attn_tile(const AttnLaunch& p, int, bool, hipStream_t) { ++g.tile; g.last = p; return hipSuccess; }
+hipError_t launch_attn_tile(const AttnLaunch& p, int, bool, bool serial, hipStream_t) { ++g.tile; g.serial += serial; g.last = p; return hipSuccess; }
 hipError_t launch_combine(const AttnLaunch&, int, bool, hipStream_t) { ++g.combine; return hipSuccess; }
 hipError_t launch_merge(float*, float*, const float*, const float*, int64_t, int64_t, int32_t, int32_t, int32_t, int64_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_fill_empty(float*, float*, int64_t, int64_t, int32_t, int32_t, int32_t, int64_t, hipStream_t) { return hipSuccess; }
@@ -54,6 +54,15 @@ static Plan forward(const tasp_schedule_t* s, tasp_attn_args a, size_t ws) {    
   if (validate(s, &a, &sh) != TASP_OK || join_steps(s, &a, &js) != TASP_OK) return {};
   const FwdPlan p = plan_forward(&a, js, tasp_chunk_attn_workspace_bytes(s, &a), ws ? ws : tasp_chunk_attn_best_workspace_bytes(s, &a));
   return {p.joined, p.tile, p.n_split[0], p.n_split[1], 0, p.table_bytes + p.part_bytes};
+}
+static Plan forward_none(const tasp_schedule_t* s, tasp_attn_args a) {     // lists in device memory: not joined without a workspace
+  JoinedSteps js{};
+  Shape sh;
+  if (validate(s, &a, &sh) != TASP_OK || join_steps(s, &a, &js) != TASP_OK) return {};
+  if (js.segments() > static_cast<size_t>(tasp::kPoolSeg)) return forward(s, a, 0);
+  const FwdPlan p = plan_forward(&a, js, 0, 0);
+  if (p.part_bytes > 0 || p.serial != (p.n_split[0] > 1 || p.n_split[1] > 1)) return {};
+  return {p.joined, p.tile, p.n_split[0], p.n_split[1], 0, 0};
 }
 static Plan backward(const tasp_schedule_t* s, tasp_attn_bwd_args b, size_t ws) {
   JoinedSteps js{};
@@ -100,7 +109,7 @@ int main() {
     if (best.ok && need <= fixed) {
       ++fwd;
       shared += best.n0 > 1 || best.n1 > 1;
-      const Plan st = forward(s, a, fixed);
+      const Plan st = need > 0 ? forward(s, a, fixed) : forward_none(s, a);        // what the static call brings
       if (!same(best, st)) report("forward, static", a, n, best, st);
       const Plan least = forward(s, a, std::max<size_t>(need, 1));
       if (least.ok && least.bytes > std::max<size_t>(need, 1)) report("forward, least", a, n, least, least);
@@ -157,6 +166,37 @@ int main() {
 """
 
 
+STATIC = r"""
+// The static call of shapes that need no workspace: it succeeds without a GPU, so it does not ask for the array's address, and
+// the launch has the shares of the other calls but no place for pairs of them.
+int main() {
+  tasp_schedule_t* s = nullptr;
+  if (tasp_schedule_create(8, 3, &s) != TASP_OK) return 2;
+  int shared = 0;
+  for (int d : {64, 128})
+    for (int rows : {2, 70, 256, 1024, 4096}) {
+      tasp_attn_args a{};
+      a.q = a.k = a.v = a.out = reinterpret_cast<void*>(256);
+      a.lse = reinterpret_cast<float*>(256);
+      a.S = 8 * rows; a.Hq = 4; a.Hkv = 2; a.d = d; a.dtype = TASP_DTYPE_FP32; a.mask_mode = TASP_MASK_ZIGZAG_CAUSAL; a.fuse_merge = 1;
+      if (tasp_chunk_attn_workspace_bytes(s, &a) != 0) return 3;
+      g = {};
+      if (tasp_chunk_attn_static(s, &a, nullptr) != TASP_OK) return 4;
+      const Launched st = g;
+      if (st.tile != 1 || st.combine != 0 || st.last.part_o[0] != nullptr || st.last.part_o[1] != nullptr) return 5;
+      g = {};
+      a.workspace = reinterpret_cast<void*>(256);
+      a.workspace_bytes = tasp_chunk_attn_best_workspace_bytes(s, &a);
+      if (tasp_chunk_attn(s, &a, nullptr) != TASP_OK || g.serial != 0) return 6;
+      for (int t = 0; t < 2; ++t)
+        if (g.last.n_split[t] != st.last.n_split[t]) return 7;
+      shared += g.combine;
+    }
+  return shared >= 6 ? 0 : 8;
+}
+"""
+
+
 def _run(tmp_path, program):
     src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
     src.write_text(STUBS + program)
@@ -173,3 +213,7 @@ def test_plan_follows_from_the_shape(tmp_path):
 def test_a_step_takes_the_faster_kernel(tmp_path):
     """Shapes timed with either kernel, per step."""
     _run(tmp_path, STEPS)
+
+
+def test_static_calls_without_need_leave_the_array_alone(tmp_path):
+    _run(tmp_path, STATIC)
