@@ -25,8 +25,9 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0       # MI355X dense bf16 MFMA
-PEAK_FP32_TFLOPS = 157.3        # MI355X fp32 vector
+PEAK_FP32_TFLOPS = 157.3        # MI355X fp32, matrix and vector
 PEAK_HBM_GBS = 8000.0
+FEW_ROWS = 4096                 # local rows up to which the library joins the steps of a call by itself
 N_SIMD, CLOCK_HZ = 256 * 4, 2.4e9
 
 # The second bound of the bf16 attention kernel: the vector issue port of a SIMD.  Measured on this
@@ -274,13 +275,14 @@ def main():
         if rec.get("attn_bf16_hip_sha16") == sha:
             traffic = rec.get("attn_bytes_per_launch")
     roofline = {
-        "bound": "mfma" if is_bf16 else "alu", "kernel": "attn_bf16_kernel" if is_bf16 else "attn_tile_kernel",
+        "bound": "mfma", "kernel": "attn_tile_kernel" if not is_bf16 else "attn_bf16_kernel" if w.L > FEW_ROWS else "attn_bf16_kernel or attn_tile_kernel",
         "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak, "traffic": traffic,
         "avg_launch_ms": attn_avg_ms, "launches_per_call": attn_n // n_prof,
     }
-    # the vector issue port, the pipe that actually bounds the bf16 kernel (above all at d = 64)
+    # the vector issue port, the pipe that actually bounds the large bf16 kernel (above all at d = 64); the port
+    # prices are that kernel's, so with few local rows, where another one may run, there is no such line
     roofline_valu = None
-    if is_bf16:
+    if is_bf16 and w.L > FEW_ROWS:
         vp = valu_peak_tflops(w.d)
         roofline_valu = {"bound": "valu", "kernel": "attn_bf16_kernel", "achieved": achieved, "peak": vp, "unit": "TFLOP/s",
                          "frac": achieved / vp, "port_cycles": PORT_CYCLES, "per_tile_and_wavefront": TILE_MIX[w.d],
@@ -324,8 +326,9 @@ def main():
                 merge = merge_stats(a_ms, a_n, n_prof)
         del alt
 
-    # all steps in one launch (no per-step launch, set-up or merge); reported beside `value`, which
-    # stays the step-by-step form with a merge after every block
+    # all steps in one launch (no per-step launch, set-up or merge); reported beside `value`, which is the
+    # step-by-step form with a merge after every block where a rank has more than FEW_ROWS local rows (with
+    # fewer the library joins the steps by itself, and the three modes are one)
     single = None
     if is_bf16 and not args.no_other_mode:
         try:

@@ -24,6 +24,18 @@ def bwd_asm(tmp_path_factory):
     return asm_checks.compile_to_asm("attn_bwd_bf16.hip", str(out))
 
 
+@pytest.fixture(scope="module")
+def tile_asm(tmp_path_factory):
+    out = tmp_path_factory.mktemp("asm") / "attn_tile.s"
+    return asm_checks.compile_to_asm("attn_tile.hip", str(out))
+
+
+@pytest.fixture(scope="module")
+def bwd_fp32_asm(tmp_path_factory):
+    out = tmp_path_factory.mktemp("asm") / "attn_bwd_fp32.s"
+    return asm_checks.compile_to_asm("attn_bwd_fp32.hip", str(out))
+
+
 def test_checker_flags_a_planted_violation():
     ok = [(1, "ds_read_b128 v[4:7], v1 offset:0"), (2, "s_waitcnt lgkmcnt(0)"), (3, "v_mov_b32_e32 v9, v4")]
     early = [(1, "ds_read_b128 v[4:7], v1 offset:0"), (2, "v_mov_b32_e32 v9, v4"), (3, "s_waitcnt lgkmcnt(0)")]
@@ -123,11 +135,11 @@ def test_m0_checker_flags_planted_uses():
     assert [b[0] for b in _m0_misuse([(1, "s_mov_b32 m0, s4"), (2, "v_mov_b32_e32 v0, v1"), (3, "global_load_lds_dwordx4 v1, s[2:3]")])] == [1, 3]
 
 
-def test_m0_belongs_to_the_direct_loads_only(attn_asm, bwd_asm):
+def test_m0_belongs_to_the_direct_loads_only(attn_asm, bwd_asm, tile_asm, bwd_fp32_asm):
     """The asm statement of the direct global->LDS load writes m0 without declaring it.  That is
     sound as long as the compiler itself never keeps a value in m0: in the generated code of every
     kernel that uses these loads, m0 appears in that statement's three instructions and nowhere else."""
-    for asm in (attn_asm, bwd_asm):
+    for asm in (attn_asm, bwd_asm, tile_asm, bwd_fp32_asm):
         for name, ins in asm_checks.kernels(asm).items():
             if any(_is_lds_load(s) for _, s in ins):
                 assert _m0_misuse(ins) == [], (name, _m0_misuse(ins)[:3])
@@ -195,3 +207,38 @@ def test_backward_loops_never_wait_on_vector_memory_by_themselves(bwd_asm):
     assert len(ks) == 6, list(ks)
     for name, ins in ks.items():
         assert _vmcnt_waits_in_matrix_loop(ins) == [], (name, _vmcnt_waits_in_matrix_loop(ins)[:3])
+
+
+# ---------------------------------------------------------------- kernels for short calls and fp32
+def _matrix_streams(ins, gap=400):
+    """The instructions from the first to the last matrix instruction of every run of them with fewer than `gap` others in between:
+    the loop bodies of a kernel, one by one."""
+    ops = [(l, s) for l, s in ins if not s.endswith(":")]
+    mf = [i for i, (_, s) in enumerate(ops) if s.startswith("v_mfma_")]
+    runs, beg = [], mf[0]
+    for a, b in zip(mf, mf[1:] + [None]):
+        if b is None or b - a > gap:
+            runs.append(ops[beg:a + 1])
+            beg = b
+    return runs
+
+
+def test_tile_kernels_keep_their_loops_clean(tile_asm, bwd_fp32_asm):
+    """No spills (the form that walks the shares of a tile in turn may park a few values between them), and in the loops
+    over tiles no flat or scratch accesses and no wait on vector memory but the hand-written one before the barrier."""
+    spills = {n: (c, b) for asm in (tile_asm, bwd_fp32_asm) for n, c, b in asm_checks.spill_report(asm)}
+    seen = 0
+    for asm, part, runs in ((tile_asm, "attn_tile_kernel", 1), (bwd_fp32_asm, "bwd_fp32_kernel", 2)):
+        for name, ins in asm_checks.kernels(asm).items():
+            if part not in name:
+                continue
+            seen += 1
+            serial = "ELb1EEE" in name
+            assert spills[name][0] <= (4 if serial else 0) and (serial or spills[name][1] == 0), (name, spills[name])
+            streams = _matrix_streams(ins)
+            assert len(streams) == runs, (name, [len(r) for r in streams])
+            for r in streams:
+                assert not any(s.startswith(("flat_", "scratch_")) for _, s in r), name
+                assert _vmcnt_waits_in_matrix_loop(r) == [], (name, _vmcnt_waits_in_matrix_loop(r)[:3])
+    assert seen == 8, seen       # both head sizes: fp32, fp32 without a workspace, bf16; fp32 backward
+    assert asm_checks.scratch_in_loops(tile_asm, "attn_tile_kernel", min_depth=2) == []

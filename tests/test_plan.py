@@ -197,6 +197,40 @@ int main() {
 """
 
 
+PATHS = r"""
+// n, rank, sequence length, heads, KV heads, d, mask, batch: shapes whose steps are tested one by one and joined
+struct Path { int n, rank, S, hq, hkv, d, mask, batch; };
+static const Path kPaths[] = {
+  {4, 1, 8 * 2051, 4, 2, 128, 1, 1}, {4, 3, 4 * 4099, 3, 1, 128, 0, 1}, {4, 2, 8 * 2051, 2, 1, 64, 1, 1}, {4, 0, 8 * 2310, 2, 2, 64, 1, 1}, {4, 2, 8 * 2049, 2, 1, 128, 1, 2},
+  {4, 0, 8 * 2310, 8, 8, 64, 1, 6},
+};
+
+int main() {
+  for (const Path& c : kPaths) {
+    tasp_schedule_t* s = nullptr;
+    if (tasp_schedule_create(c.n, c.rank, &s) != TASP_OK) return 2;
+    tasp_attn_args a{};
+    a.q = a.k = a.v = a.out = a.workspace = reinterpret_cast<void*>(256);
+    a.lse = reinterpret_cast<float*>(256);
+    a.workspace_bytes = size_t{1} << 40;
+    a.S = c.S; a.Hq = c.hq; a.Hkv = c.hkv; a.d = c.d; a.batch = c.batch;
+    a.dtype = TASP_DTYPE_BF16; a.mask_mode = c.mask ? TASP_MASK_ZIGZAG_CAUSAL : TASP_MASK_FULL;
+    for (int fuse : {0, 1}) {
+      g = {};
+      a.fuse_merge = fuse;
+      if (tasp_chunk_attn(s, &a, nullptr) != TASP_OK || g.large != c.n || g.tile != 0) return 3;      // the large kernel, step by step
+    }
+    g = {};
+    a.fuse_steps = 1;
+    if (tasp_chunk_attn(s, &a, nullptr) != TASP_OK) return 4;
+    std::printf("S %d, d %d: joined by the %s kernel\n", c.S, c.d, g.large ? "large" : "small");
+    tasp_schedule_destroy(s);
+  }
+  return 0;
+}
+"""
+
+
 def _run(tmp_path, program):
     src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
     src.write_text(STUBS + program)
@@ -217,3 +251,8 @@ def test_a_step_takes_the_faster_kernel(tmp_path):
 
 def test_static_calls_without_need_leave_the_array_alone(tmp_path):
     _run(tmp_path, STATIC)
+
+
+def test_more_than_4096_rows_run_step_by_step(tmp_path):
+    """The shapes of tests/test_gpu_step_path.py take the large kernel, a launch per step."""
+    _run(tmp_path, PATHS)
