@@ -479,7 +479,8 @@ int fill_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args* b, const AttnLa
 // share of the query tiles.  Mirrors what the kernel and the hardware do: the work list is (sequence,
 // KV head, head, share, key tile) in that order, every XCD gets one contiguous eighth of it (exactly so when
 // the KV heads of the call are a multiple of 8; otherwise XCDs share heads, which this estimate
-// ignores), and each of its slots/8 workgroup slots takes the next workgroup when it is free.  A workgroup walks, for
+// ignores, as it does the windows of several KV heads that are met together: xcd_window), and each of its
+// slots/8 workgroup slots takes the next workgroup when it is free.  A workgroup walks, for
 // each query block, the tiles from the first one that holds a row at or after its first key.
 int64_t dkv_makespan(const tasp::BwdLaunch& bp, int d, int kv_split, int64_t batch, int slots) {
   const int bs = d == 128 ? 256 : 128, bt = 64;

@@ -61,7 +61,7 @@ struct Cfg {
   static constexpr int NTHREADS = 64 * NWAVES;
   static constexpr int BM = 32 * NS * NWAVES;         // query rows per workgroup (256)
   static constexpr int UNITS = D / 8;                 // 16-byte units per row
-  static constexpr int RPP = NTHREADS / UNITS >= BN ? BN : (NTHREADS / UNITS >= 32 ? 32 : 16);   // rows filled per pass
+  static constexpr int RPP = NTHREADS / UNITS >= BN ? BN : 32;   // rows filled per pass
   static constexpr int LOADERS = RPP * UNITS;         // threads that fetch tiles (the first LOADERS / 64 wavefronts)
   static constexpr int PASSES = BN / RPP;
   static constexpr int ROWS_PER_LINE = 16 / UNITS;    // rows per 256-byte bank line (1 or 2)

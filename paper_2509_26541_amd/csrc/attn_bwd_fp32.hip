@@ -4,7 +4,7 @@
 //
 // One launch holds two kinds of workgroups, which do not depend on each other:
 //   dq:   X = (Q, dout) of 64 (local row, query head of the group) pairs, Y = (K, V) of the keys they see;
-//         the keys are dealt to n_split workgroups, whose sums launch_bwd_sum_f32 adds up in order;
+//         the keys are dealt to n_split workgroups, whose sums launch_bwd_sum adds up in order;
 //   dkv:  X = (K, V) of 64 keys, Y = (Q, dout) of every (local row, head) pair that sees one of them.
 // Both form  T1 = Y1 X1^T,  T2 = Y2 X2^T  (scores and dout.v, one X row per lane column),  p and ds from
 // them in registers, and  acc1 += Y1^T ds  (dkv: also  acc2 += Y2^T p),  where the score registers are
