@@ -294,13 +294,8 @@ __device__ __forceinline__ void bwd_tile(const BwdLaunch& p, int block, unsigned
 #pragma unroll 4
       for (int r = 0; r < 16; ++r) {
         const int at = w_row + (8 * (r / 4) + r % 4) * C::RB + (wc ^ ((8 * (r / 4 % 2) + r % 4) * 16));
-        const float* y1 = reinterpret_cast<const float*>(st1 + at);
-        const float* y2 = reinterpret_cast<const float*>(st2 + at);
-#pragma unroll
-        for (int e = 0; e < NDB; ++e) {
-          z = __builtin_fmaf(y1[e], 0.f, z);
-          if constexpr (DKV) z = __builtin_fmaf(y2[e], 0.f, z);
-        }
+        z = add_zero_times<NDB>(st1 + at, z);
+        if constexpr (DKV) z = add_zero_times<NDB>(st2 + at, z);
       }
       if (__builtin_amdgcn_ballot_w64(!(z == 0.f)) != 0) { odd_tiles = true; continue; }
     }

@@ -324,11 +324,7 @@ __global__ __launch_bounds__(NTHREADS, (D == 64 ? 3 : 2) - SERIAL) void attn_til
       if (masked) {                              // see odd_tiles
         float z = 0.f;
 #pragma unroll 4
-        for (int r = 0; r < 16; ++r) {
-          const float* va = reinterpret_cast<const float*>(st + v_adr[0] + (8 * (r / 4) + r % 4) * C::RB);
-#pragma unroll
-          for (int e = 0; e < NDB; ++e) z = __builtin_fmaf(va[e], 0.f, z);
-        }
+        for (int r = 0; r < 16; ++r) z = add_zero_times<NDB>(st + v_adr[0] + (8 * (r / 4) + r % 4) * C::RB, z);
         if (__builtin_amdgcn_ballot_w64(!(z == 0.f)) != 0) { odd_tiles = true; continue; }
       }
     }

@@ -88,6 +88,24 @@ __device__ inline void buffer_to_lds_16(const u32x4& rsrc, unsigned soff, unsign
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" : : "s"(lds_addr), "v"(off), "s"(rsrc), "s"(soff));
 }
 
+// z plus 0 times each of the N floats at p (LDS, 4 N-byte aligned): 0 stays 0 as long as they are finite.
+template <int N>
+__device__ inline float add_zero_times(const unsigned char* p, float z) {
+  static_assert(N == 2 || N == 4, "");
+  float v[N];
+  if constexpr (N == 4) {
+    const f32x4 x = *reinterpret_cast<const f32x4*>(p);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = x[e];
+  } else {
+    const f32x2 x = *reinterpret_cast<const f32x2*>(p);
+    v[0] = x[0]; v[1] = x[1];
+  }
+#pragma unroll
+  for (int e = 0; e < N; ++e) z = __builtin_fmaf(v[e], 0.f, z);
+  return z;
+}
+
 // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2); this maps the hardware
 // index to a work index such that every XCD gets one contiguous run of the work list.
 __device__ inline int xcd_contiguous(int block, int nblocks) {
