@@ -231,6 +231,28 @@ int main() {
 """
 
 
+FEW_SHARES = r"""
+// 16 ranks of two nodes, 20 heads of 64, 104 832 tokens, all steps in one launch: 2.73 ms with the small kernel and no
+// shares, 3.30 with the large one.  The small one it is, whoever brings the workspace.
+int main() {
+  tasp_schedule_t* s = nullptr;
+  if (tasp_schedule_create_multinode(8, 2, 12, &s) != TASP_OK) return 2;
+  tasp_attn_args a{};
+  a.q = a.k = a.v = a.out = a.workspace = reinterpret_cast<void*>(256);
+  a.lse = reinterpret_cast<float*>(256);
+  a.S = 104832; a.Hq = a.Hkv = 20; a.d = 64; a.dtype = TASP_DTYPE_BF16; a.mask_mode = TASP_MASK_ZIGZAG_CAUSAL; a.fuse_steps = 1;
+  for (size_t bytes : {tasp_chunk_attn_workspace_bytes(s, &a), tasp_chunk_attn_best_workspace_bytes(s, &a), static_cast<size_t>(TASP_STATIC_SCRATCH_BYTES)}) {
+    a.workspace_bytes = bytes;
+    g = {};
+    if (tasp_chunk_attn(s, &a, nullptr) != TASP_OK) return 3;
+    std::printf("%zu bytes: large %d, small %d with %d and %d shares\n", bytes, g.large, g.tile, g.last.n_split[0], g.last.n_split[1]);
+    if (g.tile != 1) return 4;
+  }
+  return 0;
+}
+"""
+
+
 def _run(tmp_path, program):
     src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
     src.write_text(STUBS + program)
@@ -256,3 +278,7 @@ def test_static_calls_without_need_leave_the_array_alone(tmp_path):
 def test_more_than_4096_rows_run_step_by_step(tmp_path):
     """The shapes of tests/test_gpu_step_path.py take the large kernel, a launch per step."""
     _run(tmp_path, PATHS)
+
+
+def test_a_joined_call_takes_the_faster_kernel_without_shares(tmp_path):
+    _run(tmp_path, FEW_SHARES)
