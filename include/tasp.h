@@ -137,11 +137,13 @@ int tasp_step_segments(const tasp_schedule_t* s, int64_t S, int32_t mask_mode, i
  *             contents undefined on entry and exit.
  *   fuse_steps 0: one attention launch per step, each followed by update_out_lse as above (the
  *                 form in which a step can start as soon as its sub-chunks have arrived).  With few
- *                 local rows (L <= 4096) the library joins the steps as for 1 where the lists allow
- *                 it: K and V are there, and the launches would cost more than their work;
- *              1: ONE launch walks the sub-chunks of all N steps in arrival order and carries the
- *                 running max / sum / output across them, so no partial pair is ever written or
- *                 merged (the log-sum-exp rescale happens in registers).  For callers whose K and V
+ *                 local rows (L <= 4096) the library joins the steps as for 1: K and V are there,
+ *                 and the launches would cost more than their work;
+ *              1: ONE launch walks the keys of all N steps and carries the running max / sum /
+ *                 output across them, so no partial pair is ever written or merged (the log-sum-exp
+ *                 rescale happens in registers).  It takes the keys by position: over the steps every
+ *                 key comes once, and the order (of arrival, or this one) is one of rounding only.
+ *                 For callers whose K and V
  *                 are resident when the call is made; it removes the per-step launch, set-up and
  *                 merge costs, which dominate for short sequences.  At most
  *                 TASP_MAX_FUSED_SEGMENTS visible segments per query block over all steps
@@ -201,9 +203,7 @@ int    tasp_chunk_attn(const tasp_schedule_t* s, const tasp_attn_args* a, void* 
  *     has to start at zero (step 0 of every call overwrites what it uses), but two calls that overlap
  *     on one GPU (different streams, or different threads) race.  Serialise them.  A call whose
  *     tasp_chunk_attn_workspace_bytes() is 0 does not touch the array and may overlap with any other.
- * Results are those of tasp_chunk_attn (the same kernels run) bit for bit; a call that needs no workspace
- * and whose lists of segments need device memory there (some hundred sub-chunks per query block) runs
- * step by step and differs in rounding. */
+ * Results are those of tasp_chunk_attn (the same kernels run) bit for bit. */
 #define TASP_STATIC_SCRATCH_BYTES (64u << 20)
 int tasp_chunk_attn_static(const tasp_schedule_t* s, const tasp_attn_args* a, void* hip_stream);
 

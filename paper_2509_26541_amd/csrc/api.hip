@@ -120,7 +120,7 @@ int build_step(const tasp_schedule_t* s, const tasp_attn_args* a, int step, Attn
   return TASP_OK;
 }
 
-// The tasks of all steps joined per query block, in arrival order, for one launch over them.
+// The tasks of all steps joined per query block, for one launch over them.
 struct JoinedSteps {
   AttnLaunch all;
   std::vector<int32_t> table[tasp::kMaxTasks];   // per task of `all`: (start, end) pairs
@@ -128,16 +128,24 @@ struct JoinedSteps {
   size_t segments() const { return (table[0].size() + table[1].size()) / 2; }
 };
 
-int join_steps(const tasp_schedule_t* s, const tasp_attn_args* a, JoinedSteps* js) {
+// With the lists of the steps one behind the other (`arrival`), or with the keys by position: over the steps every key
+// of the sequence comes once, and what a launch that does not wait for arrivals adds up does not depend on the order but
+// for rounding.  By position a tile is a run of neighbouring keys (4 x 12K tokens x 32 sequences, sub-chunks of 110: 342 us a
+// call against 365; 20 x 3K x 128: 697 against 716).  With fuse_steps a call whose lists are longer than
+// TASP_MAX_FUSED_SEGMENTS is refused, whichever the order.
+int join_steps(const tasp_schedule_t* s, const tasp_attn_args* a, JoinedSteps* js, bool arrival = false) {
   init_launch(s, a, &js->all);
   for (int qb = 0; qb < tasp::n_query_blocks(a->mask_mode); ++qb) {
     tasp::QueryBlock blk;
     int st = tasp::query_block(*s, a->S, a->mask_mode, qb, &blk);
     if (st != TASP_OK) return st;
-    st = tasp::all_step_segments(*s, a->S, a->mask_mode, a->order, qb, &js->table[qb]);
-    if (st != TASP_OK) return st;
-    const std::vector<int32_t>& g = js->table[qb];
-    if (g.empty() || g.size() / 2 > static_cast<size_t>(tasp::kMaxSegAll)) return TASP_EUNSUPPORTED_SHAPE;
+    std::vector<int32_t>& g = js->table[qb];
+    if (arrival || a->fuse_steps) {
+      st = tasp::all_step_segments(*s, a->S, a->mask_mode, a->order, qb, &g);
+      if (st != TASP_OK) return st;
+      if (g.empty() || g.size() / 2 > static_cast<size_t>(tasp::kMaxSegAll)) return TASP_EUNSUPPORTED_SHAPE;
+    }
+    if (!arrival) g = {0, static_cast<int32_t>(a->mask_mode == TASP_MASK_ZIGZAG_CAUSAL ? blk.pos0 + blk.rows : a->S)};
     for (size_t i = 0; i < g.size(); i += 2) js->keys[qb] += g[i + 1] - g[i];
     AttnTask& t = js->all.task[js->all.n_tasks++];
     t.q_row0 = static_cast<int32_t>(blk.local_row0);
@@ -152,21 +160,18 @@ int join_steps(const tasp_schedule_t* s, const tasp_attn_args* a, JoinedSteps* j
     std::swap(js->keys[0], js->keys[1]);
   }
   js->all.all_steps = 1;
+  js->all.task[1].seg0 = static_cast<int32_t>(js->table[0].size() / 2);
+  if (js->segments() <= static_cast<size_t>(tasp::kPoolSeg))
+    std::copy(js->table[1].begin(), js->table[1].end(), std::copy(js->table[0].begin(), js->table[0].end(), js->all.pool));
   return TASP_OK;
 }
 
-// Puts the joined lists where the launch finds them: in its descriptor, or, where they do not fit,
-// one behind the other in `dev_table` (kFusedTableBytes of device memory, written by small kernels).
-int place_lists(JoinedSteps* js, bool in_descriptor, int32_t* dev_table, hipStream_t stream) {
-  js->all.task[0].seg0 = 0;
-  js->all.task[1].seg0 = static_cast<int32_t>(js->table[0].size() / 2);
-  if (in_descriptor) {
-    std::copy(js->table[1].begin(), js->table[1].end(), std::copy(js->table[0].begin(), js->table[0].end(), js->all.pool));
-    return TASP_OK;
-  }
-  std::vector<int32_t> flat(js->table[0]);
-  flat.insert(flat.end(), js->table[1].begin(), js->table[1].end());
-  for (int t = 0; t < js->all.n_tasks; ++t) js->all.seg_ext[t] = dev_table + 2 * js->all.task[t].seg0;
+// Puts lists that do not fit the descriptor of a backward launch one behind the other in `dev_table` (kFusedTableBytes of
+// device memory, written by small kernels).
+int place_lists(const JoinedSteps& js, tasp::BwdLaunch* bp, int32_t* dev_table, hipStream_t stream) {
+  std::vector<int32_t> flat(js.table[0]);
+  flat.insert(flat.end(), js.table[1].begin(), js.table[1].end());
+  for (int t = 0; t < bp->n_tasks; ++t) bp->seg_ext[t] = dev_table + 2 * js.all.task[t].seg0;
   return tasp::launch_write_i32(dev_table, flat.data(), static_cast<int64_t>(flat.size()), stream) == hipSuccess ? TASP_OK : TASP_EHIP;
 }
 
@@ -177,7 +182,7 @@ struct FwdPlan {
   bool tile = false;                  // attn_tile_kernel
   bool serial = false;                // a workgroup of it takes all shares of its tile: no partial pairs
   int32_t n_split[tasp::kMaxTasks] = {1, 1};
-  size_t table_bytes = 0;             // device memory for the segment lists, in front of the partial pairs
+  size_t table_bytes = 0;             // of device memory in front of the partial pairs: none, the keys go by position
   size_t part_bytes = 0;              // of the shares' pairs
 };
 
@@ -203,9 +208,9 @@ constexpr int64_t kMaxSplit = 32;    // shares of one tile
 // the shares that one of them would get alone, the results of such a batch are bit for bit those of separate
 // calls; they are not where the partial pairs of all take more than the workspace that is planned for.
 int64_t plan_batch(int64_t batch, int64_t tiles_of_one) { return batch <= 4 && batch * tiles_of_one <= 128 ? 1 : batch; }
-int64_t plan_batch(const AttnLaunch& lp) {
+int64_t plan_batch(const AttnLaunch& lp, int rows) {
   int64_t tiles = 0;
-  for (int t = 0; t < lp.n_tasks; ++t) tiles += (static_cast<int64_t>(lp.task[t].n_q) * (lp.Hq / lp.Hkv) + tasp::kTileRows - 1) / tasp::kTileRows * lp.Hkv;
+  for (int t = 0; t < lp.n_tasks; ++t) tiles += (static_cast<int64_t>(lp.task[t].n_q) * (lp.Hq / lp.Hkv) + rows - 1) / rows * lp.Hkv;
   return plan_batch(lp.batch, tiles);
 }
 
@@ -218,10 +223,10 @@ int64_t plan_batch(const AttnLaunch& lp) {
 void deal_keys(const AttnLaunch& lp, int d, bool fp32, const int64_t* keys, size_t room, int32_t* n_split) {
   const double per_us = (fp32 ? 7.0 : 72.0) * (d == 64 ? (fp32 ? 2.0 : 1.5) : 1.0);     // keys of a tile that a CU walks in a microsecond
   const int64_t step = fp32 ? 32 : 64, least = fp32 ? 64 : 128;
-  const int64_t G = lp.Hq / lp.Hkv, B = plan_batch(lp);
+  const int64_t G = lp.Hq / lp.Hkv, rows = tasp::tile_rows(fp32, d), B = plan_batch(lp, rows);
   int64_t tiles[tasp::kMaxTasks] = {0, 0}, longest = 0;
   for (int t = 0; t < lp.n_tasks; ++t) {
-    tiles[t] = (lp.task[t].n_q * G + tasp::kTileRows - 1) / tasp::kTileRows * lp.Hkv * B;
+    tiles[t] = (lp.task[t].n_q * G + rows - 1) / rows * lp.Hkv * B;
     longest = std::max(longest, keys[t]);
   }
   auto shares = [&](int64_t per_wg, int64_t (&n)[tasp::kMaxTasks]) {
@@ -273,7 +278,8 @@ void deal_keys(const AttnLaunch& lp, int d, bool fp32, const int64_t* keys, size
 constexpr double kStepMargin = 0.89;
 bool tile_is_faster(const AttnLaunch& lp, int d, const int64_t* keys, const int32_t* n_split, bool step = false) {
   constexpr double kCus = 256.0;
-  const double B = static_cast<double>(plan_batch(lp)), G = lp.Hq / lp.Hkv;
+  constexpr int kTileRows = tasp::tile_rows(false, 0);
+  const double B = static_cast<double>(plan_batch(lp, kTileRows)), G = lp.Hq / lp.Hkv;
   auto padded = [](double x, double m) { return std::ceil(x / m) * m; };
   double rows8 = 0, rows12 = 0;
   for (int t = 0; t < lp.n_tasks; ++t) { rows8 += padded(lp.task[t].n_q, 256); rows12 += padded(lp.task[t].n_q, 384); }
@@ -285,9 +291,9 @@ bool tile_is_faster(const AttnLaunch& lp, int d, const int64_t* keys, const int3
     big_one[t] = bm * (k + fixed);
     big_n[t] = padded(n, bm) / bm * lp.Hq * B;
     big += big_one[t] * big_n[t];
-    tile_one[t] = tasp::kTileRows * (1.14 * k / ns + 300);
-    tile_n[t] = padded(n * G, tasp::kTileRows) / tasp::kTileRows * lp.Hkv * B * ns;
-    tile += tile_one[t] * padded(n * G, 32) / tasp::kTileRows * lp.Hkv * B * ns;
+    tile_one[t] = kTileRows * (1.14 * k / ns + 300);
+    tile_n[t] = padded(n * G, kTileRows) / kTileRows * lp.Hkv * B * ns;
+    tile += tile_one[t] * padded(n * G, 32) / kTileRows * lp.Hkv * B * ns;
     split |= ns > 1;
   }
   auto duration = [&](double total, const double* one, const double* n, double alone, double pair) {
@@ -312,10 +318,7 @@ FwdPlan plan_forward(const tasp_attn_args* a, const JoinedSteps& js, size_t need
   FwdPlan pl;
   const bool fp32 = a->dtype == TASP_DTYPE_FP32;
   pl.joined = true;
-  if (js.segments() > static_cast<size_t>(tasp::kPoolSeg)) pl.table_bytes = kFusedTableBytes;
-  if (pl.table_bytes > ws_bytes) { pl.joined = false; return pl; }
-  const size_t least = std::max(need, pl.table_bytes) - pl.table_bytes;
-  size_t room = std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES) - pl.table_bytes;
+  size_t room = std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES);
   for (;;) {
     int32_t n_split[tasp::kMaxTasks] = {1, 1};
     deal_keys(js.all, a->d, fp32, js.keys, room, n_split);
@@ -323,16 +326,16 @@ FwdPlan plan_forward(const tasp_attn_args* a, const JoinedSteps& js, size_t need
     if (!pl.tile) {
       // what is estimated to lose with all shares may win with the few that the least workspace holds, or none (20 heads of 64,
       // 104 832 tokens of 16 ranks in one launch: 2.73 ms, the large kernel 3.30)
-      if (room <= least) return pl;
-      room = least;
+      if (room <= need) return pl;
+      room = need;
       continue;
     }
     pl.part_bytes = all_share_bytes(js.all, a->d, n_split);
     for (int t = 0; t < js.all.n_tasks; ++t) pl.n_split[t] = n_split[t];
-    if (pl.part_bytes <= ws_bytes - pl.table_bytes) return pl;
+    if (pl.part_bytes <= ws_bytes) return pl;
     if (fp32 && ws_bytes == 0) { pl.serial = true; pl.part_bytes = 0; return pl; }
-    room = ws_bytes - pl.table_bytes;                 // what is dealt for this much fits
-    pl = FwdPlan{true, false, false, {1, 1}, pl.table_bytes, 0};
+    room = ws_bytes;                                  // what is dealt for this much fits
+    pl = FwdPlan{true, false, false, {1, 1}, 0, 0};
   }
 }
 
@@ -449,7 +452,7 @@ int fill_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args* b, const AttnLa
   bp->Hq = lp.Hq; bp->Hkv = lp.Hkv; bp->group = tasp::make_divider(static_cast<uint32_t>(lp.Hq / lp.Hkv)); bp->causal = lp.causal; bp->scale = lp.scale; bp->batch = lp.batch;
   bp->q_bstride = lp.q_bstride; bp->kv_bstride = lp.kv_bstride; bp->lse_bstride = lp.lse_bstride;
   bp->n_tasks = lp.n_tasks;
-  for (int t = 0; t < lp.n_tasks; ++t) { bp->task[t] = lp.task[t]; bp->seg_ext[t] = lp.seg_ext[t]; }
+  for (int t = 0; t < lp.n_tasks; ++t) bp->task[t] = lp.task[t];
   std::copy(lp.pool, lp.pool + 2 * tasp::kPoolSeg, bp->pool);
   bp->n_split = 1;
   bp->n_blk = tasp::n_query_blocks(b->mask_mode);
@@ -572,7 +575,7 @@ size_t plan_bytes(const BwdPlan& pl, const tasp_attn_bwd_args* b, const Shape& s
 int build_bwd_joined(const tasp_schedule_t* s, const tasp_attn_bwd_args* b, const tasp_attn_args* a, tasp::BwdLaunch* bp, JoinedSteps* js) {
   AttnLaunch lp{};
   if (b->fuse_steps) {
-    const int st = join_steps(s, a, js);
+    const int st = join_steps(s, a, js, true);
     if (st != TASP_OK) return st;
     lp = js->all;
   } else {
@@ -619,7 +622,7 @@ size_t tasp_chunk_attn_best_workspace_bytes(const tasp_schedule_t* s, const tasp
     JoinedSteps js{};
     if (join_steps(s, a, &js) != TASP_OK) return need;
     const FwdPlan pl = plan_forward(a, js, need, std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES));
-    return pl.joined ? std::max(need, pl.table_bytes + pl.part_bytes) : need;
+    return std::max(need, pl.part_bytes);
   } catch (...) {
     return need;
   }
@@ -691,20 +694,14 @@ static int run_chunk_attn(const tasp_schedule_t* s, const tasp_attn_args* a, voi
     if (a->fuse_steps || sh.L <= kJoinRows) {
       JoinedSteps js{};
       st = join_steps(s, a, &js);
-      if (st != TASP_OK && a->fuse_steps) return st;
-      FwdPlan pl;
+      if (st != TASP_OK) return st;
       // a call that needs no workspace (need = 0) takes any pointer; one that is not aligned is left alone
       const bool usable = a->workspace != nullptr && (reinterpret_cast<uintptr_t>(a->workspace) & (kAlign - 1)) == 0;
-      if (st == TASP_OK) pl = plan_forward(a, js, need, usable ? a->workspace_bytes : 0);
-      if (pl.joined) {
-        {
-          Scope sc(pl.table_bytes > 0 ? prof : nullptr, Profiler::kOther);
-          st = place_lists(&js, pl.table_bytes == 0, reinterpret_cast<int32_t*>(a->workspace), stream);
-          if (st != TASP_OK) return st;
-        }
+      const FwdPlan pl = plan_forward(a, js, need, usable ? a->workspace_bytes : 0);
+      {
         AttnLaunch& all = js.all;
         all.out_final = a->out; all.lse_dst = a->lse; all.merge = 0;
-        size_t at = pl.table_bytes;
+        size_t at = 0;
         for (int t = 0; t < all.n_tasks; ++t) {
           all.n_split[t] = pl.n_split[t];
           if (pl.n_split[t] < 2 || pl.serial) continue;
@@ -960,12 +957,10 @@ static int run_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args
       set_buffers(&bp);
       const bool listed = js.segments() > static_cast<size_t>(tasp::kPoolSeg);
       const BwdPlan pl = plan_backward(b, sh, bp, listed ? kFusedTableBytes : 0, std::min(b->workspace_bytes, std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES)));
-      if (b->fuse_steps) {
-        Scope sc(listed ? prof : nullptr, BwdSpans::kOther);
-        st2 = place_lists(&js, !listed, reinterpret_cast<int32_t*>(after_rows), stream);
+      if (listed) {
+        Scope sc(prof, BwdSpans::kOther);
+        st2 = place_lists(js, &bp, reinterpret_cast<int32_t*>(after_rows), stream);
         if (st2 != TASP_OK) return st2;
-        for (int t = 0; t < bp.n_tasks; ++t) { bp.task[t] = js.all.task[t]; bp.seg_ext[t] = js.all.seg_ext[t]; }
-        std::copy(js.all.pool, js.all.pool + 2 * tasp::kPoolSeg, bp.pool);
       }
       unsigned char* at = after_rows + pl.table_bytes;
       bp.n_split = pl.n_split;

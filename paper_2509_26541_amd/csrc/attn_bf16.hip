@@ -177,13 +177,13 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void attn_bf16_kernel(const AttnLa
   __shared__ __attribute__((aligned(16))) unsigned char smem[C::SMEM];   // four K tiles, then four V tiles
   __shared__ __attribute__((aligned(16))) int s_tok[C::STAGES][BN];   // global position of every key row of a tile (INT_MAX: none)
   // Effective segments: the segments are disjoint ranges of the sequence, so at most one of them
-  // holds the first position of the query tile and is split in two; hence kMaxSegAll + 2 entries.
-  __shared__ int e_vbeg[kMaxSegAll + 2];   // start in the virtual concatenation
-  __shared__ int e_goff[kMaxSegAll + 2];   //   global position minus virtual position
+  // holds the first position of the query tile and is split in two; hence kMaxSeg + 2 entries.
+  __shared__ int e_vbeg[kMaxSeg + 2];   // start in the virtual concatenation
+  __shared__ int e_goff[kMaxSeg + 2];   //   global position minus virtual position
   __shared__ int e_n;
   // Runs of tiles that need the element-wise mask (sorted, the last run is open-ended: m_hi = INT_MAX).
   // A diagonal part holds at least one of the tile's own positions.
-  constexpr int MAX_RUNS = (kMaxSegAll < BM ? kMaxSegAll : BM) + 2;
+  constexpr int MAX_RUNS = kMaxSeg + 2;
   __shared__ int m_lo[MAX_RUNS], m_hi[MAX_RUNS];
 
   const int tid = threadIdx.x;
@@ -239,15 +239,9 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void attn_bf16_kernel(const AttnLa
   }
   // ---- effective segment list of this query tile: drop what the causal mask hides from every
   // row, split the rest into a part every row sees and a part that straddles the diagonal.
-  // The list - from the descriptor, or in single-launch mode from device memory - is staged in
-  // the (still unused) tile ring first.
-  const int32_t* seg_ext = p.seg_ext[tsk];
+  // The list of the descriptor is staged in the (still unused) tile ring first.
   int* seg_raw = reinterpret_cast<int*>(smem);
-  if (seg_ext != nullptr) {
-    for (int i = tid; i < 2 * T.n_seg; i += C::NTHREADS) seg_raw[i] = seg_ext[i];
-  } else {
-    for (int i = tid; i < 2 * T.n_seg; i += C::NTHREADS) seg_raw[i] = p.pool[2 * T.seg0 + i];
-  }
+  for (int i = tid; i < 2 * T.n_seg; i += C::NTHREADS) seg_raw[i] = p.pool[2 * T.seg0 + i];
   __syncthreads();
   // The first wavefront builds the list, 64 segments per round: every lane classifies one segment
   // on its own; only the positions in the list and in the virtual concatenation are running sums

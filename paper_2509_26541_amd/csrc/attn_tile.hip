@@ -1,4 +1,4 @@
-// Blockwise attention for fp32 inputs of any size and for short bf16 calls: 128 query rows per
+// Blockwise attention for fp32 inputs of any size and for short bf16 calls: 128 query rows (fp32 with d = 128: 256) per
 // workgroup, the keys of a query tile dealt to as many workgroups as it takes to fill the chip.
 //
 // The large bf16 kernel (attn_bf16.hip) gives a workgroup 256 rows of one head and all its keys; a
@@ -7,25 +7,28 @@
 // of the group) pairs, so that grouped heads fill tiles and share K/V, and n_split workgroups each
 // take an equal run of the tile's visible keys; launch_combine adds the partial pairs up.
 //
-// Per wavefront 32 of the tile's rows, S^T = K Q^T and O^T = V^T P^T: one query per lane column, so
-// the softmax is in-lane but for one exchange, and the score registers are the B operand of the second
-// product as they stand.  bf16: v_mfma_f32_32x32x16_bf16, V through the transposing LDS read.  fp32:
-// v_mfma_f32_32x32x2_f32 (full fp32 products and sums); the 16 bytes a lane reads of a K row feed
-// four of them, and so do the 16 bytes (d = 64: two, from 8) it reads of a V row, because block c of
-// O^T takes the columns 4 i + c (2 i + c) instead of 32 neighbouring ones.  K and V tiles come through
-// direct global->LDS loads into two stages.
+// Per wavefront 32 of the tile's rows, S^T = K Q^T and O^T = V^T P^T with v_mfma_f32_32x32x16: one query per lane
+// column, so the softmax is in-lane but for one exchange, and the score registers are the B operand of the second
+// product as they stand; V through the transposing LDS read, K and V tiles by direct global->LDS loads.
 //
-// What bounds it: fp32 the matrix pipe (a fp32 matrix instruction holds it for 64 cycles, which
-// leaves room for everything else a SIMD has to issue); bf16 the issue slots (1 330 of the 1 450 cycles
-// a SIMD takes for 32 rows by 64 keys at d = 64), and in the shortest calls the launch, the set-up and
-// the latency of the first tiles.  Measured, whole calls:
-//   fp32, 16 heads of 128, 2 048 of 16 384 tokens, causal: 1.12 ms (123 TFLOP/s of the 152 a large fp32
-//     product reaches) against 20.1 ms with a wavefront per query row;
-//   fp32, 4 heads of 64, 256 of 1 024 tokens: 16 us against 308;
-//   bf16, 8 heads of 128, 512 of 4 096 tokens: 25 us against 117 with the large kernel on 16 CUs (a workgroup of
-//     it: set-up 2.8 us, first tile 1.3, four tiles 8.4, epilogue 2.3);
-//   bf16, 128 sequences of 3 072 tokens, 20 heads of 64: 0.71 ms against 0.91 with the large kernel,
-//     which pads 192 rows to 256 and searches for the rows of 27-token sub-chunks in every tile.
+// fp32 products are formed from two 16-bit floats each (v_mfma_f32_32x32x16_f16, three for one product; see the loop): a
+// matrix instruction of that kind does in 32 cycles what eight fp32 ones do in 512.  The rows of K and V are split where
+// they were fetched, in LDS and by the wavefront that fetched them, one tile ahead.  Eight wavefronts share a tile at d = 128:
+// with four, a wavefront to a SIMD, twice the splitting and accumulators moved about, 16 heads of 128 took 797 us, not 506.
+//
+// Joined steps take the keys by position (a tile is a run of neighbouring keys: nothing to look up, the addresses are
+// scalar), a step by itself walks its segments.
+//
+// What bounds it: the issue slots.  fp32 d = 128: 360 vector and 48 matrix instructions for 32 rows by 32 keys, 3 300 cycles of a
+// SIMD of which the matrix pipe is busy 1 536; bf16 1 330 of the 1 450 cycles a SIMD takes for 32 rows by 64 keys at
+// d = 64; in the shortest calls the launch, the set-up and the latency of the first tiles.  Measured, whole calls:
+//   fp32, 16 heads of 128, 2 048 of 16 384 tokens, causal: 0.48 ms (287 TFLOP/s of products of floats) against 1.13 ms with
+//     fp32 matrix instructions (their floor is 0.90); error of the output against 64 bits, 2 heads of 128, 5 120 of
+//     20 480 tokens: 4.4e-7 against 5.8e-7; no mask, 2 heads of 64, 8 192 of 32 768: 5.3e-7 against 5.8e-7;
+//   fp32, 4 heads of 64, 256 of 1 024 tokens: 16 us;
+//   bf16, 8 heads of 128, 512 of 4 096 tokens: 23 us against 117 with the large kernel on 16 CUs;
+//   bf16, 128 sequences of 3 072 tokens, 20 heads of 64: 0.70 ms (0.72 with the sub-chunks in their order of arrival,
+//     0.91 with the large kernel, which pads 192 rows to 256).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -40,29 +43,40 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kRescaleGap = 8.0f;      // the running max is only raised when it grew by more than 2^8
+constexpr float kRescaleGapF32 = 2.0f;   // fp32: 2^2, the probabilities go to 16-bit floats (below 2^16) scaled by 2^kProbExp
+constexpr int kProbExp = 13;
+constexpr int kSpread = 16;              // fp32: exponents that the rows of a piece of K or V may be apart
 constexpr float kNegBig = -1.0e30f;
-constexpr int BM = kTileRows;            // rows per workgroup: four wavefronts of 32
-constexpr int NTHREADS = 256;
 constexpr int CHUNK = 512;               // keys located at a time
+constexpr int RUNS = 512;                // fp32: entries of the table of tiles with something left to the end
 
 template <typename T, int D>
 struct TCfg {
   static constexpr bool F32 = sizeof(T) == 4;
+  static constexpr int BM = tile_rows(F32, D);          // rows per workgroup, 32 to a wavefront
+  static constexpr int NW = BM / 32, NTHREADS = 64 * NW;
   static constexpr int BT = F32 ? 32 : 64;              // keys per tile
   static constexpr int NKB = BT / 32;                   // 32-key blocks
   static constexpr int RB = D * static_cast<int>(sizeof(T));   // bytes of a row
   static constexpr int UNITS = RB / 16;                 // 16-byte units per row
   static constexpr int RPP = NTHREADS / UNITS;          // rows filled per pass
   static constexpr int PASSES = BT / RPP;
+  static constexpr int OWN = BT / NW;                   // fp32: rows of a tile that a wavefront fetches and converts, a pair of units a lane
   static constexpr int TILE_BYTES = BT * RB;
   static constexpr int STAGE_BYTES = 2 * TILE_BYTES;    // K tile, V tile
+  static constexpr int STAGES = F32 ? 3 : 2;
   static constexpr int RPL = UNITS >= 16 ? 1 : 16 / UNITS;   // rows per 256-byte bank line
   static constexpr int NDB = D / 32;                    // 32-column blocks of O^T
-  // Physical unit of logical unit u of row r.  K is read row-wise (32 lanes, one row each, the same
-  // unit): neighbouring bank lines differ.  V: fp32 rows are read whole; bf16 through the transposing
-  // read (4 rows, 2 units).
+  // bf16: physical unit of logical unit u of row r.  K is read row-wise (32 lanes, one row each, the same
+  // unit): neighbouring bank lines differ.  V through the transposing read (4 rows, 2 units).
   __device__ static int swz_k(int r, int u) { return u ^ ((r / RPL) % (UNITS < 16 ? UNITS : 16)); }
-  __device__ static int swz_v(int r, int u) { return F32 ? u : u ^ (4 * ((r / RPL) % (UNITS / 4))); }
+  __device__ static int swz_v(int r, int u) { return u ^ (4 * ((r / RPL) % (UNITS / 4))); }
+  // fp32: eight columns are two 16-byte units, fetched as eight floats and turned in place into the high halves
+  // (unit 0 of the pair) and the low halves (unit 1) of their split.  Pair c of row r sits at pair c ^ x of the
+  // row, its units swapped where y is 1: the fragment reads (K: 16 rows, one pair, one unit; V: 4 rows, 4 pairs,
+  // one unit) and those of the conversion (neighbouring pairs, one unit) all meet 16 units of a 256-byte line.
+  __device__ static int pair_x(bool v, int r) { return v ? 4 * (r & 1) : r & 7; }
+  __device__ static int pair_y(bool v, int r, int pair) { return ((v ? r >> 1 : r >> 3) ^ (D == 128 ? pair >> 3 : r)) & 1; }   // pair: the physical one
 };
 
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -72,6 +86,62 @@ __device__ inline f32x16 zero16() {
   for (int i = 0; i < 16; ++i) z[i] = 0.f;
   return z;
 }
+// Eight floats times sa and sb (powers of two, for four each) as two sets of eight 16-bit floats, hi + lo = s x to 22 bits and a sign.  In one
+// piece of assembly: one instruction for each half (scaled, subtracted, rounded once and packed; the compiler takes
+// three for both).  Instructions that write half a register stand four apart from those that read it.
+__device__ __forceinline__ void split8(const f32x4& a, const f32x4& b, float sa, float sb, u32x4& hi, u32x4& lo) {
+  unsigned h0, h1, h2, h3, l0, l1, l2, l3;
+  asm("v_fma_mixlo_f16 %0, %8, %16, 0\n\tv_fma_mixlo_f16 %1, %10, %16, 0\n\tv_fma_mixlo_f16 %2, %12, %17, 0\n\tv_fma_mixlo_f16 %3, %14, %17, 0\n\t"
+      "v_fma_mixhi_f16 %0, %9, %16, 0\n\tv_fma_mixhi_f16 %1, %11, %16, 0\n\tv_fma_mixhi_f16 %2, %13, %17, 0\n\tv_fma_mixhi_f16 %3, %15, %17, 0\n\t"
+      "v_fma_mixlo_f16 %4, %8, %16, -%0 op_sel_hi:[0,0,1]\n\tv_fma_mixlo_f16 %5, %10, %16, -%1 op_sel_hi:[0,0,1]\n\t"
+      "v_fma_mixlo_f16 %6, %12, %17, -%2 op_sel_hi:[0,0,1]\n\tv_fma_mixlo_f16 %7, %14, %17, -%3 op_sel_hi:[0,0,1]\n\t"
+      "v_fma_mixhi_f16 %4, %9, %16, -%0 op_sel:[0,0,1] op_sel_hi:[0,0,1]\n\tv_fma_mixhi_f16 %5, %11, %16, -%1 op_sel:[0,0,1] op_sel_hi:[0,0,1]\n\t"
+      "v_fma_mixhi_f16 %6, %13, %17, -%2 op_sel:[0,0,1] op_sel_hi:[0,0,1]\n\tv_fma_mixhi_f16 %7, %15, %17, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]"
+      : "=&v"(h0), "=&v"(h1), "=&v"(h2), "=&v"(h3), "=&v"(l0), "=&v"(l1), "=&v"(l2), "=&v"(l3)
+      : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(sa), "v"(sb));
+  hi = u32x4{h0, h1, h2, h3};
+  lo = u32x4{l0, l1, l2, l3};
+}
+__device__ inline f32x16 mfma_f16(const u32x4& a, const u32x4& b, const f32x16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+}
+// The largest |x| of eight floats, NaN passed over unless there is nothing else, and m.
+__device__ __forceinline__ float abs_max3(float m, float a, float b) {     // (as assembly: the compiler would quiet every input first)
+  float r;
+  asm("v_max3_f32 %0, %1, abs(%2), abs(%3)" : "=v"(r) : "v"(m), "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ float abs_max8(const f32x4& a, const f32x4& b, float m) {
+  m = abs_max3(abs_max3(m, a[0], a[1]), a[2], a[3]);
+  return abs_max3(abs_max3(m, b[0], b[1]), b[2], b[3]);
+}
+// Exponents, 2^e <= max < 2^(e + 1) and not below kLeastExp, 128 for an infinity, of the largest row of a wavefront's lanes and
+// of the smallest one that is not all zeros (127 if all are); W lanes to a row, x their maxima as integers (>= 0: ordered like
+// the floats).  Leaves the maximum of every row in its last lane.
+constexpr int kLeastExp = -100;
+template <int CTRL>
+__device__ __forceinline__ int dpp_max(int x) { return max(x, __builtin_amdgcn_update_dpp(0, x, CTRL, 15, 15, true)); }
+template <int W>
+__device__ __forceinline__ void row_exps(int& x, int& most, int& least) {
+  x = dpp_max<0x111>(x);                                 // shifts inside 16 lanes
+  x = dpp_max<0x112>(x);
+  x = dpp_max<0x114>(x);
+  int lo, hi = x;
+  if constexpr (W == 16) {
+    hi = x = dpp_max<0x118>(x);
+    lo = x - 1;
+  } else {
+    lo = x - 1;                                          // (zero: the largest of all, as an unsigned number)
+    hi = dpp_max<0x118>(x);
+    lo = static_cast<int>(min(static_cast<unsigned>(lo), static_cast<unsigned>(__builtin_amdgcn_update_dpp(lo, lo, 0x118, 15, 15, false))));
+  }
+  auto at = [](int v, int l) { return static_cast<unsigned>(__builtin_amdgcn_readlane(v, l)); };
+  const unsigned m = max(max(at(hi, 15), at(hi, 31)), max(at(hi, 47), at(hi, 63)));
+  const unsigned n = min(min(at(lo, 15), at(lo, 31)), min(at(lo, 47), at(lo, 63)));
+  most = max(static_cast<int>(m >> 23) - 127, kLeastExp);
+  least = max(min(static_cast<int>(n >> 23) - 127, 127), kLeastExp);
+}
+__device__ __forceinline__ float pow2(int e) { return __builtin_bit_cast(float, (e + 127) << 23); }     // -126 .. 127
 __device__ inline bf16x8 lds_tr8(const unsigned char* lo, const unsigned char* hi) {
   const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lds_void_ptr)const_cast<unsigned char*>(lo));
   const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lds_void_ptr)const_cast<unsigned char*>(hi));
@@ -92,37 +162,47 @@ __device__ inline void fold(float lse, float& mx, float& den, float& r, float& w
 // SERIAL (fp32): a workgroup takes all shares of its tile one after the other and folds their pairs in the output
 // itself, as combine_kernel does from memory: the same bits without a workspace.
 template <typename T, int D, bool SERIAL>
-__global__ __launch_bounds__(NTHREADS, (D == 64 ? 3 : 2) - SERIAL) void attn_tile_kernel(const AttnLaunch p) {
+__global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F32 ? 3 : 2)) void attn_tile_kernel(const AttnLaunch p) {
   using C = TCfg<T, D>;
   constexpr bool F32 = C::F32;
+  constexpr int BM = C::BM, NTHREADS = C::NTHREADS, NW = C::NW;
   constexpr int BT = C::BT, NKB = C::NKB, NDB = C::NDB, NJ = C::UNITS / 2;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * C::STAGE_BYTES];
-  __shared__ __attribute__((aligned(16))) int s_tok[2 * CHUNK];   // global positions of the keys (INT_MAX: none)
-  __shared__ __attribute__((aligned(16))) int s_msk[2][4];    // per wavefront: it fetched a key some row of the tile must not see
-  // Effective segments of this workgroup's share of the keys.
-  __shared__ int e_vbeg[kMaxSegAll + 1];   // start in the share
-  __shared__ int e_goff[kMaxSegAll];       //   global position minus that
+  __shared__ __attribute__((aligned(16))) unsigned char smem[C::STAGES * C::STAGE_BYTES];
+  // fp32: per four rows of a tile (rows 8 i + 4 h ..: entry 4 h + i) the power of two below their largest |K| (less 14) and
+  // |V|.  Where a wavefront found infinities: s_vx is infinite, the power is in s_vt, the rows it cleared are in s_bad;
+  // s_odd marks the runs of `run` tiles that hold keys to be added at the end.
+  __shared__ __attribute__((aligned(16))) float s_kx[C::STAGES][F32 ? 8 : 1], s_vx[C::STAGES][F32 ? 8 : 1], s_vt[C::STAGES][F32 ? 8 : 1];
+  __shared__ int s_bad[C::STAGES][NW], s_odd[F32 ? RUNS : 1];
+  // One step's launch: global positions of the keys (INT_MAX: none), whether a wavefront fetched a key that some row of the
+  // tile must not see, and the effective segments of the tile.
+  __shared__ __attribute__((aligned(16))) int s_tok[2 * CHUNK];
+  __shared__ __attribute__((aligned(16))) int s_msk[C::STAGES][NW];
+  __shared__ int e_vbeg[kMaxSeg + 1];      // start in their concatenation
+  __shared__ int e_goff[kMaxSeg];          //   global position minus that
   __shared__ int e_n;
+  __shared__ float s_all[SERIAL ? 2 : 1][SERIAL ? NTHREADS : 1];     // SERIAL: running maximum and sum of the shares so far
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, lq = lane & 31;
+  const int thread = threadIdx.x, wave_u = __builtin_amdgcn_readfirstlane(thread >> 6);
 
   // What the set-up needs of the kernel arguments is asked for here, in one go and at fixed places: they
   // come from far (a first dependent read of them costs about as much as a tile).
   const AttnTask t0 = p.task[0], t1 = p.task[1];
-  const int32_t* const seg_ext0 = p.seg_ext[0];
-  const int32_t* const seg_ext1 = p.seg_ext[1];
-  int* const s_pool = reinterpret_cast<int*>(smem);           // in the still unused tile stages
-  static_assert(2 * kPoolSeg * 4 <= C::STAGE_BYTES, "");
-  int pooled[2 * kPoolSeg / NTHREADS];
+  const bool linear = p.all_steps != 0;    // the keys of a tile are one run of positions, from the first key on
+  int pair0[2] = {0, 0}, pair1[2] = {0, 0};
+  if (!linear) {
 #pragma unroll
-  for (int i = 0; i < 2 * kPoolSeg / NTHREADS; ++i) pooled[i] = p.pool[NTHREADS * i + tid];
+    for (int e = 0; e < 2; ++e) {
+      pair0[e] = p.pool[2 * min(t0.seg0 + (thread & 63), kPoolSeg - 1) + e];
+      pair1[e] = p.pool[2 * min(t1.seg0 + (thread & 63), kPoolSeg - 1) + e];
+    }
+  }
 
   // ---- which (sequence, KV head, task, row tile, share of the keys)
   const int G = p.Hq / p.Hkv;
   const int m0 = t0.n_q * G, m1 = p.n_tasks > 1 ? t1.n_q * G : 0;
   const int tiles0 = (m0 + BM - 1) / BM, tiles1 = (m1 + BM - 1) / BM;
   const int items0 = tiles0 * (SERIAL ? 1 : p.n_split[0]), per_g = items0 + tiles1 * (SERIAL ? 1 : p.n_split[1]);
-  const int w_all = xcd_balanced(blockIdx.x, p.batch * p.Hkv, per_g, xcd_window(D == 64 ? 96 : 64, per_g));
+  const int w_all = xcd_balanced(blockIdx.x, p.batch * p.Hkv, per_g, xcd_window(F32 ? (D == 64 ? 64 : 32) : D == 64 ? 96 : 64, per_g));
   if (w_all < 0) return;
   const int bg = w_all / per_g;
   int rem = w_all - bg * per_g;
@@ -135,174 +215,611 @@ __global__ __launch_bounds__(NTHREADS, (D == 64 ? 3 : 2) - SERIAL) void attn_til
   // under the causal mask the later tiles of a block see more keys: they start first
   const int tile = p.causal ? (second ? tiles1 : tiles0) - 1 - rem / per_share : rem / per_share;
   const int q_row0 = second ? t1.q_row0 : t0.q_row0, q_pos0 = second ? t1.q_pos0 : t0.q_pos0;
-  const int n_seg = second ? t1.n_seg : t0.n_seg, seg0 = second ? t1.seg0 : t0.seg0;
-  const int32_t* const seg_ext = second ? seg_ext1 : seg_ext0;
+  const int n_seg = second ? t1.n_seg : t0.n_seg;
   const int m_all = second ? m1 : m0;
   // The strip of 32 rows a wavefront takes moves with the work item: wavefront i of a workgroup runs on
   // SIMD i, and tiles with few rows left leave strips without work.
-  const int strip = (wave + w_all) & 3;
-  const int m = tile * BM + strip * 32 + lq;                 // row of the tile: (local row, head of the group)
-  const bool q_valid = m < m_all;
-  const int mc = q_valid ? m : m_all - 1;
-  const int row = mc / G, hq = g * G + mc - row * G;
-  const int q_pos = p.causal ? q_pos0 + row : INT_MAX - 1;
+  const int strip = (wave_u + w_all) % NW;
+  // the lane's row: (local row of the task, query head), its index among the call's (row, head) pairs of the sequence, whether it exists
+  struct Row { int row; int64_t idx; bool valid; };
+  auto row_of = [&](int column) __attribute__((always_inline)) {
+    const int m = tile * BM + strip * 32 + column, mc = min(m, m_all - 1), row = mc / G;
+    return Row{row, static_cast<int64_t>(q_row0 + row) * p.Hq + g * G + mc - row * G, m < m_all};
+  };
+  const Row mine = row_of(thread & 31);
+  const int q_pos = p.causal ? q_pos0 + mine.row : INT_MAX - 1;
   const int q_last = q_pos0 + (min(tile * BM + BM, m_all) - 1) / G;
   const int q_first = p.causal ? q_pos0 + tile * BM / G : INT_MAX - 1;   // a key at or before it is seen by every row
 
-  // ---- Q fragments (B operand): 16-byte units 2 j + h of the lane's row
-  const int64_t qoff = bi * p.q_bstride + (static_cast<int64_t>(q_row0 + row) * p.Hq + hq) * D;
+  // ---- Q fragments (B operand), bf16: 16-byte units 2 j + h of the lane's row; fp32: units 4 j + 2 h and the one behind it,
+  // later the high and the low halves of these eight columns
   u32x4 qf[NJ];
   {
-    const u32x4* src = reinterpret_cast<const u32x4*>(static_cast<const T*>(p.q) + qoff) + h;
+    const u32x4* src = reinterpret_cast<const u32x4*>(static_cast<const T*>(p.q) + bi * p.q_bstride + mine.idx * D) + (thread >> 5 & 1) * (F32 ? 2 : 1);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) qf[j] = src[2 * j];
+    for (int j = 0; j < NJ; ++j) qf[j] = src[F32 ? 4 * (j / 2) + j % 2 : 2 * j];
   }
+  float cq = p.scale * kLog2e;          // fp32: times the power of two that the row was divided by
+  bool q_inf = false;                   // fp32: the row holds an infinity
 
-  float mx_all = -__builtin_inff(), den_all = 0.f;       // SERIAL: of the shares so far
+  auto split_q = [&]() __attribute__((always_inline)) {            // fp32: Q to halves
+    constexpr int KS = D / 16;
+    float m = 0.f;
+#pragma unroll
+    for (int j = 0; j < KS; ++j) m = abs_max8(__builtin_bit_cast(f32x4, qf[2 * j]), __builtin_bit_cast(f32x4, qf[2 * j + 1]), m);
+    m = fmaxf(m, __shfl_xor(m, 32));
+    q_inf = m == __builtin_inff();
+    if (q_inf) m = 0.f;
+    const int e = max((__builtin_bit_cast(int, m) >> 23) - 127, kLeastExp);
+    const float s = q_inf ? 0.f : pow2(14 - e);            // (NaN: what comes of infinities is thrown away)
+#pragma unroll
+    for (int j = 0; j < KS; ++j) split8(__builtin_bit_cast(f32x4, qf[2 * j]), __builtin_bit_cast(f32x4, qf[2 * j + 1]), s, s, qf[2 * j], qf[2 * j + 1]);
+    cq *= pow2(e - 14);
+  };
+  if constexpr (F32 && SERIAL) split_q();
+
   for (int round = 0; SERIAL ? round < ns : round == 0; ++round) {
+  int tid = thread;
   if constexpr (SERIAL) {
     share = round;
-    if (round > 0) {
-#pragma unroll
-      for (int i = 0; i < 2 * kPoolSeg / NTHREADS; ++i) pooled[i] = p.pool[NTHREADS * i + tid];
-      __syncthreads();               // nobody reads the tiles and lists of the share before any more
-    }
+    asm volatile("" : "+v"(tid));        // (what follows from it is formed in every round, not kept across the epilogue of the one before)
+    if (round > 0) __syncthreads();      // nobody reads the tiles of the share before any more
   }
-  // ---- effective segments: what the mask leaves of every segment for this tile, then the share of it
-  // that is this workgroup's.  The first wavefront works through the list, 64 segments per round.
-  if (seg_ext == nullptr) {
-#pragma unroll
-    for (int i = 0; i < 2 * kPoolSeg / NTHREADS; ++i) s_pool[NTHREADS * i + tid] = pooled[i];
-  }
-  __syncthreads();
-  if (wave == 0) {
-    auto visible = [&](int s, int& a) __attribute__((always_inline)) {
-      a = 0;
-      if (s >= n_seg) return 0;
-      int e;
-      if (seg_ext != nullptr) { a = seg_ext[2 * s]; e = seg_ext[2 * s + 1]; }
-      else { a = s_pool[2 * (seg0 + s)]; e = s_pool[2 * (seg0 + s) + 1]; }
-      return max(0, (p.causal ? min(e, q_last + 1) : e) - a);
-    };
-    int lo = 0, hi = INT_MAX;                     // this workgroup's share of the tile's visible keys
-    if (ns > 1) {                                 // only with joined steps: over them every key of the sequence comes once
-      const int total = p.causal ? q_last + 1 : p.last_key + 1;
-      const int chunk = ((total + ns - 1) / ns + BT - 1) / BT * BT;
-      lo = share * chunk;
-      hi = lo + chunk;
+  const int lane = tid & 63, wave = tid >> 6, h = lane >> 5, lq = lane & 31;
+  if constexpr (F32)
+    for (int i = tid; i < RUNS; i += NTHREADS) s_odd[i] = 0;
+  // ---- the keys.  Joined steps: over them every key of the sequence comes once, so this workgroup's share is a run of
+  // positions, n_keys of them from goff on.
+  int n_keys, goff = 0, n_eff = 1;
+  if (SERIAL || linear) {
+    n_keys = p.causal ? q_last + 1 : p.last_key + 1;
+    if (ns > 1) {
+      const int chunk = ((n_keys + ns - 1) / ns + BT - 1) / BT * BT;
+      goff = share * chunk;
+      n_keys = max(0, min(n_keys - goff, chunk));
     }
-    int n_base = 0, v_base = 0, o_base = 0;
-    for (int s0 = 0; s0 < n_seg; s0 += 64) {
-      int a;
-      const int len = visible(s0 + lane, a);
+  } else {
+    // One step: what the mask leaves of its segments (at most one to a lane) for this tile, laid end to end.
+    if (wave == 0) {
+      const int a = second ? pair1[0] : pair0[0], e = second ? pair1[1] : pair0[1];
+      const int len = lane < n_seg ? max(0, (p.causal ? min(e, q_last + 1) : e) - a) : 0;
       int sl = len;                               // inclusive scan of the lengths
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) { const int t = __shfl_up(sl, o); if (lane >= o) sl += t; }
-      const int beg = v_base + sl - len;          // position in the tile's visible keys
-      const int cb = max(beg, lo), ce = min(beg + len, hi), clen = max(0, ce - cb);
-      const unsigned long long has = __builtin_amdgcn_ballot_w64(clen > 0);
-      if (clen > 0) {
-        const int idx = n_base + __builtin_popcountll(has & ((1ull << lane) - 1));
-        e_vbeg[idx] = cb - lo;
-        e_goff[idx] = a + (cb - beg) - (cb - lo);
-        o_base = ce - lo;                         // (the last one of the round is taken below)
+      const unsigned long long has = __builtin_amdgcn_ballot_w64(len > 0);
+      if (len > 0) {
+        const int idx = __builtin_popcountll(has & ((1ull << lane) - 1));
+        e_vbeg[idx] = sl - len;
+        e_goff[idx] = a - (sl - len);
       }
-      if (has != 0) o_base = __shfl(o_base, 63 - __builtin_clzll(has));
-      n_base += __builtin_popcountll(has);
-      v_base += __shfl(sl, 63);
+      if (lane == 63) { e_n = __builtin_popcountll(has); e_vbeg[__builtin_popcountll(has)] = sl; }
     }
-    if (lane == 0) { e_vbeg[n_base] = o_base; e_n = n_base; }
+    __syncthreads();
+    n_eff = e_n;
+    n_keys = e_vbeg[n_eff];
   }
-  __syncthreads();
-  const int n_eff = e_n, n_keys = e_vbeg[n_eff];
   const int n_tiles = (n_keys + BT - 1) / BT;
+  static_assert(kMaxSeg <= 64, "");
 
-  // ---- positions of the keys, looked up for CHUNK of them at a time: chunk c in half c % 2 of s_tok.
+  // ---- positions of the keys of a step, looked up for CHUNK of them at a time: chunk c in half c % 2 of s_tok.
   // With sub-chunks of a few dozen keys most tiles cross a segment boundary; a search per tile and
   // row cost more than the tile's exponentials.
+  auto find = [&](int v) __attribute__((always_inline)) {
+    int lo = 0, n = n_eff;                                          // the last segment that begins at or before v
+    while (n > 1) {
+      const int half = n >> 1;
+      if (e_vbeg[lo + half] <= v) lo += half;
+      n -= half;
+    }
+    return v < n_keys ? v + e_goff[lo] : INT_MAX;
+  };
   auto locate = [&](int chunk) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < CHUNK / NTHREADS; ++i) {
-      const int v = chunk * CHUNK + i * NTHREADS + tid;
-      int lo = 0, n = n_eff;                                        // the last segment that begins at or before v
-      while (n > 1) {
-        const int half = n >> 1;
-        if (e_vbeg[lo + half] <= v) lo += half;
-        n -= half;
-      }
-      s_tok[(chunk & 1) * CHUNK + i * NTHREADS + tid] = v < n_keys ? v + e_goff[lo] : INT_MAX;
-    }
+    for (int i = 0; i < CHUNK / NTHREADS; ++i) s_tok[(chunk & 1) * CHUNK + i * NTHREADS + tid] = find(chunk * CHUNK + i * NTHREADS + tid);
   };
 
-  // ---- loader: this thread fills rows fr + RPP i, physical unit fu of the K and the V tile
-  const int fr = tid / C::UNITS, fu = tid % C::UNITS;
+  // ---- loader, bf16: this thread fills rows fr + RPP i, physical unit fu of the K and the V tile.  fp32: a
+  // wavefront fills the rows that it will convert itself, OWN wave + RPW i.
+  constexpr int RPW = 64 / C::UNITS, PASSES = F32 ? C::OWN / RPW : C::PASSES;
+  const int fu = tid % C::UNITS;
+  auto fill_row = [&](int i, int ln) __attribute__((always_inline)) { return (F32 ? C::OWN * wave_u + RPW * i : RPW * wave_u + C::RPP * i) + ln / C::UNITS; };
+  auto column = [&](bool v, int r) __attribute__((always_inline)) {                              // what goes to physical unit fu of row r
+    if constexpr (F32) return (2 * (fu / 2 ^ C::pair_x(v, r)) + (fu % 2 ^ C::pair_y(v, r, fu / 2))) * 16;
+    else return (v ? C::swz_v(r, fu) : C::swz_k(r, fu)) * 16;
+  };
   const unsigned row_bytes = static_cast<unsigned>(p.Hkv) * C::RB;
   const int64_t head0 = (bi * p.kv_bstride + static_cast<int64_t>(g) * D) * static_cast<int64_t>(sizeof(T));
   const unsigned char* Kg = static_cast<const unsigned char*>(p.k) + head0;
   const unsigned char* Vg = static_cast<const unsigned char*>(p.v) + head0;
   const u32x4 k_buf = raw_buffer(Kg), v_buf = raw_buffer(Vg);
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  const unsigned k_col = column(false, fill_row(0, lane)), v_col = column(true, fill_row(0, lane));
+  static_assert(!F32 || PASSES == 2, "");
+  static_assert(F32 || (C::RPP % 16 == 0), "the swizzle of a thread's rows does not depend on the pass");
+  // Rows past the end are masked.  A step fetches the first key for them: every row sees that one, so nothing it holds
+  // reaches a row that it should not (0 times infinity).  A run of positions fetches its last key, whose products the tile has anyway.
   auto fetch = [&](int t, int stage) __attribute__((always_inline)) {
-    unsigned char* dst = smem + stage * C::STAGE_BYTES + wave_u * 1024;
-    int tok[C::PASSES], last = -1;
+    unsigned char* dst = smem + stage * C::STAGE_BYTES + wave_u * (F32 ? C::OWN * C::RB : 1024);
+    constexpr int PASS_BYTES = F32 ? 1024 : NTHREADS * 16;
+    // fp32: the columns of a later pass are those of the first but for a bit (pair_x of K and, at d = 128, pair_y of V);
+    // formed here, not held in registers across the loop
+    unsigned ck = k_col, cv = v_col;
+    int ln = lane;
+    if constexpr (F32) asm volatile("" : "+v"(ck), "+v"(cv), "+v"(ln));
+    auto k_of = [&](int i) __attribute__((always_inline)) { return F32 ? ck ^ (32u * RPW * i) : ck; };
+    auto v_of = [&](int i) __attribute__((always_inline)) { return F32 ? cv ^ (D == 128 ? 16u * i : 0u) : cv; };
+    if (linear) {
+      // RPW neighbouring rows to a load: their common base is scalar
 #pragma unroll
-    for (int i = 0; i < C::PASSES; ++i) tok[i] = s_tok[(t * BT + fr + C::RPP * i) & (2 * CHUNK - 1)];     // one round trip for all passes
+      for (int i = 0; i < PASSES; ++i) {
+        const int first = t * BT + (F32 ? C::OWN * wave_u + RPW * i : RPW * wave_u + C::RPP * i);
+        unsigned more = static_cast<unsigned>(ln / C::UNITS) * row_bytes;
+        int base = first;
+        if ((t + 1) * BT > n_keys) {
+          base = min(first, n_keys - 1);
+          more = static_cast<unsigned>(min(first + ln / C::UNITS, n_keys - 1) - base) * row_bytes;
+        }
+        base += goff;
+        if constexpr (F32) {                                        // tensors may exceed what a 32-bit offset reaches
+          const unsigned long long at = static_cast<unsigned long long>(static_cast<unsigned>(base)) * row_bytes;
+          global_to_lds_16<true>(Kg + at, more + k_of(i), dst + i * PASS_BYTES);
+          global_to_lds_16<true>(Vg + at, more + v_of(i), dst + C::TILE_BYTES + i * PASS_BYTES);
+        } else {
+          const unsigned at = static_cast<unsigned>(base) * row_bytes;
+          buffer_to_lds_16<true>(k_buf, at, more + k_of(i), dst + i * PASS_BYTES);
+          buffer_to_lds_16<true>(v_buf, at, more + v_of(i), dst + C::TILE_BYTES + i * PASS_BYTES);
+        }
+      }
+      return;
+    }
+    int tok[PASSES], last = -1;
 #pragma unroll
-    for (int i = 0; i < C::PASSES; ++i) {
-      const int r = fr + C::RPP * i;
+    for (int i = 0; i < PASSES; ++i) tok[i] = s_tok[(t * BT + fill_row(i, ln)) & (2 * CHUNK - 1)];     // one round trip for all passes
+#pragma unroll
+    for (int i = 0; i < PASSES; ++i) {
       last = max(last, tok[i]);
-      // rows past the end fetch the first key and are masked; every row sees that one, so nothing it holds reaches
-      // a row that it should not (0 times infinity)
       const unsigned key = tok[i] == INT_MAX ? 0u : static_cast<unsigned>(tok[i]);
-      if constexpr (F32) {                                          // tensors may exceed what a 32-bit offset reaches
-        const unsigned long long off = static_cast<unsigned long long>(key) * row_bytes;
-        global_to_lds_16_far(Kg + off + C::swz_k(r, fu) * 16, dst + i * NTHREADS * 16);
-        global_to_lds_16_far(Vg + off + C::swz_v(r, fu) * 16, dst + C::TILE_BYTES + i * NTHREADS * 16);
+      if constexpr (F32) {
+        const unsigned long long at = static_cast<unsigned long long>(key) * row_bytes;
+        global_to_lds_16_far(Kg + (at + k_of(i)), dst + i * PASS_BYTES);
+        global_to_lds_16_far(Vg + (at + v_of(i)), dst + C::TILE_BYTES + i * PASS_BYTES);
       } else {                                                      // both factors are below 2^24 (host check)
         const unsigned off = __umul24(key, row_bytes);
-        buffer_to_lds_16<true>(k_buf, 0u, off + C::swz_k(r, fu) * 16, dst + i * NTHREADS * 16);
-        buffer_to_lds_16<true>(v_buf, 0u, off + C::swz_v(r, fu) * 16, dst + C::TILE_BYTES + i * NTHREADS * 16);
+        buffer_to_lds_16<true>(k_buf, 0u, off + k_of(i), dst + i * PASS_BYTES);
+        buffer_to_lds_16<true>(v_buf, 0u, off + v_of(i), dst + C::TILE_BYTES + i * PASS_BYTES);
       }
     }
     const bool any = __builtin_amdgcn_ballot_w64(last > q_first) != 0;
     if (lane == 0) s_msk[stage][wave] = any ? 1 : 0;
   };
+  // whether tile t takes the element-wise mask; and the mask: keys 32 kb + 8 (i / 4) + 4 h + i % 4 of the tile
+  auto is_masked = [&](int t, int stage) __attribute__((always_inline)) {
+    if (linear) return (t + 1) * BT > n_keys || goff + (t + 1) * BT - 1 > q_first;
+    int mk = 0;
+#pragma unroll
+    for (int i = 0; i < NW / 4; ++i) {
+      const i32x4 m4 = *reinterpret_cast<const i32x4*>(&s_msk[stage][4 * i]);
+      mk |= m4[0] | m4[1] | m4[2] | m4[3];
+    }
+    return __builtin_amdgcn_readfirstlane(mk) != 0;
+  };
+  auto mask_block = [&](int t, int kb, f32x16& S) __attribute__((always_inline)) {
+    const int* tok = &s_tok[((t * BT) & (2 * CHUNK - 1)) + 32 * kb + 4 * h];
+    const int last = linear ? min(q_pos, goff + n_keys - 1) : q_pos, at = goff + t * BT + 32 * kb + 4 * h;
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      i32x4 tk = {at + 8 * i4, at + 8 * i4 + 1, at + 8 * i4 + 2, at + 8 * i4 + 3};
+      if (!linear) tk = *reinterpret_cast<const i32x4*>(tok + 8 * i4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (tk[e] > last) S[4 * i4 + e] = -__builtin_inff();
+    }
+  };
 
   // ---- LDS read addresses inside a stage
-  const int k_row = lq * C::RB, k_sw = C::swz_k(lq, h) * 16;        // unit 2 j + h sits at k_sw ^ 32 j
-  int v_adr[NDB];                                                   // bf16: as in the large kernel
-  if constexpr (F32) {
-    v_adr[0] = C::TILE_BYTES + 4 * h * C::RB + lq * (C::RB / 32);   // key 4 h (+ 8 (r / 4) + r % 4), 32 equal pieces of the row
-  } else {
+  // K: bf16 unit 2 j + h sits at k_adr ^ 32 j; fp32 pair 2 j + h at k_adr ^ 64 j (d = 128: ^ 16 from pair 8 on), the low halves ^ 16
+  const int k_adr = lq * C::RB + (F32 ? 32 * (h ^ C::pair_x(false, lq)) + 16 * C::pair_y(false, lq, h ^ C::pair_x(false, lq)) : C::swz_k(lq, h) * 16);
+  // V: as in the large kernel; fp32 the high halves of block db at v_adr[0] ^ 128 db (^ 16 from block 2 on), the low halves ^ 16
+  int v_adr[F32 ? 1 : NDB];
+  {
     const int ga = lane >> 4, jj = lane & 15;
     const int vrow = 4 * (ga >> 1) + (jj >> 2);
 #pragma unroll
-    for (int db = 0; db < NDB; ++db)
-      v_adr[db] = C::TILE_BYTES + (vrow * C::UNITS + C::swz_v(vrow, 4 * db + 2 * (ga & 1) + ((jj & 3) >> 1))) * 16 + 8 * (jj & 1);
+    for (int db = 0; db < (F32 ? 1 : NDB); ++db) {
+      const int u = 4 * db + 2 * (ga & 1) + ((jj & 3) >> 1), pair = u ^ C::pair_x(true, vrow);
+      v_adr[db] = C::TILE_BYTES + vrow * C::RB + (F32 ? 32 * pair + 16 * C::pair_y(true, vrow, pair) : C::swz_v(vrow, u) * 16) + 8 * (jj & 1);
+    }
   }
 
   f32x16 o[NDB];
 #pragma unroll
   for (int db = 0; db < NDB; ++db) o[db] = zero16();
-  // fp32: what FLUSH tiles have added goes to a second set of sums, so that the error of the chain of additions does
-  // not grow with the number of keys (2 048 of 16 384 tokens: error of the output 9.9e-7 with one set, 5.1e-7 so, for 1 % of the time)
-  constexpr int FLUSH = 8;
-  f32x16 o_sum[F32 ? NDB : 1];
-#pragma unroll
-  for (int db = 0; db < (F32 ? NDB : 1); ++db) o_sum[db] = zero16();
   // running max (exp2 domain), sum in two levels (the last 64 tiles, everything before: one fp32
   // accumulator would swallow the many small terms behind a few large ones), and what rounding added
   // to the largest probabilities (bf16), as in the large kernel
   float m_run = kNegBig, l_run = 0.f, l_lo = 0.f, r_fix = 0.f;
   const float c = p.scale * kLog2e;
 
-  // fp32: an infinity or NaN in V of a key that a row does not see would come to it as 0 times that.  Only tiles with the
-  // element-wise mask hold such pairs; those of them with such a V are left out and added key by key after the others.
-  bool odd_tiles = false;
   const bool idle = __builtin_amdgcn_readfirstlane(tile * BM + strip * 32) >= m_all;
+  if constexpr (F32) {
+    // ---- fp32.  A product a b of floats is formed from their halves as  a_lo b_hi + a_hi b_lo + a_hi b_hi  on the 16-bit
+    // matrix pipe, which is sixteen times as fast as the fp32 one.  A half holds 11 bits, and the rows are scaled by
+    // powers of two so that the largest value of each piece is in [2^14, 2^15): q by row, K and V by the eight rows a
+    // wavefront fetches, p by the piece of V it meets; what is left out, a_lo b_lo and the rounding of lo, is 2^-24 of
+    // |a b| and 2^-40 of the largest one.  That is less than the rounding of a sum of fp32 products (relative error of
+    // 128-term dot products 1.4e-7 against 2.0e-7), and sixteen products are added up before a sum is rounded.
+    //
+    // Tile t is converted in place, by the wavefront that fetched it, while tile t - 1 is worked on; tile t + 1 is on its way.
+    //
+    // Two kinds of keys are cleared, masked and added one by one at the end, from memory: those with an infinity, which has no
+    // halves (inf - inf), and those more than 2^kSpread times as large as another of their piece, whose halves would
+    // leave the other too few bits.  A row of Q with an infinity is done again key by key.  Tiles with the element-wise mask
+    // and a NaN in V, which would come to the rows that do not see its key as 0 times that, are left to the end as a whole.
+    constexpr int KS = D / 16, LOADS = 2 * PASSES;       // contraction steps, loads a fetch issues
+    static_assert(C::OWN * (D / 8) == 64, "");
+    const int run = (n_tiles + RUNS - 1) / RUNS;
+    bool odd = false;
+    auto mark_odd = [&](int t) __attribute__((always_inline)) {
+      odd = true;
+      if (lane == 0) s_odd[t / run] = 1;
+    };
+    f32x4 raw[2][2];
+    float conv_s[2];
+    int conv_adr[2];
+#pragma unroll
+    for (int kv = 0; kv < 2; ++kv) {
+      const int r = C::OWN * wave + lane / (D / 8), pair = lane % (D / 8);
+      conv_adr[kv] = kv * C::TILE_BYTES + r * C::RB + 32 * pair + 16 * C::pair_y(kv, r, pair);
+    }
+    auto conv_read = [&](int stage, int kv) __attribute__((always_inline)) {
+      const unsigned char* st = smem + stage * C::STAGE_BYTES;
+      raw[kv][0] = *reinterpret_cast<const f32x4*>(st + conv_adr[kv]);
+      raw[kv][1] = *reinterpret_cast<const f32x4*>(st + (conv_adr[kv] ^ 16));
+    };
+    auto conv_scale = [&](int stage) __attribute__((always_inline)) {
+      int mk = __builtin_bit_cast(int, abs_max8(raw[0][0], raw[0][1], 0.f)), mv = __builtin_bit_cast(int, abs_max8(raw[1][0], raw[1][1], 0.f));
+      int ek, ev, lk, lv;
+      row_exps<D / 8>(mk, ek, lk);
+      row_exps<D / 8>(mv, ev, lv);
+      const bool bad = max(ek, ev) == 128 || max(ek - lk, ev - lv) > kSpread;
+      const int at = C::OWN == 4 ? 4 * (wave & 1) + (wave >> 1) : 4 * (lane & 1) + wave;
+      if (__builtin_expect(bad, 0)) {
+        int rows = 0;
+        unsigned top_k = 0, top_v = 0;
+#pragma unroll
+        for (int r = 0; r < C::OWN; ++r) {
+          const unsigned xk = __builtin_amdgcn_readlane(mk, D / 8 * r + D / 8 - 1), xv = __builtin_amdgcn_readlane(mv, D / 8 * r + D / 8 - 1);
+          const int rk = static_cast<int>(xk >> 23) - 127, rv = static_cast<int>(xv >> 23) - 127;
+          if (rk == 128 || rv == 128 || rk - lk > kSpread || rv - lv > kSpread) { rows |= 1 << r; continue; }
+          top_k = max(top_k, xk);
+          top_v = max(top_v, xv);
+        }
+        ek = max(static_cast<int>(top_k >> 23) - 127, kLeastExp);
+        ev = max(static_cast<int>(top_v >> 23) - 127, kLeastExp);
+        if (rows >> (lane / (D / 8)) & 1) {
+#pragma unroll
+          for (int kv = 0; kv < 2; ++kv) raw[kv][0] = raw[kv][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        if (lane < 2) s_vt[stage][at] = pow2(ev);
+        if (lane == 0) s_bad[stage][wave] = rows << (C::OWN * wave);
+      }
+      conv_s[0] = pow2(14 - ek);
+      conv_s[1] = pow2(14 - ev);
+      if (lane < 2) {                         // (four rows: one entry)
+        s_kx[stage][at] = pow2(ek - 14);
+        s_vx[stage][at] = bad ? __builtin_inff() : pow2(ev);
+      }
+    };
+    auto conv_write = [&](int stage, int kv) __attribute__((always_inline)) {
+      unsigned char* st = smem + stage * C::STAGE_BYTES;
+      u32x4 hi, lo;
+      split8(raw[kv][0], raw[kv][1], conv_s[kv], conv_s[kv], hi, lo);
+      *reinterpret_cast<u32x4*>(st + conv_adr[kv]) = hi;
+      *reinterpret_cast<u32x4*>(st + (conv_adr[kv] ^ 16)) = lo;
+    };
+    auto convert = [&](int stage) __attribute__((always_inline)) {
+      conv_read(stage, 0);
+      conv_read(stage, 1);
+      conv_scale(stage);
+      conv_write(stage, 0);
+      conv_write(stage, 1);
+    };
+    if constexpr (!SERIAL) split_q();          // (here its loads have landed)
+    // o holds the sums of P V times 2^(kProbExp + 14 - o_exp); o_exp follows the V of the tiles: up with every larger one, down
+    // where one is 2^4 smaller, but not more than 2^64 below the largest so far (o may not overflow)
+    int o_exp = kLeastExp, o_top = kLeastExp;
+    // d = 64 has the registers for a second set of sums, which takes what 16 tiles have added to the first.  Relative error of
+    // the output, no mask, 32 768 tokens: 5.9e-7 with one set, 5.3e-7 with two
+    constexpr int FLUSH = 16, NSUM = D == 64 ? NDB : 0;
+    f32x16 o_sum[NSUM > 0 ? NSUM : 1];
+#pragma unroll
+    for (int db = 0; db < NSUM; ++db) o_sum[db] = zero16();
+    auto scale_sums = [&](float x) __attribute__((always_inline)) {
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) o[db] *= x;
+#pragma unroll
+      for (int db = 0; db < NSUM; ++db) o_sum[db] *= x;
+    };
+
+    if (n_tiles > 0) {
+      if (!linear) {
+        locate(0);
+        __syncthreads();
+      }
+      fetch(0, 0);
+      if (n_tiles > 1) {
+        fetch(1, 1);
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(LOADS) : "memory");
+      } else {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
+      convert(0);
+    }
+    int stage = 0;
+    for (int t = 0; t < n_tiles; ++t, stage = stage == 2 ? 0 : stage + 1) {
+      __syncthreads();               // tile t is converted; nobody reads tile t - 1 any more
+      const int next = stage == 2 ? 0 : stage + 1;
+      if (t + 2 < n_tiles) {
+        fetch(t + 2, next == 2 ? 0 : next + 1);
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(LOADS) : "memory");     // what this wavefront converts of tile t + 1
+      } else {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
+      // three tiles before a chunk of keys begins: the half of the table it goes to has been left behind
+      if (!linear && (t + 3) % (CHUNK / BT) == 0 && t + 3 < n_tiles) locate((t + 3) / (CHUNK / BT));
+      const unsigned char* st = smem + stage * C::STAGE_BYTES;
+      const f32x4 kx = *reinterpret_cast<const f32x4*>(&s_kx[stage][4 * h]);
+      f32x4 vx = *reinterpret_cast<const f32x4*>(&s_vx[stage][4 * h]);
+      auto top_exp = [&](const float* x) __attribute__((always_inline)) {
+        const f32x4 a = *reinterpret_cast<const f32x4*>(x), b = *reinterpret_cast<const f32x4*>(x + 4);
+        const float top = fmaxf(fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])), fmaxf(fmaxf(b[0], b[1]), fmaxf(b[2], b[3])));
+        return (__builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, top)) >> 23) - 127;
+      };
+      int e_top = top_exp(&s_vx[stage][0]), bad = 0;
+      if (__builtin_expect(e_top == 128, 0)) {
+        e_top = kLeastExp;
+        for (int w = 0; w < 8; ++w) {
+          const float x = s_vx[stage][w] == __builtin_inff() ? s_vt[stage][w] : s_vx[stage][w];
+          e_top = max(e_top, (__builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)) >> 23) - 127);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (vx[i] == __builtin_inff()) {
+            vx[i] = s_vt[stage][4 * h + i];
+            bad |= s_bad[stage][C::OWN == 4 ? 2 * i + h : i];
+          }
+        mark_odd(t);
+      }
+      const bool masked = is_masked(t, stage);   // by element
+      bool leave = idle;
+      if (masked && !idle) {                     // a NaN in V
+        f16x2 z = {0, 0};
+#pragma unroll 2
+        for (int i = 0; i < D / 16; ++i) {
+          const f16x8 x = *reinterpret_cast<const f16x8*>(st + C::TILE_BYTES + lq * C::RB + 32 * (i + h * (D / 16)) + 16 * C::pair_y(true, lq, i + h * (D / 16)));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) z = f16x2{x[2 * e], x[2 * e + 1]} * f16x2{0, 0} + z;
+        }
+        if (__builtin_amdgcn_ballot_w64(!(z[0] == 0 && z[1] == 0)) != 0) {
+          mark_odd(t);
+          leave = true;
+        }
+      }
+      if (leave) {
+        convert(next);
+        continue;
+      }
+      // ---- scores; the floats of tile t + 1 are read and their exponents found beside them
+      f32x16 S = zero16();
+      // (formed where they are used: held across the loop the fragment addresses are registers too many; the stage is a multiple
+      // of what the swizzle moves)
+      int ka = k_adr + stage * C::STAGE_BYTES, va = v_adr[0] + stage * C::STAGE_BYTES;
+      asm volatile("" : "+v"(ka), "+v"(va));
+      constexpr int PK = 2;
+      u32x4 k_hi[PK], k_lo[PK];
+      auto read_k = [&](auto jj) __attribute__((always_inline)) {
+        constexpr int J = decltype(jj)::value;
+        // pair 2 J + h: bit 3 of it (d = 128, J >= 4) stands as it is, 256 bytes on, and swaps the units of the pair
+        constexpr int lo = 64 * (J % 4) ^ (D == 128 && J >= 4 ? 0 : 16), hi = lo ^ 16, on = J / 4 * 256;
+        k_lo[J % PK] = *reinterpret_cast<const u32x4*>(smem + (ka ^ lo) + on);
+        k_hi[J % PK] = *reinterpret_cast<const u32x4*>(smem + (ka ^ hi) + on);
+      };
+      static_for<PK>(read_k);
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<KS>([&](auto jj) __attribute__((always_inline)) {
+        constexpr int J = decltype(jj)::value;
+        S = mfma_f16(k_lo[J % PK], qf[2 * J], S);
+        if constexpr (J == 0) { conv_read(next, 0); conv_read(next, 1); }
+        S = mfma_f16(k_hi[J % PK], qf[2 * J + 1], S);
+        S = mfma_f16(k_hi[J % PK], qf[2 * J], S);
+        if constexpr (J + PK < KS) read_k(std::integral_constant<int, J + PK>{});
+        if constexpr (J == 1) conv_scale(next);
+        if constexpr (J >= KS - 2) conv_write(next, J - (KS - 2));
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      // ---- V^T fragments: a block of O^T after the other, for each 16-key group
+      constexpr int NV = 2 * NDB, PV = 2;
+      u32x4 v_hi[PV], v_lo[PV];
+      auto read_v = [&](auto ff) __attribute__((always_inline)) {
+        constexpr int F = decltype(ff)::value;
+        constexpr int db = F / 2, rows = F % 2 * 16 * C::RB;
+        constexpr int xh = 128 * (db % 2) ^ (db >= 2 ? 16 : 0), xl = xh ^ 16, on = db / 2 * 256 + rows;
+        v_hi[F % PV] = __builtin_bit_cast(u32x4, lds_tr8(smem + (va ^ xh) + on, smem + (va ^ xh) + on + 8 * C::RB));
+        v_lo[F % PV] = __builtin_bit_cast(u32x4, lds_tr8(smem + (va ^ xl) + on, smem + (va ^ xl) + on + 8 * C::RB));
+      };
+      static_for<PV>(read_v);
+      if (masked) mask_block(t, 0, S);
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad != 0) != 0, 0)) {
+        const int mine = bad >> 4 * h;
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (mine >> (8 * (i / 4) + i % 4) & 1) S[i] = -__builtin_inff();
+      }
+      float f[4], mx = -__builtin_inff();
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) {
+        f[i4] = __builtin_amdgcn_fmed3f(cq * kx[i4], 1.17549435e-38f, 3.402823466e38f);     // (0 and infinite times the mask's -inf and 0 are NaN)
+        mx = fmaxf(mx, fmaxf(fmaxf(S[4 * i4], S[4 * i4 + 1]), fmaxf(S[4 * i4 + 2], S[4 * i4 + 3])) * f[i4]);
+      }
+      int new_exp = o_exp;
+      o_top = max(o_top, e_top);
+      if (e_top > o_exp) new_exp = e_top;
+      else if (e_top < o_exp - 4 && e_top > kLeastExp) new_exp = max(e_top, o_top - 64);
+      if (__builtin_amdgcn_ballot_w64(mx > m_run + kRescaleGapF32) != 0 || new_exp != o_exp) {
+        const float m_new = fmaxf(m_run, fmaxf(mx, __shfl_xor(mx, 32)));         // both halves of a row agree
+        float alpha = fast_exp2(m_run - m_new);
+        m_run = m_new;
+        l_run *= alpha; l_lo *= alpha;
+        alpha *= pow2(max(o_exp - new_exp, -126));
+        o_exp = new_exp;
+        scale_sums(alpha);
+      }
+      // ---- probabilities, and their products with the pieces of V; pieces more than 2^6 below the largest, whose
+      // probabilities would be left too few bits, in further passes
+      float sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        S[i] = fast_exp2(__builtin_fmaf(S[i], f[i / 4], -m_run));
+        sum[i & 3] += S[i];
+      }
+      float lim = pow2(max(o_exp - 6, -126)), above = __builtin_inff();
+      bool more;
+      do {
+        more = __builtin_amdgcn_ballot_w64(fminf(fminf(vx[0], vx[1]), fminf(vx[2], vx[3])) < lim) != 0;
+        const float p_scale = pow2(kProbExp - o_exp);
+        float ps[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ps[i] = vx[i] * p_scale;
+        if (__builtin_expect(more || above < __builtin_inff(), 0)) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) ps[i] = vx[i] >= lim && vx[i] < above ? ps[i] : 0.f;
+        }
+        u32x4 p_hi[2], p_lo[2];
+#pragma unroll
+        for (int gg = 0; gg < 2; ++gg)
+          split8(f32x4{S[8 * gg], S[8 * gg + 1], S[8 * gg + 2], S[8 * gg + 3]}, f32x4{S[8 * gg + 4], S[8 * gg + 5], S[8 * gg + 6], S[8 * gg + 7]},
+                 ps[2 * gg], ps[2 * gg + 1], p_hi[gg], p_lo[gg]);
+        __builtin_amdgcn_sched_barrier(0);
+        // A tile's products are summed for themselves and then added to o, so that the error of the chain of additions grows
+        // with the tiles, not with the products.
+        f32x16 acc;
+        static_for<NV>([&](auto ff) __attribute__((always_inline)) {
+          constexpr int F = decltype(ff)::value, gg = F % 2, db = F / 2;
+          acc = mfma_f16(v_lo[F % PV], p_hi[gg], gg == 0 ? zero16() : acc);
+          acc = mfma_f16(v_hi[F % PV], p_lo[gg], acc);
+          acc = mfma_f16(v_hi[F % PV], p_hi[gg], acc);
+          if constexpr (F + PV < NV) read_v(std::integral_constant<int, F + PV>{});
+          if constexpr (gg == 1) o[db] += acc;
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        if (__builtin_expect(more, 0)) {
+          above = lim;
+          float top = 0.f;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) top = fmaxf(top, vx[i] < above ? vx[i] : 0.f);
+          top = fmaxf(top, __shfl_xor(top, 32));
+          const int e = (__builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, top)) >> 23) - 127;
+          if (e <= kLeastExp) break;                       // what is left is zero
+          new_exp = max(e, o_top - 64);
+          const float up = pow2(min(o_exp - new_exp, 127));
+          lim = new_exp > e ? 0.f : pow2(max(e - 6, -126));
+          o_exp = new_exp;
+          scale_sums(up);
+          static_for<PV>(read_v);
+        }
+      } while (more);
+      l_lo += (sum[0] + sum[1]) + (sum[2] + sum[3]);
+      if ((t & 63) == 63) { l_run += l_lo; l_lo = 0.f; }
+      if (NSUM > 0 && t % FLUSH == FLUSH - 1) {
+#pragma unroll
+        for (int db = 0; db < NSUM; ++db) { o_sum[db] += o[db]; o[db] = zero16(); }
+      }
+    }
+#pragma unroll
+    for (int db = 0; db < NSUM; ++db) o[db] += o_sum[db];
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) o[db] *= pow2(o_exp - kProbExp - 14);
+    // ---- what was left to the end, key by key.  As slow as it is rare.
+    int late = lane;                 // (addresses formed anew, not kept across the loop)
+    asm volatile("" : "+v"(late));
+    const f32x4* const qr = reinterpret_cast<const f32x4*>(static_cast<const float*>(p.q) + bi * p.q_bstride + row_of(late & 31).idx * D) + (late >> 5);
+    auto add_key = [&](int key, bool wanted) __attribute__((always_inline)) {
+      const f32x4* const kk = reinterpret_cast<const f32x4*>(Kg + static_cast<unsigned long long>(key) * row_bytes) + h;
+      float dot = 0.f;
+#pragma unroll 4
+      for (int j = 0; j < D / 8; ++j) {
+        const f32x4 a = kk[2 * j], b = qr[2 * j];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dot = __builtin_fmaf(a[e], b[e], dot);
+      }
+      dot += __shfl_xor(dot, 32);
+      if (key > q_pos || !wanted) return;
+      const float m_new = fmaxf(m_run, dot * c), alpha = fast_exp2(m_run - m_new), pk = fast_exp2(__builtin_fmaf(dot, c, -m_new));
+      m_run = m_new;
+      l_run *= alpha;
+      l_lo = l_lo * alpha + (h == 0 ? pk : 0.f);
+      const float* vk = reinterpret_cast<const float*>(Vg + static_cast<unsigned long long>(key) * row_bytes);
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) o[db][i] = __builtin_fmaf(pk, vk[32 * db + 8 * (i / 4) + 4 * h + i % 4], o[db][i] * alpha);
+    };
+    const bool any_q_inf = !idle && __builtin_amdgcn_ballot_w64(q_inf) != 0;
+    if (any_q_inf && q_inf) {                    // from the start again
+      m_run = kNegBig;
+      l_run = l_lo = 0.f;
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) o[db] = zero16();
+    }
+    if (odd || any_q_inf) {
+#pragma unroll 1
+      for (int t = 0; t < n_tiles; ++t) {
+        // rows of Q with an infinity are settled (NaN) with the first score that is infinite and positive
+        const bool redo = any_q_inf && __builtin_amdgcn_ballot_w64(q_inf && l_run + l_lo == l_run + l_lo) != 0;
+        const bool look = s_odd[t / run] != 0;
+        if (!redo && !look) continue;
+        const int v = t * BT + lq, tok = linear ? (v < n_keys ? goff + v : INT_MAX) : find(v);
+        unsigned left = 0;
+        if (look) {
+          const unsigned long long at = static_cast<unsigned long long>(tok != INT_MAX ? tok : linear ? goff + n_keys - 1 : 0) * row_bytes;
+          const float* const kr = reinterpret_cast<const float*>(Kg + at) + h * (D / 2);
+          const float* const vr = reinterpret_cast<const float*>(Vg + at) + h * (D / 2);
+          float mk = 0.f, mv = 0.f, z = 0.f;
+#pragma unroll 1
+          for (int e = 0; e < D / 2; ++e) {
+            mk = abs_max3(mk, kr[e], kr[e]);
+            mv = abs_max3(mv, vr[e], vr[e]);
+            z = __builtin_fmaf(vr[e], 0.f, z);
+          }
+          // as in conv_scale: exponents of the row, and of the smallest of its piece
+          auto far = [&](float m) __attribute__((always_inline)) {
+            const unsigned x = __builtin_bit_cast(int, fmaxf(m, __shfl_xor(m, 32)));
+            unsigned least = x - 1;
+#pragma unroll
+            for (int o = 1; o < C::OWN; o <<= 1) least = min(least, static_cast<unsigned>(__shfl_xor(static_cast<int>(least), o)));
+            const int e = static_cast<int>(x >> 23) - 127;
+            return e == 128 || e - max(min(static_cast<int>(least >> 23) - 127, 127), kLeastExp) > kSpread;
+          };
+          const bool far_k = far(mk), far_v = far(mv);
+          const unsigned bad = static_cast<unsigned>(__builtin_amdgcn_ballot_w64(far_k || far_v));      // (both halves have the same)
+          const unsigned long long nan = __builtin_amdgcn_ballot_w64(!(z == 0.f) && !(bad >> lq & 1));
+          const bool masked = __builtin_amdgcn_ballot_w64(tok > q_first) != 0;
+          left = masked && nan != 0 ? ~0u : bad;
+        }
+#pragma unroll 1
+        for (int k = 0; k < BT; ++k) {
+          const int key = __builtin_amdgcn_readlane(tok, k);
+          if (key == INT_MAX) break;               // past the end, as all that follow
+          const bool mine = left >> k & 1;
+          if (mine || redo) add_key(key, q_inf || mine);
+        }
+      }
+    }
+  } else {
   if (n_tiles > 0) {
-    locate(0);
-    __syncthreads();
+    if (!linear) {
+      locate(0);
+      __syncthreads();
+    }
     fetch(0, 0);
   }
 #pragma unroll
@@ -313,39 +830,19 @@ __global__ __launch_bounds__(NTHREADS, (D == 64 ? 3 : 2) - SERIAL) void attn_til
     __syncthreads();                 // tile t is complete; nobody reads the other stage any more
     if (t + 1 < n_tiles) fetch(t + 1, stage ^ 1);
     // two tiles before a chunk of keys begins: the half of the table it goes to has been left behind
-    if ((t + 2) % (CHUNK / BT) == 0 && t + 2 < n_tiles) locate((t + 2) / (CHUNK / BT));
+    if (!linear && (t + 2) % (CHUNK / BT) == 0 && t + 2 < n_tiles) locate((t + 2) / (CHUNK / BT));
     if (idle) continue;
     const unsigned char* st = smem + stage * C::STAGE_BYTES;
 
-    bool masked = false;             // by element
-    if constexpr (F32) {             // (asked here, where few registers are taken; bf16: under way with the V fragments)
-      const i32x4 mk = *reinterpret_cast<const i32x4*>(&s_msk[stage][0]);
-      masked = __builtin_amdgcn_readfirstlane(mk[0] | mk[1] | mk[2] | mk[3]) != 0;
-      if (masked) {                              // see odd_tiles
-        float z = 0.f;
-#pragma unroll 4
-        for (int r = 0; r < 16; ++r) z = add_zero_times<NDB>(st + v_adr[0] + (8 * (r / 4) + r % 4) * C::RB, z);
-        if (__builtin_amdgcn_ballot_w64(!(z == 0.f)) != 0) { odd_tiles = true; continue; }
-      }
-    }
     // The matrix instructions of both products take their A operands as streams of fragments read ahead, so
-    // that a wavefront alone on its SIMD does not wait for LDS at each of them (one fp32 K fragment feeds four
-    // long instructions: the compiler's order does).
+    // that a wavefront alone on its SIMD does not wait for LDS at each of them.
     f32x16 S[NKB];
-    if constexpr (F32) {
-      S[0] = zero16();
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const f32x4 af = *reinterpret_cast<const f32x4*>(st + k_row + (k_sw ^ (32 * j))), bf = __builtin_bit_cast(f32x4, qf[j]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) S[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[e], bf[e], S[0], 0, 0, 0);
-      }
-    } else {
+    {
       constexpr int NF = NKB * NJ, PD = 6;
       bf16x8 ring[PD];
       auto read_k = [&](auto ff) __attribute__((always_inline)) {
         constexpr int F = decltype(ff)::value;
-        ring[F % PD] = *reinterpret_cast<const bf16x8*>(st + k_row + F / NJ * 32 * C::RB + (k_sw ^ (32 * (F % NJ))));
+        ring[F % PD] = *reinterpret_cast<const bf16x8*>(st + F / NJ * 32 * C::RB + (k_adr ^ (32 * (F % NJ))));
       };
       static_for<PD>(read_k);
       __builtin_amdgcn_sched_barrier(0);
@@ -357,28 +854,17 @@ __global__ __launch_bounds__(NTHREADS, (D == 64 ? 3 : 2) - SERIAL) void attn_til
         __builtin_amdgcn_sched_barrier(0);
       });
     }
-    constexpr int NV = F32 ? 1 : 2 * NKB * NDB, PV = 4;       // bf16 V^T fragments: 16-key group f / NDB, block f % NDB of O^T
+    constexpr int NV = 2 * NKB * NDB, PV = 4;       // bf16 V^T fragments: 16-key group f / NDB, block f % NDB of O^T
     bf16x8 vring[PV];
     auto read_v = [&](auto ff) __attribute__((always_inline)) {
       constexpr int F = decltype(ff)::value;
       const unsigned char* va = st + v_adr[F % NDB] + F / NDB * 16 * C::RB;
       vring[F % PV] = lds_tr8(va, va + 8 * C::RB);
     };
-    if constexpr (!F32) static_for<PV>(read_v);               // on their way during the maxima
-    if constexpr (!F32) {
-      const i32x4 mk = *reinterpret_cast<const i32x4*>(&s_msk[stage][0]);
-      masked = __builtin_amdgcn_readfirstlane(mk[0] | mk[1] | mk[2] | mk[3]) != 0;
-    }
-    if (masked) {
+    static_for<PV>(read_v);               // on their way during the maxima
+    if (is_masked(t, stage)) {       // by element
 #pragma unroll
-      for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-          const i32x4 tk = *reinterpret_cast<const i32x4*>(&s_tok[((t * BT) & (2 * CHUNK - 1)) + 32 * kb + 8 * i4 + 4 * h]);
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (tk[e] > q_pos) S[kb][4 * i4 + e] = -__builtin_inff();
-        }
+      for (int kb = 0; kb < NKB; ++kb) mask_block(t, kb, S[kb]);
     }
     float mx = S[0][0];
 #pragma unroll
@@ -393,12 +879,9 @@ __global__ __launch_bounds__(NTHREADS, (D == 64 ? 3 : 2) - SERIAL) void attn_til
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          o[db][i] *= alpha;
-          if constexpr (F32) o_sum[db][i] *= alpha;
-        }
+        for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
     }
-    if constexpr (!F32) {
+    {
       const float p_top = fast_exp2(__builtin_fmaf(mx, c, -m_run));
       r_fix += static_cast<float>(static_cast<__bf16>(p_top)) - p_top;
     }
@@ -410,24 +893,7 @@ __global__ __launch_bounds__(NTHREADS, (D == 64 ? 3 : 2) - SERIAL) void attn_til
         sum[i & 3] += S[i / 16][i % 16];
       }
     };
-    if constexpr (F32) {
-      exps(std::integral_constant<int, 0>{}, std::integral_constant<int, 16>{});
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {             // keys 8 (r / 4) + r % 4 and four further on (the lane halves)
-        const unsigned char* va = st + v_adr[0] + (8 * (r / 4) + r % 4) * C::RB;
-        float vv[NDB];
-        if constexpr (NDB == 4) {
-          const f32x4 x = *reinterpret_cast<const f32x4*>(va);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) vv[e] = x[e];
-        } else {
-          const f32x2 x = *reinterpret_cast<const f32x2*>(va);
-          vv[0] = x[0]; vv[1] = x[1];
-        }
-#pragma unroll
-        for (int db = 0; db < NDB; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv[db], S[0][r], o[db], 0, 0, 0);
-      }
-    } else {
+    {
       // the exponentials of a 16-key group ride beside the matrix instructions of the group before
       constexpr int PER = 8 / NDB;
       exps(std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{});
@@ -446,58 +912,7 @@ __global__ __launch_bounds__(NTHREADS, (D == 64 ? 3 : 2) - SERIAL) void attn_til
     }
     l_lo += (sum[0] + sum[1]) + (sum[2] + sum[3]);
     if ((t & 63) == 63) { l_run += l_lo; l_lo = 0.f; }
-    if constexpr (F32) {
-      if (t % FLUSH == FLUSH - 1) {
-#pragma unroll
-        for (int db = 0; db < NDB; ++db) { o_sum[db] += o[db]; o[db] = zero16(); }
-      }
-    }
   }
-  if constexpr (F32) {
-#pragma unroll
-    for (int db = 0; db < NDB; ++db) o[db] += o_sum[db];
-    if (odd_tiles) {
-#pragma unroll 1
-      for (int t = 0; t < n_tiles; ++t) {
-        const int v = t * BT + lq;
-        int lo = 0, n = n_eff;                     // as in locate
-        while (n > 1) {
-          const int half = n >> 1;
-          if (e_vbeg[lo + half] <= v) lo += half;
-          n -= half;
-        }
-        const int tok = v < n_keys ? v + e_goff[lo] : INT_MAX;
-        if (__builtin_amdgcn_ballot_w64(tok > q_first) == 0) continue;
-        const float* vr = reinterpret_cast<const float*>(Vg + static_cast<unsigned long long>(tok == INT_MAX ? 0 : tok) * row_bytes) + h * (D / 2);
-        float z = 0.f;
-        for (int e = 0; e < D / 2; ++e) z = __builtin_fmaf(vr[e], 0.f, z);
-        if (__builtin_amdgcn_ballot_w64(!(z == 0.f)) == 0) continue;
-#pragma unroll 1
-        for (int k = 0; k < BT; ++k) {
-          const int key = __builtin_amdgcn_readlane(tok, k);
-          if (key == INT_MAX) break;               // past the end, as all that follow
-          const u32x4* kr = reinterpret_cast<const u32x4*>(Kg + static_cast<unsigned long long>(key) * row_bytes) + h;
-          float dot = 0.f;
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) {
-            const f32x4 a = __builtin_bit_cast(f32x4, kr[2 * j]), b = __builtin_bit_cast(f32x4, qf[j]);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) dot = __builtin_fmaf(a[e], b[e], dot);
-          }
-          dot += __shfl_xor(dot, 32);
-          if (key > q_pos) continue;
-          const float m_new = fmaxf(m_run, dot * c), alpha = fast_exp2(m_run - m_new), pk = fast_exp2(__builtin_fmaf(dot, c, -m_new));
-          m_run = m_new;
-          l_run *= alpha;
-          l_lo = l_lo * alpha + (h == 0 ? pk : 0.f);
-          const float* vk = reinterpret_cast<const float*>(Vg + static_cast<unsigned long long>(key) * row_bytes);
-#pragma unroll
-          for (int i = 0; i < 16; ++i)
-#pragma unroll
-            for (int db = 0; db < NDB; ++db) o[db][i] = __builtin_fmaf(pk, vk[NDB * (8 * (i / 4) + 4 * h + i % 4) + db], o[db][i] * alpha);
-        }
-      }
-    }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // no fetch may still be writing LDS when the workgroup ends
 
@@ -507,28 +922,23 @@ __global__ __launch_bounds__(NTHREADS, (D == 64 ? 3 : 2) - SERIAL) void attn_til
   const bool seen = l_tot > 0.f;
   float wb = seen && r_tot > 0.f ? 1.f / r_tot : 0.f;
   float lse_new = seen ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -__builtin_inff();
-  const int64_t ooff = bi * p.o_bstride + (static_cast<int64_t>(q_row0 + row) * p.Hq + hq) * D;
-  const int64_t loff = bi * p.lse_bstride + static_cast<int64_t>(q_row0 + row) * p.Hq + hq;
-  // columns of register quad q of the lane: bf16 block q / 4, 32 (q / 4) + 8 (q % 4) + 4 h; fp32 d = 128
-  // row i of the blocks, 4 i; d = 64 rows i, i + 1, 2 i, where i = 8 (r / 4) + 4 h + r % 4
+  int late = lane;                   // (the row's place formed anew, not kept across the loop)
+  asm volatile("" : "+v"(late));
+  const Row to = row_of(late & 31);
+  const bool q_valid = to.valid;
+  const int64_t ooff = bi * p.o_bstride + to.idx * D, loff = bi * p.lse_bstride + to.idx;
+  // columns of register quad q of the lane: block q / 4 of O^T, 32 (q / 4) + 8 (q % 4) + 4 h
   auto quad = [&](auto qq, f32x4& x) __attribute__((always_inline)) {
     constexpr int Q = decltype(qq)::value;
-    if constexpr (!F32) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) x[e] = o[Q / 4][4 * (Q % 4) + e];
-      return 32 * (Q / 4) + 8 * (Q % 4) + 4 * h;
-    } else if constexpr (NDB == 4) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) x[e] = o[e][Q];
-      return 4 * (8 * (Q / 4) + 4 * h + Q % 4);
-    } else {
-      x = f32x4{o[0][2 * Q], o[1][2 * Q], o[0][2 * Q + 1], o[1][2 * Q + 1]};
-      return 2 * (8 * (2 * Q / 4) + 4 * h + (2 * Q) % 4);
-    }
+    for (int e = 0; e < 4; ++e) x[e] = o[Q / 4][4 * (Q % 4) + e];
+    return 32 * (Q / 4) + 8 * (Q % 4) + 4 * h;
   };
   if (SERIAL && ns > 1) {
-    float r, w;
+    float r, w, mx_all = round > 0 ? s_all[0][thread] : -__builtin_inff(), den_all = round > 0 ? s_all[1][thread] : 0.f;
     fold(lse_new, mx_all, den_all, r, w);
+    s_all[0][thread] = mx_all;
+    s_all[1][thread] = den_all;
     const bool last = round == ns - 1;
     const float inv = den_all > 0.f ? 1.f / den_all : 0.f;
     float* od = static_cast<float*>(p.out_final) + ooff;
@@ -552,7 +962,7 @@ __global__ __launch_bounds__(NTHREADS, (D == 64 ? 3 : 2) - SERIAL) void attn_til
   } else if (p.merge == 0 && (ns > 1 || p.out_final == nullptr)) {
     // a share's pair, or the partial pair of a step
     const int64_t n_q = second ? t1.n_q : t0.n_q;
-    const int64_t rh = ns > 1 ? ((static_cast<int64_t>(share) * p.batch + bi) * n_q + row) * p.Hq + hq : 0;
+    const int64_t rh = ns > 1 ? (static_cast<int64_t>(share) * p.batch + bi) * n_q * p.Hq + to.idx - static_cast<int64_t>(q_row0) * p.Hq : 0;
     float* od = ns > 1 ? (second ? p.part_o[1] : p.part_o[0]) + rh * D : p.o_dst + ooff;
     float* ld = ns > 1 ? (second ? p.part_lse[1] : p.part_lse[0]) + rh : p.lse_dst + loff;
     static_for<D / 8>([&](auto qq) __attribute__((always_inline)) {
@@ -608,6 +1018,8 @@ __global__ __launch_bounds__(NTHREADS, (D == 64 ? 3 : 2) - SERIAL) void attn_til
 
 template <typename T, int D, bool SERIAL = false>
 hipError_t launch_tile_variant(const AttnLaunch& p, hipStream_t stream) {
+  constexpr int BM = TCfg<T, D>::BM;
+  if (SERIAL && !p.all_steps) return hipErrorInvalidValue;
   const int64_t G = p.Hq / p.Hkv;
   int64_t per_g = 0;
   for (int t = 0; t < p.n_tasks; ++t) {
@@ -619,7 +1031,7 @@ hipError_t launch_tile_variant(const AttnLaunch& p, hipStream_t stream) {
   if (per_g * units > INT_MAX) return hipErrorInvalidValue;
   const int64_t blocks = xcd_balanced_blocks(units, per_g);
   if (blocks > INT_MAX) return hipErrorInvalidValue;
-  return TASP_LAUNCH((attn_tile_kernel<T, D, SERIAL>), dim3(static_cast<unsigned>(blocks)), dim3(NTHREADS), stream, p);
+  return TASP_LAUNCH((attn_tile_kernel<T, D, SERIAL>), dim3(static_cast<unsigned>(blocks)), dim3(TCfg<T, D>::NTHREADS), stream, p);
 }
 
 // The pairs of a row's shares added up as in tasp_lse_merge_many, D / 4 lanes of 4 columns to a (row, head).

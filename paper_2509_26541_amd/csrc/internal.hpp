@@ -10,7 +10,8 @@ namespace tasp {
 
 constexpr int kMaxSeg = 64;      // KV segments one query block can see in one step (2(N-1) for zig-zag)
 constexpr int kMaxTasks = 2;     // query blocks per step (the two half-chunks of the zig-zag layout)
-constexpr int kTileRows = 128;   // rows (local row, head of the group) of a query tile of attn_tile_kernel
+// Rows (local row, head of the group) of a query tile of attn_tile_kernel.
+constexpr int tile_rows(bool fp32, int d) { return fp32 && d == 128 ? 256 : 128; }
 constexpr int kMaxSegAll = 1024; // segments of one query block over ALL steps (steps joined in one launch)
 // Segments a launch descriptor holds, all its query blocks together.  A launch of all steps of eight
 // ranks fits (at most 112 + 56) and so do most of twelve; longer lists go through device memory, which
@@ -44,9 +45,6 @@ struct AttnLaunch {
   int64_t q_bstride, kv_bstride, o_bstride, lse_bstride;
   int32_t n_tasks;
   AttnTask task[kMaxTasks];
-  // With many steps in one launch the segment lists may not fit the pool: they then live in device
-  // memory, task[t].n_seg (start, end) pairs at seg_ext[t], and the pool is unused.
-  const int32_t* seg_ext[kMaxTasks];
   int32_t n_items;    // work items of the launch, for persistent workgroups; filled in by the launcher
   void* out_final;    // not null: the rows are final and go here in the inputs' type, not to o_dst (merge = 0)
   // attn_tile_kernel: task t's keys are dealt to n_split[t] workgroups per query tile.  Where that is
@@ -55,7 +53,7 @@ struct AttnLaunch {
   int32_t n_split[kMaxTasks];
   float* part_o[kMaxTasks];
   float* part_lse[kMaxTasks];
-  int32_t all_steps;  // the steps of the call are joined in this launch
+  int32_t all_steps;  // the steps of the call are joined in this launch: every task has one segment, from key 0 on
   int32_t pool[2 * kPoolSeg];
 };
 static_assert(sizeof(AttnLaunch) <= 4096, "kernel arguments");
@@ -88,7 +86,9 @@ struct BwdLaunch {
   int64_t q_bstride, kv_bstride, lse_bstride;   // elements between sequences
   int32_t n_tasks;
   AttnTask task[kMaxTasks];
-  const int32_t* seg_ext[kMaxTasks];   // as in AttnLaunch (all steps in one launch)
+  // The lists of all steps may not fit the pool: they then live in device memory, task[t].n_seg (start, end) pairs at
+  // seg_ext[t], and the pool is unused.
+  const int32_t* seg_ext[kMaxTasks];
   int32_t pool[2 * kPoolSeg];
   int32_t n_blk;
   BwdBlock blk[kMaxTasks];
