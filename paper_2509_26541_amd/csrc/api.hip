@@ -208,57 +208,75 @@ constexpr int64_t kMaxSplit = 32;    // shares of one tile
 // the shares that one of them would get alone, the results of such a batch are bit for bit those of separate
 // calls; they are not where the partial pairs of all take more than the workspace that is planned for.
 int64_t plan_batch(int64_t batch, int64_t tiles_of_one) { return batch <= 4 && batch * tiles_of_one <= 128 ? 1 : batch; }
-int64_t plan_batch(const AttnLaunch& lp, int rows) {
+int64_t plan_batch(const AttnLaunch& lp) {
+  constexpr int rows = tasp::tile_rows(false, 0);
   int64_t tiles = 0;
   for (int t = 0; t < lp.n_tasks; ++t) tiles += (static_cast<int64_t>(lp.task[t].n_q) * (lp.Hq / lp.Hkv) + rows - 1) / rows * lp.Hkv;
   return plan_batch(lp.batch, tiles);
 }
 
+// When the last of n0 workgroups of length l0 and n1 of length l1 is done, each free one of `slots` taking the longest left.
+double makespan(double n0, double l0, double n1, double l1, double slots) {
+  if (l0 < l1) { std::swap(n0, n1); std::swap(l0, l1); }
+  const double full = std::floor(n0 / slots), more = n0 - full * slots, few = slots - more;      // `more` slots have one of the long ones more than `few`
+  const double high = (full + (more > 0 ? 1 : 0)) * l0, low = full * l0;
+  if (n1 <= 0) return high;
+  const double fit = std::floor((high - low) / l1);        // short ones that fit beside the last long ones, on each of the few
+  if (n1 <= few * fit) return std::max(more > 0 ? high : 0, low + std::ceil(n1 / few) * l1);
+  n1 -= few * (fit + 1);                                   // one more on each of them, then one on each of the others, and so on
+  if (n1 <= 0) return low + (fit + 1) * l1;
+  const double rounds = std::floor(n1 / slots), rest = n1 - rounds * slots;
+  return rest == 0 ? std::max(low + (fit + 1 + rounds) * l1, more > 0 ? high + rounds * l1 : 0)
+                   : rest <= more ? std::max(high + (rounds + 1) * l1, low + (fit + 1 + rounds) * l1) : low + (fit + 2 + rounds) * l1;
+}
+
 // Deals the keys of the query tiles of attn_tile_kernel to n_split[t] workgroups each; keys[t] = keys the
-// last row of task t sees.  A lone workgroup of the kernel uses about half a CU and several share one, so
-// what counts is the length of the longest share times the workgroups of the fullest CU: shares as long as
-// 256, 512, ... workgroups in all make them, each against its fixed cost (set-up, first fetches, epilogue: 4 us)
-// and the way of the partial pairs through memory.  (With as many shares as the work asks for, without
-// regard to whole rounds of the CUs, 4 heads of 128 over 4 096 of 32 768 tokens took 211 us against 179.)
-void deal_keys(const AttnLaunch& lp, int d, bool fp32, const int64_t* keys, size_t room, int32_t* n_split) {
-  const double per_us = (fp32 ? 7.0 : 72.0) * (d == 64 ? (fp32 ? 2.0 : 1.5) : 1.0);     // keys of a tile that a CU walks in a microsecond
-  const int64_t step = fp32 ? 32 : 64, least = fp32 ? 64 : 128;
-  const int64_t G = lp.Hq / lp.Hkv, rows = tasp::tile_rows(fp32, d), B = plan_batch(lp, rows);
-  int64_t tiles[tasp::kMaxTasks] = {0, 0}, longest = 0;
+// last row of task t sees.  Shares are weighed by when the last workgroup would be done: R workgroups of a CU side by side,
+// each at 1 / R of its rate, one by itself at 1 / alone; a workgroup's fixed cost (set-up, first fetches, epilogue) as so many
+// keys more; and with shares the launch that adds them up and the way of the partial pairs through memory.
+// Fitted to 1 900 calls of each type (512 to 32K tokens, both d, batches of 1 to 4), each with up to 57 ways to deal them: over the
+// best of these, which is partly the luckiest, the choice takes 1.5 % more (fp32, d = 128; 3.4 % at d = 64, bf16 3.7 and 6.3 %),
+// where shares of equal length in whole rounds of the CUs took 20 % (7 %; 7 and 8 %).
+void deal_keys(const AttnLaunch& lp, int d, bool fp32, const int64_t* keys, size_t room, int32_t* n_split, int64_t B) {
+  struct Fit { double R, alone, fixed, per_us; };          // (fixed in keys, per_us: keys a CU walks in a microsecond)
+  const Fit fit = fp32 ? (d == 64 ? Fit{2, 1.4, 60, 28} : Fit{1, 1, 60, 10}) : (d == 64 ? Fit{2, 1.4, 300, 80} : Fit{2, 1.6, 200, 60});
+  const double add_us = 3, add_bytes_us = fp32 && d == 128 ? 6e6 : 4e6;
+  const int64_t step = fp32 ? 32 : 64, G = lp.Hq / lp.Hkv, rows = tasp::tile_rows(fp32, d);
+  double tiles[tasp::kMaxTasks] = {0, 0}, bytes[tasp::kMaxTasks] = {0, 0};
   for (int t = 0; t < lp.n_tasks; ++t) {
-    tiles[t] = (lp.task[t].n_q * G + rows - 1) / rows * lp.Hkv * B;
-    longest = std::max(longest, keys[t]);
+    tiles[t] = static_cast<double>((lp.task[t].n_q * G + rows - 1) / rows * lp.Hkv * B);
+    bytes[t] = 8.0 * lp.task[t].n_q * lp.Hq * B * d;
   }
-  auto shares = [&](int64_t per_wg, int64_t (&n)[tasp::kMaxTasks]) {
-    int64_t total = 0;
-    for (int t = 0; t < lp.n_tasks; ++t) {
-      n[t] = std::max<int64_t>(1, std::min((keys[t] + per_wg - 1) / per_wg, kMaxSplit));
-      total += tiles[t] * n[t];
-    }
-    return total;
-  };
+  static constexpr int32_t kWays[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 14, 16, 20, 24, kMaxSplit};
   double best = -1;
-  for (int k = 0; k <= 8; ++k) {                  // k = 0: every tile in one share
-    int64_t lo = least / step, hi = std::max(lo, (longest + step - 1) / step), n[tasp::kMaxTasks] = {1, 1};
-    if (k == 0) lo = hi;
-    else if (shares(hi * step, n) > 256 * k) continue;
-    while (lo < hi) {                             // the shortest shares with at most 256 k workgroups
-      const int64_t mid = (lo + hi) / 2;
-      if (shares(mid * step, n) <= 256 * k) hi = mid; else lo = mid + 1;
-    }
-    const int64_t total = shares(hi * step, n);
-    const int32_t n32[tasp::kMaxTasks] = {static_cast<int32_t>(n[0]), static_cast<int32_t>(n[1])};
-    if (all_share_bytes(lp, d, n32) > room) continue;
-    double one = 0, bytes = 0;
+  auto weigh = [&](int32_t n0, int32_t n1) {
+    const int32_t n[tasp::kMaxTasks] = {n0, n1};
+    if (all_share_bytes(lp, d, n) > room) return;
+    double len[tasp::kMaxTasks] = {0, 0}, wgs[tasp::kMaxTasks] = {0, 0}, moved = 0;
     for (int t = 0; t < lp.n_tasks; ++t) {
-      one = std::max(one, static_cast<double>(keys[t]) / n[t]);
-      bytes += n[t] > 1 ? 8.0 * n[t] * lp.task[t].n_q * lp.Hq * B * d : 0;
+      const int64_t chunk = ((keys[t] + n[t] - 1) / n[t] + step - 1) / step * step;
+      len[t] = static_cast<double>(chunk) + fit.fixed;
+      wgs[t] = tiles[t] * n[t];
+      moved += n[t] > 1 ? n[t] * bytes[t] : 0;
     }
-    const double rounds = std::max(1.8, std::ceil(total / 256.0));
-    const double cost = (one + 4 * per_us) * rounds + (n[0] > 1 || n[1] > 1 ? (4 + bytes / 8e6) * per_us : 0);
-    if (best < 0 || cost < best) {
-      best = cost;
-      for (int t = 0; t < lp.n_tasks; ++t) n_split[t] = static_cast<int32_t>(n[t]);
+    if (len[1] > 1.1 * len[0]) return;                     // (task 1 starts last: its shares would be the tail)
+    const double alone = std::max(len[0], len[1]) * fit.alone;
+    double cost = wgs[0] + wgs[1] <= 256 ? alone : std::max(alone, makespan(wgs[0], len[0], wgs[1], len[1], 256 * fit.R) * fit.R);
+    cost = cost / fit.per_us + (moved > 0 ? add_us + moved / add_bytes_us : 0);
+    // Items are dealt to XCDs in turn: with an even number of shares an XCD meets few of them.  8 heads over 2 and over 8, 512
+    // and 768 rows: 8, 10 and 12 shares took 3 % more than their odd neighbours.
+    if (n0 >= 4 && n0 % 2 == 0) cost *= 1.03;
+    if (best < 0 || cost < best) { best = cost; n_split[0] = n0; n_split[1] = n1; }
+  };
+  for (const int32_t n : kWays) {
+    if (n > 1 && (n - 1) * step >= keys[0]) break;         // (task 0 has the most keys)
+    weigh(n, 1);
+    if (lp.n_tasks > 1 && n > 1) {
+      const int64_t chunk = ((keys[0] + n - 1) / n + step - 1) / step * step;
+      const int32_t alike = static_cast<int32_t>((keys[1] + chunk - 1) / chunk);      // shares of the same length
+      if (alike > 1) weigh(n, alike);
+      if (alike < n) weigh(n, alike + 1);
+      if (alike + 1 < n) weigh(n, n);
     }
   }
 }
@@ -279,7 +297,7 @@ constexpr double kStepMargin = 0.89;
 bool tile_is_faster(const AttnLaunch& lp, int d, const int64_t* keys, const int32_t* n_split, bool step = false) {
   constexpr double kCus = 256.0;
   constexpr int kTileRows = tasp::tile_rows(false, 0);
-  const double B = static_cast<double>(plan_batch(lp, kTileRows)), G = lp.Hq / lp.Hkv;
+  const double B = static_cast<double>(plan_batch(lp)), G = lp.Hq / lp.Hkv;
   auto padded = [](double x, double m) { return std::ceil(x / m) * m; };
   double rows8 = 0, rows12 = 0;
   for (int t = 0; t < lp.n_tasks; ++t) { rows8 += padded(lp.task[t].n_q, 256); rows12 += padded(lp.task[t].n_q, 384); }
@@ -321,7 +339,10 @@ FwdPlan plan_forward(const tasp_attn_args* a, const JoinedSteps& js, size_t need
   size_t room = std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES);
   for (;;) {
     int32_t n_split[tasp::kMaxTasks] = {1, 1};
-    deal_keys(js.all, a->d, fp32, js.keys, room, n_split);
+    // a few sequences as one of them by itself, unless the partial pairs of all then take more than there is room for
+    const int64_t one = plan_batch(js.all);
+    deal_keys(js.all, a->d, fp32, js.keys, SIZE_MAX, n_split, one);
+    if (all_share_bytes(js.all, a->d, n_split) > room) deal_keys(js.all, a->d, fp32, js.keys, room, n_split, js.all.batch);
     pl.tile = fp32 || tile_is_faster(js.all, a->d, js.keys, n_split);
     if (!pl.tile) {
       // what is estimated to lose with all shares may win with the few that the least workspace holds, or none (20 heads of 64,
