@@ -210,7 +210,7 @@ int tasp_chunk_attn_static(const tasp_schedule_t* s, const tasp_attn_args* a, vo
 /* The same call with every kernel launch bracketed by HIP events on `hip_stream`, for measurement.
  * Synchronises the stream before returning.  Times are sums over launches, in milliseconds:
  * attn = attention kernels, merge = update_out_lse kernels, other = the final bf16 cast, or what a call
- * with joined steps launches beside the attention kernel (segment lists, the sum over shares of the keys). */
+ * with joined steps launches beside the attention kernel (the sum over shares of the keys). */
 typedef struct tasp_profile {
   double  attn_ms, merge_ms, other_ms;
   int32_t attn_launches, merge_launches, other_launches;

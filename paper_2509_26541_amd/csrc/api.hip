@@ -630,7 +630,8 @@ size_t tasp_chunk_attn_workspace_bytes(const tasp_schedule_t* s, const tasp_attn
   const size_t lse_bytes = align_up(B * L * a->Hq * sizeof(float));
   size_t total = 0;
   if (a->dtype == TASP_DTYPE_BF16) total += o_bytes;              // running fp32 output
-  if (a->fuse_steps) return total + align_up(kFusedTableBytes);   // the segment lists of the single launch
+  // what the single launch asks for beside: room for the pairs of a few shares (its keys go by position, it lists no segments)
+  if (a->fuse_steps) return total + align_up(kFusedTableBytes);
   if (!a->fuse_merge) total += o_bytes + lse_bytes;               // partial (out_s, lse_s) of a step
   return total;
 }

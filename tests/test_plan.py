@@ -253,6 +253,29 @@ int main() {
 """
 
 
+MAKESPAN = r"""
+// Each workgroup to the slot that is free first, the longer kind first.
+static double deal(int n0, double l0, int n1, double l1, int slots) {
+  std::vector<double> done(slots, 0.0);
+  if (l0 < l1) { std::swap(n0, n1); std::swap(l0, l1); }
+  for (int i = 0; i < n0 + n1; ++i) *std::min_element(done.begin(), done.end()) += i < n0 ? l0 : l1;
+  return *std::max_element(done.begin(), done.end());
+}
+int main() {
+  std::mt19937 rng(1);
+  auto upto = [&](int n) { return static_cast<int>(rng() % (n + 1)); };
+  double worst = 0;
+  for (int i = 0; i < 200000; ++i) {
+    const int slots = 1 + upto(11), n0 = 1 + upto(5 * slots), n1 = i % 5 == 0 ? 0 : upto(8 * slots);
+    const double l0 = 1 + upto(39), l1 = n1 == 0 ? 0 : 1 + upto(39);
+    const double want = deal(n0, l0, n1, l1, slots), got = makespan(n0, l0, n1, l1, slots), gap = std::abs(got - want) / want;
+    if (gap > worst) { worst = gap; std::printf("%d of %g, %d of %g, %d slots: %g, dealt one by one %g\n", n0, l0, n1, l1, slots, got, want); }
+  }
+  return worst > 1e-12 ? 3 : 0;
+}
+"""
+
+
 def _run(tmp_path, program):
     src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
     src.write_text(STUBS + program)
@@ -282,3 +305,8 @@ def test_more_than_4096_rows_run_step_by_step(tmp_path):
 
 def test_a_joined_call_takes_the_faster_kernel_without_shares(tmp_path):
     _run(tmp_path, FEW_SHARES)
+
+
+def test_when_the_last_workgroup_is_done(tmp_path):
+    """The formula by which shares are weighed, against dealing workgroup by workgroup."""
+    _run(tmp_path, MAKESPAN)
