@@ -738,7 +738,8 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
     for (int db = 0; db < NSUM; ++db) o[db] += o_sum[db];
 #pragma unroll
     for (int db = 0; db < NDB; ++db) o[db] *= pow2(o_exp - kProbExp - 14);
-    // ---- what was left to the end, key by key.  As slow as it is rare.
+    // ---- what was left to the end, key by key.  As slow as it is rare: 16 heads of 128, 2 048 of 16 384 tokens, 583 us with
+    // one infinite key (559 with none, in the same run), 3.1 ms with every 64th V row 2^20 times as large as the others.
     int late = lane;                 // (addresses formed anew, not kept across the loop)
     asm volatile("" : "+v"(late));
     const f32x4* const qr = reinterpret_cast<const f32x4*>(static_cast<const float*>(p.q) + bi * p.q_bstride + row_of(late & 31).idx * D) + (late >> 5);
