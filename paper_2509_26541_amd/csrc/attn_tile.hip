@@ -11,20 +11,22 @@
 // column, so the softmax is in-lane but for one exchange, and the score registers are the B operand of the second
 // product as they stand; V through the transposing LDS read, K and V tiles by direct global->LDS loads.
 //
-// fp32 products are formed from two 16-bit floats each (v_mfma_f32_32x32x16_f16, three for one product; see the loop): a
-// matrix instruction of that kind does in 32 cycles what eight fp32 ones do in 512.  The rows of K and V are split where
-// they were fetched, in LDS and by the wavefront that fetched them, one tile ahead.  Eight wavefronts share a tile at d = 128:
-// with four, a wavefront to a SIMD, twice the splitting and accumulators moved about, 16 heads of 128 took 797 us, not 506.
+// fp32 products are formed from three bf16 each (six products for one; see the loop): exact to the last bit or so whatever the
+// range of the inputs, and six bf16 matrix instructions take 192 cycles where eight fp32 ones take 512.  The rows of K and V
+// are split by the wavefront that fetched them, one tile ahead.  Eight wavefronts share a tile at d = 128: each splits
+// an eighth of it.
 //
 // Joined steps take the keys by position (a tile is a run of neighbouring keys: nothing to look up, the addresses are
 // scalar), a step by itself walks its segments.
 //
-// What bounds it: the issue slots.  fp32 d = 128: 360 vector and 48 matrix instructions for 32 rows by 32 keys, 3 300 cycles of a
-// SIMD of which the matrix pipe is busy 1 536; bf16 1 330 of the 1 450 cycles a SIMD takes for 32 rows by 64 keys at
-// d = 64; in the shortest calls the launch, the set-up and the latency of the first tiles.  Measured, whole calls:
-//   fp32, 16 heads of 128, 2 048 of 16 384 tokens, causal: 0.48 ms (287 TFLOP/s of products of floats) against 1.13 ms with
-//     fp32 matrix instructions (their floor is 0.90); error of the output against 64 bits, 2 heads of 128, 5 120 of
-//     20 480 tokens: 4.4e-7 against 5.8e-7; no mask, 2 heads of 64, 8 192 of 32 768: 5.3e-7 against 5.8e-7;
+// What bounds it: fp32 d = 128: the matrix pipe, 96 instructions or 3 072 of the 4 600 cycles a SIMD takes for 32 rows by 32 keys,
+// beside some 400 vector instructions that two wavefronts in step do not always hide; bf16: the issue slots, 1 330 of the 1 450
+// cycles a SIMD takes for 32 rows by 64 keys at d = 64; in the shortest calls the launch, the set-up and the latency of the
+// first tiles.  Measured, whole calls:
+//   fp32, 16 heads of 128, 2 048 of 16 384 tokens, causal: 0.67 ms (206 TFLOP/s of products of floats; the floor of six
+//     products 0.44) against 1.13 ms with fp32 matrix instructions (0.90); two 16-bit floats to a value took 0.48 but hold a
+//     narrow range only.  Error of the output against 64 bits: 3.0e-7 (fp32 instructions 5.2e-7, 16-bit floats 3.7e-7);
+//     no mask, 4 heads of 64, 3 072 of 24 576 tokens: 4.7e-7 (5.7e-7, 4.9e-7);
 //   fp32, 4 heads of 64, 256 of 1 024 tokens: 16 us;
 //   bf16, 8 heads of 128, 512 of 4 096 tokens: 23 us against 117 with the large kernel on 16 CUs;
 //   bf16, 128 sequences of 3 072 tokens, 20 heads of 64: 0.70 ms (0.72 with the sub-chunks in their order of arrival,
@@ -43,9 +45,9 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kRescaleGap = 8.0f;      // the running max is only raised when it grew by more than 2^8
-constexpr float kRescaleGapF32 = 2.0f;   // fp32: 2^2, the probabilities go to 16-bit floats (below 2^16) scaled by 2^kProbExp
-constexpr int kProbExp = 13;
-constexpr int kSpread = 16;              // fp32: exponents that the rows of a piece of K or V may be apart
+constexpr float kRescaleGapF32 = 2.0f;   // fp32: 2^2, see kHuge
+constexpr int kHuge = (104 + 127) << 23; // fp32: bits of 2^104.  Rows with a value that large are left to the end, see the loop
+constexpr float kVScale = 65536.f;       // fp32: V is taken times 2^16
 constexpr float kNegBig = -1.0e30f;
 constexpr int CHUNK = 512;               // keys located at a time
 constexpr int RUNS = 512;                // fp32: entries of the table of tiles with something left to the end
@@ -57,53 +59,58 @@ struct TCfg {
   static constexpr int NW = BM / 32, NTHREADS = 64 * NW;
   static constexpr int BT = F32 ? 32 : 64;              // keys per tile
   static constexpr int NKB = BT / 32;                   // 32-key blocks
-  static constexpr int RB = D * static_cast<int>(sizeof(T));   // bytes of a row
-  static constexpr int UNITS = RB / 16;                 // 16-byte units per row
-  static constexpr int RPP = NTHREADS / UNITS;          // rows filled per pass
+  static constexpr int RB = D * static_cast<int>(sizeof(T));   // bytes of a row in memory
+  static constexpr int LB = 2 * D;                      // bytes of a row in LDS (fp32: of one of its three pieces)
+  static constexpr int UNITS = LB / 16;                 // 16-byte units of it
+  static constexpr int RPP = NTHREADS / UNITS;          // bf16: rows filled per pass
   static constexpr int PASSES = BT / RPP;
-  static constexpr int OWN = BT / NW;                   // fp32: rows of a tile that a wavefront fetches and converts, a pair of units a lane
-  static constexpr int TILE_BYTES = BT * RB;
+  static constexpr int OWN = BT / NW;                   // fp32: rows of a tile that a wavefront fetches and converts, eight columns a lane
+  static constexpr int PLANES = F32 ? 3 : 1;            // pieces of a value, each kind in a tile of its own
+  static constexpr int PLANE_BYTES = BT * LB;
+  static constexpr int TILE_BYTES = PLANES * PLANE_BYTES;
   static constexpr int STAGE_BYTES = 2 * TILE_BYTES;    // K tile, V tile
-  static constexpr int STAGES = F32 ? 3 : 2;
+  static constexpr int STAGES = 2;
+  static constexpr int RAW_BYTES = F32 ? 2 * BT * RB : 0;   // fp32: rows of K and V as fetched, behind the stages
   static constexpr int RPL = UNITS >= 16 ? 1 : 16 / UNITS;   // rows per 256-byte bank line
   static constexpr int NDB = D / 32;                    // 32-column blocks of O^T
-  // bf16: physical unit of logical unit u of row r.  K is read row-wise (32 lanes, one row each, the same
+  // Physical unit of logical unit u of row r.  K is read row-wise (32 lanes, one row each, the same
   // unit): neighbouring bank lines differ.  V through the transposing read (4 rows, 2 units).
   __device__ static int swz_k(int r, int u) { return u ^ ((r / RPL) % (UNITS < 16 ? UNITS : 16)); }
   __device__ static int swz_v(int r, int u) { return u ^ (4 * ((r / RPL) % (UNITS / 4))); }
-  // fp32: eight columns are two 16-byte units, fetched as eight floats and turned in place into the high halves
-  // (unit 0 of the pair) and the low halves (unit 1) of their split.  Pair c of row r sits at pair c ^ x of the
-  // row, its units swapped where y is 1: the fragment reads (K: 16 rows, one pair, one unit; V: 4 rows, 4 pairs,
-  // one unit) and those of the conversion (neighbouring pairs, one unit) all meet 16 units of a 256-byte line.
-  __device__ static int pair_x(bool v, int r) { return v ? 4 * (r & 1) : r & 7; }
-  __device__ static int pair_y(bool v, int r, int pair) { return ((v ? r >> 1 : r >> 3) ^ (D == 128 ? pair >> 3 : r)) & 1; }   // pair: the physical one
 };
 
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+// The lane's number, formed anew: for code off the ordinary way, so that no register holds it for that.
+__device__ __forceinline__ int lane_id() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
 __device__ inline f32x16 zero16() {
   f32x16 z;
 #pragma unroll
   for (int i = 0; i < 16; ++i) z[i] = 0.f;
   return z;
 }
-// Eight floats times sa and sb (powers of two, for four each) as two sets of eight 16-bit floats, hi + lo = s x to 22 bits and a sign.  In one
-// piece of assembly: one instruction for each half (scaled, subtracted, rounded once and packed; the compiler takes
-// three for both).  Instructions that write half a register stand four apart from those that read it.
-__device__ __forceinline__ void split8(const f32x4& a, const f32x4& b, float sa, float sb, u32x4& hi, u32x4& lo) {
-  unsigned h0, h1, h2, h3, l0, l1, l2, l3;
-  asm("v_fma_mixlo_f16 %0, %8, %16, 0\n\tv_fma_mixlo_f16 %1, %10, %16, 0\n\tv_fma_mixlo_f16 %2, %12, %17, 0\n\tv_fma_mixlo_f16 %3, %14, %17, 0\n\t"
-      "v_fma_mixhi_f16 %0, %9, %16, 0\n\tv_fma_mixhi_f16 %1, %11, %16, 0\n\tv_fma_mixhi_f16 %2, %13, %17, 0\n\tv_fma_mixhi_f16 %3, %15, %17, 0\n\t"
-      "v_fma_mixlo_f16 %4, %8, %16, -%0 op_sel_hi:[0,0,1]\n\tv_fma_mixlo_f16 %5, %10, %16, -%1 op_sel_hi:[0,0,1]\n\t"
-      "v_fma_mixlo_f16 %6, %12, %17, -%2 op_sel_hi:[0,0,1]\n\tv_fma_mixlo_f16 %7, %14, %17, -%3 op_sel_hi:[0,0,1]\n\t"
-      "v_fma_mixhi_f16 %4, %9, %16, -%0 op_sel:[0,0,1] op_sel_hi:[0,0,1]\n\tv_fma_mixhi_f16 %5, %11, %16, -%1 op_sel:[0,0,1] op_sel_hi:[0,0,1]\n\t"
-      "v_fma_mixhi_f16 %6, %13, %17, -%2 op_sel:[0,0,1] op_sel_hi:[0,0,1]\n\tv_fma_mixhi_f16 %7, %15, %17, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]"
-      : "=&v"(h0), "=&v"(h1), "=&v"(h2), "=&v"(h3), "=&v"(l0), "=&v"(l1), "=&v"(l2), "=&v"(l3)
-      : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(sa), "v"(sb));
-  hi = u32x4{h0, h1, h2, h3};
-  lo = u32x4{l0, l1, l2, l3};
+// Floats as three bf16 each, x = x1 + x2 + x3 exactly (8 bits each, rounded to nearest, so that the signs of the later ones
+// vary): x2 is at most 2^-8 x and x3 2^-16 x.  The next piece of eight floats, which are left with the rest.
+__device__ __forceinline__ u32x4 next_piece(f32x4& a, f32x4& b) {
+  u32x4 r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float x = i < 2 ? a[2 * i] : b[2 * i - 4], y = i < 2 ? a[2 * i + 1] : b[2 * i - 3];
+    const bf16x2 h = {static_cast<__bf16>(x), static_cast<__bf16>(y)};
+    unsigned u = __builtin_bit_cast(unsigned, h);
+    asm("" : "+v"(u));               // (or the compiler rounds x once more, by itself)
+    x -= __builtin_bit_cast(float, u << 16);
+    y -= __builtin_bit_cast(float, u & 0xffff0000u);
+    if (i < 2) { a[2 * i] = x; a[2 * i + 1] = y; } else { b[2 * i - 4] = x; b[2 * i - 3] = y; }
+    r[i] = u;
+  }
+  return r;
 }
-__device__ inline f32x16 mfma_f16(const u32x4& a, const u32x4& b, const f32x16& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+__device__ inline f32x16 mfma_bf16(const u32x4& a, const u32x4& b, const f32x16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 // The largest |x| of eight floats, NaN passed over unless there is nothing else, and m.
 __device__ __forceinline__ float abs_max3(float m, float a, float b) {     // (as assembly: the compiler would quiet every input first)
@@ -115,33 +122,6 @@ __device__ __forceinline__ float abs_max8(const f32x4& a, const f32x4& b, float 
   m = abs_max3(abs_max3(m, a[0], a[1]), a[2], a[3]);
   return abs_max3(abs_max3(m, b[0], b[1]), b[2], b[3]);
 }
-// Exponents, 2^e <= max < 2^(e + 1) and not below kLeastExp, 128 for an infinity, of the largest row of a wavefront's lanes and
-// of the smallest one that is not all zeros (127 if all are); W lanes to a row, x their maxima as integers (>= 0: ordered like
-// the floats).  Leaves the maximum of every row in its last lane.
-constexpr int kLeastExp = -100;
-template <int CTRL>
-__device__ __forceinline__ int dpp_max(int x) { return max(x, __builtin_amdgcn_update_dpp(0, x, CTRL, 15, 15, true)); }
-template <int W>
-__device__ __forceinline__ void row_exps(int& x, int& most, int& least) {
-  x = dpp_max<0x111>(x);                                 // shifts inside 16 lanes
-  x = dpp_max<0x112>(x);
-  x = dpp_max<0x114>(x);
-  int lo, hi = x;
-  if constexpr (W == 16) {
-    hi = x = dpp_max<0x118>(x);
-    lo = x - 1;
-  } else {
-    lo = x - 1;                                          // (zero: the largest of all, as an unsigned number)
-    hi = dpp_max<0x118>(x);
-    lo = static_cast<int>(min(static_cast<unsigned>(lo), static_cast<unsigned>(__builtin_amdgcn_update_dpp(lo, lo, 0x118, 15, 15, false))));
-  }
-  auto at = [](int v, int l) { return static_cast<unsigned>(__builtin_amdgcn_readlane(v, l)); };
-  const unsigned m = max(max(at(hi, 15), at(hi, 31)), max(at(hi, 47), at(hi, 63)));
-  const unsigned n = min(min(at(lo, 15), at(lo, 31)), min(at(lo, 47), at(lo, 63)));
-  most = max(static_cast<int>(m >> 23) - 127, kLeastExp);
-  least = max(min(static_cast<int>(n >> 23) - 127, 127), kLeastExp);
-}
-__device__ __forceinline__ float pow2(int e) { return __builtin_bit_cast(float, (e + 127) << 23); }     // -126 .. 127
 __device__ inline bf16x8 lds_tr8(const unsigned char* lo, const unsigned char* hi) {
   const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lds_void_ptr)const_cast<unsigned char*>(lo));
   const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lds_void_ptr)const_cast<unsigned char*>(hi));
@@ -166,17 +146,15 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
   using C = TCfg<T, D>;
   constexpr bool F32 = C::F32;
   constexpr int BM = C::BM, NTHREADS = C::NTHREADS, NW = C::NW;
-  constexpr int BT = C::BT, NKB = C::NKB, NDB = C::NDB, NJ = C::UNITS / 2;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[C::STAGES * C::STAGE_BYTES];
-  // fp32: per four rows of a tile (rows 8 i + 4 h ..: entry 4 h + i) the power of two below their largest |K| (less 14) and
-  // |V|.  Where a wavefront found infinities: s_vx is infinite, the power is in s_vt, the rows it cleared are in s_bad;
-  // s_odd marks the runs of `run` tiles that hold keys to be added at the end.
-  __shared__ __attribute__((aligned(16))) float s_kx[C::STAGES][F32 ? 8 : 1], s_vx[C::STAGES][F32 ? 8 : 1], s_vt[C::STAGES][F32 ? 8 : 1];
-  __shared__ int s_bad[C::STAGES][NW], s_odd[F32 ? RUNS : 1];
+  constexpr int BT = C::BT, NKB = C::NKB, NDB = C::NDB, NJ = D / 16;       // NJ: contraction steps of the scores
+  __shared__ __attribute__((aligned(16))) unsigned char smem[C::STAGES * C::STAGE_BYTES + C::RAW_BYTES];
+  // fp32: the rows of a tile that a wavefront cleared, and the runs of `run` tiles that hold keys to be added at the end.
+  __shared__ __attribute__((aligned(16))) int s_bad[F32 ? C::STAGES : 1][NW];
+  __shared__ int s_odd[F32 ? RUNS : 1];
   // One step's launch: global positions of the keys (INT_MAX: none), whether a wavefront fetched a key that some row of the
   // tile must not see, and the effective segments of the tile.
   __shared__ __attribute__((aligned(16))) int s_tok[2 * CHUNK];
-  __shared__ __attribute__((aligned(16))) int s_msk[C::STAGES][NW];
+  __shared__ __attribute__((aligned(16))) int s_msk[4][NW];
   __shared__ int e_vbeg[kMaxSeg + 1];      // start in their concatenation
   __shared__ int e_goff[kMaxSeg];          //   global position minus that
   __shared__ int e_n;
@@ -231,30 +209,27 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
   const int q_last = q_pos0 + (min(tile * BM + BM, m_all) - 1) / G;
   const int q_first = p.causal ? q_pos0 + tile * BM / G : INT_MAX - 1;   // a key at or before it is seen by every row
 
-  // ---- Q fragments (B operand), bf16: 16-byte units 2 j + h of the lane's row; fp32: units 4 j + 2 h and the one behind it,
-  // later the high and the low halves of these eight columns
-  u32x4 qf[NJ];
+  // ---- Q fragments (B operand), columns 16 j + 8 h .. of the lane's row; fp32: as floats, two of `qf` each, later as three pieces
+  u32x4 qf[(F32 ? 2 : 1) * NJ], qp[F32 ? 3 : 1][NJ];
   {
     const u32x4* src = reinterpret_cast<const u32x4*>(static_cast<const T*>(p.q) + bi * p.q_bstride + mine.idx * D) + (thread >> 5 & 1) * (F32 ? 2 : 1);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) qf[j] = src[F32 ? 4 * (j / 2) + j % 2 : 2 * j];
+    for (int j = 0; j < (F32 ? 2 : 1) * NJ; ++j) qf[j] = src[F32 ? 4 * (j / 2) + j % 2 : 2 * j];
   }
-  float cq = p.scale * kLog2e;          // fp32: times the power of two that the row was divided by
-  bool q_inf = false;                   // fp32: the row holds an infinity
-
-  auto split_q = [&]() __attribute__((always_inline)) {            // fp32: Q to halves
-    constexpr int KS = D / 16;
+  unsigned long long q_odd_rows = 0;    // fp32: lanes whose row holds an infinity or a value of 2^104 or more
+  auto split_q = [&]() __attribute__((always_inline)) {
+    if constexpr (F32) {
     float m = 0.f;
 #pragma unroll
-    for (int j = 0; j < KS; ++j) m = abs_max8(__builtin_bit_cast(f32x4, qf[2 * j]), __builtin_bit_cast(f32x4, qf[2 * j + 1]), m);
-    m = fmaxf(m, __shfl_xor(m, 32));
-    q_inf = m == __builtin_inff();
-    if (q_inf) m = 0.f;
-    const int e = max((__builtin_bit_cast(int, m) >> 23) - 127, kLeastExp);
-    const float s = q_inf ? 0.f : pow2(14 - e);            // (NaN: what comes of infinities is thrown away)
+    for (int j = 0; j < NJ; ++j) m = abs_max8(__builtin_bit_cast(f32x4, qf[2 * j]), __builtin_bit_cast(f32x4, qf[2 * j + 1]), m);
+    q_odd_rows = __builtin_amdgcn_ballot_w64(__builtin_bit_cast(int, fmaxf(m, __shfl_xor(m, 32))) >= kHuge);
 #pragma unroll
-    for (int j = 0; j < KS; ++j) split8(__builtin_bit_cast(f32x4, qf[2 * j]), __builtin_bit_cast(f32x4, qf[2 * j + 1]), s, s, qf[2 * j], qf[2 * j + 1]);
-    cq *= pow2(e - 14);
+    for (int j = 0; j < NJ; ++j) {
+      f32x4 a = __builtin_bit_cast(f32x4, qf[2 * j]), b = __builtin_bit_cast(f32x4, qf[2 * j + 1]);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) qp[i][j] = next_piece(a, b);
+    }
+    }
   };
   if constexpr (F32 && SERIAL) split_q();
 
@@ -262,7 +237,7 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
   int tid = thread;
   if constexpr (SERIAL) {
     share = round;
-    asm volatile("" : "+v"(tid));        // (what follows from it is formed in every round, not kept across the epilogue of the one before)
+    tid = 64 * wave_u + lane_id();       // (formed anew, and what follows from it, in every round, not kept across the epilogue of the one before)
     if (round > 0) __syncthreads();      // nobody reads the tiles of the share before any more
   }
   const int lane = tid & 63, wave = tid >> 6, h = lane >> 5, lq = lane & 31;
@@ -319,12 +294,13 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
   };
 
   // ---- loader, bf16: this thread fills rows fr + RPP i, physical unit fu of the K and the V tile.  fp32: a
-  // wavefront fills the rows that it will convert itself, OWN wave + RPW i.
-  constexpr int RPW = 64 / C::UNITS, PASSES = F32 ? C::OWN / RPW : C::PASSES;
-  const int fu = tid % C::UNITS;
-  auto fill_row = [&](int i, int ln) __attribute__((always_inline)) { return (F32 ? C::OWN * wave_u + RPW * i : RPW * wave_u + C::RPP * i) + ln / C::UNITS; };
+  // wavefront fetches the rows that it will convert itself, OWN wave + RPW i, to a place of its own; of a row the even units of
+  // four floats first, then the odd ones, so that a lane's eight columns are read without bank conflicts.
+  constexpr int UPR = C::RB / 16, RPW = 64 / UPR, PASSES = F32 ? C::OWN / RPW : C::PASSES;
+  const int fu = tid % UPR;
+  auto fill_row = [&](int i, int ln) __attribute__((always_inline)) { return (F32 ? C::OWN * wave_u + RPW * i : RPW * wave_u + C::RPP * i) + ln / UPR; };
   auto column = [&](bool v, int r) __attribute__((always_inline)) {                              // what goes to physical unit fu of row r
-    if constexpr (F32) return (2 * (fu / 2 ^ C::pair_x(v, r)) + (fu % 2 ^ C::pair_y(v, r, fu / 2))) * 16;
+    if constexpr (F32) return (2 * (fu % (UPR / 2)) + fu / (UPR / 2)) * 16;
     else return (v ? C::swz_v(r, fu) : C::swz_k(r, fu)) * 16;
   };
   const unsigned row_bytes = static_cast<unsigned>(p.Hkv) * C::RB;
@@ -333,40 +309,37 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
   const unsigned char* Vg = static_cast<const unsigned char*>(p.v) + head0;
   const u32x4 k_buf = raw_buffer(Kg), v_buf = raw_buffer(Vg);
   const unsigned k_col = column(false, fill_row(0, lane)), v_col = column(true, fill_row(0, lane));
-  static_assert(!F32 || PASSES == 2, "");
+  static_assert(!F32 || (PASSES == 2 && C::OWN * C::UNITS == 64), "");
   static_assert(F32 || (C::RPP % 16 == 0), "the swizzle of a thread's rows does not depend on the pass");
   // Rows past the end are masked.  A step fetches the first key for them: every row sees that one, so nothing it holds
   // reaches a row that it should not (0 times infinity).  A run of positions fetches its last key, whose products the tile has anyway.
   auto fetch = [&](int t, int stage) __attribute__((always_inline)) {
-    unsigned char* dst = smem + stage * C::STAGE_BYTES + wave_u * (F32 ? C::OWN * C::RB : 1024);
-    constexpr int PASS_BYTES = F32 ? 1024 : NTHREADS * 16;
-    // fp32: the columns of a later pass are those of the first but for a bit (pair_x of K and, at d = 128, pair_y of V);
-    // formed here, not held in registers across the loop
+    unsigned char* dst = smem + (F32 ? C::STAGES * C::STAGE_BYTES + wave_u * 2 * C::OWN * C::RB : stage * C::STAGE_BYTES + wave_u * 1024);
+    constexpr int PASS_BYTES = F32 ? 1024 : NTHREADS * 16, V_AT = F32 ? C::OWN * C::RB : C::TILE_BYTES;
     unsigned ck = k_col, cv = v_col;
     int ln = lane;
-    if constexpr (F32) asm volatile("" : "+v"(ck), "+v"(cv), "+v"(ln));
-    auto k_of = [&](int i) __attribute__((always_inline)) { return F32 ? ck ^ (32u * RPW * i) : ck; };
-    auto v_of = [&](int i) __attribute__((always_inline)) { return F32 ? cv ^ (D == 128 ? 16u * i : 0u) : cv; };
+    if constexpr (F32) asm volatile("" : "+v"(ck), "+v"(ln));        // (formed here, not held in registers across the loop)
+    if constexpr (F32) cv = ck;
     if (linear) {
       // RPW neighbouring rows to a load: their common base is scalar
 #pragma unroll
       for (int i = 0; i < PASSES; ++i) {
         const int first = t * BT + (F32 ? C::OWN * wave_u + RPW * i : RPW * wave_u + C::RPP * i);
-        unsigned more = static_cast<unsigned>(ln / C::UNITS) * row_bytes;
+        unsigned more = static_cast<unsigned>(ln / UPR) * row_bytes;
         int base = first;
         if ((t + 1) * BT > n_keys) {
           base = min(first, n_keys - 1);
-          more = static_cast<unsigned>(min(first + ln / C::UNITS, n_keys - 1) - base) * row_bytes;
+          more = static_cast<unsigned>(min(first + ln / UPR, n_keys - 1) - base) * row_bytes;
         }
         base += goff;
         if constexpr (F32) {                                        // tensors may exceed what a 32-bit offset reaches
           const unsigned long long at = static_cast<unsigned long long>(static_cast<unsigned>(base)) * row_bytes;
-          global_to_lds_16<true>(Kg + at, more + k_of(i), dst + i * PASS_BYTES);
-          global_to_lds_16<true>(Vg + at, more + v_of(i), dst + C::TILE_BYTES + i * PASS_BYTES);
+          global_to_lds_16<true>(Kg + at, more + ck, dst + i * PASS_BYTES);
+          global_to_lds_16<true>(Vg + at, more + cv, dst + V_AT + i * PASS_BYTES);
         } else {
           const unsigned at = static_cast<unsigned>(base) * row_bytes;
-          buffer_to_lds_16<true>(k_buf, at, more + k_of(i), dst + i * PASS_BYTES);
-          buffer_to_lds_16<true>(v_buf, at, more + v_of(i), dst + C::TILE_BYTES + i * PASS_BYTES);
+          buffer_to_lds_16<true>(k_buf, at, more + ck, dst + i * PASS_BYTES);
+          buffer_to_lds_16<true>(v_buf, at, more + cv, dst + V_AT + i * PASS_BYTES);
         }
       }
       return;
@@ -380,24 +353,24 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
       const unsigned key = tok[i] == INT_MAX ? 0u : static_cast<unsigned>(tok[i]);
       if constexpr (F32) {
         const unsigned long long at = static_cast<unsigned long long>(key) * row_bytes;
-        global_to_lds_16_far(Kg + (at + k_of(i)), dst + i * PASS_BYTES);
-        global_to_lds_16_far(Vg + (at + v_of(i)), dst + C::TILE_BYTES + i * PASS_BYTES);
+        global_to_lds_16_far(Kg + (at + ck), dst + i * PASS_BYTES);
+        global_to_lds_16_far(Vg + (at + cv), dst + V_AT + i * PASS_BYTES);
       } else {                                                      // both factors are below 2^24 (host check)
         const unsigned off = __umul24(key, row_bytes);
-        buffer_to_lds_16<true>(k_buf, 0u, off + k_of(i), dst + i * PASS_BYTES);
-        buffer_to_lds_16<true>(v_buf, 0u, off + v_of(i), dst + C::TILE_BYTES + i * PASS_BYTES);
+        buffer_to_lds_16<true>(k_buf, 0u, off + ck, dst + i * PASS_BYTES);
+        buffer_to_lds_16<true>(v_buf, 0u, off + cv, dst + V_AT + i * PASS_BYTES);
       }
     }
     const bool any = __builtin_amdgcn_ballot_w64(last > q_first) != 0;
-    if (lane == 0) s_msk[stage][wave] = any ? 1 : 0;
+    if (lane == 0) s_msk[t & 3][wave] = any ? 1 : 0;
   };
   // whether tile t takes the element-wise mask; and the mask: keys 32 kb + 8 (i / 4) + 4 h + i % 4 of the tile
-  auto is_masked = [&](int t, int stage) __attribute__((always_inline)) {
+  auto is_masked = [&](int t) __attribute__((always_inline)) {
     if (linear) return (t + 1) * BT > n_keys || goff + (t + 1) * BT - 1 > q_first;
     int mk = 0;
 #pragma unroll
     for (int i = 0; i < NW / 4; ++i) {
-      const i32x4 m4 = *reinterpret_cast<const i32x4*>(&s_msk[stage][4 * i]);
+      const i32x4 m4 = *reinterpret_cast<const i32x4*>(&s_msk[t & 3][4 * i]);
       mk |= m4[0] | m4[1] | m4[2] | m4[3];
     }
     return __builtin_amdgcn_readfirstlane(mk) != 0;
@@ -416,18 +389,15 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
   };
 
   // ---- LDS read addresses inside a stage
-  // K: bf16 unit 2 j + h sits at k_adr ^ 32 j; fp32 pair 2 j + h at k_adr ^ 64 j (d = 128: ^ 16 from pair 8 on), the low halves ^ 16
-  const int k_adr = lq * C::RB + (F32 ? 32 * (h ^ C::pair_x(false, lq)) + 16 * C::pair_y(false, lq, h ^ C::pair_x(false, lq)) : C::swz_k(lq, h) * 16);
-  // V: as in the large kernel; fp32 the high halves of block db at v_adr[0] ^ 128 db (^ 16 from block 2 on), the low halves ^ 16
+  // K: unit 2 j + h sits at k_adr ^ 32 j; V: block db at v_adr[db], fp32 at v_adr[0] ^ 64 db
+  const int k_adr = lq * C::LB + C::swz_k(lq, h) * 16;
   int v_adr[F32 ? 1 : NDB];
   {
     const int ga = lane >> 4, jj = lane & 15;
     const int vrow = 4 * (ga >> 1) + (jj >> 2);
 #pragma unroll
-    for (int db = 0; db < (F32 ? 1 : NDB); ++db) {
-      const int u = 4 * db + 2 * (ga & 1) + ((jj & 3) >> 1), pair = u ^ C::pair_x(true, vrow);
-      v_adr[db] = C::TILE_BYTES + vrow * C::RB + (F32 ? 32 * pair + 16 * C::pair_y(true, vrow, pair) : C::swz_v(vrow, u) * 16) + 8 * (jj & 1);
-    }
+    for (int db = 0; db < (F32 ? 1 : NDB); ++db)
+      v_adr[db] = C::TILE_BYTES + vrow * C::LB + C::swz_v(vrow, 4 * db + 2 * (ga & 1) + ((jj & 3) >> 1)) * 16 + 8 * (jj & 1);
   }
 
   f32x16 o[NDB];
@@ -441,104 +411,76 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
 
   const bool idle = __builtin_amdgcn_readfirstlane(tile * BM + strip * 32) >= m_all;
   if constexpr (F32) {
-    // ---- fp32.  A product a b of floats is formed from their halves as  a_lo b_hi + a_hi b_lo + a_hi b_hi  on the 16-bit
-    // matrix pipe, which is sixteen times as fast as the fp32 one.  A half holds 11 bits, and the rows are scaled by
-    // powers of two so that the largest value of each piece is in [2^14, 2^15): q by row, K and V by the eight rows a
-    // wavefront fetches, p by the piece of V it meets; what is left out, a_lo b_lo and the rounding of lo, is 2^-24 of
-    // |a b| and 2^-40 of the largest one.  That is less than the rounding of a sum of fp32 products (relative error of
-    // 128-term dot products 1.4e-7 against 2.0e-7), and sixteen products are added up before a sum is rounded.
+    // ---- fp32.  A float is the sum of three bf16 (next_piece), exactly, and a product a b of floats is formed on the bf16 matrix pipe
+    // as  a3 b1 + a2 b2 + a1 b3 + a2 b1 + a1 b2 + a1 b1.  What is left out, a2 b3 + a3 b2 + a3 b3, is at most 2^-24 and
+    // typically 2^-27 of a b: every product is as good as rounded to fp32, whatever stands beside it in its row, its column or
+    // the tile, since bf16 has the exponents of fp32.  (Two 16-bit floats to a value, three products: 2^-40 of the largest
+    // value of a row was lost, so that a column of V 2^30 times as large as the others left these two decimals.)
+    // That holds down to 2^-109, below which the third piece begins to lose bits (the pipe keeps subnormals).  For V, whose
+    // products go to the output as they are, that is the whole range of floats: it is split times 2^16, and a tile's sums
+    // are multiplied by 2^-16.  For K and Q what is lost, 2^-134, is nothing beside a score unless the other factor is near 2^104.
     //
-    // Tile t is converted in place, by the wavefront that fetched it, while tile t - 1 is worked on; tile t + 1 is on its way.
+    // Tile t + 1 is split, by the wavefront that fetched it, while tile t is worked on; tile t + 2 is on its way.
     //
-    // Two kinds of keys are cleared, masked and added one by one at the end, from memory: those with an infinity, which has no
-    // halves (inf - inf), and those more than 2^kSpread times as large as another of their piece, whose halves would
-    // leave the other too few bits.  A row of Q with an infinity is done again key by key.  Tiles with the element-wise mask
-    // and a NaN in V, which would come to the rows that do not see its key as 0 times that, are left to the end as a whole.
-    constexpr int KS = D / 16, LOADS = 2 * PASSES;       // contraction steps, loads a fetch issues
-    static_assert(C::OWN * (D / 8) == 64, "");
+    // Keys with an infinity, which has no pieces (inf - inf), or a value of 2^104 or more (2^2 probabilities of it times 2^16 of 32
+    // keys stay below 2^128) are cleared, masked and added one by one at the end, from memory.  A row of Q with one is done
+    // again key by key.  Tiles with the element-wise mask and a NaN in V, which would come to the rows that do not see its
+    // key as 0 times that, are left to the end as a whole.
     const int run = (n_tiles + RUNS - 1) / RUNS;
     bool odd = false;
     auto mark_odd = [&](int t) __attribute__((always_inline)) {
       odd = true;
       if (lane == 0) s_odd[t / run] = 1;
     };
-    f32x4 raw[2][2];
-    float conv_s[2];
-    int conv_adr[2];
+    const int conv_row = C::OWN * wave + lane / C::UNITS, conv_unit = lane % C::UNITS;
+    const int raw_adr = C::STAGES * C::STAGE_BYTES + wave * 2 * C::OWN * C::RB + lane / C::UNITS * C::RB + conv_unit * 16;
+    const int conv_adr[2] = {conv_row * C::LB + C::swz_k(conv_row, conv_unit) * 16, C::TILE_BYTES + conv_row * C::LB + C::swz_v(conv_row, conv_unit) * 16};
+    // Rows of K (kv = 0) or V of the fetched tile to pieces.  The rows with a huge value count as if they were not there, their scores
+    // are replaced; only what V would bring to 0 times infinity has to go.
+    int huge_rows = 0;
+    f32x4 raw[2];
+    auto conv_read = [&](int kv) __attribute__((always_inline)) {
 #pragma unroll
-    for (int kv = 0; kv < 2; ++kv) {
-      const int r = C::OWN * wave + lane / (D / 8), pair = lane % (D / 8);
-      conv_adr[kv] = kv * C::TILE_BYTES + r * C::RB + 32 * pair + 16 * C::pair_y(kv, r, pair);
-    }
-    auto conv_read = [&](int stage, int kv) __attribute__((always_inline)) {
-      const unsigned char* st = smem + stage * C::STAGE_BYTES;
-      raw[kv][0] = *reinterpret_cast<const f32x4*>(st + conv_adr[kv]);
-      raw[kv][1] = *reinterpret_cast<const f32x4*>(st + (conv_adr[kv] ^ 16));
-    };
-    auto conv_scale = [&](int stage) __attribute__((always_inline)) {
-      int mk = __builtin_bit_cast(int, abs_max8(raw[0][0], raw[0][1], 0.f)), mv = __builtin_bit_cast(int, abs_max8(raw[1][0], raw[1][1], 0.f));
-      int ek, ev, lk, lv;
-      row_exps<D / 8>(mk, ek, lk);
-      row_exps<D / 8>(mv, ev, lv);
-      const bool bad = max(ek, ev) == 128 || max(ek - lk, ev - lv) > kSpread;
-      const int at = C::OWN == 4 ? 4 * (wave & 1) + (wave >> 1) : 4 * (lane & 1) + wave;
-      if (__builtin_expect(bad, 0)) {
-        int rows = 0;
-        unsigned top_k = 0, top_v = 0;
-#pragma unroll
-        for (int r = 0; r < C::OWN; ++r) {
-          const unsigned xk = __builtin_amdgcn_readlane(mk, D / 8 * r + D / 8 - 1), xv = __builtin_amdgcn_readlane(mv, D / 8 * r + D / 8 - 1);
-          const int rk = static_cast<int>(xk >> 23) - 127, rv = static_cast<int>(xv >> 23) - 127;
-          if (rk == 128 || rv == 128 || rk - lk > kSpread || rv - lv > kSpread) { rows |= 1 << r; continue; }
-          top_k = max(top_k, xk);
-          top_v = max(top_v, xv);
-        }
-        ek = max(static_cast<int>(top_k >> 23) - 127, kLeastExp);
-        ev = max(static_cast<int>(top_v >> 23) - 127, kLeastExp);
-        if (rows >> (lane / (D / 8)) & 1) {
-#pragma unroll
-          for (int kv = 0; kv < 2; ++kv) raw[kv][0] = raw[kv][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-        if (lane < 2) s_vt[stage][at] = pow2(ev);
-        if (lane == 0) s_bad[stage][wave] = rows << (C::OWN * wave);
-      }
-      conv_s[0] = pow2(14 - ek);
-      conv_s[1] = pow2(14 - ev);
-      if (lane < 2) {                         // (four rows: one entry)
-        s_kx[stage][at] = pow2(ek - 14);
-        s_vx[stage][at] = bad ? __builtin_inff() : pow2(ev);
-      }
+      for (int e = 0; e < 2; ++e) raw[e] = *reinterpret_cast<const f32x4*>(smem + raw_adr + kv * C::OWN * C::RB + e * (C::RB / 2));
     };
     auto conv_write = [&](int stage, int kv) __attribute__((always_inline)) {
-      unsigned char* st = smem + stage * C::STAGE_BYTES;
-      u32x4 hi, lo;
-      split8(raw[kv][0], raw[kv][1], conv_s[kv], conv_s[kv], hi, lo);
-      *reinterpret_cast<u32x4*>(st + conv_adr[kv]) = hi;
-      *reinterpret_cast<u32x4*>(st + (conv_adr[kv] ^ 16)) = lo;
+      const unsigned long long huge = __builtin_amdgcn_ballot_w64(__builtin_bit_cast(int, abs_max8(raw[0], raw[1], 0.f)) >= kHuge);
+      if (kv == 0) huge_rows = 0;
+      if (__builtin_expect(huge != 0, 0)) {
+        unsigned lo = static_cast<unsigned>(huge), hi = static_cast<unsigned>(huge >> 32);
+        asm("" : "+s"(lo), "+s"(hi));          // (as one 64-bit number the compiler compares it with constants from memory)
+        int rows = 0;
+#pragma unroll
+        for (int r = 0; r < C::OWN; ++r) {
+          const unsigned half = C::UNITS * r < 32 ? lo : hi;
+          rows |= (half >> (C::UNITS * r % 32) & ((1u << C::UNITS) - 1)) != 0 ? 1 << r : 0;
+        }
+        if (kv == 1 && (rows >> (lane_id() / C::UNITS) & 1)) raw[0] = raw[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        huge_rows |= rows;
+      }
+      if (kv == 1) {
+        raw[0] *= kVScale;
+        raw[1] *= kVScale;
+        if (lane == 0) s_bad[stage][wave] = huge_rows << (C::OWN * wave);
+      }
+#pragma unroll
+      for (int i = 0; i < 3; ++i) *reinterpret_cast<u32x4*>(smem + stage * C::STAGE_BYTES + conv_adr[kv] + i * C::PLANE_BYTES) = next_piece(raw[0], raw[1]);
     };
-    auto convert = [&](int stage) __attribute__((always_inline)) {
-      conv_read(stage, 0);
-      conv_read(stage, 1);
-      conv_scale(stage);
-      conv_write(stage, 0);
-      conv_write(stage, 1);
+    // ... of tile t, all of it, and then the fetch of the next into the place that it leaves.  (What has been written was read.)
+    auto convert = [&](int t) __attribute__((always_inline)) {
+      conv_read(0);
+      conv_write(t & 1, 0);
+      conv_read(1);
+      conv_write(t & 1, 1);
+      if (t + 1 < n_tiles) fetch(t + 1, 0);
     };
     if constexpr (!SERIAL) split_q();          // (here its loads have landed)
-    // o holds the sums of P V times 2^(kProbExp + 14 - o_exp); o_exp follows the V of the tiles: up with every larger one, down
-    // where one is 2^4 smaller, but not more than 2^64 below the largest so far (o may not overflow)
-    int o_exp = kLeastExp, o_top = kLeastExp;
     // d = 64 has the registers for a second set of sums, which takes what 16 tiles have added to the first.  Relative error of
     // the output, no mask, 32 768 tokens: 5.9e-7 with one set, 5.3e-7 with two
     constexpr int FLUSH = 16, NSUM = D == 64 ? NDB : 0;
     f32x16 o_sum[NSUM > 0 ? NSUM : 1];
 #pragma unroll
     for (int db = 0; db < NSUM; ++db) o_sum[db] = zero16();
-    auto scale_sums = [&](float x) __attribute__((always_inline)) {
-#pragma unroll
-      for (int db = 0; db < NDB; ++db) o[db] *= x;
-#pragma unroll
-      for (int db = 0; db < NSUM; ++db) o_sum[db] *= x;
-    };
 
     if (n_tiles > 0) {
       if (!linear) {
@@ -546,187 +488,151 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
         __syncthreads();
       }
       fetch(0, 0);
-      if (n_tiles > 1) {
-        fetch(1, 1);
-        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(LOADS) : "memory");
-      } else {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       convert(0);
     }
-    int stage = 0;
-    for (int t = 0; t < n_tiles; ++t, stage = stage == 2 ? 0 : stage + 1) {
-      __syncthreads();               // tile t is converted; nobody reads tile t - 1 any more
-      const int next = stage == 2 ? 0 : stage + 1;
-      if (t + 2 < n_tiles) {
-        fetch(t + 2, next == 2 ? 0 : next + 1);
-        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(LOADS) : "memory");     // what this wavefront converts of tile t + 1
-      } else {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      }
+    for (int t = 0; t < n_tiles; ++t) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wavefront's rows of tile t + 1
+      __syncthreads();               // tile t is split; nobody reads tile t - 1 any more
+      const int stage = t & 1, next = stage ^ 1;
       // three tiles before a chunk of keys begins: the half of the table it goes to has been left behind
       if (!linear && (t + 3) % (CHUNK / BT) == 0 && t + 3 < n_tiles) locate((t + 3) / (CHUNK / BT));
       const unsigned char* st = smem + stage * C::STAGE_BYTES;
-      const f32x4 kx = *reinterpret_cast<const f32x4*>(&s_kx[stage][4 * h]);
-      f32x4 vx = *reinterpret_cast<const f32x4*>(&s_vx[stage][4 * h]);
-      auto top_exp = [&](const float* x) __attribute__((always_inline)) {
-        const f32x4 a = *reinterpret_cast<const f32x4*>(x), b = *reinterpret_cast<const f32x4*>(x + 4);
-        const float top = fmaxf(fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])), fmaxf(fmaxf(b[0], b[1]), fmaxf(b[2], b[3])));
-        return (__builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, top)) >> 23) - 127;
-      };
-      int e_top = top_exp(&s_vx[stage][0]), bad = 0;
-      if (__builtin_expect(e_top == 128, 0)) {
-        e_top = kLeastExp;
-        for (int w = 0; w < 8; ++w) {
-          const float x = s_vx[stage][w] == __builtin_inff() ? s_vt[stage][w] : s_vx[stage][w];
-          e_top = max(e_top, (__builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)) >> 23) - 127);
-        }
+      int bad = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (vx[i] == __builtin_inff()) {
-            vx[i] = s_vt[stage][4 * h + i];
-            bad |= s_bad[stage][C::OWN == 4 ? 2 * i + h : i];
-          }
-        mark_odd(t);
+      for (int i = 0; i < NW / 4; ++i) {
+        const i32x4 b = *reinterpret_cast<const i32x4*>(&s_bad[stage][4 * i]);
+        bad |= b[0] | b[1] | b[2] | b[3];
       }
-      const bool masked = is_masked(t, stage);   // by element
+      bad = __builtin_amdgcn_readfirstlane(bad);
+      if (__builtin_expect(bad != 0, 0)) mark_odd(t);
+      const bool masked = is_masked(t);          // by element
       bool leave = idle;
       if (masked && !idle) {                     // a NaN in V
-        f16x2 z = {0, 0};
+        unsigned top = 0;
 #pragma unroll 2
         for (int i = 0; i < D / 16; ++i) {
-          const f16x8 x = *reinterpret_cast<const f16x8*>(st + C::TILE_BYTES + lq * C::RB + 32 * (i + h * (D / 16)) + 16 * C::pair_y(true, lq, i + h * (D / 16)));
+          const u32x4 x = *reinterpret_cast<const u32x4*>(st + C::TILE_BYTES + lq * C::LB + (i + h * (D / 16)) * 16);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) z = f16x2{x[2 * e], x[2 * e + 1]} * f16x2{0, 0} + z;
+          for (int e = 0; e < 4; ++e) top = max(top, max(x[e] << 16 & 0x7fffffffu, x[e] & 0x7fffffffu));
         }
-        if (__builtin_amdgcn_ballot_w64(!(z[0] == 0 && z[1] == 0)) != 0) {
+        if (__builtin_amdgcn_ballot_w64(top >= 0x7f810000u) != 0) {
           mark_odd(t);
           leave = true;
         }
       }
       if (leave) {
-        convert(next);
+        convert(t + 1);
         continue;
       }
-      // ---- scores; the floats of tile t + 1 are read and their exponents found beside them
+      // ---- scores; tile t + 1 is split beside them
       f32x16 S = zero16();
       // (formed where they are used: held across the loop the fragment addresses are registers too many; the stage is a multiple
       // of what the swizzle moves)
       int ka = k_adr + stage * C::STAGE_BYTES, va = v_adr[0] + stage * C::STAGE_BYTES;
       asm volatile("" : "+v"(ka), "+v"(va));
-      constexpr int PK = 2;
-      u32x4 k_hi[PK], k_lo[PK];
-      auto read_k = [&](auto jj) __attribute__((always_inline)) {
-        constexpr int J = decltype(jj)::value;
-        // pair 2 J + h: bit 3 of it (d = 128, J >= 4) stands as it is, 256 bytes on, and swaps the units of the pair
-        constexpr int lo = 64 * (J % 4) ^ (D == 128 && J >= 4 ? 0 : 16), hi = lo ^ 16, on = J / 4 * 256;
-        k_lo[J % PK] = *reinterpret_cast<const u32x4*>(smem + (ka ^ lo) + on);
-        k_hi[J % PK] = *reinterpret_cast<const u32x4*>(smem + (ka ^ hi) + on);
+      // A fragment's place takes that of the next step as soon as its last product is under way.  The products of the first pieces
+      // and the others, 2^-8 of them, are summed for themselves: fewer roundings of the large sum.
+      u32x4 kf[3];
+      auto read_k = [&](auto jj, auto ii) __attribute__((always_inline)) {
+        constexpr int J = decltype(jj)::value, I = decltype(ii)::value;
+        if constexpr (J < NJ) kf[I] = *reinterpret_cast<const u32x4*>(smem + (ka ^ (32 * J)) + I * C::PLANE_BYTES);
       };
-      static_for<PK>(read_k);
+      static_for<3>([&](auto i) __attribute__((always_inline)) { read_k(std::integral_constant<int, 0>{}, i); });
       __builtin_amdgcn_sched_barrier(0);
-      static_for<KS>([&](auto jj) __attribute__((always_inline)) {
+      f32x16 S_lo = zero16();
+      __builtin_amdgcn_s_setprio(1);             // the matrix pipe before the other wavefront's vector work: 2 to 4 % (40 960 tokens, 8 heads of 128, 4.42 -> 4.25 ms)
+      static_for<NJ>([&](auto jj) __attribute__((always_inline)) {
         constexpr int J = decltype(jj)::value;
-        S = mfma_f16(k_lo[J % PK], qf[2 * J], S);
-        if constexpr (J == 0) { conv_read(next, 0); conv_read(next, 1); }
-        S = mfma_f16(k_hi[J % PK], qf[2 * J + 1], S);
-        S = mfma_f16(k_hi[J % PK], qf[2 * J], S);
-        if constexpr (J + PK < KS) read_k(std::integral_constant<int, J + PK>{});
-        if constexpr (J == 1) conv_scale(next);
-        if constexpr (J >= KS - 2) conv_write(next, J - (KS - 2));
+        constexpr std::integral_constant<int, J + 1> on{};
+        S_lo = mfma_bf16(kf[2], qp[0][J], S_lo);
+        read_k(on, std::integral_constant<int, 2>{});
+        S_lo = mfma_bf16(kf[0], qp[2][J], S_lo);
+        S_lo = mfma_bf16(kf[0], qp[1][J], S_lo);
+        S = mfma_bf16(kf[0], qp[0][J], S);
+        read_k(on, std::integral_constant<int, 0>{});
+        S_lo = mfma_bf16(kf[1], qp[1][J], S_lo);
+        S_lo = mfma_bf16(kf[1], qp[0][J], S_lo);
+        read_k(on, std::integral_constant<int, 1>{});
+        if constexpr (J == 0) conv_read(0);
+        if constexpr (J == 1) { conv_write(next, 0); conv_read(1); }
+        if constexpr (J == 2) conv_write(next, 1);
+        if constexpr (J == 3) { if (t + 2 < n_tiles) fetch(t + 2, 0); }
         __builtin_amdgcn_sched_barrier(0);
       });
+      __builtin_amdgcn_s_setprio(0);
+      S += S_lo;
       // ---- V^T fragments: a block of O^T after the other, for each 16-key group
-      constexpr int NV = 2 * NDB, PV = 2;
-      u32x4 v_hi[PV], v_lo[PV];
-      auto read_v = [&](auto ff) __attribute__((always_inline)) {
-        constexpr int F = decltype(ff)::value;
-        constexpr int db = F / 2, rows = F % 2 * 16 * C::RB;
-        constexpr int xh = 128 * (db % 2) ^ (db >= 2 ? 16 : 0), xl = xh ^ 16, on = db / 2 * 256 + rows;
-        v_hi[F % PV] = __builtin_bit_cast(u32x4, lds_tr8(smem + (va ^ xh) + on, smem + (va ^ xh) + on + 8 * C::RB));
-        v_lo[F % PV] = __builtin_bit_cast(u32x4, lds_tr8(smem + (va ^ xl) + on, smem + (va ^ xl) + on + 8 * C::RB));
+      constexpr int NV = 2 * NDB;
+      u32x4 vf[3];
+      auto read_v = [&](auto ff, auto ii) __attribute__((always_inline)) {
+        constexpr int F = decltype(ff)::value, I = decltype(ii)::value;
+        if constexpr (F < NV) {
+          const unsigned char* at = smem + (va ^ (64 * (F / 2))) + F % 2 * 16 * C::LB + I * C::PLANE_BYTES;
+          vf[I] = __builtin_bit_cast(u32x4, lds_tr8(at, at + 8 * C::LB));
+        }
       };
-      static_for<PV>(read_v);
+      static_for<3>([&](auto i) __attribute__((always_inline)) { read_v(std::integral_constant<int, 0>{}, i); });
       if (masked) mask_block(t, 0, S);
-      if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad != 0) != 0, 0)) {
+      if (__builtin_expect(bad != 0, 0)) {
         const int mine = bad >> 4 * h;
 #pragma unroll
         for (int i = 0; i < 16; ++i)
           if (mine >> (8 * (i / 4) + i % 4) & 1) S[i] = -__builtin_inff();
       }
-      float f[4], mx = -__builtin_inff();
+      float mx = S[0];
 #pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        f[i4] = __builtin_amdgcn_fmed3f(cq * kx[i4], 1.17549435e-38f, 3.402823466e38f);     // (0 and infinite times the mask's -inf and 0 are NaN)
-        mx = fmaxf(mx, fmaxf(fmaxf(S[4 * i4], S[4 * i4 + 1]), fmaxf(S[4 * i4 + 2], S[4 * i4 + 3])) * f[i4]);
-      }
-      int new_exp = o_exp;
-      o_top = max(o_top, e_top);
-      if (e_top > o_exp) new_exp = e_top;
-      else if (e_top < o_exp - 4 && e_top > kLeastExp) new_exp = max(e_top, o_top - 64);
-      if (__builtin_amdgcn_ballot_w64(mx > m_run + kRescaleGapF32) != 0 || new_exp != o_exp) {
-        const float m_new = fmaxf(m_run, fmaxf(mx, __shfl_xor(mx, 32)));         // both halves of a row agree
-        float alpha = fast_exp2(m_run - m_new);
+      for (int i = 1; i < 16; ++i) mx = fmaxf(mx, S[i]);
+      if (__builtin_amdgcn_ballot_w64(mx * c > m_run + kRescaleGapF32) != 0) {
+        const float m_new = fmaxf(m_run, fmaxf(mx, __shfl_xor(mx, 32)) * c);     // both halves of a row agree
+        const float alpha = fast_exp2(m_run - m_new);
         m_run = m_new;
         l_run *= alpha; l_lo *= alpha;
-        alpha *= pow2(max(o_exp - new_exp, -126));
-        o_exp = new_exp;
-        scale_sums(alpha);
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) o[db] *= alpha;
+#pragma unroll
+        for (int db = 0; db < NSUM; ++db) o_sum[db] *= alpha;
       }
-      // ---- probabilities, and their products with the pieces of V; pieces more than 2^6 below the largest, whose
-      // probabilities would be left too few bits, in further passes
+      // ---- probabilities, those of the second 16 keys beside the first products with V
       float sum[4] = {0.f, 0.f, 0.f, 0.f};
+      u32x4 pf[2][3];
+      auto probs = [&](auto g2) __attribute__((always_inline)) {
+        constexpr int GG = decltype(g2)::value;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        S[i] = fast_exp2(__builtin_fmaf(S[i], f[i / 4], -m_run));
-        sum[i & 3] += S[i];
-      }
-      float lim = pow2(max(o_exp - 6, -126)), above = __builtin_inff();
-      bool more;
-      do {
-        more = __builtin_amdgcn_ballot_w64(fminf(fminf(vx[0], vx[1]), fminf(vx[2], vx[3])) < lim) != 0;
-        const float p_scale = pow2(kProbExp - o_exp);
-        float ps[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) ps[i] = vx[i] * p_scale;
-        if (__builtin_expect(more || above < __builtin_inff(), 0)) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) ps[i] = vx[i] >= lim && vx[i] < above ? ps[i] : 0.f;
+        for (int i = 8 * GG; i < 8 * GG + 8; ++i) {
+          S[i] = fast_exp2(__builtin_fmaf(S[i], c, -m_run));
+          sum[i & 3] += S[i];
         }
-        u32x4 p_hi[2], p_lo[2];
+        f32x4 a = {S[8 * GG], S[8 * GG + 1], S[8 * GG + 2], S[8 * GG + 3]}, b = {S[8 * GG + 4], S[8 * GG + 5], S[8 * GG + 6], S[8 * GG + 7]};
 #pragma unroll
-        for (int gg = 0; gg < 2; ++gg)
-          split8(f32x4{S[8 * gg], S[8 * gg + 1], S[8 * gg + 2], S[8 * gg + 3]}, f32x4{S[8 * gg + 4], S[8 * gg + 5], S[8 * gg + 6], S[8 * gg + 7]},
-                 ps[2 * gg], ps[2 * gg + 1], p_hi[gg], p_lo[gg]);
+        for (int i = 0; i < 3; ++i) pf[GG][i] = next_piece(a, b);
+      };
+      probs(std::integral_constant<int, 0>{});
+      __builtin_amdgcn_sched_barrier(0);
+      // A tile's products are summed for themselves and then added to o, so that the error of the chain of additions grows
+      // with the tiles, not with the products.
+      f32x16 acc;
+      __builtin_amdgcn_s_setprio(1);
+      static_for<NV>([&](auto ff) __attribute__((always_inline)) {
+        constexpr int F = decltype(ff)::value, gg = F % 2, db = F / 2;
+        constexpr std::integral_constant<int, F + 1> on{};
+        acc = mfma_bf16(vf[2], pf[gg][0], gg == 0 ? zero16() : acc);
+        read_v(on, std::integral_constant<int, 2>{});
+        acc = mfma_bf16(vf[0], pf[gg][2], acc);
+        acc = mfma_bf16(vf[0], pf[gg][1], acc);
+        acc = mfma_bf16(vf[0], pf[gg][0], acc);
+        read_v(on, std::integral_constant<int, 0>{});
+        acc = mfma_bf16(vf[1], pf[gg][1], acc);
+        acc = mfma_bf16(vf[1], pf[gg][0], acc);
+        read_v(on, std::integral_constant<int, 1>{});
+        if constexpr (F == 0) probs(std::integral_constant<int, 1>{});
+        if constexpr (gg == 1) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) o[db][i] = __builtin_fmaf(acc[i], 1.f / kVScale, o[db][i]);
+        }
         __builtin_amdgcn_sched_barrier(0);
-        // A tile's products are summed for themselves and then added to o, so that the error of the chain of additions grows
-        // with the tiles, not with the products.
-        f32x16 acc;
-        static_for<NV>([&](auto ff) __attribute__((always_inline)) {
-          constexpr int F = decltype(ff)::value, gg = F % 2, db = F / 2;
-          acc = mfma_f16(v_lo[F % PV], p_hi[gg], gg == 0 ? zero16() : acc);
-          acc = mfma_f16(v_hi[F % PV], p_lo[gg], acc);
-          acc = mfma_f16(v_hi[F % PV], p_hi[gg], acc);
-          if constexpr (F + PV < NV) read_v(std::integral_constant<int, F + PV>{});
-          if constexpr (gg == 1) o[db] += acc;
-          __builtin_amdgcn_sched_barrier(0);
-        });
-        if (__builtin_expect(more, 0)) {
-          above = lim;
-          float top = 0.f;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) top = fmaxf(top, vx[i] < above ? vx[i] : 0.f);
-          top = fmaxf(top, __shfl_xor(top, 32));
-          const int e = (__builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, top)) >> 23) - 127;
-          if (e <= kLeastExp) break;                       // what is left is zero
-          new_exp = max(e, o_top - 64);
-          const float up = pow2(min(o_exp - new_exp, 127));
-          lim = new_exp > e ? 0.f : pow2(max(e - 6, -126));
-          o_exp = new_exp;
-          scale_sums(up);
-          static_for<PV>(read_v);
-        }
-      } while (more);
+      });
+      __builtin_amdgcn_s_setprio(0);
       l_lo += (sum[0] + sum[1]) + (sum[2] + sum[3]);
       if ((t & 63) == 63) { l_run += l_lo; l_lo = 0.f; }
       if (NSUM > 0 && t % FLUSH == FLUSH - 1) {
@@ -736,10 +642,7 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
     }
 #pragma unroll
     for (int db = 0; db < NSUM; ++db) o[db] += o_sum[db];
-#pragma unroll
-    for (int db = 0; db < NDB; ++db) o[db] *= pow2(o_exp - kProbExp - 14);
-    // ---- what was left to the end, key by key.  As slow as it is rare: 16 heads of 128, 2 048 of 16 384 tokens, 583 us with
-    // one infinite key (559 with none, in the same run), 3.1 ms with every 64th V row 2^20 times as large as the others.
+    // ---- what was left to the end, key by key: as slow as it is rare.
     int late = lane;                 // (addresses formed anew, not kept across the loop)
     asm volatile("" : "+v"(late));
     const f32x4* const qr = reinterpret_cast<const f32x4*>(static_cast<const float*>(p.q) + bi * p.q_bstride + row_of(late & 31).idx * D) + (late >> 5);
@@ -764,18 +667,19 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
 #pragma unroll
         for (int db = 0; db < NDB; ++db) o[db][i] = __builtin_fmaf(pk, vk[32 * db + 8 * (i / 4) + 4 * h + i % 4], o[db][i] * alpha);
     };
-    const bool any_q_inf = !idle && __builtin_amdgcn_ballot_w64(q_inf) != 0;
-    if (any_q_inf && q_inf) {                    // from the start again
+    const bool any_q_odd = !idle && q_odd_rows != 0, q_odd = any_q_odd && (q_odd_rows >> late & 1) != 0;
+    if (any_q_odd && q_odd) {                    // from the start again
       m_run = kNegBig;
       l_run = l_lo = 0.f;
 #pragma unroll
       for (int db = 0; db < NDB; ++db) o[db] = zero16();
     }
-    if (odd || any_q_inf) {
+    if (odd || any_q_odd) {
 #pragma unroll 1
       for (int t = 0; t < n_tiles; ++t) {
-        // rows of Q with an infinity are settled (NaN) with the first score that is infinite and positive
-        const bool redo = any_q_inf && __builtin_amdgcn_ballot_w64(q_inf && l_run + l_lo == l_run + l_lo) != 0;
+        // rows of Q with an infinity are settled (NaN) with the first score that is infinite and positive, those with a finite value of
+        // 2^104 or more take every key
+        const bool redo = any_q_odd && __builtin_amdgcn_ballot_w64(q_odd && l_run + l_lo == l_run + l_lo) != 0;
         const bool look = s_odd[t / run] != 0;
         if (!redo && !look) continue;
         const int v = t * BT + lq, tok = linear ? (v < n_keys ? goff + v : INT_MAX) : find(v);
@@ -791,17 +695,8 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
             mv = abs_max3(mv, vr[e], vr[e]);
             z = __builtin_fmaf(vr[e], 0.f, z);
           }
-          // as in conv_scale: exponents of the row, and of the smallest of its piece
-          auto far = [&](float m) __attribute__((always_inline)) {
-            const unsigned x = __builtin_bit_cast(int, fmaxf(m, __shfl_xor(m, 32)));
-            unsigned least = x - 1;
-#pragma unroll
-            for (int o = 1; o < C::OWN; o <<= 1) least = min(least, static_cast<unsigned>(__shfl_xor(static_cast<int>(least), o)));
-            const int e = static_cast<int>(x >> 23) - 127;
-            return e == 128 || e - max(min(static_cast<int>(least >> 23) - 127, 127), kLeastExp) > kSpread;
-          };
-          const bool far_k = far(mk), far_v = far(mv);
-          const unsigned bad = static_cast<unsigned>(__builtin_amdgcn_ballot_w64(far_k || far_v));      // (both halves have the same)
+          auto huge = [&](float m) __attribute__((always_inline)) { return __builtin_bit_cast(int, fmaxf(m, __shfl_xor(m, 32))) >= kHuge; };    // as in conv_check
+          const unsigned bad = static_cast<unsigned>(__builtin_amdgcn_ballot_w64(huge(fmaxf(mk, mv))));      // (both halves have the same)
           const unsigned long long nan = __builtin_amdgcn_ballot_w64(!(z == 0.f) && !(bad >> lq & 1));
           const bool masked = __builtin_amdgcn_ballot_w64(tok > q_first) != 0;
           left = masked && nan != 0 ? ~0u : bad;
@@ -811,7 +706,7 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
           const int key = __builtin_amdgcn_readlane(tok, k);
           if (key == INT_MAX) break;               // past the end, as all that follow
           const bool mine = left >> k & 1;
-          if (mine || redo) add_key(key, q_inf || mine);
+          if (mine || redo) add_key(key, q_odd || mine);
         }
       }
     }
@@ -863,7 +758,7 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
       vring[F % PV] = lds_tr8(va, va + 8 * C::RB);
     };
     static_for<PV>(read_v);               // on their way during the maxima
-    if (is_masked(t, stage)) {       // by element
+    if (is_masked(t)) {              // by element
 #pragma unroll
       for (int kb = 0; kb < NKB; ++kb) mask_block(t, kb, S[kb]);
     }
@@ -936,10 +831,10 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
     return 32 * (Q / 4) + 8 * (Q % 4) + 4 * h;
   };
   if (SERIAL && ns > 1) {
-    float r, w, mx_all = round > 0 ? s_all[0][thread] : -__builtin_inff(), den_all = round > 0 ? s_all[1][thread] : 0.f;
+    float r, w, mx_all = round > 0 ? s_all[0][tid] : -__builtin_inff(), den_all = round > 0 ? s_all[1][tid] : 0.f;
     fold(lse_new, mx_all, den_all, r, w);
-    s_all[0][thread] = mx_all;
-    s_all[1][thread] = den_all;
+    s_all[0][tid] = mx_all;
+    s_all[1][tid] = den_all;
     const bool last = round == ns - 1;
     const float inv = den_all > 0.f ? 1.f / den_all : 0.f;
     float* od = static_cast<float*>(p.out_final) + ooff;

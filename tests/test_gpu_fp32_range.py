@@ -1,0 +1,131 @@
+"""fp32 forward on inputs of a wide range: between the columns of Q, K and V, between rows next to each other and between runs of
+rows.  Every product of two floats has the accuracy of fp32 whatever stands beside it, so the bounds are those of fp32 sums:
+2e-6 for every single column of the output (about 4 times what these sizes show), 1e-5 for the log-sum-exp."""
+import math
+
+import pytest
+import torch
+
+from paper_2509_26541_amd import workloads as wl
+from tests.test_gpu_fp32_halves import inputs, positions, reference
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tb():
+    assert torch.cuda.is_available(), "GPU tests need an MI355X"
+    from paper_2509_26541_amd import binding
+    return binding
+
+
+N, RANK, S, H = 4, 1, 8 * 300, 2
+SHAPES = [(64, wl.FULL), (64, wl.ZIGZAG_CAUSAL), (128, wl.FULL), (128, wl.ZIGZAG_CAUSAL)]
+IDS = ["%d-%s" % (d, "full" if m == wl.FULL else "zigzag") for d, m in SHAPES]
+
+
+def check(tb, q, k, v, mask, what, floor=0.0):
+    """Relative error of every output column and of the lse; `floor`: absolute error of an element that is let pass."""
+    out, lse = tb.tasp_chunk_attn(q, k, v, tb.tasp_schedule(N, RANK), mask, fuse_merge=True)
+    ref_o, ref_l = reference(q, k, v, positions(N, RANK, S, mask))
+    err, size = (out.double() - ref_o).norm(dim=0), ref_o.norm(dim=0)
+    worst = float(((err - floor * len(out) ** 0.5).clamp(min=0) / size).max())
+    assert worst <= 2e-6 and float((lse.double() - ref_l).abs().max()) <= 1e-5, (what, worst, float((lse.double() - ref_l).abs().max()))
+
+
+@pytest.mark.parametrize("d,mask", SHAPES, ids=IDS)
+def test_a_large_column_of_v(tb, d, mask):
+    for b in (20, 24, 30, 41, 100, -30, -100):
+        q, k, v = inputs(N, S, H, H, d, 21)
+        v[:, :, 5] *= 2.0 ** b
+        check(tb, q, k, v, mask, b)
+
+
+@pytest.mark.parametrize("d,mask", SHAPES, ids=IDS)
+def test_columns_of_q_against_k(tb, d, mask):
+    for r in (20, 30, 40, 60, -40, -60):
+        q, k, v = inputs(N, S, H, H, d, 22)
+        q[:, :, 3] *= 2.0 ** r
+        k[:, :, 3] *= 2.0 ** -r
+        check(tb, q, k, v, mask, r)
+
+
+@pytest.mark.parametrize("d,mask", SHAPES, ids=IDS)
+def test_large_rows_of_v_with_small_weight(tb, d, mask):
+    """Every other run of 64 keys 2^r larger, its weights 2^-(r + 10)."""
+    run = (torch.arange(S, device="cuda") // 64) % 2 == 1
+    for r in (20, 24, 30, 60):
+        q, k, v = inputs(N, S, H, H, d, 23)
+        q[:, :, 0] = 1.0
+        k[run, :, 0] = -(r + 10) * math.log(2.0) * d ** 0.5
+        v[run] *= 2.0 ** r
+        check(tb, q, k, v, mask, r)
+
+
+@pytest.mark.parametrize("d,mask", SHAPES, ids=IDS)
+def test_huge_rows_of_v_without_weight(tb, d, mask):
+    for b in (90, 104, 120):
+        q, k, v = inputs(N, S, H, H, d, 24)
+        q[:, :, 0] = q[:, :, 0].abs() + 1.0
+        k[32:64, :, 0] = -3000.0
+        v[32:64] *= 2.0 ** b
+        check(tb, q, k, v, mask, b)
+
+
+@pytest.mark.parametrize("d,mask", SHAPES, ids=IDS)
+def test_tiny_values(tb, d, mask):
+    """V down to the smallest normal floats; what is below 2^-126 in the output has its spacing of 2^-149.  K and Q that small give
+    scores of zero."""
+    for b in (-98, -100, -110, -120, -124):
+        q, k, v = inputs(N, S, H, H, d, 25)
+        check(tb, q, k, v * 2.0 ** b, mask, ("v", b), floor=2.0 ** -149)
+    v[:, :, 7] *= 2.0 ** -124
+    check(tb, q, k, v, mask, "a column of v", floor=2.0 ** -149)
+    q, k, v = inputs(N, S, H, H, d, 25)
+    v = v.abs()                              # (the mean of them all: of both signs it would be small against the rounding of the sums)
+    check(tb, q, k * 2.0 ** -110, v, mask, "k")
+    check(tb, q * 2.0 ** -118, k, v, mask, "q")
+
+
+@pytest.mark.parametrize("d,mask", SHAPES, ids=IDS)
+def test_rows_of_different_size_side_by_side(tb, d, mask):
+    """One row in four nearly zero; one in 64 very large."""
+    at = torch.arange(S, device="cuda")
+    q, k, v = inputs(N, S, H, H, d, 26)
+    k[at % 4 == 1] *= 1e-9
+    v[at % 4 == 1] *= 1e-9
+    check(tb, q, k, v, mask, "one in four nearly zero")
+    q, k, v = inputs(N, S, H, H, d, 27)
+    v[at % 64 == 5] *= 2.0 ** 20
+    check(tb, q, k, v, mask, "one in 64 very large")
+
+
+@pytest.mark.parametrize("heads", [(4, 4, 64), (16, 4, 128)], ids=["4x64", "16/4x128"])
+def test_the_range_costs_no_time(tb, heads):
+    """Rows nearly zero or very large, and columns that are: no slower than without (a quarter is for the noise of single calls)."""
+    hq, hkv, d = heads
+    s = tb.tasp_schedule(8, 2)
+    q, k, v = inputs(8, 8192, hq, hkv, d, 28)
+    at = torch.arange(8192, device="cuda")
+
+    def best_ms(k, v):
+        plan = tb.ChunkAttnPlan(s, q, k, v, wl.ZIGZAG_CAUSAL)
+        times = []
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            plan.run()
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    clean = best_ms(k, v)
+    tiny, large, column = v.clone(), v.clone(), v.clone()
+    tiny[at % 4 == 1] *= 1e-9
+    large[at % 64 == 5] *= 2.0 ** 20
+    column[:, :, 5] *= 2.0 ** 40
+    for name, x in (("tiny", tiny), ("large", large), ("column", column)):
+        got = best_ms(k, x)
+        print(name, clean, got, flush=True)
+        assert got <= 1.25 * clean + 0.005, (name, clean, got)
