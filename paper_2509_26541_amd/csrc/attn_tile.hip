@@ -25,8 +25,8 @@
 // first tiles.  Measured, whole calls:
 //   fp32, 16 heads of 128, 2 048 of 16 384 tokens, causal: 0.67 ms (206 TFLOP/s of products of floats; the floor of six
 //     products 0.44) against 1.13 ms with fp32 matrix instructions (0.90); two 16-bit floats to a value took 0.48 but hold a
-//     narrow range only.  Error of the output against 64 bits: 3.0e-7 (fp32 instructions 5.2e-7, 16-bit floats 3.7e-7);
-//     no mask, 4 heads of 64, 3 072 of 24 576 tokens: 4.7e-7 (5.7e-7, 4.9e-7);
+//     narrow range only.  Error of the output against 64 bits: 2.9e-7 (fp32 instructions 5.2e-7, 16-bit floats 3.7e-7);
+//     no mask, 4 heads of 64, 3 072 of 24 576 tokens: 4.1e-7 (5.7e-7, 4.9e-7);
 //   fp32, 4 heads of 64, 256 of 1 024 tokens: 16 us;
 //   bf16, 8 heads of 128, 512 of 4 096 tokens: 23 us against 117 with the large kernel on 16 CUs;
 //   bf16, 128 sequences of 3 072 tokens, 20 heads of 64: 0.70 ms (0.72 with the sub-chunks in their order of arrival,
@@ -443,6 +443,9 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
 #pragma unroll
       for (int e = 0; e < 2; ++e) raw[e] = *reinterpret_cast<const f32x4*>(smem + raw_adr + kv * C::OWN * C::RB + e * (C::RB / 2));
     };
+    // The matrix pipe cuts the sum of an instruction off downwards.  Over many tiles that would add up (131 072 keys: the mean of all errors 5e-7 of
+    // the output, of an error of 8e-7); so V is taken with the other sign in every other tile, and the tile's sums are subtracted.
+    auto v_scale = [](int stage) { return stage == 0 ? kVScale : -kVScale; };
     auto conv_write = [&](int stage, int kv) __attribute__((always_inline)) {
       const unsigned long long huge = __builtin_amdgcn_ballot_w64(__builtin_bit_cast(int, abs_max8(raw[0], raw[1], 0.f)) >= kHuge);
       if (kv == 0) huge_rows = 0;
@@ -459,8 +462,8 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
         huge_rows |= rows;
       }
       if (kv == 1) {
-        raw[0] *= kVScale;
-        raw[1] *= kVScale;
+        raw[0] *= v_scale(stage);
+        raw[1] *= v_scale(stage);
         if (lane == 0) s_bad[stage][wave] = huge_rows << (C::OWN * wave);
       }
 #pragma unroll
@@ -612,6 +615,7 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
       // A tile's products are summed for themselves and then added to o, so that the error of the chain of additions grows
       // with the tiles, not with the products.
       f32x16 acc;
+      const float v_back = 1.f / kVScale * (stage == 0 ? 1.f : -1.f);
       __builtin_amdgcn_s_setprio(1);
       static_for<NV>([&](auto ff) __attribute__((always_inline)) {
         constexpr int F = decltype(ff)::value, gg = F % 2, db = F / 2;
@@ -628,7 +632,7 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
         if constexpr (F == 0) probs(std::integral_constant<int, 1>{});
         if constexpr (gg == 1) {
 #pragma unroll
-          for (int i = 0; i < 16; ++i) o[db][i] = __builtin_fmaf(acc[i], 1.f / kVScale, o[db][i]);
+          for (int i = 0; i < 16; ++i) o[db][i] = __builtin_fmaf(acc[i], v_back, o[db][i]);
         }
         __builtin_amdgcn_sched_barrier(0);
       });
