@@ -331,7 +331,8 @@ bool tile_is_faster(const AttnLaunch& lp, int d, const int64_t* keys, const int3
 // (none do with the large kernel): the results do not depend on who brings the workspace, if it is the reported
 // one or larger.  With less the shares are dealt anew, and the kernel is chosen for them.  A call without any workspace
 // (fp32 with the merge folded in needs none) has its workgroups take the shares in turn: the same results, without
-// the gain, and nothing that calls on other streams could write over.
+// the gain, and nothing that calls on other streams could write over.  Only where the shares have more keys than one set of
+// sums takes, they are then more (kSumTiles): the results differ in rounding.
 FwdPlan plan_forward(const tasp_attn_args* a, const JoinedSteps& js, size_t need, size_t ws_bytes) {
   FwdPlan pl;
   const bool fp32 = a->dtype == TASP_DTYPE_FP32;
@@ -354,7 +355,13 @@ FwdPlan plan_forward(const tasp_attn_args* a, const JoinedSteps& js, size_t need
     pl.part_bytes = all_share_bytes(js.all, a->d, n_split);
     for (int t = 0; t < js.all.n_tasks; ++t) pl.n_split[t] = n_split[t];
     if (pl.part_bytes <= ws_bytes) return pl;
-    if (fp32 && ws_bytes == 0) { pl.serial = true; pl.part_bytes = 0; return pl; }
+    if (fp32 && ws_bytes == 0) {
+      for (int t = 0; t < js.all.n_tasks && a->d == 128; ++t)
+        pl.n_split[t] = std::max(pl.n_split[t], static_cast<int32_t>((js.keys[t] + tasp::kSumTiles * 32 - 1) / (tasp::kSumTiles * 32)));
+      pl.serial = true;
+      pl.part_bytes = 0;
+      return pl;
+    }
     room = ws_bytes;                                  // what is dealt for this much fits
     pl = FwdPlan{true, false, false, {1, 1}, 0, 0};
   }

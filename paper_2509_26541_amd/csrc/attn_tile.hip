@@ -43,11 +43,13 @@ namespace tasp {
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kLog2eLow = 1.92596298909e-8f;      // what it leaves of log2(e)
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kRescaleGap = 8.0f;      // the running max is only raised when it grew by more than 2^8
 constexpr float kRescaleGapF32 = 2.0f;   // fp32: 2^2, see kHuge
 constexpr int kHuge = (104 + 127) << 23; // fp32: bits of 2^104.  Rows with a value that large are left to the end, see the loop
 constexpr float kVScale = 65536.f;       // fp32: V is taken times 2^16
+constexpr float kLn2Low = -1.904654323e-9f;          // and of ln(2)
 constexpr float kNegBig = -1.0e30f;
 constexpr int CHUNK = 512;               // keys located at a time
 constexpr int RUNS = 512;                // fp32: entries of the table of tiles with something left to the end
@@ -151,6 +153,7 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
   // fp32: the rows of a tile that a wavefront cleared, and the runs of `run` tiles that hold keys to be added at the end.
   __shared__ __attribute__((aligned(16))) int s_bad[F32 ? C::STAGES : 1][NW];
   __shared__ int s_odd[F32 ? RUNS : 1];
+  __shared__ float s_scale[F32 && D == 128 && !SERIAL ? NTHREADS : 1];      // running maximum that the sums in memory refer to
   // One step's launch: global positions of the keys (INT_MAX: none), whether a wavefront fetched a key that some row of the
   // tile must not see, and the effective segments of the tile.
   __shared__ __attribute__((aligned(16))) int s_tok[2 * CHUNK];
@@ -410,6 +413,21 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
   const float c = p.scale * kLog2e;
 
   const bool idle = __builtin_amdgcn_readfirstlane(tile * BM + strip * 32) >= m_all;
+  // LEVELS: sums of many tiles are added up in memory, at the row's place in the call's output or in the pair of its share
+  constexpr bool LEVELS = F32 && D == 128 && !SERIAL;
+  const bool long_run = LEVELS && n_tiles > kSumTiles;
+  int sum_next = kSumTiles;
+  struct Place { float *o, *lse; bool valid; };
+  auto place_of = [&](int id) __attribute__((always_inline)) {
+    const Row to = row_of(id & 31);
+    if (ns > 1) {
+      const int64_t n_q = second ? t1.n_q : t0.n_q;
+      const int64_t rh = (static_cast<int64_t>(share) * p.batch + bi) * n_q * p.Hq + to.idx - static_cast<int64_t>(q_row0) * p.Hq;
+      return Place{(second ? p.part_o[1] : p.part_o[0]) + rh * D, (second ? p.part_lse[1] : p.part_lse[0]) + rh, to.valid};
+    }
+    float* const to_o = p.merge == 0 && p.out_final != nullptr ? static_cast<float*>(p.out_final) : p.o_dst;
+    return Place{to_o + bi * p.o_bstride + to.idx * D, p.lse_dst + bi * p.lse_bstride + to.idx, to.valid};
+  };
   if constexpr (F32) {
     // ---- fp32.  A float is the sum of three bf16 (next_piece), exactly, and a product a b of floats is formed on the bf16 matrix pipe
     // as  a3 b1 + a2 b2 + a1 b3 + a2 b1 + a1 b2 + a1 b1.  What is left out, a2 b3 + a3 b2 + a3 b3, is at most 2^-24 and
@@ -478,12 +496,57 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
       if (t + 1 < n_tiles) fetch(t + 1, 0);
     };
     if constexpr (!SERIAL) split_q();          // (here its loads have landed)
-    // d = 64 has the registers for a second set of sums, which takes what 16 tiles have added to the first.  Relative error of
-    // the output, no mask, 32 768 tokens: 5.9e-7 with one set, 5.3e-7 with two
+    // d = 64 has the registers for a second set of sums, which takes what 16 tiles have added to the first.  With d = 128 the
+    // sums of kSumTiles join those of the tiles before in memory, where the row's result goes in the end.  Error of the output, no
+    // mask, 524 288 tokens, one launch: d = 64 6.3e-7, d = 128 4.9e-7 (2.3e-6 with one set for all tiles; fp32 matrix
+    // instructions, two sets: 9.4e-7, 9.7e-7).
     constexpr int FLUSH = 16, NSUM = D == 64 ? NDB : 0;
     f32x16 o_sum[NSUM > 0 ? NSUM : 1];
 #pragma unroll
     for (int db = 0; db < NSUM; ++db) o_sum[db] = zero16();
+    // Sums in memory: those at the row's place, which refer to a maximum of their own, and o are added up there (`keep`; o starts
+    // again) or in o, to which all else then refers.  A step that is folded into a running pair meets that pair there; its
+    // weight is taken from its lse as it stands, and the new keys keep to their own maximum, so that nothing is rounded more.
+    const bool from_pair = LEVELS && long_run && p.merge != 0 && !idle;
+    auto pair_weight = [&](float lse, float ref) __attribute__((always_inline)) { return fast_exp2(__builtin_fmaf(lse, kLog2e, -ref) + lse * kLog2eLow); };
+    auto sums_in_memory = [&](bool keep) __attribute__((always_inline)) {
+      const int id = lane_id();
+      const Place to = place_of(id);
+      const bool first = sum_next == kSumTiles;            // nothing of this launch is there
+      float ref = m_run, alpha = 0.f;
+      const float lse_old = from_pair ? *to.lse : -__builtin_inff();
+      const bool old = lse_old != -__builtin_inff();
+      if (!first) {
+        const float s = s_scale[64 * wave_u + id];
+        ref = fmaxf(s, m_run);
+        alpha = fast_exp2(s - ref);
+      } else if (old) {
+        ref = fmaxf(lse_old * kLog2e, m_run);
+        alpha = pair_weight(lse_old, ref);
+      }
+      const float beta = fast_exp2(m_run - ref);
+      if (to.valid && !(q_odd_rows >> id & 1)) {
+        static_for<D / 8>([&](auto qq) __attribute__((always_inline)) {
+          constexpr int Q = decltype(qq)::value;
+          f32x4* const at = reinterpret_cast<f32x4*>(to.o + 32 * (Q / 4) + 8 * (Q % 4) + 4 * (id >> 5));
+          f32x4 x = {0.f, 0.f, 0.f, 0.f};
+          if (!first || from_pair) x = *at;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            x[e] = __builtin_fmaf(x[e], alpha, o[Q / 4][4 * (Q % 4) + e] * beta);
+            o[Q / 4][4 * (Q % 4) + e] = keep ? 0.f : x[e];
+          }
+          if (keep) *at = x;
+        });
+      }
+      if (keep) {
+        s_scale[64 * wave_u + id] = ref;
+      } else {
+        m_run = ref;
+        l_run *= beta;
+        l_lo = l_lo * beta + (old && id < 32 ? pair_weight(lse_old, ref) : 0.f);
+      }
+    };
 
     if (n_tiles > 0) {
       if (!linear) {
@@ -527,6 +590,10 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
       if (leave) {
         convert(t + 1);
         continue;
+      }
+      if (LEVELS && __builtin_expect(t >= sum_next, 0)) {
+        sums_in_memory(true);
+        sum_next = t / kSumTiles * kSumTiles + kSumTiles;
       }
       // ---- scores; tile t + 1 is split beside them
       f32x16 S = zero16();
@@ -646,6 +713,7 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
     }
 #pragma unroll
     for (int db = 0; db < NSUM; ++db) o[db] += o_sum[db];
+    if (LEVELS && !idle && (sum_next > kSumTiles || from_pair)) sums_in_memory(false);
     // ---- what was left to the end, key by key: as slow as it is rare.
     int late = lane;                 // (addresses formed anew, not kept across the loop)
     asm volatile("" : "+v"(late));
@@ -677,6 +745,20 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
       l_run = l_lo = 0.f;
 #pragma unroll
       for (int db = 0; db < NDB; ++db) o[db] = zero16();
+      if (from_pair) {                           // (sums_in_memory has left the row's pair alone)
+        const Place to = place_of(late);
+        const float lse_old = *to.lse;
+        if (lse_old != -__builtin_inff()) {
+          m_run = lse_old * kLog2e;
+          l_lo = h == 0 ? 1.f : 0.f;
+        }
+        static_for<D / 8>([&](auto qq) __attribute__((always_inline)) {
+          constexpr int Q = decltype(qq)::value;
+          const f32x4 x = *reinterpret_cast<const f32x4*>(to.o + 32 * (Q / 4) + 8 * (Q % 4) + 4 * (late >> 5));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[Q / 4][4 * (Q % 4) + e] = x[e];
+        });
+      }
     }
     if (odd || any_q_odd) {
 #pragma unroll 1
@@ -821,11 +903,17 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
   const float l_tot = l_mine + __shfl_xor(l_mine, 32), r_tot = l_tot + (r_fix + __shfl_xor(r_fix, 32));
   const bool seen = l_tot > 0.f;
   float wb = seen && r_tot > 0.f ? 1.f / r_tot : 0.f;
-  float lse_new = seen ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -__builtin_inff();
+  float lse_new = -__builtin_inff();
+  if (seen) {
+    const float l2 = __builtin_amdgcn_logf(l_tot);
+    // fp32: rounded once (running pairs that go through many steps would gather the rounding of the base-two number as well)
+    if constexpr (F32) lse_new = __builtin_fmaf(m_run, kLn2, __builtin_fmaf(l2, kLn2, m_run * kLn2Low));
+    else lse_new = (m_run + l2) * kLn2;
+  }
   int late = lane;                   // (the row's place formed anew, not kept across the loop)
   asm volatile("" : "+v"(late));
   const Row to = row_of(late & 31);
-  const bool q_valid = to.valid;
+  const bool q_valid = to.valid, folded = p.merge != 0 && !(LEVELS && long_run);      // (there the old pair is in the sums)
   const int64_t ooff = bi * p.o_bstride + to.idx * D, loff = bi * p.lse_bstride + to.idx;
   // columns of register quad q of the lane: block q / 4 of O^T, 32 (q / 4) + 8 (q % 4) + 4 h
   auto quad = [&](auto qq, f32x4& x) __attribute__((always_inline)) {
@@ -859,7 +947,7 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
     }
   } else if (!q_valid) {
     // nothing
-  } else if (p.merge == 0 && (ns > 1 || p.out_final == nullptr)) {
+  } else if (!folded && (ns > 1 || p.out_final == nullptr)) {
     // a share's pair, or the partial pair of a step
     const int64_t n_q = second ? t1.n_q : t0.n_q;
     const int64_t rh = ns > 1 ? (static_cast<int64_t>(share) * p.batch + bi) * n_q * p.Hq + to.idx - static_cast<int64_t>(q_row0) * p.Hq : 0;
@@ -873,7 +961,7 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
       *reinterpret_cast<f32x4*>(od + col) = x;
     });
     if (h == 0) *ld = lse_new;
-  } else if (p.merge == 0) {
+  } else if (!folded) {
     T* od = static_cast<T*>(p.out_final) + ooff;
     static_for<D / 8>([&](auto qq) __attribute__((always_inline)) {
       f32x4 x;

@@ -12,6 +12,8 @@ constexpr int kMaxSeg = 64;      // KV segments one query block can see in one s
 constexpr int kMaxTasks = 2;     // query blocks per step (the two half-chunks of the zig-zag layout)
 // Rows (local row, head of the group) of a query tile of attn_tile_kernel.
 constexpr int tile_rows(bool fp32, int d) { return fp32 && d == 128 ? 256 : 128; }
+// Tiles of 32 keys that attn_tile_kernel<float, 128> adds up in registers before their sums join those in memory.
+constexpr int kSumTiles = 512;
 constexpr int kMaxSegAll = 1024; // segments of one query block over ALL steps (steps joined in one launch)
 // Segments a launch descriptor holds, all its query blocks together.  A launch of all steps of eight
 // ranks fits (at most 112 + 56) and so do most of twelve; longer lists go through device memory, which
