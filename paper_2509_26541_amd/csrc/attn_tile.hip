@@ -150,9 +150,10 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
   constexpr int BM = C::BM, NTHREADS = C::NTHREADS, NW = C::NW;
   constexpr int BT = C::BT, NKB = C::NKB, NDB = C::NDB, NJ = D / 16;       // NJ: contraction steps of the scores
   __shared__ __attribute__((aligned(16))) unsigned char smem[C::STAGES * C::STAGE_BYTES + C::RAW_BYTES];
-  // fp32: the rows of a tile that a wavefront cleared, and the runs of `run` tiles that hold keys to be added at the end.
+  // fp32: the rows of a tile that a wavefront cleared; for runs of `run` tiles, whether they hold such rows (with a tile to a run:
+  // which), and whether a tile that is left to the end as a whole.
   __shared__ __attribute__((aligned(16))) int s_bad[F32 ? C::STAGES : 1][NW];
-  __shared__ int s_odd[F32 ? RUNS : 1];
+  __shared__ int s_odd[F32 ? RUNS : 1], s_all_odd[F32 ? RUNS : 1];
   __shared__ float s_scale[F32 && D == 128 && !SERIAL ? NTHREADS : 1];      // running maximum that the sums in memory refer to
   // One step's launch: global positions of the keys (INT_MAX: none), whether a wavefront fetched a key that some row of the
   // tile must not see, and the effective segments of the tile.
@@ -245,7 +246,7 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
   }
   const int lane = tid & 63, wave = tid >> 6, h = lane >> 5, lq = lane & 31;
   if constexpr (F32)
-    for (int i = tid; i < RUNS; i += NTHREADS) s_odd[i] = 0;
+    for (int i = tid; i < RUNS; i += NTHREADS) s_odd[i] = s_all_odd[i] = 0;
   // ---- the keys.  Joined steps: over them every key of the sequence comes once, so this workgroup's share is a run of
   // positions, n_keys of them from goff on.
   int n_keys, goff = 0, n_eff = 1;
@@ -276,7 +277,8 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
     n_eff = e_n;
     n_keys = e_vbeg[n_eff];
   }
-  const int n_tiles = (n_keys + BT - 1) / BT;
+  // (with the segments of a step it comes from LDS: the compiler is told that all lanes have the same)
+  const int n_tiles = F32 ? __builtin_amdgcn_readfirstlane((n_keys + BT - 1) / BT) : (n_keys + BT - 1) / BT;
   static_assert(kMaxSeg <= 64, "");
 
   // ---- positions of the keys of a step, looked up for CHUNK of them at a time: chunk c in half c % 2 of s_tok.
@@ -446,9 +448,9 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
     // key as 0 times that, are left to the end as a whole.
     const int run = (n_tiles + RUNS - 1) / RUNS;
     bool odd = false;
-    auto mark_odd = [&](int t) __attribute__((always_inline)) {
+    auto mark_odd = [&](int* s, int t, int keys) __attribute__((always_inline)) {    // (the same from every wavefront, and each reads what it has written)
       odd = true;
-      if (lane == 0) s_odd[t / run] = 1;
+      if (lane == 0) s[t / run] = keys;
     };
     const int conv_row = C::OWN * wave + lane / C::UNITS, conv_unit = lane % C::UNITS;
     const int raw_adr = C::STAGES * C::STAGE_BYTES + wave * 2 * C::OWN * C::RB + lane / C::UNITS * C::RB + conv_unit * 16;
@@ -571,7 +573,7 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
         bad |= b[0] | b[1] | b[2] | b[3];
       }
       bad = __builtin_amdgcn_readfirstlane(bad);
-      if (__builtin_expect(bad != 0, 0)) mark_odd(t);
+      if (__builtin_expect(bad != 0, 0)) mark_odd(s_odd, t, bad);
       const bool masked = is_masked(t);          // by element
       bool leave = idle;
       if (masked && !idle) {                     // a NaN in V
@@ -583,7 +585,7 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
           for (int e = 0; e < 4; ++e) top = max(top, max(x[e] << 16 & 0x7fffffffu, x[e] & 0x7fffffffu));
         }
         if (__builtin_amdgcn_ballot_w64(top >= 0x7f810000u) != 0) {
-          mark_odd(t);
+          mark_odd(s_all_odd, t, 1);
           leave = true;
         }
       }
@@ -714,30 +716,73 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
 #pragma unroll
     for (int db = 0; db < NSUM; ++db) o[db] += o_sum[db];
     if (LEVELS && !idle && (sum_next > kSumTiles || from_pair)) sums_in_memory(false);
-    // ---- what was left to the end, key by key: as slow as it is rare.
-    int late = lane;                 // (addresses formed anew, not kept across the loop)
-    asm volatile("" : "+v"(late));
+    // ---- what was left to the end, four keys at a time.  16 heads of 128, 2 048 of 16 384 tokens: 0.99 ms with
+    // one V row in 64 infinite (0.78 without, in the same run; key by key 3.2), 14 ms with all V beyond 2^104.
+    const int late = lane_id(), h = late >> 5, lq = late & 31;      // (addresses formed anew, not kept across the loop)
     const f32x4* const qr = reinterpret_cast<const f32x4*>(static_cast<const float*>(p.q) + bi * p.q_bstride + row_of(late & 31).idx * D) + (late >> 5);
-    auto add_key = [&](int key, bool wanted) __attribute__((always_inline)) {
-      const f32x4* const kk = reinterpret_cast<const f32x4*>(Kg + static_cast<unsigned long long>(key) * row_bytes) + h;
-      float dot = 0.f;
+    // Keys wait in a register, one to a lane, until there are four: then the rows that see them take them, those of `q_left` all of these,
+    // the others those that are done again.
+    int queue = 0, n_queue = 0;
+    unsigned q_left = 0;
+    auto add_keys = [&](bool again) __attribute__((always_inline)) {
+      const unsigned char *kk[4], *vv[4];
+      bool on[4];
+      float dot[4] = {0.f, 0.f, 0.f, 0.f};
+      const f32x4* qs = qr;
+      asm volatile("" : "+v"(qs));               // (the row is read anew for every four keys, not held)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int key = __builtin_amdgcn_readlane(queue, u < n_queue ? u : 0);          // (the first once more, for nobody)
+        kk[u] = Kg + static_cast<unsigned long long>(key) * row_bytes;
+        vv[u] = Vg + static_cast<unsigned long long>(key) * row_bytes;
+        on[u] = u < n_queue && key <= q_pos && ((q_left >> u & 1) != 0 || again);
+      }
+      n_queue = 0;
+      q_left = 0;
 #pragma unroll 4
       for (int j = 0; j < D / 8; ++j) {
-        const f32x4 a = kk[2 * j], b = qr[2 * j];
+        const f32x4 b = qs[2 * j];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) dot = __builtin_fmaf(a[e], b[e], dot);
+        for (int u = 0; u < 4; ++u) {
+          const f32x4 a = reinterpret_cast<const f32x4*>(kk[u])[2 * j + h];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dot[u] = __builtin_fmaf(a[e], b[e], dot[u]);
+        }
       }
-      dot += __shfl_xor(dot, 32);
-      if (key > q_pos || !wanted) return;
-      const float m_new = fmaxf(m_run, dot * c), alpha = fast_exp2(m_run - m_new), pk = fast_exp2(__builtin_fmaf(dot, c, -m_new));
+      float m_new = m_run, alpha, pk[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        dot[u] += __shfl_xor(dot[u], 32);
+        if (on[u]) m_new = fmaxf(m_new, dot[u] * c);
+      }
+      alpha = fast_exp2(m_run - m_new);
       m_run = m_new;
       l_run *= alpha;
-      l_lo = l_lo * alpha + (h == 0 ? pk : 0.f);
-      const float* vk = reinterpret_cast<const float*>(Vg + static_cast<unsigned long long>(key) * row_bytes);
+      l_lo *= alpha;
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
+      for (int u = 0; u < 4; ++u) {
+        pk[u] = fast_exp2(__builtin_fmaf(dot[u], c, -m_new));
+        if (on[u] && h == 0) l_lo += pk[u];
+      }
 #pragma unroll
-        for (int db = 0; db < NDB; ++db) o[db][i] = __builtin_fmaf(pk, vk[32 * db + 8 * (i / 4) + 4 * h + i % 4], o[db][i] * alpha);
+      for (int db = 0; db < NDB; ++db) {
+        o[db] *= alpha;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {           // (the call without a workspace has Q in registers here)
+          f32x4 x[4][2];
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int i4 = 0; i4 < 2; ++i4) x[u][i4] = reinterpret_cast<const f32x4*>(vv[u])[8 * db + 4 * half + 2 * i4 + h];
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (on[u]) {
+#pragma unroll
+              for (int i = 0; i < 8; ++i) o[db][8 * half + i] = __builtin_fmaf(pk[u], x[u][i / 4][i % 4], o[db][8 * half + i]);
+            }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
     };
     const bool any_q_odd = !idle && q_odd_rows != 0, q_odd = any_q_odd && (q_odd_rows >> late & 1) != 0;
     if (any_q_odd && q_odd) {                    // from the start again
@@ -761,39 +806,48 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
       }
     }
     if (odd || any_q_odd) {
+      int t = 0, tok = 0;
+      unsigned todo = 0, left = 0;               // keys of tile t - 1 that are still to be taken, and which of them by all rows
+      for (;;) {
+        // rows of Q with an infinity are settled (NaN) with the first score that is NaN or infinite and positive, those with a finite
+        // value of 2^104 or more take every key
+        const bool redo = any_q_odd && __builtin_amdgcn_ballot_w64(q_odd && h == 0 && l_run + l_lo == l_run + l_lo) != 0;
+        if (!redo) todo &= left;
 #pragma unroll 1
-      for (int t = 0; t < n_tiles; ++t) {
-        // rows of Q with an infinity are settled (NaN) with the first score that is infinite and positive, those with a finite value of
-        // 2^104 or more take every key
-        const bool redo = any_q_odd && __builtin_amdgcn_ballot_w64(q_odd && l_run + l_lo == l_run + l_lo) != 0;
-        const bool look = s_odd[t / run] != 0;
-        if (!redo && !look) continue;
-        const int v = t * BT + lq, tok = linear ? (v < n_keys ? goff + v : INT_MAX) : find(v);
-        unsigned left = 0;
-        if (look) {
-          const unsigned long long at = static_cast<unsigned long long>(tok != INT_MAX ? tok : linear ? goff + n_keys - 1 : 0) * row_bytes;
-          const float* const kr = reinterpret_cast<const float*>(Kg + at) + h * (D / 2);
-          const float* const vr = reinterpret_cast<const float*>(Vg + at) + h * (D / 2);
-          float mk = 0.f, mv = 0.f, z = 0.f;
-#pragma unroll 1
-          for (int e = 0; e < D / 2; ++e) {
-            mk = abs_max3(mk, kr[e], kr[e]);
-            mv = abs_max3(mv, vr[e], vr[e]);
-            z = __builtin_fmaf(vr[e], 0.f, z);
+        while (n_queue < 4 && (todo != 0 || t < n_tiles)) {
+          if (todo == 0) {
+            left = s_all_odd[t / run] != 0 ? ~0u : static_cast<unsigned>(s_odd[t / run]);
+            left = __builtin_amdgcn_readfirstlane(static_cast<int>(left));
+            const int v = t++ * BT + lq;
+            if (!redo && left == 0) continue;
+            tok = linear ? (v < n_keys ? goff + v : INT_MAX) : find(v);
+            if (left != 0 && run > 1) {
+              const unsigned long long at = static_cast<unsigned long long>(tok != INT_MAX ? tok : linear ? goff + n_keys - 1 : 0) * row_bytes;
+              const f32x4* const kr = reinterpret_cast<const f32x4*>(Kg + at) + h * (D / 8);
+              const f32x4* const vr = reinterpret_cast<const f32x4*>(Vg + at) + h * (D / 8);
+              float m = 0.f, z = 0.f;
+#pragma unroll 4
+              for (int e = 0; e < D / 8; ++e) {
+                const f32x4 x = kr[e], y = vr[e];
+                m = abs_max8(x, y, m);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) z = __builtin_fmaf(y[i], 0.f, z);
+              }
+              const bool huge = __builtin_bit_cast(int, fmaxf(m, __shfl_xor(m, 32))) >= kHuge;       // as in conv_write
+              left = static_cast<unsigned>(__builtin_amdgcn_ballot_w64(huge));                       // (both halves have the same)
+              const unsigned long long nan = __builtin_amdgcn_ballot_w64(!(z == 0.f) && !(left >> lq & 1));
+              if (nan != 0 && __builtin_amdgcn_ballot_w64(tok > q_first) != 0) left = ~0u;
+            }
+            todo = (redo ? ~0u : left) & static_cast<unsigned>(__builtin_amdgcn_ballot_w64(tok != INT_MAX));
+            continue;
           }
-          auto huge = [&](float m) __attribute__((always_inline)) { return __builtin_bit_cast(int, fmaxf(m, __shfl_xor(m, 32))) >= kHuge; };    // as in conv_check
-          const unsigned bad = static_cast<unsigned>(__builtin_amdgcn_ballot_w64(huge(fmaxf(mk, mv))));      // (both halves have the same)
-          const unsigned long long nan = __builtin_amdgcn_ballot_w64(!(z == 0.f) && !(bad >> lq & 1));
-          const bool masked = __builtin_amdgcn_ballot_w64(tok > q_first) != 0;
-          left = masked && nan != 0 ? ~0u : bad;
+          const int k = __builtin_ctz(todo), key = __builtin_amdgcn_readlane(tok, k);
+          todo &= todo - 1;
+          queue = late == n_queue ? key : queue;
+          q_left |= (left >> k & 1) << n_queue++;
         }
-#pragma unroll 1
-        for (int k = 0; k < BT; ++k) {
-          const int key = __builtin_amdgcn_readlane(tok, k);
-          if (key == INT_MAX) break;               // past the end, as all that follow
-          const bool mine = left >> k & 1;
-          if (mine || redo) add_key(key, q_odd || mine);
-        }
+        if (n_queue == 0) break;
+        add_keys(q_odd);
       }
     }
   } else {

@@ -176,6 +176,38 @@ def test_many_keys_in_one_launch(tb, n, S, heads, mask):
         assert S == 131072 or (torch.equal(out, out2) and torch.equal(lse, lse2))
 
 
+@pytest.mark.parametrize("fuse_steps", [False, True], ids=["steps", "joined"])
+@pytest.mark.parametrize("d,mask", SHAPES, ids=IDS)
+def test_keys_left_to_the_end_among_many(tb, d, mask, fuse_steps):
+    """More than 512 tiles of 32 keys to a row: values beyond 2^104 without weight and with one that counts, an infinite K that
+    no row gives weight, a NaN in V in a tile that not all rows see.  Bound: the weight that counts is exp(-95 ln 2 = -66), and a dot
+    product of that size has been rounded some 32 times: 66 sqrt(32) 2^-24 / sqrt(3) = 1.3e-5 for the weight, times three."""
+    n, rank, size = 4, 1, 8 * 10241
+    q, k, v = inputs(n, size, 1, 1, d, 32)
+    pos = positions(n, rank, size, mask)
+    q[:, :, 0] = 1.0
+    gone = torch.tensor([0, 31, 32, 5000, 5001, 5002, 5003, 5004, 9000, 20480, 30000, size - 1], device="cuda")
+    k[gone, :, 0] = -float("inf")
+    v[gone] *= 2.0 ** 110
+    k[[7000, 7007], :, 0] = -95 * math.log(2.0) * d ** 0.5
+    v[[7000, 7007]] *= 2.0 ** 105
+    kf, vf = k.clone(), v.clone()
+    kf[gone, :, 0] = -1e6
+    vf[gone] = 0.0
+    L = size // n
+    pick = torch.cat([torch.arange(0, 40), torch.arange(L // 2 - 20, L // 2 + 20), torch.arange(L - 40, L)]).cuda()
+    at = int(pos[20]) if mask else size - 5              # seen by some of the rows of a tile, or by all
+    v[at, 0, 3] = float("nan")
+    vf[at, 0, 3] = 0.0
+    ref_o, ref_l = reference(q[pick], kf, vf, pos[pick])
+    out, lse = tb.tasp_chunk_attn(q, k, v, tb.tasp_schedule(n, rank), mask, fuse_merge=True, fuse_steps=fuse_steps)
+    sees = pos >= at
+    assert bool(out[sees, 0, 3].isnan().all()) and not bool(out[~sees].isnan().any())
+    out = out[pick].clone()
+    out[sees[pick], 0, 3] = ref_o[sees[pick], 0, 3].float()
+    assert rel(out, ref_o) <= 4e-5 and float((lse[pick].double() - ref_l).abs().max()) <= 1e-5
+
+
 @pytest.mark.parametrize("heads", [(4, 4, 64), (16, 4, 128)], ids=["4x64", "16/4x128"])
 def test_the_range_costs_no_time(tb, heads):
     """Rows nearly zero or very large, and columns that are: no slower than without (a quarter is for the noise of single calls)."""
@@ -205,3 +237,14 @@ def test_the_range_costs_no_time(tb, heads):
         got = best_ms(k, x)
         print(name, clean, got, flush=True)
         assert got <= 1.25 * clean + 0.005, (name, clean, got)
+    # key by key: one in 64 with an infinity twice a clean call, a row of Q that is done again no longer than its first keys
+    # take (it is NaN with the first of them)
+    some = v.clone()
+    some[at % 64 == 5] = float("inf")
+    got = best_ms(k, some)
+    print("one in 64 infinite", clean, got, flush=True)
+    assert got <= 2 * clean, (clean, got)
+    q[7] = float("inf")
+    got = best_ms(k, v)
+    print("a row of Q infinite", clean, got, flush=True)
+    assert got <= 2 * clean, (clean, got)
