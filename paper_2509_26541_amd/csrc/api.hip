@@ -24,6 +24,8 @@ using tasp::AttnLaunch;
 using tasp::AttnTask;
 
 constexpr size_t kAlign = 256;
+// Segment lists of a joined backward launch.  A forward call with fuse_steps, whose keys go by position, asks for the same number of bytes: room
+// for the pairs of a few shares.
 constexpr size_t kFusedTableBytes = static_cast<size_t>(tasp::kMaxTasks) * 2 * tasp::kMaxSegAll * sizeof(int32_t);
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -131,16 +133,17 @@ struct JoinedSteps {
 // With the lists of the steps one behind the other (`arrival`), or with the keys by position: over the steps every key
 // of the sequence comes once, and what a launch that does not wait for arrivals adds up does not depend on the order but
 // for rounding.  By position a tile is a run of neighbouring keys (4 x 12K tokens x 32 sequences, sub-chunks of 110: 342 us a
-// call against 365; 20 x 3K x 128: 697 against 716).  With fuse_steps a call whose lists are longer than
-// TASP_MAX_FUSED_SEGMENTS is refused, whichever the order.
+// call against 365; 20 x 3K x 128: 697 against 716).  With fuse_steps a call whose lists would be longer than
+// TASP_MAX_FUSED_SEGMENTS is refused, whichever the order; by position they are made for that only where it can be.
 int join_steps(const tasp_schedule_t* s, const tasp_attn_args* a, JoinedSteps* js, bool arrival = false) {
   init_launch(s, a, &js->all);
+  const int64_t pieces = static_cast<int64_t>(s->n) * (a->order == TASP_ORDER_RING ? 1 : s->n_rings) * (a->mask_mode == TASP_MASK_ZIGZAG_CAUSAL ? 2 : 1);
   for (int qb = 0; qb < tasp::n_query_blocks(a->mask_mode); ++qb) {
     tasp::QueryBlock blk;
     int st = tasp::query_block(*s, a->S, a->mask_mode, qb, &blk);
     if (st != TASP_OK) return st;
     std::vector<int32_t>& g = js->table[qb];
-    if (arrival || a->fuse_steps) {
+    if (arrival || (a->fuse_steps && pieces > tasp::kMaxSegAll)) {
       st = tasp::all_step_segments(*s, a->S, a->mask_mode, a->order, qb, &g);
       if (st != TASP_OK) return st;
       if (g.empty() || g.size() / 2 > static_cast<size_t>(tasp::kMaxSegAll)) return TASP_EUNSUPPORTED_SHAPE;
@@ -175,14 +178,11 @@ int place_lists(const JoinedSteps& js, tasp::BwdLaunch* bp, int32_t* dev_table, 
   return tasp::launch_write_i32(dev_table, flat.data(), static_cast<int64_t>(flat.size()), stream) == hipSuccess ? TASP_OK : TASP_EHIP;
 }
 
-// How a forward call runs: step by step, or all steps in one launch, in that case possibly with the
-// keys of a query tile dealt to several workgroups.
+// How all steps of a forward call run in one launch, possibly with the keys of a query tile dealt to several workgroups.
 struct FwdPlan {
-  bool joined = false;
   bool tile = false;                  // attn_tile_kernel
   bool serial = false;                // a workgroup of it takes all shares of its tile: no partial pairs
   int32_t n_split[tasp::kMaxTasks] = {1, 1};
-  size_t table_bytes = 0;             // of device memory in front of the partial pairs: none, the keys go by position
   size_t part_bytes = 0;              // of the shares' pairs
 };
 
@@ -336,7 +336,6 @@ bool tile_is_faster(const AttnLaunch& lp, int d, const int64_t* keys, const int3
 FwdPlan plan_forward(const tasp_attn_args* a, const JoinedSteps& js, size_t need, size_t ws_bytes) {
   FwdPlan pl;
   const bool fp32 = a->dtype == TASP_DTYPE_FP32;
-  pl.joined = true;
   size_t room = std::max<size_t>(need, TASP_STATIC_SCRATCH_BYTES);
   for (;;) {
     int32_t n_split[tasp::kMaxTasks] = {1, 1};
@@ -363,7 +362,7 @@ FwdPlan plan_forward(const tasp_attn_args* a, const JoinedSteps& js, size_t need
       return pl;
     }
     room = ws_bytes;                                  // what is dealt for this much fits
-    pl = FwdPlan{true, false, false, {1, 1}, 0, 0};
+    pl = FwdPlan{};
   }
 }
 
@@ -448,9 +447,8 @@ int validate_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args* b, tasp_att
   return TASP_OK;
 }
 
-// Whether the steps of a backward call run in one launch of each kind, and how finely these are cut.
+// How finely the joined launches of a backward call are cut.
 struct BwdPlan {
-  bool joined = false;
   size_t table_bytes = 0;      // device memory for the segment lists of fuse_steps
   int32_t n_split = 1;         // workgroups the keys of a query tile are dealt to; their dq sums follow the lists
   int32_t kv_split = 0;        // BwdLaunch::kv_split; the partial dk and dv follow the dq sums
@@ -564,7 +562,6 @@ int64_t dkv_makespan(const tasp::BwdLaunch& bp, int d, int kv_split, int64_t bat
 // Fills in what depends on shapes alone; `bp` is the joined launch, `ws_bytes` the workspace.
 BwdPlan plan_backward(const tasp_attn_bwd_args* b, const Shape& sh, const tasp::BwdLaunch& bp, size_t table_bytes, size_t ws_bytes) {
   BwdPlan pl;
-  pl.joined = true;
   pl.table_bytes = table_bytes;
   const bool fp32 = b->dtype == TASP_DTYPE_FP32;
   const int64_t G = b->Hq / b->Hkv;
@@ -637,7 +634,6 @@ size_t tasp_chunk_attn_workspace_bytes(const tasp_schedule_t* s, const tasp_attn
   const size_t lse_bytes = align_up(B * L * a->Hq * sizeof(float));
   size_t total = 0;
   if (a->dtype == TASP_DTYPE_BF16) total += o_bytes;              // running fp32 output
-  // what the single launch asks for beside: room for the pairs of a few shares (its keys go by position, it lists no segments)
   if (a->fuse_steps) return total + align_up(kFusedTableBytes);
   if (!a->fuse_merge) total += o_bytes + lse_bytes;               // partial (out_s, lse_s) of a step
   return total;

@@ -1,4 +1,4 @@
-"""fp32 forward products formed from 16-bit halves: edges of tiles, magnitudes, infinities and NaN.  The reference is the
+"""fp32 forward products formed on the 16-bit matrix pipe: edges of tiles, magnitudes, infinities and NaN.  The reference is the
 softmax in 64 bits, on the GPU; scaling by powers of two has to give the same bits scaled."""
 import numpy as np
 import pytest

@@ -94,7 +94,7 @@ SMALL_BF16 = [c for c in SMALL if not c[0].startswith("fp32")]
 
 @pytest.mark.parametrize("case", SMALL_BF16, ids=[c[0] for c in SMALL_BF16])
 def test_small_all_rows_single_launch(tb, case):
-    """fuse_steps: one launch walks the sub-chunks of all steps in arrival order."""
+    """fuse_steps: one launch walks the keys of all steps."""
     name, base, n, rank, S, Hq, Hkv, d = case
     b = wl.CONFIGS[base]
     w = wl.Workload(name, n, rank, S, Hq, Hkv, d, "bf16", wl.ZIGZAG_CAUSAL if "_zz_" in name else wl.FULL,

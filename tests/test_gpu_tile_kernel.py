@@ -29,9 +29,9 @@ EDGES = [
     ("tile_plus_bf16", 8, 7, 16 * 129, 2, 2, 64, "bf16", wl.ZIGZAG_CAUSAL),
     ("many_shares", 4, 2, 4 * 1031, 1, 1, 128, "bf16", wl.FULL),             # 32 shares of a prime number of keys
     ("many_shares_fp32", 8, 6, 16 * 257, 1, 1, 64, "fp32", wl.ZIGZAG_CAUSAL),
-    ("lists_in_memory", 16, 11, 32 * 64, 4, 2, 64, "bf16", wl.ZIGZAG_CAUSAL),  # more segments than a descriptor holds
-    ("lists_in_memory_fp32", 16, 15, 32 * 31, 2, 1, 128, "fp32", wl.ZIGZAG_CAUSAL),
-    ("not_joined", 32, 17, 64 * 33, 2, 1, 64, "fp32", wl.ZIGZAG_CAUSAL),     # too many segments to join: step by step
+    ("small_pieces", 16, 11, 32 * 64, 4, 2, 64, "bf16", wl.ZIGZAG_CAUSAL),   # sub-chunks of four keys
+    ("small_pieces_fp32", 16, 15, 32 * 31, 2, 1, 128, "fp32", wl.ZIGZAG_CAUSAL),
+    ("many_ranks", 32, 17, 64 * 33, 2, 1, 64, "fp32", wl.ZIGZAG_CAUSAL),     # sub-chunks of one key
 ]
 
 
@@ -57,6 +57,22 @@ def test_short_calls_all_rows(tb, case):
             torch.cuda.synchronize()
             eo, el = max_abs(out.float().cpu().numpy(), ref_o), max_abs(lse.cpu().numpy(), ref_l)
             assert eo <= tol_o and el <= tol_l, (name, fuse, nbytes, eo, el)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_steps_of_many_segments(tb, d, dtype):
+    """Steps by themselves, the most segments a query block can have (31 rings, two each) and most of them of one key: every row
+    of the pairs of all steps, merged."""
+    n, rank, S, Hq, Hkv = 32, 17, 64 * 33, 2, 1
+    w = wl.Workload("many_segments", n, rank, S, Hq, Hkv, d, dtype, wl.ZIGZAG_CAUSAL, seed=wl.BASE_SEED + 8300 + d)
+    q, k, v = wl.make_qkv(w)
+    s = tb.tasp_schedule(n, rank)
+    ref_o, ref_l = oracle_rows(w, q, k, v, list(range(w.L)))
+    parts = [tb.tasp_step_attn(q.cuda(), k.cuda(), v.cuda(), s, w.mask_mode, i) for i in range(n)]
+    o, lse = tb.tasp_lse_merge_many([o for o, _ in parts], [l for _, l in parts])
+    tol_o, tol_l = (2e-2, 1e-3) if dtype == "bf16" else (1e-4, 1e-4)
+    assert max_abs(o.cpu().numpy(), ref_o) <= tol_o and max_abs(lse.cpu().numpy(), ref_l) <= tol_l
 
 
 def test_fp32_fused_merge_leaves_an_unaligned_workspace_alone(tb):
@@ -222,7 +238,7 @@ NOT_FINITE = [
     # name, N, rank, S, Hq, Hkv, d
     ("shares", 8, 3, 16 * 75, 4, 2, 64),
     ("tile_edges", 4, 1, 8 * 97, 3, 1, 128),
-    ("not_joined", 32, 17, 64 * 33, 2, 1, 64),                               # step by step, folded into the running pair
+    ("many_ranks", 32, 17, 64 * 33, 2, 1, 64),
 ]
 
 

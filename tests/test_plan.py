@@ -53,16 +53,15 @@ static Plan forward(const tasp_schedule_t* s, tasp_attn_args a, size_t ws) {    
   Shape sh;
   if (validate(s, &a, &sh) != TASP_OK || join_steps(s, &a, &js) != TASP_OK) return {};
   const FwdPlan p = plan_forward(&a, js, tasp_chunk_attn_workspace_bytes(s, &a), ws ? ws : tasp_chunk_attn_best_workspace_bytes(s, &a));
-  return {p.joined, p.tile, p.n_split[0], p.n_split[1], 0, p.table_bytes + p.part_bytes};
+  return {true, p.tile, p.n_split[0], p.n_split[1], 0, p.part_bytes};
 }
-static Plan forward_none(const tasp_schedule_t* s, tasp_attn_args a) {     // lists in device memory: not joined without a workspace
+static Plan forward_none(const tasp_schedule_t* s, tasp_attn_args a) {     // without a workspace: the shares are taken in turn
   JoinedSteps js{};
   Shape sh;
   if (validate(s, &a, &sh) != TASP_OK || join_steps(s, &a, &js) != TASP_OK) return {};
-  if (js.segments() > static_cast<size_t>(tasp::kPoolSeg)) return forward(s, a, 0);
   const FwdPlan p = plan_forward(&a, js, 0, 0);
   if (p.part_bytes > 0 || p.serial != (p.n_split[0] > 1 || p.n_split[1] > 1)) return {};
-  return {p.joined, p.tile, p.n_split[0], p.n_split[1], 0, 0};
+  return {true, p.tile, p.n_split[0], p.n_split[1], 0, 0};
 }
 static Plan backward(const tasp_schedule_t* s, tasp_attn_bwd_args b, size_t ws) {
   JoinedSteps js{};
