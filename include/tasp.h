@@ -203,7 +203,9 @@ int    tasp_chunk_attn(const tasp_schedule_t* s, const tasp_attn_args* a, void* 
  *     has to start at zero (step 0 of every call overwrites what it uses), but two calls that overlap
  *     on one GPU (different streams, or different threads) race.  Serialise them.  A call whose
  *     tasp_chunk_attn_workspace_bytes() is 0 does not touch the array and may overlap with any other.
- * Results are those of tasp_chunk_attn (the same kernels run) bit for bit. */
+ * Results are those of tasp_chunk_attn (the same kernels run) bit for bit; a call that needs no
+ * workspace gives those of tasp_chunk_attn without one, which for fp32 with d = 128 and tens of thousands of
+ * keys to a row may differ in rounding from what it gives with one. */
 #define TASP_STATIC_SCRATCH_BYTES (64u << 20)
 int tasp_chunk_attn_static(const tasp_schedule_t* s, const tasp_attn_args* a, void* hip_stream);
 

@@ -234,9 +234,9 @@ double makespan(double n0, double l0, double n1, double l1, double slots) {
 // last row of task t sees.  Shares are weighed by when the last workgroup would be done: R workgroups of a CU side by side,
 // each at 1 / R of its rate, one by itself at 1 / alone; a workgroup's fixed cost (set-up, first fetches, epilogue) as so many
 // keys more; and with shares the launch that adds them up and the way of the partial pairs through memory.
-// Fitted to 1 900 calls of each type (512 to 32K tokens, both d, batches of 1 to 4), each with up to 57 ways to deal them: over the
-// best of these, which is partly the luckiest, the choice takes 1.5 % more (fp32, d = 128; 3.4 % at d = 64, bf16 3.7 and 6.3 %),
-// where shares of equal length in whole rounds of the CUs took 20 % (7 %; 7 and 8 %).
+// Over 110 drawn shapes (profiles/shares_of_the_keys.txt) the choice takes for one sequence, over the best of up to 40 ways, which is partly the
+// luckiest, 0.97 (fp32, d = 64), 0.98 (128), 1.02 (bf16, both d) in the mean and 1.19 at most; batches of two to four that are planned as one
+// sequence 1.10 to 1.15.
 void deal_keys(const AttnLaunch& lp, int d, bool fp32, const int64_t* keys, size_t room, int32_t* n_split, int64_t B) {
   struct Fit { double R, alone, fixed, per_us; };          // (fixed in keys, per_us: keys a CU walks in a microsecond)
   const Fit fit = fp32 ? (d == 64 ? Fit{2, 1.4, 60, 28} : Fit{1, 1, 60, 10}) : (d == 64 ? Fit{2, 1.4, 300, 80} : Fit{2, 1.6, 200, 60});
@@ -264,7 +264,8 @@ void deal_keys(const AttnLaunch& lp, int d, bool fp32, const int64_t* keys, size
     double cost = wgs[0] + wgs[1] <= 256 ? alone : std::max(alone, makespan(wgs[0], len[0], wgs[1], len[1], 256 * fit.R) * fit.R);
     cost = cost / fit.per_us + (moved > 0 ? add_us + moved / add_bytes_us : 0);
     // Items are dealt to XCDs in turn: with an even number of shares an XCD meets few of them.  8 heads over 2 and over 8, 512
-    // and 768 rows: 8, 10 and 12 shares took 3 % more than their odd neighbours.
+    // and 768 rows, bf16: 8, 10 and 12 shares took 3 % more than their odd neighbours.  (Over the drawn shapes six shares took 0.99 to
+    // 1.02 of what five and seven take: this decides between ways that are as good as each other.)
     if (n0 >= 4 && n0 % 2 == 0) cost *= 1.03;
     if (best < 0 || cost < best) { best = cost; n_split[0] = n0; n_split[1] = n1; }
   };
