@@ -124,6 +124,13 @@ __device__ __forceinline__ float abs_max8(const f32x4& a, const f32x4& b, float 
   m = abs_max3(abs_max3(m, a[0], a[1]), a[2], a[3]);
   return abs_max3(abs_max3(m, b[0], b[1]), b[2], b[3]);
 }
+// The largest of the 32 integers that each half of a wavefront has (the same ones).
+template <int CTRL>
+__device__ __forceinline__ int dpp_max(int x) { return max(x, __builtin_amdgcn_update_dpp(0, x, CTRL, 15, 15, true)); }      // (a shift inside 16 lanes)
+__device__ __forceinline__ int max32(int x) {
+  x = dpp_max<0x118>(dpp_max<0x114>(dpp_max<0x112>(dpp_max<0x111>(x))));
+  return max(__builtin_amdgcn_readlane(x, 15), __builtin_amdgcn_readlane(x, 31));
+}
 __device__ inline bf16x8 lds_tr8(const unsigned char* lo, const unsigned char* hi) {
   const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lds_void_ptr)const_cast<unsigned char*>(lo));
   const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lds_void_ptr)const_cast<unsigned char*>(hi));
@@ -154,6 +161,7 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
   // which), and whether a tile that is left to the end as a whole.
   __shared__ __attribute__((aligned(16))) int s_bad[F32 ? C::STAGES : 1][NW];
   __shared__ int s_odd[F32 ? RUNS : 1], s_all_odd[F32 ? RUNS : 1];
+  __shared__ __attribute__((aligned(16))) int s_qtop[NW];      // fp32: largest |Q| of a wavefront's rows
   __shared__ float s_scale[F32 && D == 128 && !SERIAL ? NTHREADS : 1];      // running maximum that the sums in memory refer to
   // One step's launch: global positions of the keys (INT_MAX: none), whether a wavefront fetched a key that some row of the
   // tile must not see, and the effective segments of the tile.
@@ -226,7 +234,10 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
     float m = 0.f;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) m = abs_max8(__builtin_bit_cast(f32x4, qf[2 * j]), __builtin_bit_cast(f32x4, qf[2 * j + 1]), m);
-    q_odd_rows = __builtin_amdgcn_ballot_w64(__builtin_bit_cast(int, fmaxf(m, __shfl_xor(m, 32))) >= kHuge);
+    const int top = __builtin_bit_cast(int, fmaxf(m, __shfl_xor(m, 32)));
+    q_odd_rows = __builtin_amdgcn_ballot_w64(top >= kHuge);
+    const int all = max32(top >= kHuge ? 0 : top);
+    if ((thread & 63) == 0) s_qtop[wave_u] = all;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       f32x4 a = __builtin_bit_cast(f32x4, qf[2 * j]), b = __builtin_bit_cast(f32x4, qf[2 * j + 1]);
@@ -443,8 +454,9 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
     // Tile t + 1 is split, by the wavefront that fetched it, while tile t is worked on; tile t + 2 is on its way.
     //
     // Keys with an infinity, which has no pieces (inf - inf), or a value of 2^104 or more (2^2 probabilities of it times 2^16 of 32
-    // keys stay below 2^128) are cleared, masked and added one by one at the end, from memory.  A row of Q with one is done
-    // again key by key.  Tiles with the element-wise mask and a NaN in V, which would come to the rows that do not see its
+    // keys stay below 2^128) are masked and added at the end, from memory, and so are those whose K could let a sum of
+    // products leave the floats (`huge_k`, by the largest |Q| of the workgroup): a score of minus infinity has no weight, but the
+    // smaller products may leave them on the other side.  A row of Q with a value of 2^104 or more is done again.  Tiles with the element-wise mask and a NaN in V, which would come to the rows that do not see its
     // key as 0 times that, are left to the end as a whole.
     const int run = (n_tiles + RUNS - 1) / RUNS;
     bool odd = false;
@@ -457,7 +469,7 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
     const int conv_adr[2] = {conv_row * C::LB + C::swz_k(conv_row, conv_unit) * 16, C::TILE_BYTES + conv_row * C::LB + C::swz_v(conv_row, conv_unit) * 16};
     // Rows of K (kv = 0) or V of the fetched tile to pieces.  The rows with a huge value count as if they were not there, their scores
     // are replaced; only what V would bring to 0 times infinity has to go.
-    int huge_rows = 0;
+    int huge_rows = 0, huge_k = kHuge;
     f32x4 raw[2];
     auto conv_read = [&](int kv) __attribute__((always_inline)) {
 #pragma unroll
@@ -467,7 +479,7 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
     // the output, of an error of 8e-7); so V is taken with the other sign in every other tile, and the tile's sums are subtracted.
     auto v_scale = [](int stage) { return stage == 0 ? kVScale : -kVScale; };
     auto conv_write = [&](int stage, int kv) __attribute__((always_inline)) {
-      const unsigned long long huge = __builtin_amdgcn_ballot_w64(__builtin_bit_cast(int, abs_max8(raw[0], raw[1], 0.f)) >= kHuge);
+      const unsigned long long huge = __builtin_amdgcn_ballot_w64(__builtin_bit_cast(int, abs_max8(raw[0], raw[1], 0.f)) >= (kv == 0 ? huge_k : kHuge));
       if (kv == 0) huge_rows = 0;
       if (__builtin_expect(huge != 0, 0)) {
         unsigned lo = static_cast<unsigned>(huge), hi = static_cast<unsigned>(huge >> 32);
@@ -557,6 +569,15 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
       }
       fetch(0, 0);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      int q_top = 0;
+#pragma unroll
+      for (int i = 0; i < NW / 4; ++i) {
+        const i32x4 x = *reinterpret_cast<const i32x4*>(&s_qtop[4 * i]);
+        q_top = max(q_top, max(max(x[0], x[1]), max(x[2], x[3])));
+      }
+      // |q| < 2^(e + 1), |k| < 2^(119 - e), 128 products: below 2^127
+      huge_k = min(kHuge >> 23, 119 + 2 * 127 - (__builtin_amdgcn_readfirstlane(q_top) >> 23)) << 23;
       convert(0);
     }
     for (int t = 0; t < n_tiles; ++t) {
@@ -825,15 +846,16 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
               const unsigned long long at = static_cast<unsigned long long>(tok != INT_MAX ? tok : linear ? goff + n_keys - 1 : 0) * row_bytes;
               const f32x4* const kr = reinterpret_cast<const f32x4*>(Kg + at) + h * (D / 8);
               const f32x4* const vr = reinterpret_cast<const f32x4*>(Vg + at) + h * (D / 8);
-              float m = 0.f, z = 0.f;
+              float m = 0.f, mv = 0.f, z = 0.f;
 #pragma unroll 4
               for (int e = 0; e < D / 8; ++e) {
                 const f32x4 x = kr[e], y = vr[e];
-                m = abs_max8(x, y, m);
+                m = abs_max3(abs_max3(m, x[0], x[1]), x[2], x[3]);
+                mv = abs_max3(abs_max3(mv, y[0], y[1]), y[2], y[3]);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) z = __builtin_fmaf(y[i], 0.f, z);
               }
-              const bool huge = __builtin_bit_cast(int, fmaxf(m, __shfl_xor(m, 32))) >= kHuge;       // as in conv_write
+              const bool huge = __builtin_bit_cast(int, fmaxf(m, __shfl_xor(m, 32))) >= huge_k || __builtin_bit_cast(int, fmaxf(mv, __shfl_xor(mv, 32))) >= kHuge;   // as in conv_write
               left = static_cast<unsigned>(__builtin_amdgcn_ballot_w64(huge));                       // (both halves have the same)
               const unsigned long long nan = __builtin_amdgcn_ballot_w64(!(z == 0.f) && !(left >> lq & 1));
               if (nan != 0 && __builtin_amdgcn_ballot_w64(tok > q_first) != 0) left = ~0u;

@@ -100,6 +100,22 @@ def test_rows_of_different_size_side_by_side(tb, d, mask):
     check(tb, q, k, v, mask, "one in 64 very large")
 
 
+@pytest.mark.parametrize("d,mask", SHAPES, ids=IDS)
+def test_scores_that_overflow_downwards(tb, d, mask):
+    """Keys whose scores are below the smallest float have no weight, whichever sign the smaller products of their pieces have."""
+    for big, far in ((1e14, -1.2345678e30), (1e14, -1.2378901e30), (3e30, -7.654321e24), (1e-3, -2.9e31)):
+        q, k, v = inputs(N, S, H, H, d, 33)
+        q[:, :, 0] = big * (1.0 + 0.1 * torch.rand(q.shape[:2], device="cuda"))
+        k[:, :, 0] /= big
+        gone = torch.tensor([0, 5, 6, 7, 37, 700, 1500, S - 1], device="cuda")
+        k[gone, :, 0] = far
+        kf = k.clone()
+        kf[gone, :, 0] = -1e6 / big
+        out, lse = tb.tasp_chunk_attn(q, k, v, tb.tasp_schedule(N, RANK), mask, fuse_merge=True)
+        ref_o, ref_l = reference(q, kf, v, positions(N, RANK, S, mask))
+        assert rel(out, ref_o) <= 2e-6 and float((lse.double() - ref_l).abs().max()) <= 1e-5, (big, far)
+
+
 def long_error(tb, S, n, d, fuse_steps):
     """Errors of 512 rows of one head, no mask, over the output's root mean square."""
     q, k, v = inputs(n, S, 1, 1, d, 29)
