@@ -231,19 +231,19 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
   unsigned long long q_odd_rows = 0;    // fp32: lanes whose row holds an infinity or a value of 2^104 or more
   auto split_q = [&]() __attribute__((always_inline)) {
     if constexpr (F32) {
-    float m = 0.f;
+      float m = 0.f;
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) m = abs_max8(__builtin_bit_cast(f32x4, qf[2 * j]), __builtin_bit_cast(f32x4, qf[2 * j + 1]), m);
-    const int top = __builtin_bit_cast(int, fmaxf(m, __shfl_xor(m, 32)));
-    q_odd_rows = __builtin_amdgcn_ballot_w64(top >= kHuge);
-    const int all = max32(top >= kHuge ? 0 : top);
-    if ((thread & 63) == 0) s_qtop[wave_u] = all;
+      for (int j = 0; j < NJ; ++j) m = abs_max8(__builtin_bit_cast(f32x4, qf[2 * j]), __builtin_bit_cast(f32x4, qf[2 * j + 1]), m);
+      const int top = __builtin_bit_cast(int, fmaxf(m, __shfl_xor(m, 32)));
+      q_odd_rows = __builtin_amdgcn_ballot_w64(top >= kHuge);
+      const int all = max32(top >= kHuge ? 0 : top);
+      if ((thread & 63) == 0) s_qtop[wave_u] = all;
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      f32x4 a = __builtin_bit_cast(f32x4, qf[2 * j]), b = __builtin_bit_cast(f32x4, qf[2 * j + 1]);
+      for (int j = 0; j < NJ; ++j) {
+        f32x4 a = __builtin_bit_cast(f32x4, qf[2 * j]), b = __builtin_bit_cast(f32x4, qf[2 * j + 1]);
 #pragma unroll
-      for (int i = 0; i < 3; ++i) qp[i][j] = next_piece(a, b);
-    }
+        for (int i = 0; i < 3; ++i) qp[i][j] = next_piece(a, b);
+      }
     }
   };
   if constexpr (F32 && SERIAL) split_q();
@@ -456,8 +456,9 @@ __global__ __launch_bounds__((TCfg<T, D>::NTHREADS), (D == 64 && !TCfg<T, D>::F3
     // Keys with an infinity, which has no pieces (inf - inf), or a value of 2^104 or more (2^2 probabilities of it times 2^16 of 32
     // keys stay below 2^128) are masked and added at the end, from memory, and so are those whose K could let a sum of
     // products leave the floats (`huge_k`, by the largest |Q| of the workgroup): a score of minus infinity has no weight, but the
-    // smaller products may leave them on the other side.  A row of Q with a value of 2^104 or more is done again.  Tiles with the element-wise mask and a NaN in V, which would come to the rows that do not see its
-    // key as 0 times that, are left to the end as a whole.
+    // smaller products may leave them on the other side.  A row of Q with a value of 2^104 or more is done again.  Tiles with the
+    // element-wise mask and a NaN in V, which would come to the rows that do not see its key as 0 times that, are left to the end
+    // as a whole.
     const int run = (n_tiles + RUNS - 1) / RUNS;
     bool odd = false;
     auto mark_odd = [&](int* s, int t, int keys) __attribute__((always_inline)) {    // (the same from every wavefront, and each reads what it has written)

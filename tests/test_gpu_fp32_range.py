@@ -101,6 +101,27 @@ def test_rows_of_different_size_side_by_side(tb, d, mask):
 
 
 @pytest.mark.parametrize("d,mask", SHAPES, ids=IDS)
+def test_gradients_behind_such_a_forward(tb, d, mask):
+    """The backward pass takes out and lse from the forward: with a column of Q 2^30 times as large, K's as much smaller, the
+    probabilities still add up to one.  Bound: fp32 sums, 1e-5 of every tensor."""
+    n, rank, size = 4, 1, 8 * 100
+    q, k, v = inputs(n, size, 1, 1, d, 34)
+    q[:, :, 3] *= 2.0 ** 30
+    k[:, :, 3] *= 2.0 ** -30
+    do = inputs(n, size, 1, 1, d, 35)[0]
+    s = tb.tasp_schedule(n, rank)
+    out, lse = tb.tasp_chunk_attn(q, k, v, s, mask, fuse_merge=True)
+    got = tb.tasp_chunk_attn_bwd(q, k, v, out, lse, do, s, mask)
+    x, y, z, g = q[:, 0].double(), k[:, 0].double(), v[:, 0].double(), do[:, 0].double()
+    pos = positions(n, rank, size, mask)
+    p = torch.softmax((x @ y.T / d ** 0.5).masked_fill(torch.arange(size, device="cuda")[None, :] > pos[:, None], -math.inf), 1)
+    ds = p * (g @ z.T - (g * (p @ z)).sum(1, keepdim=True)) / d ** 0.5
+    for name, a, b in zip(("dq", "dk", "dv"), got, (ds @ y, ds.T @ x, p.T @ g)):
+        err, ref = (a[:, 0].double() - b).norm(dim=0), b.norm(dim=0)
+        assert float((err / ref).max()) <= 1e-5, (name, float((err / ref).max()))
+
+
+@pytest.mark.parametrize("d,mask", SHAPES, ids=IDS)
 def test_scores_that_overflow_downwards(tb, d, mask):
     """Keys whose scores are below the smallest float have no weight, whichever sign the smaller products of their pieces have."""
     for big, far in ((1e14, -1.2345678e30), (1e14, -1.2378901e30), (3e30, -7.654321e24), (1e-3, -2.9e31)):
