@@ -552,10 +552,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void attn_bf16_kernel(const AttnLa
       fence_o();
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
-        const unsigned mu = __builtin_bit_cast(unsigned, mx[s]);
-        const u32x2 sw = __builtin_amdgcn_permlane32_swap(mu, mu, false, false);   // the other 16 keys of a block sit 32 lanes away
-        const float m2 = max2(__builtin_bit_cast(float, sw[0]), __builtin_bit_cast(float, sw[1]));
-        const float m_cand = max2(m_run[s], m2 * c);
+        const float m_cand = max2(m_run[s], max_of_halves(mx[s]) * c);             // the other 16 keys of a block sit 32 lanes away
         const float alpha = fast_exp2(m_run[s] - m_cand);
         m_run[s] = m_cand;
         m_raise[s] = m_cand + kRescaleGap;

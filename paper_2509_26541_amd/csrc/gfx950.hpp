@@ -68,14 +68,15 @@ __device__ inline void global_to_lds_4(const unsigned char* base, unsigned off, 
 
 // The same load through a buffer descriptor: lane l reads descriptor base + soff + off, where soff
 // is a scalar register.  A gather whose lanes share a moving base then needs no vector arithmetic
-// at all: the base moves in soff.  Raw descriptor (no stride, no swizzle), 2^32 - 1 records, so
-// every offset sum below 2^32 - 4 is in range; offsets are unsigned 32-bit, like the form above.
-__device__ inline u32x4 raw_buffer(const void* base) {
+// at all: the base moves in soff.  Raw descriptor (no stride, no swizzle), by default of 2^32 - 1 bytes, so
+// every offset sum below 2^32 - 4 is in range; offsets are unsigned 32-bit, like the form above.  What lies at or behind
+// `records` (the sum of both offsets counts) is not read and lands as zeros.
+__device__ inline u32x4 raw_buffer(const void* base, unsigned records = 0xffffffffu) {
   const unsigned long long b = reinterpret_cast<unsigned long long>(base);
   u32x4 r;
   r[0] = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(b)));
   r[1] = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(b >> 32))) & 0xffffu;   // 48-bit address, stride 0
-  r[2] = 0xffffffffu;
+  r[2] = records;
   r[3] = 0x00020000u;          // 32-bit data format, raw buffer
   return r;
 }
@@ -86,6 +87,17 @@ __device__ inline void buffer_to_lds_16(const u32x4& rsrc, unsigned soff, unsign
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" : : "s"(lds_addr), "v"(off), "s"(rsrc), "s"(soff) : "memory");
   else
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" : : "s"(lds_addr), "v"(off), "s"(rsrc), "s"(soff));
+}
+
+// The larger of a lane's value and that of the lane in the other half of the wavefront.  (The operands of the swap must not be one
+// register to the compiler: given the same value twice, it takes both results for the first one, which is the lower half's.)
+__device__ __forceinline__ float max_of_halves(float x) {
+  unsigned a = __builtin_bit_cast(unsigned, x), b = a;
+  asm("" : "+v"(b));
+  const auto sw = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(sw[0]), "v"(sw[1]));
+  return r;
 }
 
 // z plus 0 times each of the N floats at p (LDS, 4 N-byte aligned): 0 stays 0 as long as they are finite.
