@@ -180,7 +180,7 @@ int place_lists(const JoinedSteps& js, tasp::BwdLaunch* bp, int32_t* dev_table, 
 
 // How all steps of a forward call run in one launch, possibly with the keys of a query tile dealt to several workgroups.
 struct FwdPlan {
-  bool tile = false;                  // attn_tile_kernel
+  bool tile = false;                  // attn_run_kernel (bf16) or attn_tile_kernel
   bool serial = false;                // a workgroup of it takes all shares of its tile: no partial pairs
   int32_t n_split[tasp::kMaxTasks] = {1, 1};
   size_t part_bytes = 0;              // of the shares' pairs
@@ -230,7 +230,7 @@ double makespan(double n0, double l0, double n1, double l1, double slots) {
                    : rest <= more ? std::max(high + (rounds + 1) * l1, low + (fit + 1 + rounds) * l1) : low + (fit + 2 + rounds) * l1;
 }
 
-// Deals the keys of the query tiles of attn_tile_kernel to n_split[t] workgroups each; keys[t] = keys the
+// Deals the keys of the query tiles of attn_tile_kernel (fp32) and attn_run_kernel (bf16) to n_split[t] workgroups each; keys[t] = keys the
 // last row of task t sees.  Shares are weighed by when the last workgroup would be done: R workgroups of a CU side by side,
 // each at 1 / R of its rate, one by itself at 1 / alone; a workgroup's fixed cost (set-up, first fetches, epilogue) as so many
 // keys more; and with shares the launch that adds them up and the way of the partial pairs through memory.
@@ -282,15 +282,18 @@ void deal_keys(const AttnLaunch& lp, int d, bool fp32, const int64_t* keys, size
   }
 }
 
-// Whether attn_tile_kernel is the faster one for a bf16 launch.  Both kernels' durations are estimated in
+// Whether the kernel for few query tiles is the faster one for a bf16 launch: attn_run_kernel where steps are joined, attn_tile_kernel
+// for a step by itself (`step`).  Both kernels' durations are estimated in
 // (row, key) pairs a CU walks: the work of all workgroups over the 256 CUs, and not less than what
 // the CUs with the most heavy workgroups have.  A workgroup's set-up, first fetches and epilogue count
 // as that many keys more.  The large kernel pads query blocks to 256 rows (d = 64: 384 where that fills
-// as well), the small one computes only the strips of 32 that have rows, walks a key in 1.14 of the
-// time, and a lone workgroup of it uses about half a CU.  Over 110 shapes (3K to 32K tokens, both d,
-// 200 to 4000 workgroups) the choice costs 0.3 % on average against always taking the faster kernel.
-// A step by itself (`step`) is another thing than joined steps: its partial pairs go out in fp32, its short lists
-// leave the small kernel more set-up per key, and there are no shares.  Over 78 shapes of it (256 to 4 700 rows a
+// as well), the small one computes only the strips of 32 that have rows.
+// Joined steps: where nothing is padded the small one walks a key in 1.04 of the large one's time at d = 128 (935 us against 900, 32 heads over
+// 8, 4 096 of 32 768 tokens), in 1.03 at d = 64 against twelve wavefronts and 1.08 against eight that are persistent (4.88 ms against 4.51,
+// 4 heads, batch 4, 16 384 of 131 072 tokens); several of its workgroups share a CU.  Over 164 shapes (1K to 430K tokens, both d) the
+// choice costs 0.3 % on average against always taking the faster kernel, 23 % at most (20 heads of 64, 7 640 of 30 560 tokens).
+// A step by itself is another thing: its partial pairs go out in fp32, its short lists
+// leave the small kernel more set-up per key (a key takes 1.14, a lone workgroup uses about half a CU), and there are no shares.  Over 78 shapes of it (256 to 4 700 rows a
 // step, both d) the small kernel took 0.53 to 1.01 of the large one's time where its estimate was below kStepMargin
 // of the other, and 1.03 to 1.21 above (16 heads over 2, 3 320 rows, no mask: 113.7 us a step against 94.3).
 // At d = 64 a second workgroup on a CU lengthened it by 1.4 (4 and 12 heads, 3 072 rows: 48.8 and 68.2 us).
@@ -303,6 +306,7 @@ bool tile_is_faster(const AttnLaunch& lp, int d, const int64_t* keys, const int3
   double rows8 = 0, rows12 = 0;
   for (int t = 0; t < lp.n_tasks; ++t) { rows8 += padded(lp.task[t].n_q, 256); rows12 += padded(lp.task[t].n_q, 384); }
   const double bm = d == 64 && rows12 * 100 <= rows8 * 101 ? 384 : 256, fixed = bm == 384 ? 400 : 900;
+  const double a_key = step ? 1.14 : d == 128 ? 1.05 : bm == 384 ? 1.1 : 1.03, start = step ? 300 : 100;
   double big = 0, tile = 0, big_one[tasp::kMaxTasks] = {}, tile_one[tasp::kMaxTasks] = {}, big_n[tasp::kMaxTasks] = {}, tile_n[tasp::kMaxTasks] = {};
   bool split = false;
   for (int t = 0; t < lp.n_tasks; ++t) {
@@ -310,7 +314,7 @@ bool tile_is_faster(const AttnLaunch& lp, int d, const int64_t* keys, const int3
     big_one[t] = bm * (k + fixed);
     big_n[t] = padded(n, bm) / bm * lp.Hq * B;
     big += big_one[t] * big_n[t];
-    tile_one[t] = kTileRows * (1.14 * k / ns + 300);
+    tile_one[t] = kTileRows * (a_key * k / ns + start);
     tile_n[t] = padded(n * G, kTileRows) / kTileRows * lp.Hkv * B * ns;
     tile += tile_one[t] * padded(n * G, 32) / kTileRows * lp.Hkv * B * ns;
     split |= ns > 1;
@@ -322,8 +326,8 @@ bool tile_is_faster(const AttnLaunch& lp, int d, const int64_t* keys, const int3
     const double on_one = std::ceil(heavy / kCus);
     return std::max(total / kCus, longest * std::max(on_one > 1 ? pair : alone, on_one));
   };
-  const double sum_shares = split ? 60000 : 0;      // the launch that adds the shares up
-  const double small = duration(tile, tile_one, tile_n, 1.8, step && d == 64 ? 2.5 : 1.8) + sum_shares;
+  const double sum_shares = split ? 40000 : 0;      // the launch that adds the shares up
+  const double small = duration(tile, tile_one, tile_n, step ? 1.8 : 1.6, !step ? 1.4 : d == 64 ? 2.5 : 1.8) + sum_shares;
   return small < (step ? kStepMargin : 1.0) * duration(big, big_one, big_n, 1.0, 1.0);
 }
 

@@ -1231,6 +1231,8 @@ hipError_t launch_attn_tile(const AttnLaunch& p, int d, bool fp32, bool serial, 
   if (serial && fp32 && d == 64) return launch_tile_variant<float, 64, true>(p, stream);
   if (serial && fp32 && d == 128) return launch_tile_variant<float, 128, true>(p, stream);
   if (serial) return hipErrorInvalidValue;
+  // bf16 with joined steps has a kernel of its own; this one has the single steps, and K and V that end within 256 rows of 2^32 bytes
+  if (!fp32 && attn_run_takes(p, d)) return launch_attn_run(p, d, stream);
   if (d == 64) return fp32 ? launch_tile_variant<float, 64>(p, stream) : launch_tile_variant<__bf16, 64>(p, stream);
   if (d == 128) return fp32 ? launch_tile_variant<float, 128>(p, stream) : launch_tile_variant<__bf16, 128>(p, stream);
   return hipErrorInvalidValue;

@@ -10,7 +10,7 @@ namespace tasp {
 
 constexpr int kMaxSeg = 64;      // KV segments one query block can see in one step (2(N-1) for zig-zag)
 constexpr int kMaxTasks = 2;     // query blocks per step (the two half-chunks of the zig-zag layout)
-// Rows (local row, head of the group) of a query tile of attn_tile_kernel.
+// Rows (local row, head of the group) of a query tile of attn_tile_kernel and attn_run_kernel.
 constexpr int tile_rows(bool fp32, int d) { return fp32 && d == 128 ? 256 : 128; }
 // Tiles of 32 keys that attn_tile_kernel<float, 128> adds up in registers before their sums join those in memory.
 constexpr int kSumTiles = 512;
@@ -49,7 +49,7 @@ struct AttnLaunch {
   AttnTask task[kMaxTasks];
   int32_t n_items;    // work items of the launch, for persistent workgroups; filled in by the launcher
   void* out_final;    // not null: the rows are final and go here in the inputs' type, not to o_dst (merge = 0)
-  // attn_tile_kernel: task t's keys are dealt to n_split[t] workgroups per query tile.  Where that is
+  // attn_tile_kernel, attn_run_kernel: task t's keys are dealt to n_split[t] workgroups per query tile.  Where that is
   // more than one, share i leaves its normalised pair in part_o[t], part_lse[t] ([n_split, B, n_q, Hq(, d)],
   // the task's rows only) for launch_combine; tasks with one share write their rows themselves.
   int32_t n_split[kMaxTasks];
@@ -135,6 +135,13 @@ inline hipError_t note_hip(hipError_t e) {
 hipError_t launch_attn_bf16(const AttnLaunch& p, int d, hipStream_t stream);
 // `serial` (fp32, out_final): a workgroup takes all shares of its tile in turn, without part_o and part_lse.
 hipError_t launch_attn_tile(const AttnLaunch& p, int d, bool fp32, bool serial, hipStream_t stream);
+// bf16, joined steps, final rows: what launch_attn_tile passes on.  Implemented in attn_run.hip, whose fetches run up to three tiles past the
+// last key with 32-bit offsets from the share's first key.
+inline bool attn_run_takes(const AttnLaunch& p, int d) {
+  return (d == 64 || d == 128) && p.all_steps != 0 && p.merge == 0 && p.out_final != nullptr &&
+         (static_cast<int64_t>(p.last_key) + 1 + 256) * p.Hkv * d * 2 <= (int64_t{1} << 32);
+}
+hipError_t launch_attn_run(const AttnLaunch& p, int d, hipStream_t stream);
 // After a launch_attn_tile with several shares: the rows of out_final and lse_dst from the pairs of the shares.
 hipError_t launch_combine(const AttnLaunch& p, int d, bool fp32, hipStream_t stream);
 // rows [row0, row0 + rows) of every one of `batch` sequences of L rows each
