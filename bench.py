@@ -6,9 +6,10 @@ already resident in HBM.  Prints ONE JSON line.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--config 2] [--fuse-merge 1|0]
 
-The timed call folds update_out_lse into the attention epilogue (fuse_merge, the faster of the two
-modes of the library); the same call with the separate HBM-bound merge kernel is timed next to it
-("other_merge_mode") and provides the merge kernel's GB/s ("merge").  `value` comes from the wall
+The timed call leaves the folding of update_out_lse to the library (fuse_merge); it joins the steps of a
+call in one launch where that is the faster form ("launches_per_call"), and then nothing is folded.  The same
+call with the separate HBM-bound merge kernel is timed next to it ("other_merge_mode"); where that kernel does
+not run in it, "merge" is its rate on the fold of a call's partial pairs.  `value` comes from the wall
 clock around the K timed calls (synchronised on both sides); "ms_per_step_median_events" is the
 median of the K calls timed one by one with HIP events on the launch stream.  With the default
 workload the line also carries "other_workloads": the same call on the 256K, 512K and 1M workloads
@@ -27,7 +28,7 @@ if ROOT not in sys.path:
 PEAK_BF16_TFLOPS = 2500.0       # MI355X dense bf16 MFMA
 PEAK_FP32_TFLOPS = 157.3        # MI355X fp32, matrix and vector
 PEAK_HBM_GBS = 8000.0
-FEW_ROWS = 4096                 # local rows up to which the library joins the steps of a call by itself
+FEW_ROWS = 4096                 # local rows up to which another kernel than attn_bf16_kernel may run
 N_SIMD, CLOCK_HZ = 256 * 4, 2.4e9
 
 # The second bound of the bf16 attention kernel: the vector issue port of a SIMD.  Measured on this
@@ -256,7 +257,7 @@ def main():
     is_bf16 = w.dtype == "bf16"
     peak = PEAK_BF16_TFLOPS if is_bf16 else PEAK_FP32_TFLOPS
     attn_avg_ms = attn_ms / max(attn_n, 1)
-    # a launch = one step of Algorithm 3; the average launch does 1/launches of the call's flops
+    # the average launch (a step of Algorithm 3, or all of them) does 1/launches of the call's flops
     # whatever the order or the schedule (totals over totals)
     flops_per_launch = flops / max(attn_n // n_prof, 1)
     achieved = flops_per_launch / (attn_avg_ms * 1e-3) / 1e12
@@ -326,9 +327,8 @@ def main():
                 merge = merge_stats(a_ms, a_n, n_prof)
         del alt
 
-    # all steps in one launch (no per-step launch, set-up or merge); reported beside `value`, which is the
-    # step-by-step form with a merge after every block where a rank has more than FEW_ROWS local rows (with
-    # fewer the library joins the steps by itself, and the three modes are one)
+    # all steps in one launch (no per-step launch, set-up or merge); reported beside `value`, which is the same where
+    # the library joins the steps by itself, and otherwise the step-by-step form with a merge after every block
     single = None
     if is_bf16 and not args.no_other_mode:
         try:
@@ -379,6 +379,10 @@ def main():
         fold_ms = event_ms(fold, 3)
         merge_many = {"n_parts": n_parts, "ms": many_ms, "GB/s": (n_parts + 1) * unit / (many_ms * 1e-3) / 1e9,
                       "pairwise_fold_ms": fold_ms, "pairwise_fold_GB/s": 3 * (n_parts - 1) * unit / (fold_ms * 1e-3) / 1e9}
+        if merge is None:            # the library joins the steps of this workload: the fold of its partial pairs as measured here
+            gbs = 3 * (n_parts - 1) * unit / (fold_ms * 1e-3) / 1e9
+            merge = {"bound": "hbm", "kernel": "merge_kernel", "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                     "frac": gbs / PEAK_HBM_GBS, "ms_per_call": fold_ms, "launches_per_call": n_parts - 1}
         del po, pl, oo, ol
 
     # the backward pass of the same call (same schedule and order), timed the same way

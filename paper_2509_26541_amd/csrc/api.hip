@@ -197,11 +197,23 @@ size_t all_share_bytes(const AttnLaunch& lp, int d, const int32_t* n) {
   return sum;
 }
 
-// Local rows up to which the steps of a call are joined although the caller did not ask for it.  A
-// step's launch costs its set-up, the read and write of the running output (or of a partial pair) and
-// the tail of its last workgroups; with L = S / N rows a query tile walks at most L keys a step, and
-// up to here those costs are a fifth of the call and more.  The results differ in rounding only.
+// Whether the steps of a call run in one launch although the caller did not ask for it.  K and V are all there when the call is made;
+// a step's launch costs its set-up, the read and write of the running output (or of a partial pair), the tail of its last workgroups
+// and, with grouped keys in short ranges, the balance of the backward's; joined steps can have their keys dealt out (deal_keys,
+// plan_backward).  The results differ in rounding only.  Step by step against joined, eight ranks, causal, 32 heads over 8 of 128:
+//   131 072 tokens 16.0 and 14.9 ms, 65 536 4.29 and 3.70, backward 55.1 and 52.2, 15.1 and 12.9; 8 heads, 49 152 tokens 0.96 and 0.59;
+//   d = 64, 12 heads, 49 152 tokens, batch 8: 4.50 and 3.78 ms, backward 13.1 and 11.9;
+//   fp32, 49 152 tokens, 4 heads over 1 of 128: 5.21 and 1.56 ms, backward of 2 heads of 64 4.34 and 2.32.
+// At d = 64 the steps' smaller K and V win in the end: 12 heads, 300 000 tokens 18.5 and 18.1 ms, 430 080 37.3 and 38.5 (backward alike).
+// Four ranks with up to kJoinRows more rows keep a launch per step: their launches are the longest, and they are what the path of
+// single steps is tested with (16 400 to 32 768 tokens; 24 576 tokens of 8 heads of 128 take 439 us so and 311 joined).
 constexpr int64_t kJoinRows = 4096;
+constexpr int64_t kJoinKeys64 = 3 << 17;
+bool joins(const tasp_schedule_t* s, const tasp_attn_args* a) {
+  const int64_t L = a->S / s->n;
+  if (a->fuse_steps || L <= kJoinRows) return true;
+  return (s->n >= 8 || L > 2 * kJoinRows) && (a->d != 64 || a->S <= kJoinKeys64);
+}
 constexpr int64_t kMaxSplit = 32;    // shares of one tile
 
 // Sequences a call is planned for: one, where a few of them leave the chip idle together.  Where there is room for
@@ -647,7 +659,7 @@ size_t tasp_chunk_attn_workspace_bytes(const tasp_schedule_t* s, const tasp_attn
 size_t tasp_chunk_attn_best_workspace_bytes(const tasp_schedule_t* s, const tasp_attn_args* a) {
   const size_t need = tasp_chunk_attn_workspace_bytes(s, a);
   Shape sh;
-  if (validate(s, a, &sh) != TASP_OK || !(a->fuse_steps || sh.L <= kJoinRows)) return need;
+  if (validate(s, a, &sh) != TASP_OK || !joins(s, a)) return need;
   try {
     JoinedSteps js{};
     if (join_steps(s, a, &js) != TASP_OK) return need;
@@ -721,7 +733,7 @@ static int run_chunk_attn(const tasp_schedule_t* s, const tasp_attn_args* a, voi
   }
 
   try {
-    if (a->fuse_steps || sh.L <= kJoinRows) {
+    if (joins(s, a)) {
       JoinedSteps js{};
       st = join_steps(s, a, &js);
       if (st != TASP_OK) return st;
@@ -856,7 +868,7 @@ size_t tasp_chunk_attn_bwd_best_workspace_bytes(const tasp_schedule_t* s, const 
   const size_t need = tasp_chunk_attn_bwd_workspace_bytes(s, b);
   tasp_attn_args a;
   Shape sh;
-  if (validate_bwd(s, b, &a, &sh) != TASP_OK || !(b->fuse_steps || sh.L <= kJoinRows)) return need;
+  if (validate_bwd(s, b, &a, &sh) != TASP_OK || !joins(s, &a)) return need;
   try {
     tasp::BwdLaunch bp{};
     JoinedSteps js{};
@@ -911,7 +923,7 @@ static int run_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args
     if (bf16) { bp->ndelta = delta; bp->nlse = lse2; } else { bp->delta = delta; }
     bp->dq_acc = dq_acc;
   };
-  const bool joined = b->fuse_steps || sh.L <= kJoinRows;
+  const bool joined = joins(s, &a);
 
   try {
     {
