@@ -145,65 +145,11 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_kernel(const BwdL
   const int q_last = T.q_pos0 + q_tile_row0 + q_rows_here - 1;
   const int q_first = p.causal ? T.q_pos0 + q_tile_row0 : INT_MAX - 1;   // a key at or before it is seen by every row
 
-  // ---- effective segments of this query tile: drop what the causal mask hides from every row.
-  // The list - from the descriptor, or with all steps in one launch from device memory - is
-  // staged in the (still unused) tile stages first.  The first wavefront builds the list, 64 segments per round: every
-  // lane clips one segment, the positions are running sums (wavefront scans).
-  const int32_t* seg_ext = p.seg_ext[tsk];
-  int* seg_raw = reinterpret_cast<int*>(smem);
-  if (seg_ext != nullptr) {
-    for (int i = tid; i < 2 * T.n_seg; i += NTHREADS) seg_raw[i] = seg_ext[i];
-  } else {
-    for (int i = tid; i < 2 * T.n_seg; i += NTHREADS) seg_raw[i] = p.pool[2 * T.seg0 + i];
-  }
-  __syncthreads();
-  if (wave == 0) {
-    auto visible = [&](int s, int& a) __attribute__((always_inline)) {
-      a = 0;
-      if (s >= T.n_seg) return 0;
-      a = seg_raw[2 * s];
-      const int e = seg_raw[2 * s + 1];
-      return max(0, (p.causal ? min(e, q_last + 1) : e) - a);
-    };
-    int lo = 0, hi = INT_MAX;                      // this workgroup's share of the tile's visible keys
-    if (p.n_split > 1) {
-      int total = 0, a;
-      for (int s0 = 0; s0 < T.n_seg; s0 += 64) total += visible(s0 + lane, a);
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) total += __shfl_xor(total, o);
-      const int chunk = ((total + p.n_split - 1) / p.n_split + BT - 1) / BT * BT;
-      lo = share * chunk;
-      hi = lo + chunk;
-    }
-    int n_base = 0, v_base = 0, end = 0;
-    for (int s0 = 0; s0 < T.n_seg; s0 += 64) {
-      int a;
-      const int len = visible(s0 + lane, a);
-      int sl = len;                                // inclusive scan
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int t2 = __shfl_up(sl, o);
-        if (lane >= o) sl += t2;
-      }
-      const int beg = v_base + sl - len, cb = max(beg, lo), ce = min(beg + len, hi);
-      const unsigned long long has = __builtin_amdgcn_ballot_w64(ce > cb);
-      if (ce > cb) {
-        const int idx = n_base + __builtin_popcountll(has & ((1ull << lane) - 1));
-        e_vbeg[idx] = cb - lo; e_goff[idx] = a + (cb - beg) - (cb - lo);
-      }
-      if (has != 0) end = __shfl(ce, 63 - __builtin_clzll(has)) - lo;
-      n_base += __builtin_popcountll(has);
-      v_base += __shfl(sl, 63);
-    }
-    if (lane == 0) { e_vbeg[n_base] = end; e_n = n_base; }
-  }
-  __syncthreads();
-  const int n_eff = e_n;
-  const int total_keys = e_vbeg[n_eff];
-  const int n_tiles = (total_keys + BT - 1) / BT;
-
-  // ---- stationary side: this lane's query (column lq of the wave's strip), d = 16 ks + 8 h .. +8
-  const int my_q = q_tile_row0 + wave * 32 + lq;
+  // ---- stationary side: this lane's query (column lq of the wave's strip), d = 16 ks + 8 h .. +8.  Asked for first: the way from
+  // memory overlaps the list of the keys.  The strip moves with the work item: wavefront i of a workgroup runs on SIMD i, and
+  // tiles with few rows left leave strips without work.
+  const int strip = (__builtin_amdgcn_readfirstlane(wave) + w_all) & 3;
+  const int my_q = q_tile_row0 + strip * 32 + lq;
   const bool q_valid = my_q < T.n_q;
   const int64_t q_row = T.q_row0 + (q_valid ? my_q : T.n_q - 1);
   const int64_t qoff = bi * p.q_bstride + (q_row * p.Hq + hq) * D;
@@ -224,6 +170,79 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_kernel(const BwdL
   float nl2 = q_valid ? p.nlse[loff] * c : -__builtin_inff();
   float nd = p.ndelta[loff];
   const int q_pos = p.causal ? T.q_pos0 + my_q : INT_MAX - 1;
+
+  // ---- effective segments of this query tile: drop what the causal mask hides from every row.
+  // The list - from the descriptor, or with all steps in one launch from device memory - is
+  // staged in the (still unused) tile stages first.  The first wavefront builds the list, 64 segments per round: every
+  // lane clips one segment, the positions are running sums (wavefront scans).
+  // A list of one segment (joined steps that were not asked for) needs none of that: every wavefront writes the entry it reads.
+  const int32_t* seg_ext = p.seg_ext[tsk];
+  int n_eff, total_keys;
+  if (T.n_seg == 1 && seg_ext == nullptr) {
+    const int a = p.pool[2 * T.seg0], e = p.pool[2 * T.seg0 + 1];
+    int lo = 0;
+    total_keys = max(0, (p.causal ? min(e, q_last + 1) : e) - a);
+    if (p.n_split > 1) {
+      const int chunk = ((total_keys + p.n_split - 1) / p.n_split + BT - 1) / BT * BT;
+      lo = share * chunk;
+      total_keys = max(0, min(total_keys - lo, chunk));
+    }
+    n_eff = total_keys > 0 ? 1 : 0;
+    if (lane == 0) { e_vbeg[0] = 0; e_goff[0] = a + lo; e_vbeg[1] = total_keys; }
+    asm volatile("" ::: "memory");
+  } else {
+    int* seg_raw = reinterpret_cast<int*>(smem);
+    if (seg_ext != nullptr) {
+      for (int i = tid; i < 2 * T.n_seg; i += NTHREADS) seg_raw[i] = seg_ext[i];
+    } else {
+      for (int i = tid; i < 2 * T.n_seg; i += NTHREADS) seg_raw[i] = p.pool[2 * T.seg0 + i];
+    }
+    __syncthreads();
+    if (wave == 0) {
+      auto visible = [&](int s, int& a) __attribute__((always_inline)) {
+        a = 0;
+        if (s >= T.n_seg) return 0;
+        a = seg_raw[2 * s];
+        const int e = seg_raw[2 * s + 1];
+        return max(0, (p.causal ? min(e, q_last + 1) : e) - a);
+      };
+      int lo = 0, hi = INT_MAX;                      // this workgroup's share of the tile's visible keys
+      if (p.n_split > 1) {
+        int total = 0, a;
+        for (int s0 = 0; s0 < T.n_seg; s0 += 64) total += visible(s0 + lane, a);
+  #pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) total += __shfl_xor(total, o);
+        const int chunk = ((total + p.n_split - 1) / p.n_split + BT - 1) / BT * BT;
+        lo = share * chunk;
+        hi = lo + chunk;
+      }
+      int n_base = 0, v_base = 0, end = 0;
+      for (int s0 = 0; s0 < T.n_seg; s0 += 64) {
+        int a;
+        const int len = visible(s0 + lane, a);
+        int sl = len;                                // inclusive scan
+  #pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int t2 = __shfl_up(sl, o);
+          if (lane >= o) sl += t2;
+        }
+        const int beg = v_base + sl - len, cb = max(beg, lo), ce = min(beg + len, hi);
+        const unsigned long long has = __builtin_amdgcn_ballot_w64(ce > cb);
+        if (ce > cb) {
+          const int idx = n_base + __builtin_popcountll(has & ((1ull << lane) - 1));
+          e_vbeg[idx] = cb - lo; e_goff[idx] = a + (cb - beg) - (cb - lo);
+        }
+        if (has != 0) end = __shfl(ce, 63 - __builtin_clzll(has)) - lo;
+        n_base += __builtin_popcountll(has);
+        v_base += __shfl(sl, 63);
+      }
+      if (lane == 0) { e_vbeg[n_base] = end; e_n = n_base; }
+    }
+    __syncthreads();
+    n_eff = e_n;
+    total_keys = e_vbeg[n_eff];
+  }
+  const int n_tiles = (total_keys + BT - 1) / BT;
 
   // ---- loader: this thread fills rows fr + RPP i, physical unit fu of the K and the V tile
   const int fr = tid / C::UNITS, fu = tid % C::UNITS;
@@ -307,6 +326,14 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_kernel(const BwdL
   };
 
   if (n_tiles > 0) fetch(0, 0);
+  if (strip * 32 >= q_rows_here) {             // no rows: fetches only
+    for (int t = 0; t < n_tiles; ++t) {
+      wait_all_loads();
+      __syncthreads();
+      if (t + 1 < n_tiles) fetch(t + 1, (t & 1) ^ 1);
+    }
+    return;
+  }
   // The compiler cannot see the hand-written waits on the tile fetches; left alone it waits inside
   // the loop for the loads of the stationary rows again, before the instructions that read them,
   // and in hardware those waits hit the fetch of the next tile.  Using the values here ends that.
@@ -431,7 +458,6 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 3) void bwd_dkv_kernel(const
   __shared__ __attribute__((aligned(16))) unsigned char smem[2 * C::STAGE_BYTES + VST_BYTES];   // stage: Q tile, dout tile
   __shared__ __attribute__((aligned(256))) float s_nl[2][BT];   // -lse / scale of the tile's queries (-inf: row contributes nothing)
   __shared__ __attribute__((aligned(256))) float s_nd[2][BT];   // -delta of the tile's queries
-  __shared__ int s_tmin, s_tmax;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, lq = lane & 31;
 
@@ -454,18 +480,14 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 3) void bwd_dkv_kernel(const
   const int q_step = SPLIT ? p.kv_split : 1, q_share = SPLIT ? part % q_step : 0;      // every q_step-th query tile is served here, the
   const int hh_beg = SPLIT ? part / q_step : 0, hh_end = SPLIT ? hh_beg + 1 : G;       //   last but q_share one first, for these query heads of the group
 
-  // smallest global position among the keys of the tile: queries before it see none of them
-  if (tid == 0) {
-    int tmin = INT_MAX, tmax = -1;
-    for (int j = 0; j < p.n_rng; ++j) {
-      const int a = max(v0, p.rng_vbeg[j]), b = min(v0 + BS, p.rng_vbeg[j + 1]);
-      if (a < b) {
-        tmin = min(tmin, p.rng_start[j] + (a - p.rng_vbeg[j]));
-        tmax = max(tmax, p.rng_start[j] + (b - 1 - p.rng_vbeg[j]));
-      }
+  // smallest and largest global position among the keys of the tile: queries before the smallest see none of them
+  int tmin = INT_MAX, tmax_keys = -1;
+  for (int j = 0; j < p.n_rng; ++j) {
+    const int a = max(v0, p.rng_vbeg[j]), b = min(v0 + BS, p.rng_vbeg[j + 1]);
+    if (a < b) {
+      tmin = min(tmin, p.rng_start[j] + (a - p.rng_vbeg[j]));
+      tmax_keys = max(tmax_keys, p.rng_start[j] + (b - 1 - p.rng_vbeg[j]));
     }
-    s_tmin = tmin;
-    s_tmax = tmax;
   }
 
   // ---- stationary side: this lane's key (column lq of the wave's strip)
@@ -489,19 +511,9 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 3) void bwd_dkv_kernel(const
     }
   }
   const float c = p.scale * kLog2e;
-  // The compiler cannot see the hand-written waits on the tile fetches; left alone it would wait
-  // for these loads again inside the loop, before every instruction that reads them, and those
-  // waits would then really wait, for the fetch of the next tile.  Using the values here ends that.
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    asm volatile("" : "+v"(kf[ks]));
-    if constexpr (!VLDS) asm volatile("" : "+v"(vf[ks]));
-  }
-  __syncthreads();
-  const int tmin = s_tmin;
   // the element-wise mask is needed for tiles with a query before the last key of the workgroup,
   // and everywhere if the workgroup holds padding keys
-  const int tmax = (v0 + BS > total_keys) ? INT_MAX : (p.causal ? s_tmax : -1);
+  const int tmax = (v0 + BS > total_keys) ? INT_MAX : (p.causal ? tmax_keys : -1);
 
   // ---- the streamed side: the 64-row tiles of every query block that hold a row at or after tmin,
   // for every query head served here.  The walk goes BACKWARDS over the tiles, from the last tile of
@@ -624,6 +636,15 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 3) void bwd_dkv_kernel(const
 
   It cur = settle(It{hh_beg, p.n_blk - 1, tiles_of(p.n_blk - 1) - 1 - q_share});
   if (cur.blk >= 0) fetch(cur, 0);
+  // The compiler cannot see the hand-written waits on the tile fetches; left alone it would wait
+  // for these loads again inside the loop, before every instruction that reads them, and those
+  // waits would then really wait, for the fetch of the next tile.  Using the values here ends that (and the
+  // first tile is on its way beside them).
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    asm volatile("" : "+v"(kf[ks]));
+    if constexpr (!VLDS) asm volatile("" : "+v"(vf[ks]));
+  }
   int stage = 0;
   while (cur.blk >= 0) {
     const It nxt = settle(It{cur.hh + 1, cur.blk, cur.qt});
