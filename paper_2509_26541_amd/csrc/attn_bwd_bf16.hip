@@ -122,23 +122,20 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_kernel(const BwdL
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, lq = lane & 31;
 
   // ---- which (sequence, KV head, task, query tile, query head): KV-head-major inside an XCD
-  const int G = p.Hq / p.Hkv;
+  const int G = divide(p.Hq, p.by_kv_heads);
   const int tiles0 = (p.task[0].n_q + BS - 1) / BS;
   const int tiles1 = p.n_tasks > 1 ? (p.task[1].n_q + BS - 1) / BS : 0;
-  const int per_g = (tiles0 + tiles1) * G * p.n_split, per_b = per_g * p.Hkv;
-  const int w_all = xcd_balanced(blockIdx.x, p.batch * p.Hkv, per_g, xcd_window(D == 64 ? 96 : 64, per_g));
-  if (w_all < 0) return;
-  const int bi = w_all / per_b;
-  const int w = w_all - bi * per_b;
-  const int g = w / per_g;
-  int rem = w - g * per_g;
-  const int share = rem % p.n_split;            // of the tile's keys
-  rem /= p.n_split;
+  int unit, item;
+  if (!xcd_item(p.map, blockIdx.x, unit, item)) return;
+  const int bi = divide(unit, p.by_kv_heads), g = unit - bi * p.Hkv;
+  int rem = divide(item, p.by_n_split);
+  const int share = item - rem * p.n_split;     // of the tile's keys
   const int tsk = rem >= tiles0 * G ? 1 : 0;
   if (tsk) rem -= tiles0 * G;
   // under the causal mask the later query tiles of a block see more keys: they start first
-  const int tile_q = p.causal ? (tsk ? tiles1 : tiles0) - 1 - rem / G : rem / G;
-  const int hq = g * G + rem % G;
+  const int tile_up = divide(rem, p.group);
+  const int tile_q = p.causal ? (tsk ? tiles1 : tiles0) - 1 - tile_up : tile_up;
+  const int hq = g * G + rem - tile_up * G;
   const AttnTask& T = p.task[tsk];
   const int q_tile_row0 = tile_q * BS;
   const int q_rows_here = min(BS, T.n_q - q_tile_row0);
@@ -148,7 +145,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_kernel(const BwdL
   // ---- stationary side: this lane's query (column lq of the wave's strip), d = 16 ks + 8 h .. +8.  Asked for first: the way from
   // memory overlaps the list of the keys.  The strip moves with the work item: wavefront i of a workgroup runs on SIMD i, and
   // tiles with few rows left leave strips without work.
-  const int strip = (__builtin_amdgcn_readfirstlane(wave) + w_all) & 3;
+  const int strip = (__builtin_amdgcn_readfirstlane(wave) + item) & 3;
   const int my_q = q_tile_row0 + strip * 32 + lq;
   const bool q_valid = my_q < T.n_q;
   const int64_t q_row = T.q_row0 + (q_valid ? my_q : T.n_q - 1);
@@ -462,21 +459,18 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 3) void bwd_dkv_kernel(const
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, lq = lane & 31;
 
   // ---- which (sequence, KV head, key tile)
-  const int G = p.Hq / p.Hkv;
+  const int G = divide(p.Hq, p.by_kv_heads);
   const int total_keys = p.rng_vbeg[p.n_rng];
   const int ktiles = (total_keys + BS - 1) / BS;
   const int per_tile = SPLIT ? G * p.kv_split : 1;          // workgroups per key tile
-  const int w_all = xcd_balanced(blockIdx.x, p.batch * p.Hkv, ktiles * per_tile, xcd_window(NW == 8 ? 32 : 96, ktiles * per_tile));
-  if (w_all < 0) return;
   // Split by head, the work list of a KV head is head-major: the workgroups an XCD runs at one time
   // then stream the query tiles of the same head through its L2, as they do without the split
   // (tile-major measured 9 % slower), and each head's tiles still come by falling work.
-  const int bi = w_all / (ktiles * p.Hkv * per_tile);
-  const int w = w_all - bi * (ktiles * p.Hkv * per_tile);
-  const int g = w / (ktiles * per_tile);
-  const int wt = w - g * (ktiles * per_tile);
-  const int v0 = (wt % ktiles) * BS;           // first key of the tile in the virtual concatenation
-  const int part = wt / ktiles;
+  int unit, wt;
+  if (!xcd_item(p.map, blockIdx.x, unit, wt)) return;
+  const int bi = divide(unit, p.by_kv_heads), g = unit - bi * p.Hkv;
+  const int part = divide(wt, p.by_ktiles);
+  const int v0 = (wt - part * ktiles) * BS;    // first key of the tile in the virtual concatenation
   const int q_step = SPLIT ? p.kv_split : 1, q_share = SPLIT ? part % q_step : 0;      // every q_step-th query tile is served here, the
   const int hh_beg = SPLIT ? part / q_step : 0, hh_end = SPLIT ? hh_beg + 1 : G;       //   last but q_share one first, for these query heads of the group
 
@@ -853,7 +847,8 @@ __global__ __launch_bounds__(256) void bwd_zero_kernel(f32x4* __restrict__ dst, 
 
 }  // namespace
 
-hipError_t launch_bwd_dq_bf16(const BwdLaunch& p, int d, hipStream_t stream) {
+hipError_t launch_bwd_dq_bf16(const BwdLaunch& p0, int d, hipStream_t stream) {
+  BwdLaunch p = p0;
   int64_t tiles = 0;
   constexpr int BS = 128;
   for (int t = 0; t < p.n_tasks; ++t) tiles += (p.task[t].n_q + BS - 1) / BS;
@@ -863,13 +858,18 @@ hipError_t launch_bwd_dq_bf16(const BwdLaunch& p, int d, hipStream_t stream) {
   const int64_t units = static_cast<int64_t>(p.batch) * p.Hkv;
   const int64_t blocks = xcd_balanced_blocks(units, items / units);
   if (blocks > INT_MAX) return hipErrorInvalidValue;
+  const int per_unit = static_cast<int>(items / units);
+  p.map = make_xcd_map(static_cast<int32_t>(units), per_unit, xcd_window(d == 64 ? 96 : 64, per_unit));
+  p.by_kv_heads = make_divider(static_cast<uint32_t>(p.Hkv));
+  p.by_n_split = make_divider(static_cast<uint32_t>(p.n_split));
   if (d == 128) return TASP_LAUNCH((bwd_dq_kernel<128>), dim3(static_cast<unsigned>(blocks)), dim3(256), stream, p);
   if (d == 64) return TASP_LAUNCH((bwd_dq_kernel<64>), dim3(static_cast<unsigned>(blocks)), dim3(256), stream, p);
   return hipErrorInvalidValue;
 }
 
 template <int D, int NW, bool VLDS>
-hipError_t launch_dkv_variant(const BwdLaunch& p, hipStream_t stream) {
+hipError_t launch_dkv_variant(const BwdLaunch& p0, hipStream_t stream) {
+  BwdLaunch p = p0;
   constexpr int BS = 32 * NW;
   const int64_t total = p.rng_vbeg[p.n_rng];
   const int64_t items = (total + BS - 1) / BS * p.Hkv * p.batch * (p.kv_split > 0 ? p.Hq / p.Hkv * p.kv_split : 1);
@@ -878,6 +878,10 @@ hipError_t launch_dkv_variant(const BwdLaunch& p, hipStream_t stream) {
   const int64_t units = static_cast<int64_t>(p.batch) * p.Hkv;
   const int64_t blocks = xcd_balanced_blocks(units, items / units);
   if (blocks > INT_MAX) return hipErrorInvalidValue;
+  const int per_unit = static_cast<int>(items / units);
+  p.map = make_xcd_map(static_cast<int32_t>(units), per_unit, xcd_window(NW == 8 ? 32 : 96, per_unit));
+  p.by_kv_heads = make_divider(static_cast<uint32_t>(p.Hkv));
+  p.by_ktiles = make_divider(static_cast<uint32_t>((total + BS - 1) / BS));
   const dim3 grid(static_cast<unsigned>(blocks)), block(64 * NW);
   if (p.kv_split > 0) return TASP_LAUNCH((bwd_dkv_kernel<D, NW, VLDS, true>), grid, block, stream, p);
   return TASP_LAUNCH((bwd_dkv_kernel<D, NW, VLDS, false>), grid, block, stream, p);

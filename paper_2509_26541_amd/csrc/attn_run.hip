@@ -84,8 +84,7 @@ struct RunTask {
   float* part_o;
   float* part_lse;
 };
-// What the kernel needs of an AttnLaunch, with every division prepared (a division by a number that only the launch knows is some
-// forty dependent instructions, and the address of the first load is behind five of them).
+// What the kernel needs of an AttnLaunch, with every division prepared.
 struct RunLaunch {
   const void* q;
   const void* k;
@@ -96,8 +95,8 @@ struct RunLaunch {
   int32_t Hq, Hkv, G, causal, n_keys, batch;
   float scale_log2e;
   int32_t items0;                               // work items of a unit (sequence, KV head) that belong to the first task
-  int32_t per_unit, window, units, len, shared; // as in xcd_balanced: items of a unit; units met together; units and items of a group of XCDs; XCDs of a group (a power of two)
-  Divider by_window, by_full, by_rest, by_kv_heads, by_group;
+  XcdMap map;
+  Divider by_kv_heads, by_group;
   RunTask task[kMaxTasks];
 };
 
@@ -109,12 +108,9 @@ __global__ __launch_bounds__(RunCfg<D>::NTHREADS, D == 64 ? 3 : 2) void attn_run
 
   const int thread = threadIdx.x, wave_u = __builtin_amdgcn_readfirstlane(thread >> 6);
   const int lane = thread & 63, h = lane >> 5, lq = lane & 31;
-  // ---- which (sequence, KV head) unit and which item of it: xcd_balanced
-  const int xcd = blockIdx.x & 7, j = static_cast<int>(blockIdx.x >> 3) * p.shared + (xcd & (p.shared - 1));
-  if (j >= p.len) return;
-  const int w0 = divide(j, p.by_window) * p.window, wn = min(p.units - w0, p.window), jj = j - w0 * p.per_unit;
-  const int item = divide(jj, wn == p.window ? p.by_full : p.by_rest);
-  const int unit = xcd / p.shared * p.units + w0 + jj - item * wn;
+  // ---- which (sequence, KV head) and which item of it
+  int unit, item;
+  if (!xcd_item(p.map, blockIdx.x, unit, item)) return;
   const int bi = divide(unit, p.by_kv_heads), g = unit - bi * p.Hkv;
   const bool second = item >= p.items0;
   const RunTask& T = p.task[second ? 1 : 0];
@@ -123,7 +119,7 @@ __global__ __launch_bounds__(RunCfg<D>::NTHREADS, D == 64 ? 3 : 2) void attn_run
   const int tile = p.causal ? T.tiles - 1 - tile_up : tile_up;
   // The strip of 32 rows a wavefront takes moves with the work item: wavefront i of a workgroup runs on
   // SIMD i, and tiles with few rows left leave strips without work.
-  const int strip = (wave_u + j) % NW, left = T.rows - tile * BM;
+  const int strip = (wave_u + item) % NW, left = T.rows - tile * BM;
   const int m = tile * BM + strip * 32 + lq, mc = min(m, T.rows - 1), q_row = divide(mc, p.by_group);
   const bool q_valid = m < T.rows;
   const int64_t q_idx = static_cast<int64_t>(T.q_row0 + q_row) * p.Hq + g * p.G + mc - q_row * p.G;
@@ -436,14 +432,7 @@ hipError_t launch_variant(const AttnLaunch& p, hipStream_t stream) {
   if (per_unit * units > INT_MAX) return hipErrorInvalidValue;
   const int64_t blocks = xcd_balanced_blocks(units, per_unit);
   if (blocks > INT_MAX) return hipErrorInvalidValue;
-  r.shared = xcd_balanced_share(static_cast<int>(units));
-  r.per_unit = static_cast<int32_t>(per_unit);
-  r.units = static_cast<int32_t>(units / (8 / r.shared));
-  r.len = r.units * r.per_unit;
-  r.window = std::min(xcd_window(D == 64 ? 96 : 64, r.per_unit), r.units);
-  r.by_window = make_divider(static_cast<uint32_t>(r.window) * r.per_unit);
-  r.by_full = make_divider(static_cast<uint32_t>(r.window));
-  r.by_rest = make_divider(static_cast<uint32_t>(r.units % r.window != 0 ? r.units % r.window : 1));
+  r.map = make_xcd_map(static_cast<int32_t>(units), static_cast<int32_t>(per_unit), xcd_window(D == 64 ? 96 : 64, static_cast<int>(per_unit)));
   r.by_kv_heads = make_divider(static_cast<uint32_t>(r.Hkv));
   r.by_group = make_divider(static_cast<uint32_t>(r.G));
   return TASP_LAUNCH((attn_run_kernel<D>), dim3(static_cast<unsigned>(blocks)), dim3(RunCfg<D>::NTHREADS), stream, r);

@@ -112,6 +112,9 @@ struct BwdLaunch {
   float* part_dq;
   int64_t part_stride;
   void* dq_final;
+  // the work items of the launch and what else the bf16 kernels divide by; filled in by the launchers
+  XcdMap map;
+  Divider by_kv_heads, by_n_split, by_ktiles;
 };
 static_assert(sizeof(BwdLaunch) <= 4096, "kernel arguments");
 
