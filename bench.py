@@ -276,7 +276,7 @@ def main():
         if rec.get("attn_bf16_hip_sha16") == sha:
             traffic = rec.get("attn_bytes_per_launch")
     roofline = {
-        "bound": "mfma", "kernel": "attn_tile_kernel" if not is_bf16 else "attn_bf16_kernel" if w.L > FEW_ROWS else "attn_bf16_kernel or attn_tile_kernel",
+        "bound": "mfma", "kernel": "attn_tile_kernel" if not is_bf16 else "attn_bf16_kernel" if w.L > FEW_ROWS else "attn_bf16_kernel or attn_run_kernel",
         "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak, "traffic": traffic,
         "avg_launch_ms": attn_avg_ms, "launches_per_call": attn_n // n_prof,
     }
