@@ -552,7 +552,13 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void attn_bf16_kernel(const AttnLa
       fence_o();
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
-        const float m_cand = max2(m_run[s], max_of_halves(mx[s]) * c);             // the other 16 keys of a block sit 32 lanes away
+        // The other 16 keys of a block sit 32 lanes away.  The lower half's maximum will do as long as the upper one's is within the gap
+        // that scores may have anyway: what follows rounds the probabilities, so the reference stays where it is if it can.
+        float lower, upper;
+        both_halves(mx[s], lower, upper);
+        lower *= c;
+        upper *= c;
+        const float m_cand = max2(m_run[s], upper > lower + kRescaleGap ? upper : lower);
         const float alpha = fast_exp2(m_run[s] - m_cand);
         m_run[s] = m_cand;
         m_raise[s] = m_cand + kRescaleGap;

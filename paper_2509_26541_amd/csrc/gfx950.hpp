@@ -89,14 +89,20 @@ __device__ inline void buffer_to_lds_16(const u32x4& rsrc, unsigned soff, unsign
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" : : "s"(lds_addr), "v"(off), "s"(rsrc), "s"(soff));
 }
 
-// The larger of a lane's value and that of the lane in the other half of the wavefront.  (The operands of the swap must not be one
-// register to the compiler: given the same value twice, it takes both results for the first one, which is the lower half's.)
-__device__ __forceinline__ float max_of_halves(float x) {
+// A lane's value as the lower and the upper half of the wavefront have it.  (The results are copied to scalars first: a
+// __builtin_bit_cast of an element of a vector reads its first element, whichever was named.)
+__device__ __forceinline__ void both_halves(float x, float& lower, float& upper) {
   unsigned a = __builtin_bit_cast(unsigned, x), b = a;
   asm("" : "+v"(b));
   const auto sw = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-  float r;
-  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(sw[0]), "v"(sw[1]));
+  const unsigned lo = sw[0], up = sw[1];
+  lower = __builtin_bit_cast(float, lo);
+  upper = __builtin_bit_cast(float, up);
+}
+__device__ __forceinline__ float max_of_halves(float x) {
+  float lower, upper, r;
+  both_halves(x, lower, upper);
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(lower), "v"(upper));
   return r;
 }
 
