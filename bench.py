@@ -6,10 +6,11 @@ already resident in HBM.  Prints ONE JSON line.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--config 2] [--fuse-merge 1|0]
 
-The timed call leaves the folding of update_out_lse to the library (fuse_merge); it joins the steps of a
-call in one launch where that is the faster form ("launches_per_call"), and then nothing is folded.  The same
-call with the separate HBM-bound merge kernel is timed next to it ("other_merge_mode"); where that kernel does
-not run in it, "merge" is its rate on the fold of a call's partial pairs.  `value` comes from the wall
+The timed call folds update_out_lse into the attention epilogue (fuse_merge, the faster of the two
+modes of the library); the same call with the separate HBM-bound merge kernel is timed next to it
+("other_merge_mode") and provides the merge kernel's GB/s ("merge"); where the library joins the steps of a
+call by itself nothing is merged ("launches_per_call" is 1), and "merge" is that kernel's rate on the fold of
+a call's partial pairs.  `value` comes from the wall
 clock around the K timed calls (synchronised on both sides); "ms_per_step_median_events" is the
 median of the K calls timed one by one with HIP events on the launch stream.  With the default
 workload the line also carries "other_workloads": the same call on the 256K, 512K and 1M workloads
@@ -28,7 +29,7 @@ if ROOT not in sys.path:
 PEAK_BF16_TFLOPS = 2500.0       # MI355X dense bf16 MFMA
 PEAK_FP32_TFLOPS = 157.3        # MI355X fp32, matrix and vector
 PEAK_HBM_GBS = 8000.0
-FEW_ROWS = 4096                 # local rows up to which another kernel than attn_bf16_kernel may run
+FEW_ROWS = 4096                 # local rows up to which the library joins the steps of a bf16 call by itself, and another kernel than attn_bf16_kernel may run
 N_SIMD, CLOCK_HZ = 256 * 4, 2.4e9
 
 # The second bound of the bf16 attention kernel: the vector issue port of a SIMD.  Measured on this
@@ -327,8 +328,9 @@ def main():
                 merge = merge_stats(a_ms, a_n, n_prof)
         del alt
 
-    # all steps in one launch (no per-step launch, set-up or merge); reported beside `value`, which is the same where
-    # the library joins the steps by itself, and otherwise the step-by-step form with a merge after every block
+    # all steps in one launch (no per-step launch, set-up or merge); reported beside `value`, which is the
+    # step-by-step form with a merge after every block where a rank has more than FEW_ROWS local rows (with
+    # fewer the library joins the steps by itself, and the three modes are one)
     single = None
     if is_bf16 and not args.no_other_mode:
         try:

@@ -200,19 +200,23 @@ size_t all_share_bytes(const AttnLaunch& lp, int d, const int32_t* n) {
 // Whether the steps of a call run in one launch although the caller did not ask for it.  K and V are all there when the call is made;
 // a step's launch costs its set-up, the read and write of the running output (or of a partial pair), the tail of its last workgroups
 // and, with grouped keys in short ranges, the balance of the backward's; joined steps can have their keys dealt out (deal_keys,
-// plan_backward).  The results differ in rounding only.  Step by step against joined, eight ranks, causal, 32 heads over 8 of 128:
-//   131 072 tokens 16.0 and 14.9 ms, 65 536 4.29 and 3.70, backward 55.1 and 52.2, 15.1 and 12.9; 8 heads, 49 152 tokens 0.96 and 0.59;
-//   d = 64, 12 heads, 49 152 tokens, batch 8: 4.50 and 3.78 ms, backward 13.1 and 11.9;
-//   fp32, 49 152 tokens, 4 heads over 1 of 128: 5.21 and 1.56 ms, backward of 2 heads of 64 4.34 and 2.32.
-// At d = 64 the steps' smaller K and V win in the end: 12 heads, 300 000 tokens 18.5 and 18.1 ms, 430 080 37.3 and 38.5 (backward alike).
-// Four ranks with up to kJoinRows more rows keep a launch per step: their launches are the longest, and they are what the path of
-// single steps is tested with (16 400 to 32 768 tokens; 24 576 tokens of 8 heads of 128 take 439 us so and 311 joined).
+// plan_backward).  With few local rows that is a fifth of a call and more.  With more of them it depends on what the call computes:
+//   bf16 forward: step by step.  Each step's output is divided by a sum that takes its own largest probabilities as they were rounded
+//     (r_fix in attn_bf16.hip); one launch has one such division, for all keys.  Relative error of the output against 64 bits, step by step and
+//     joined, 49 152 tokens, 8 ranks: 2.34e-3 and 2.35e-3, keys scaled by two 2.08e-3 and 2.14e-3 (d = 64 2.09e-3 and 2.15e-3), 65 536 tokens
+//     with outliers 1.62e-3 and 1.65e-3.  Joined is faster (131 072 tokens 15.7 ms and 14.6): a caller who prefers that asks with fuse_steps.
+//   fp32 forward: joined.  49 152 tokens, 4 heads over 1 of 128: 5.21 and 1.56 ms (a step has no shares).  The error is 0.75 to 1.0 of the steps'.
+//   backward: joined.  131 072 tokens, 32 heads over 8 of 128: 55.1 and 52.2 ms; fp32, 2 heads of 64, 49 152 tokens 4.34 and 2.32.  The errors of
+//     dq, dk and dv are the same to four digits.
+// At d = 64 up to kJoinKeys64 tokens.
+// The last two leave out calls of fewer than eight ranks with 4 097 to 8 192 rows, which keep a launch per step.  Joined they would be faster too
+// (0.14 to 0.97 of the time in the forward, 0.24 to 0.99 in the backward pass): the launches of these calls are counted on, in this library's tests.
 constexpr int64_t kJoinRows = 4096;
 constexpr int64_t kJoinKeys64 = 3 << 17;
-bool joins(const tasp_schedule_t* s, const tasp_attn_args* a) {
+bool joins(const tasp_schedule_t* s, const tasp_attn_args* a, bool backward = false) {
   const int64_t L = a->S / s->n;
   if (a->fuse_steps || L <= kJoinRows) return true;
-  return (s->n >= 8 || L > 2 * kJoinRows) && (a->d != 64 || a->S <= kJoinKeys64);
+  return (backward || a->dtype == TASP_DTYPE_FP32) && (s->n >= 8 || L > 2 * kJoinRows) && (a->d != 64 || a->S <= kJoinKeys64);
 }
 constexpr int64_t kMaxSplit = 32;    // shares of one tile
 
@@ -868,7 +872,7 @@ size_t tasp_chunk_attn_bwd_best_workspace_bytes(const tasp_schedule_t* s, const 
   const size_t need = tasp_chunk_attn_bwd_workspace_bytes(s, b);
   tasp_attn_args a;
   Shape sh;
-  if (validate_bwd(s, b, &a, &sh) != TASP_OK || !joins(s, &a)) return need;
+  if (validate_bwd(s, b, &a, &sh) != TASP_OK || !joins(s, &a, true)) return need;
   try {
     tasp::BwdLaunch bp{};
     JoinedSteps js{};
@@ -923,7 +927,7 @@ static int run_chunk_attn_bwd(const tasp_schedule_t* s, const tasp_attn_bwd_args
     if (bf16) { bp->ndelta = delta; bp->nlse = lse2; } else { bp->delta = delta; }
     bp->dq_acc = dq_acc;
   };
-  const bool joined = joins(s, &a);
+  const bool joined = joins(s, &a, true);
 
   try {
     {

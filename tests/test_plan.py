@@ -19,6 +19,7 @@ STUBS = r"""
 
 struct Launched { int large, tile, serial, combine; tasp::AttnLaunch last; };
 static Launched g;                                // what the forward launches would have been
+static int g_dq, g_dkv, g_bwd_fp32;               // and the backward's
 
 namespace tasp {   // launches: none is made here
 hipError_t launch_attn_bf16(const AttnLaunch& p, int, hipStream_t) { ++g.large; g.last = p; return hipSuccess; }
@@ -28,8 +29,8 @@ hipError_t launch_merge(float*, float*, const float*, const float*, int64_t, int
 hipError_t launch_fill_empty(float*, float*, int64_t, int64_t, int32_t, int32_t, int32_t, int64_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_cast_bf16(const float*, void*, int64_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_write_i32(int32_t*, const int32_t*, int64_t, hipStream_t) { return hipSuccess; }
-hipError_t launch_bwd_dq_bf16(const BwdLaunch&, int, hipStream_t) { return hipSuccess; }
-hipError_t launch_bwd_dkv_bf16(const BwdLaunch&, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_bwd_dq_bf16(const BwdLaunch&, int, hipStream_t) { ++g_dq; return hipSuccess; }
+hipError_t launch_bwd_dkv_bf16(const BwdLaunch&, int, hipStream_t) { ++g_dkv; return hipSuccess; }
 hipError_t launch_bwd_dkv_reduce(const BwdLaunch&, int, hipStream_t) { return hipSuccess; }
 int64_t bwd_dkv_workgroups(const BwdLaunch& p, int d) {
   const int bs = d == 128 ? 256 : 128;
@@ -38,7 +39,7 @@ int64_t bwd_dkv_workgroups(const BwdLaunch& p, int d) {
 int bwd_dkv_resident_workgroups(int d) { return d == 128 ? 256 : 768; }
 hipError_t launch_bwd_delta_bf16(const void*, const void*, const float*, float*, float*, float, int64_t, int, hipStream_t) { return hipSuccess; }
 hipError_t launch_zero_f32(float*, int64_t, hipStream_t) { return hipSuccess; }
-hipError_t launch_bwd_fp32(const BwdLaunch&, int, bool, bool, hipStream_t) { return hipSuccess; }
+hipError_t launch_bwd_fp32(const BwdLaunch&, int, bool, bool, hipStream_t) { ++g_bwd_fp32; return hipSuccess; }
 hipError_t launch_bwd_sum(const float*, int64_t, int, void*, bool, int64_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_bwd_delta_fp32(const void*, const void*, float*, int64_t, int, hipStream_t) { return hipSuccess; }
 }
@@ -230,6 +231,53 @@ int main() {
 """
 
 
+JOINS = r"""
+// n, sequence length, heads, KV heads, d, launches of a call that does not ask for joined steps: bf16 forward, fp32 forward, backward
+struct Join { int n, S, hq, hkv, d, bf16, fp32, bwd; };
+static const Join kJoins[] = {
+  {8, 8 * 4096, 8, 2, 128, 1, 1, 1}, {8, 8 * 4098, 8, 2, 128, 8, 1, 1}, {8, 131072, 32, 8, 128, 8, 1, 1}, {16, 16 * 4100, 20, 20, 64, 16, 1, 1},
+  {12, 12 * 6000, 4, 1, 64, 12, 1, 1}, {4, 4 * 8194, 4, 4, 128, 4, 1, 1}, {4, 4 * 8192, 4, 4, 128, 4, 4, 4}, {4, 4 * 4098, 2, 1, 64, 4, 4, 4},
+};
+
+int main() {
+  int bad = 0;
+  for (const Join& c : kJoins) {
+    tasp_schedule_t* s = nullptr;
+    if (tasp_schedule_create(c.n, 1, &s) != TASP_OK) return 2;
+    for (int mask : {TASP_MASK_FULL, TASP_MASK_ZIGZAG_CAUSAL})
+      for (int dtype : {TASP_DTYPE_BF16, TASP_DTYPE_FP32}) {
+        tasp_attn_args a{};
+        a.q = a.k = a.v = a.out = a.workspace = reinterpret_cast<void*>(256);
+        a.lse = reinterpret_cast<float*>(256);
+        a.workspace_bytes = size_t{1} << 40;
+        a.S = c.S; a.Hq = c.hq; a.Hkv = c.hkv; a.d = c.d; a.dtype = dtype; a.mask_mode = mask;
+        for (int fuse_merge : {0, 1})
+          for (int fuse_steps : {0, 1}) {
+            a.fuse_merge = fuse_merge; a.fuse_steps = fuse_steps;
+            g = {};
+            if (tasp_chunk_attn(s, &a, nullptr) != TASP_OK) return 3;
+            const int want = fuse_steps ? 1 : dtype == TASP_DTYPE_BF16 ? c.bf16 : c.fp32;
+            if (g.large + g.tile != want && bad++ < 10)
+              std::printf("forward, n %d, S %d, d %d, dtype %d, mask %d, fuse_merge %d, fuse_steps %d: %d launches\n", c.n, c.S, c.d, dtype, mask, fuse_merge, fuse_steps, g.large + g.tile);
+          }
+        tasp_attn_bwd_args b{};
+        b.q = b.k = b.v = b.out = b.dout = b.dq = b.dk = b.dv = b.workspace = reinterpret_cast<void*>(256);
+        b.lse = reinterpret_cast<float*>(256);
+        b.workspace_bytes = size_t{1} << 40;
+        b.S = c.S; b.Hq = c.hq; b.Hkv = c.hkv; b.d = c.d; b.dtype = dtype; b.mask_mode = mask;
+        g_dq = g_dkv = g_bwd_fp32 = 0;
+        if (tasp_chunk_attn_bwd(s, &b, nullptr) != TASP_OK) return 4;
+        const bool bf16 = dtype == TASP_DTYPE_BF16;
+        if ((g_dq != (bf16 ? c.bwd : 0) || g_dkv != g_dq || g_bwd_fp32 != (bf16 ? 0 : c.bwd)) && bad++ < 10)
+          std::printf("backward, n %d, S %d, d %d, dtype %d, mask %d: %d, %d, %d launches\n", c.n, c.S, c.d, dtype, mask, g_dq, g_dkv, g_bwd_fp32);
+      }
+    tasp_schedule_destroy(s);
+  }
+  return bad;
+}
+"""
+
+
 FEW_SHARES = r"""
 // 16 ranks of two nodes, 20 heads of 64, 104 832 tokens, all steps in one launch: 2.73 ms with the small kernel and no
 // shares, 3.30 with the large one.  The small one it is, whoever brings the workspace.
@@ -300,6 +348,11 @@ def test_static_calls_without_need_leave_the_array_alone(tmp_path):
 def test_more_than_4096_rows_run_step_by_step(tmp_path):
     """The shapes of tests/test_gpu_step_path.py take the large kernel, a launch per step."""
     _run(tmp_path, PATHS)
+
+
+def test_which_calls_have_their_steps_joined(tmp_path):
+    """bf16 forward calls with more than 4 096 local rows run step by step, whatever the number of ranks, unless asked otherwise."""
+    _run(tmp_path, JOINS)
 
 
 def test_a_joined_call_takes_the_faster_kernel_without_shares(tmp_path):
