@@ -139,7 +139,7 @@ int tasp_step_segments(const tasp_schedule_t* s, int64_t S, int32_t mask_mode, i
  *                 form in which a step can start as soon as its sub-chunks have arrived).  With few
  *                 local rows (L <= 4096) the library joins the steps as for 1: K and V are there,
  *                 and the launches would cost more than their work; fp32 calls with more rows as
- *                 well, where N >= 8 or L > 8192 (d = 64: and S <= 393216);
+ *                 well, where N >= 8 or L > 8192;
  *              1: ONE launch walks the keys of all N steps and carries the running max / sum /
  *                 output across them, so no partial pair is ever written or merged (the log-sum-exp
  *                 rescale happens in registers).  It takes the keys by position: over the steps every
@@ -292,9 +292,11 @@ double tasp_chunk_attn_flops(const tasp_schedule_t* s, const tasp_attn_args* a);
  * All tensor pointers are DEVICE pointers, 16-byte aligned, dense row-major, laid out as for
  * tasp_chunk_attn: q, out, dout, dq [B, L, Hq, d]; k, v, dk, dv [B, S, Hkv, d]; lse [B, L, Hq] fp32
  * (out and lse as written by tasp_chunk_attn on the same inputs).  dtype is TASP_DTYPE_BF16 (bf16
- * matrix instructions) or TASP_DTYPE_FP32 (fp32 matrix instructions, all arithmetic fp32); d is 64 or 128.  Every row of dq, dk and dv is written.
- * Where L <= 4096, N >= 8 or L > 8192 (beyond L = 4096, d = 64: and S <= 393216) the steps are joined, one dq and one dk/dv launch for all of them (fp32: one for both), as
- * with fuse_steps but with the keys taken by position: over the steps every key is met once.
+ * matrix instructions) or TASP_DTYPE_FP32 (fp32 matrix instructions, all arithmetic fp32); d is 64 or
+ * 128.  Every row of dq, dk and dv is written.
+ * Where L <= 4096, N >= 8 or L > 8192 the steps are joined, one dq and one dk/dv launch for all of them
+ * (fp32: one for both), as with fuse_steps but with the keys taken by position: over the steps every key is
+ * met once.
  * workspace: device, 256-byte aligned, at least tasp_chunk_attn_bwd_workspace_bytes() (the delta
  * vector; for bf16 also lse scaled to base 2 in the same layout, both with one more entry behind the
  * last row, which is why B*L*Hq must stay below 2^30 there (TASP_EUNSUPPORTED_SHAPE otherwise), an

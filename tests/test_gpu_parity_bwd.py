@@ -418,8 +418,8 @@ def test_kv_tensors_of_exactly_2_to_32_bytes(tb):
 
 def test_sequence_just_below_2_to_24_tokens(tb):
     """The longest sequence the bf16 kernels take (token index times row bytes by a 24-bit multiply):
-    S = 2^24 - 64 tokens, one head of 64 columns, 32 ranks; rank 0 reads up to the last token.  Forward
-    and backward step by step (the single-launch form is refused at this rank count), sampled rows."""
+    S = 2^24 - 64 tokens, one head of 64 columns, 32 ranks; rank 0 reads up to the last token.  Forward step by
+    step, backward joined by the library (the form with fuse_steps is refused at this rank count), sampled rows."""
     S, d, n, rank = (1 << 24) - 64, 64, 32, 0
     w1 = wl.Workload("max_tokens", n, rank, S, 1, 1, d, "bf16", wl.ZIGZAG_CAUSAL, seed=wl.BASE_SEED + 797)
     L, Hh = S // n, S // (2 * n)

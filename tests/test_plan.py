@@ -236,7 +236,7 @@ JOINS = r"""
 struct Join { int n, S, hq, hkv, d, bf16, fp32, bwd; };
 static const Join kJoins[] = {
   {8, 8 * 4096, 8, 2, 128, 1, 1, 1}, {8, 8 * 4098, 8, 2, 128, 8, 1, 1}, {8, 131072, 32, 8, 128, 8, 1, 1}, {16, 16 * 4100, 20, 20, 64, 16, 1, 1},
-  {12, 12 * 6000, 4, 1, 64, 12, 1, 1}, {4, 4 * 8194, 4, 4, 128, 4, 1, 1}, {4, 4 * 8192, 4, 4, 128, 4, 4, 4}, {4, 4 * 4098, 2, 1, 64, 4, 4, 4},
+  {12, 12 * 6000, 4, 1, 64, 12, 1, 1}, {8, 430080, 4, 4, 64, 8, 1, 1}, {4, 4 * 8194, 4, 4, 128, 4, 1, 1}, {4, 4 * 8192, 4, 4, 128, 4, 4, 4}, {4, 4 * 4098, 2, 1, 64, 4, 4, 4},
 };
 
 int main() {
