@@ -140,7 +140,8 @@ __global__ __launch_bounds__(RunCfg<D>::NTHREADS, D == 64 ? 3 : 2) void attn_run
   const int64_t head0 = (bi * p.kv_bstride + static_cast<int64_t>(g) * D) * 2 + static_cast<int64_t>(goff) * row_bytes;
   const unsigned records = n_keys > 0 ? static_cast<unsigned>(n_keys - 1) * row_bytes + C::RB : 0u;
   // Records end with the share's last key: what is fetched behind it, in the last tile and by the fetches that run ahead, comes
-  // as zeros.  (The range check adds the scalar offset; offsets stay below 2^32, see launch_attn_run.)
+  // as zeros.  The range check of a raw buffer is "vector offset >= records - scalar offset", so a scalar offset stops at the
+  // records' end: beyond it the difference would be below zero.  (Before that, offsets stay below 2^32, see attn_run_takes.)
   const u32x4 k_buf = raw_buffer(static_cast<const unsigned char*>(p.k) + head0, records), v_buf = raw_buffer(static_cast<const unsigned char*>(p.v) + head0, records);
   const int fr = C::RPW * wave_u + lane / C::UNITS, fu = lane % C::UNITS;
   const unsigned lane_row = static_cast<unsigned>(lane / C::UNITS) * row_bytes;
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(RunCfg<D>::NTHREADS, D == 64 ? 3 : 2) void attn_run
     unsigned char* const dst = smem + (V ? 2 * C::TILE_BYTES : 0) + st * C::TILE_BYTES + wave_u * 1024;
     const unsigned at = static_cast<unsigned>(u * BT + C::RPW * wave_u) * row_bytes;
 #pragma unroll
-    for (int i = 0; i < C::PASSES; ++i) buffer_to_lds_16<true>(V ? v_buf : k_buf, at + i * C::RPP * row_bytes, V ? v_lane : k_lane, dst + i * C::NTHREADS * 16);
+    for (int i = 0; i < C::PASSES; ++i) buffer_to_lds_16<true>(V ? v_buf : k_buf, min(at + i * C::RPP * row_bytes, records), V ? v_lane : k_lane, dst + i * C::NTHREADS * 16);
   };
   constexpr std::false_type K{};
   constexpr std::true_type V{};

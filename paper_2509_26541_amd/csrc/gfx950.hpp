@@ -70,7 +70,7 @@ __device__ inline void global_to_lds_4(const unsigned char* base, unsigned off, 
 // is a scalar register.  A gather whose lanes share a moving base then needs no vector arithmetic
 // at all: the base moves in soff.  Raw descriptor (no stride, no swizzle), by default of 2^32 - 1 bytes, so
 // every offset sum below 2^32 - 4 is in range; offsets are unsigned 32-bit, like the form above.  What lies at or behind
-// `records` (the sum of both offsets counts) is not read and lands as zeros.
+// `records` (the sum of both offsets counts; soff by itself is not to exceed it) is not read and lands as zeros.
 __device__ inline u32x4 raw_buffer(const void* base, unsigned records = 0xffffffffu) {
   const unsigned long long b = reinterpret_cast<unsigned long long>(base);
   u32x4 r;

@@ -50,6 +50,26 @@ def result_hazards(instructions, need=12):
     return sorted(bad)
 
 
+def unbounded_offsets(instructions):
+    """Direct loads whose scalar offset is not the result of a minimum (with the descriptor's records: the range check takes their
+    difference, which must not be below zero)."""
+    bad = []
+    for i, (line, s) in enumerate(instructions):
+        if not s.startswith("buffer_load_dwordx4"):
+            continue
+        offset = s.split(",")[2].split()[0]
+        writer = next((t for _, t in reversed(instructions[:i]) if not t.endswith(":") and t.split()[1:2] == [offset + ","]), "")
+        if not writer.startswith("s_min_u32"):
+            bad.append((line, s, writer))
+    return bad
+
+
+def test_offset_checker_flags_a_planted_sum():
+    load = "buffer_load_dwordx4 v1, s[0:3], s9 offen lds"
+    assert unbounded_offsets([(1, "s_add_i32 s9, s8, s7"), (2, "s_min_u32 s9, s9, s6"), (3, load)]) == []
+    assert [b[0] for b in unbounded_offsets([(1, "s_min_u32 s9, s8, s6"), (2, "s_add_i32 s9, s9, s7"), (3, load)])] == [3]
+
+
 def test_hazard_checker_flags_a_planted_copy():
     mfma = "v_mfma_f32_32x32x16_bf16 v[0:15], v[16:19], v[20:23], v[0:15]"
     assert [b[0] for b in result_hazards([(1, mfma), (2, "v_mov_b32_e32 v30, v15")])] == [2]
@@ -72,6 +92,7 @@ def test_generated_code(tmp_path):
         assert result_hazards(ins) == [], name
         loads = [s for _, s in ins if s.startswith("buffer_load_dwordx4")]
         assert len(loads) >= 8 and all(s.endswith("offen lds") and ", s[" in s for s in loads), (name, loads[:2])
+        assert unbounded_offsets(ins) == [], name
 
 
 # ---------------------------------------------------------------- against the oracle
@@ -119,3 +140,36 @@ def test_joined_steps_all_rows(case):
         assert err <= 4 * 2.0 ** -9, (name, b, err)
     for b in range(2, B):                              # the same sequences again
         assert torch.equal(out[b], out[b % 2]) and torch.equal(lse[b], lse[b % 2])
+
+
+# N, S, Hq, Hkv, d, sequences: key counts with one row in the last tile, just below and above one, two and three tiles, and shares
+TAILS = [(4, 4, 2, 1, 64, 1), (4, 4, 2, 1, 128, 1), (4, 60, 2, 1, 128, 1), (4, 68, 2, 1, 64, 1), (4, 68, 2, 2, 128, 1), (4, 124, 2, 2, 64, 1), (4, 132, 2, 1, 64, 1),
+         (4, 132, 2, 1, 128, 1), (4, 2404, 2, 1, 64, 1), (4, 2404, 2, 1, 128, 1), (4, 68, 2, 1, 128, 2), (4, 196, 2, 2, 64, 2)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", TAILS, ids=["S%d_d%d_batch%d" % (c[1], c[4], c[5]) for c in TAILS])
+def test_what_lies_behind_the_last_key_is_not_seen(case):
+    """K and V are the front of larger arrays, or the first of two sequences, and what follows is NaN: the rows of a tile behind the last key
+    come as zeros (a probability of zero times NaN would be NaN), so the result has the bits of one with zeros there."""
+    from paper_2509_26541_amd import binding as tb
+    n, S, Hq, Hkv, d, B = case
+    gen = torch.Generator(device="cuda").manual_seed(wl.BASE_SEED + 9990 + S + d)
+    draw = lambda rows, heads: torch.randn((rows, heads, d), generator=gen, device="cuda").to(torch.bfloat16)
+    q, k, v = draw(S // n, Hq), draw(S, Hkv), draw(S, Hkv)
+    results = []
+    for tail in (0.0, float("nan")):
+        if B == 1:
+            kt, vt = (torch.cat([t, torch.full((512, Hkv, d), tail, device="cuda", dtype=t.dtype)])[:S] for t in (k, v))
+            qt = q
+        else:
+            kt, vt = (torch.stack([t, torch.full_like(t, tail)]) for t in (k, v))
+            qt = torch.stack([q, q])
+        plan = tb.ChunkAttnPlan(tb.tasp_schedule(n, 1), qt, kt, vt, wl.FULL, fuse_steps=True)
+        plan.out.fill_(float("nan"))
+        plan.lse.fill_(float("nan"))
+        out, lse = plan.run()
+        torch.cuda.synchronize()
+        results.append((out, lse) if B == 1 else (out[0], lse[0]))
+    assert all(bool(torch.isfinite(x.float()).all()) for x in results[1])
+    assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
