@@ -3,7 +3,7 @@
 // The same cut of the work as attn_tile_kernel: a tile's rows are packed over the heads of a group, and n_split workgroups
 // each take an equal run of the tile's visible keys.  Over joined steps the keys are one run of positions, so there is no list
 // to walk: the loader is a scalar offset per load, and the loop is pipelined by hand like that of the large kernel
-// (attn_bf16.hip).  With 32 (d = 64) and 64 KiB (d = 128) of LDS and 162 and 212 registers three and two workgroups share a CU;
+// (attn_bf16.hip).  With 32 (d = 64) and 64 KiB (d = 128) of LDS and 162 and 213 registers three and two workgroups share a CU;
 // they are at different places in their loops, so one's set-up, barrier and epilogue are filled by the others' work, where the
 // large kernel has a CU to itself.
 //

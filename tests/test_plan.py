@@ -323,13 +323,19 @@ int main() {
 """
 
 
-def _run(tmp_path, program):
+def run_planner(tmp_path, program, text=""):
+    """What `program` prints, compiled with the planner for the host, given `text`; it has to end with 0."""
     src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
     src.write_text(STUBS + program)
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I" + os.path.join(asm_checks.ROOT, "include"), "-I" + asm_checks.CSRC,
                     "-x", "hip", str(src), os.path.join(asm_checks.CSRC, "schedule.cpp"), "-o", str(exe)], check=True, capture_output=True, text=True)
-    res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
+    res = subprocess.run([str(exe)], input=text, capture_output=True, text=True, timeout=300)
     assert res.returncode == 0, res.stdout
+    return res.stdout
+
+
+def _run(tmp_path, program):
+    run_planner(tmp_path, program)
 
 
 def test_plan_follows_from_the_shape(tmp_path):

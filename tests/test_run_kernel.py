@@ -1,5 +1,5 @@
-"""Joined steps of bf16 calls with few query tiles (csrc/attn_run.hip): the generated code around its hand-placed waits (CPU), and
-every row against the oracle at the edges of its tiles, shares and key counts (GPU)."""
+"""Joined steps of bf16 calls with few query tiles (csrc/attn_run.hip): the generated code around its hand-placed waits and which of the
+shapes below take it, with how many shares (CPU), and every row against the oracle at the edges of its tiles, shares and key counts (GPU)."""
 import os
 import shutil
 
@@ -7,7 +7,7 @@ import pytest
 import torch
 
 from paper_2509_26541_amd import workloads as wl
-from tests import asm_checks
+from tests import asm_checks, test_plan
 from tests.helpers import max_abs, oracle_rows
 
 
@@ -81,8 +81,9 @@ def test_hazard_checker_flags_a_planted_copy():
 
 @pytest.mark.skipif(shutil.which(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")) is None, reason="hipcc not found")
 def test_generated_code(tmp_path):
-    """No spills, no register of an LDS read in flight is touched, no matrix result is read too early, every direct load has its
-    descriptor and offset in scalar registers."""
+    """Nothing is kept in scratch and no vector register elsewhere (at d = 128 scalar ones are, in a vector register, where a tile's elements are
+    masked), no register of an LDS read in flight is touched, no matrix result is read too early, every direct load has its descriptor and
+    offset in scalar registers."""
     asm = asm_checks.compile_to_asm("attn_run.hip", str(tmp_path / "attn_run.s"))
     ks = {n: i for n, i in asm_checks.kernels(asm).items() if "attn_run_kernel" in n}
     assert len(ks) == 2, list(ks)
@@ -96,27 +97,74 @@ def test_generated_code(tmp_path):
 
 
 # ---------------------------------------------------------------- against the oracle
-# name, N, rank, S, Hq, Hkv, d, mask, batch.  Rows of a block times heads of a group: around 128 and 32; keys: around one and two
-# tiles of 64 and even and odd counts of them; several shares, with keys and without.
+# name, N, rank, S, Hq, Hkv, d, mask, batch, (shares, tiles of 64 keys of the longest) of each block of rows.  Rows of a block times heads of
+# a group: around 128 and 32; keys: around one and two tiles and even and odd counts of them; several shares, with keys and without.
 CASES = [
-    ("one_tile_of_keys", 4, 0, 8 * 8, 2, 1, 64, wl.ZIGZAG_CAUSAL, 1),
-    ("two_tiles_of_keys_less_one", 4, 1, 4 * 31, 1, 1, 128, wl.FULL, 1),
-    ("two_tiles_and_one", 4, 3, 4 * 33, 3, 1, 64, wl.FULL, 2),
-    ("strip_and_one", 4, 2, 8 * 33, 1, 1, 128, wl.ZIGZAG_CAUSAL, 1),                # 33 rows: a strip with one
-    ("tile_g3", 8, 5, 16 * 43, 6, 2, 128, wl.ZIGZAG_CAUSAL, 1),                     # 129 rows of pairs
-    ("odd_tiles", 8, 3, 16 * 75, 4, 4, 64, wl.ZIGZAG_CAUSAL, 16),                   # last tile full, odd number of tiles in a share
-    ("even_tiles", 8, 3, 16 * 83, 4, 4, 64, wl.ZIGZAG_CAUSAL, 4),
-    ("no_shares", 8, 3, 16 * 75, 20, 20, 64, wl.ZIGZAG_CAUSAL, 20),
-    ("no_shares_d128", 8, 6, 16 * 67, 16, 8, 128, wl.ZIGZAG_CAUSAL, 12),
-    ("more_than_64_tiles", 8, 7, 16 * 300, 1, 1, 64, wl.FULL, 40),                  # the sum of probabilities in two levels
+    ("one_tile_of_keys", 4, 0, 8 * 8, 2, 1, 64, wl.ZIGZAG_CAUSAL, 1, ((1, 1), (1, 1))),
+    ("two_tiles_of_keys_less_one", 4, 1, 4 * 31, 1, 1, 128, wl.FULL, 1, ((1, 2),)),
+    ("two_tiles_and_one", 4, 3, 4 * 33, 3, 1, 64, wl.FULL, 2, ((1, 3),)),
+    ("strip_and_one", 4, 2, 8 * 33, 1, 1, 128, wl.ZIGZAG_CAUSAL, 1, ((4, 1), (2, 1))),                # 33 rows: a strip with one
+    ("tile_g3", 8, 5, 16 * 43, 6, 2, 128, wl.ZIGZAG_CAUSAL, 1, ((8, 1), (5, 1))),                     # 129 rows of pairs
+    ("odd_tiles", 8, 3, 16 * 75, 4, 4, 64, wl.ZIGZAG_CAUSAL, 16, ((3, 6), (1, 5))),                   # last tile full, odd number of tiles in a share
+    ("even_tiles", 8, 3, 16 * 83, 4, 4, 64, wl.ZIGZAG_CAUSAL, 4, ((9, 2), (3, 2))),
+    ("no_shares", 8, 3, 16 * 75, 20, 20, 64, wl.ZIGZAG_CAUSAL, 20, ((1, 16), (1, 5))),
+    ("no_shares_d128", 8, 6, 16 * 67, 16, 8, 128, wl.ZIGZAG_CAUSAL, 12, ((1, 11), (1, 8))),
+    ("long_shares", 8, 7, 16 * 300, 1, 1, 64, wl.FULL, 40, ((2, 38),)),
+    # the sum of probabilities in two levels: the first 64 tiles, and 128, are put by, with an odd and an even number left
+    ("more_than_64_tiles", 8, 7, 16 * 292, 4, 4, 64, wl.FULL, 40, ((1, 73),)),
+    ("more_than_64_tiles_d128", 8, 2, 16 * 296, 4, 4, 128, wl.FULL, 24, ((1, 74),)),
+    ("more_than_128_tiles", 8, 7, 16 * 520, 4, 4, 64, wl.FULL, 24, ((1, 130),)),
+    ("more_than_128_tiles_d128", 8, 0, 16 * 524, 8, 4, 128, wl.FULL, 12, ((1, 131),)),
 ]
+
+
+# N, S, Hq, Hkv, d, sequences: key counts with one row in the last tile, just below and above one, two and three tiles, and shares
+TAILS = [(4, 4, 2, 1, 64, 1), (4, 4, 2, 1, 128, 1), (4, 60, 2, 1, 128, 1), (4, 68, 2, 1, 64, 1), (4, 68, 2, 2, 128, 1), (4, 124, 2, 2, 64, 1), (4, 132, 2, 1, 64, 1),
+         (4, 132, 2, 1, 128, 1), (4, 2404, 2, 1, 64, 1), (4, 2404, 2, 1, 128, 1), (4, 68, 2, 1, 128, 2), (4, 196, 2, 2, 64, 2)]
+
+WHICH = r"""
+int main() {
+  int n, rank, S, hq, hkv, d, mask, batch;
+  while (std::scanf("%d %d %d %d %d %d %d %d", &n, &rank, &S, &hq, &hkv, &d, &mask, &batch) == 8) {
+    tasp_schedule_t* s = nullptr;
+    if (tasp_schedule_create(n, rank, &s) != TASP_OK) return 2;
+    tasp_attn_args a{};
+    a.q = a.k = a.v = a.out = a.workspace = reinterpret_cast<void*>(256);
+    a.lse = reinterpret_cast<float*>(256);
+    a.S = S; a.Hq = hq; a.Hkv = hkv; a.d = d; a.batch = batch; a.dtype = TASP_DTYPE_BF16; a.mask_mode = mask; a.fuse_steps = 1;
+    a.workspace_bytes = tasp_chunk_attn_best_workspace_bytes(s, &a);
+    g = {};
+    if (tasp_chunk_attn(s, &a, nullptr) != TASP_OK) return 3;
+    std::printf("%d", g.tile == 1 && g.large == 0 && tasp::attn_run_takes(g.last, d));
+    for (int t = 0; t < g.last.n_tasks; ++t) {
+      const int keys = mask ? g.last.task[t].q_pos0 + g.last.task[t].n_q : S, ns = g.last.n_split[t];
+      std::printf(" %d %d", ns, ((keys + ns - 1) / ns + 63) / 64);
+    }
+    std::printf("\n");
+    tasp_schedule_destroy(s);
+  }
+  return 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")) is None, reason="hipcc not found")
+def test_the_shapes_below_take_this_kernel(tmp_path):
+    """The planner, compiled for the host: kernel, shares and tiles of the longest share for every shape that is run on the GPU below."""
+    shapes = [c[1:9] for c in CASES] + [(n, 1, S, Hq, Hkv, d, wl.FULL, B) for n, S, Hq, Hkv, d, B in TAILS]
+    lines = test_plan.run_planner(tmp_path, WHICH, "\n".join(" ".join(str(int(x)) for x in c) for c in shapes)).split("\n")
+    for i, c in enumerate(shapes):
+        got = [int(x) for x in lines[i].split()]
+        assert got[0] == 1, c
+        if i < len(CASES):
+            assert got[1:] == [x for t in CASES[i][9] for x in t], (CASES[i][0], got)
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 def test_joined_steps_all_rows(case):
     from paper_2509_26541_amd import binding as tb
-    name, n, rank, S, Hq, Hkv, d, mode, B = case
+    name, n, rank, S, Hq, Hkv, d, mode, B, _ = case
     ws = [wl.Workload(name, n, rank, S, Hq, Hkv, d, "bf16", mode, seed=wl.BASE_SEED + 9900 + S + b) for b in range(min(B, 2))]
     qkv = [wl.make_qkv(w) for w in ws]
     q, k, v = ((torch.stack([qkv[b % 2][i] for b in range(B)]) if B > 1 else qkv[0][i]).cuda() for i in range(3))
@@ -140,11 +188,6 @@ def test_joined_steps_all_rows(case):
         assert err <= 4 * 2.0 ** -9, (name, b, err)
     for b in range(2, B):                              # the same sequences again
         assert torch.equal(out[b], out[b % 2]) and torch.equal(lse[b], lse[b % 2])
-
-
-# N, S, Hq, Hkv, d, sequences: key counts with one row in the last tile, just below and above one, two and three tiles, and shares
-TAILS = [(4, 4, 2, 1, 64, 1), (4, 4, 2, 1, 128, 1), (4, 60, 2, 1, 128, 1), (4, 68, 2, 1, 64, 1), (4, 68, 2, 2, 128, 1), (4, 124, 2, 2, 64, 1), (4, 132, 2, 1, 64, 1),
-         (4, 132, 2, 1, 128, 1), (4, 2404, 2, 1, 64, 1), (4, 2404, 2, 1, 128, 1), (4, 68, 2, 1, 128, 2), (4, 196, 2, 2, 64, 2)]
 
 
 @pytest.mark.gpu
