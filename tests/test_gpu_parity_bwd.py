@@ -177,9 +177,10 @@ def bwd_plan(tb, w, q, k, v, do, **kw):
 
 
 def test_which_dkv_launches_are_split_by_query_head(tb):
-    """A step's dk/dv launch with few, unequal key tiles runs one workgroup per key tile and query
-    head and is followed by the launch that adds the partial sums up; seen from outside as one more
-    launch per step among the profile's `other` launches (delta + clearing dq, and the cast of dq)."""
+    """A dk/dv launch with few, unequal key tiles (here of all steps together) runs one workgroup per key tile,
+    query head and share of the query tiles and is followed by the launch that adds the partial sums up; seen from
+    outside as one more among the profile's `other` launches (delta, and the sum of dq's shares).
+    test_step_by_step counts those of single steps."""
     w = small_workload(SMALL[0])                      # causal, 4 query heads per KV head
     q, k, v = wl.make_qkv(w)
     do = wl.make_dout(w)
@@ -210,6 +211,56 @@ def test_grouped_heads_step_by_step_with_equal_key_tiles(tb):
     close("dk", dk, rk); close("dv", dv, rv)
 
 
+# Four ranks, more than 4 096 local rows: a dq and a dk/dv launch per step.
+STEPS = [
+    # name, rank, S, Hq, Hkv, d, mask, sequences, steps whose dk/dv launch is split by query head
+    ("d128_grouped_ragged", 1, 8 * 2051, 4, 2, 128, wl.ZIGZAG_CAUSAL, 1, 4),
+    ("d64_grouped_ragged", 2, 8 * 2051, 4, 1, 64, wl.ZIGZAG_CAUSAL, 1, 4),
+    ("d128_full_ragged", 3, 4 * 4099, 3, 1, 128, wl.FULL, 1, 4),
+    ("d128_two_sequences", 2, 8 * 2049, 2, 1, 128, wl.ZIGZAG_CAUSAL, 2, 4),
+    ("d128_three_of_four_split", 1, 32768, 16, 8, 128, wl.ZIGZAG_CAUSAL, 1, 3),
+    ("d128_heads_by_themselves", 0, 8 * 2310, 2, 2, 128, wl.ZIGZAG_CAUSAL, 1, 0),
+]
+
+
+@pytest.mark.parametrize("case", STEPS, ids=[c[0] for c in STEPS])
+def test_step_by_step(tb, case):
+    """bf16 gradients step by step, dq summed up over the steps in fp32, dk and dv written by the step that meets their keys, with partial sums
+    per query head or without; then with the dk/dv launches on a second stream.  Upstream gradient on sampled rows of every sequence."""
+    name, rank, S, Hq, Hkv, d, mode, B, split = case
+    n = 4
+    ws = [wl.Workload("bwd_steps_%s_%d" % (name, b), n, rank, S, Hq, Hkv, d, "bf16", mode, seed=wl.BASE_SEED + 860 + d + 17 * b) for b in range(B)]
+    data = [wl.make_qkv(w) + (wl.make_dout(w),) for w in ws]
+    half = ws[0].L // 2
+    keep = sorted(set(wl.sample_rows(ws[0], 12)) | {0, 127, 128, half - 1, half, ws[0].L - 1})
+    for x in data:
+        sparse = torch.zeros_like(x[3])
+        sparse[keep] = x[3][keep]
+        x[3].copy_(sparse)
+    q, k, v, do = ((torch.stack([x[i] for x in data]) if B > 1 else data[0][i]).cuda() for i in range(4))
+    s = tb.tasp_schedule(n, rank)
+    out, lse = tb.tasp_chunk_attn(q, k, v, s, mode, fuse_merge=True)
+    plan = tb.ChunkAttnBwdPlan(s, q, k, v, out, lse, do, mode)
+    prof = plan.profile()
+    assert prof.dq_launches == n and prof.dkv_launches == n
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert prof.other_launches == 2 + split                 # delta with the clearing of dq, the cast of dq, and the sums
+    for t in (plan.dq, plan.dk, plan.dv):
+        t.fill_(float("nan"))
+    one = [t.clone() for t in plan.run()]
+    side = torch.cuda.Stream()
+    two = tb.ChunkAttnBwdPlan(s, q, k, v, out, lse, do, mode, aux_stream=side).run()
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(one, two))
+    for b in range(B):
+        dq, dk, dv = (t[b] if B > 1 else t for t in one)
+        rq, rk, rv = oracle_grads(ws[b], *data[b], rows=keep)
+        close("dq kept rows", dq[keep], rq)
+        rest = np.setdiff1d(np.arange(ws[b].L), keep)
+        assert float(dq[rest].float().abs().max()) == 0.0
+        close("dk", dk, rk); close("dv", dv, rv)
+
+
 def test_rows_without_upstream_gradient_get_none(tb):
     """dout = 0 on a row: its dq is exactly zero and it adds nothing to dk, dv (linearity in dout)."""
     w = small_workload(SMALL[0])
@@ -232,8 +283,9 @@ def test_rows_without_upstream_gradient_get_none(tb):
 def test_full_size_sparse_upstream_gradient(tb, capsys, idx, n_random):
     """Full size, every element of dq, dk and dv: the upstream gradient is non-zero on sampled rows
     only, which the oracle can afford (the kernels do the same work whatever dout holds).  The 128K
-    workload is the configuration bench.py times; the 256K one has no mask (dk/dv launches never
-    split), the 512K one eight query heads per KV head (dk/dv launches split by query head)."""
+    workload is the configuration bench.py times; the 256K one has no mask, the 512K one eight query heads
+    per KV head.  The steps are joined in either form: by position, and (fuse_steps) as the lists of the
+    steps one behind the other.  test_step_by_step has the form in which they are not."""
     w = wl.CONFIGS[idx]
 
     def say(msg):            # progress past pytest's capture: a silent minute reads as a hang on the GPU box

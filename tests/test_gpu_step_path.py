@@ -1,5 +1,5 @@
-"""Calls that run step by step (more than 4 096 local rows, all steps not asked for in one launch), with half-chunks that no
-tile divides: the partial pair of a step written and merged by the merge kernel, and folded in by the attention kernel.
+"""Forward calls that run step by step (more than 4 096 local rows, all steps not asked for in one launch; fp32: four ranks with up to 8 192
+rows), with half-chunks that no tile divides: the partial pair of a step written and merged by the merge kernel, and folded in by the attention kernel.
 Sampled rows against the oracle; the number of launches shows which path ran."""
 import numpy as np
 import pytest

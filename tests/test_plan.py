@@ -45,8 +45,7 @@ hipError_t launch_bwd_delta_fp32(const void*, const void*, float*, int64_t, int,
 }
 """
 
-PLAN = r"""
-
+PLANS = r"""
 struct Plan { bool ok, tile; int n0, n1, kv; size_t bytes; };
 
 static Plan forward(const tasp_schedule_t* s, tasp_attn_args a, size_t ws) {     // ws = 0: as much as is reported for the call
@@ -76,7 +75,9 @@ static Plan backward(const tasp_schedule_t* s, tasp_attn_bwd_args b, size_t ws) 
   return {plan_bytes(p, &b, sh) <= used, false, p.n_split, 0, p.kv_split, plan_bytes(p, &b, sh)};
 }
 static bool same(const Plan& x, const Plan& y) { return x.ok == y.ok && x.tile == y.tile && x.n0 == y.n0 && x.n1 == y.n1 && x.kv == y.kv; }
+"""
 
+PLAN = PLANS + r"""
 int main() {
   std::mt19937 rng(5);
   auto pick = [&](std::initializer_list<int> l) { return l.begin()[rng() % l.size()]; };
@@ -131,6 +132,72 @@ int main() {
   }
   std::printf("%d forward (%d with shares), %d backward, %d differ\n", fwd, shared, bwd, bad);
   return bad != 0 || fwd < 8000 || shared < 2000 || bwd < 8000;
+}
+"""
+
+# With more than kJoinRows local rows: fp32 calls and the backward pass.
+PLAN_LONG = PLANS + r"""
+int main() {
+  std::mt19937 rng(6);
+  auto pick = [&](std::initializer_list<int> l) { return l.begin()[rng() % l.size()]; };
+  const size_t fixed = TASP_STATIC_SCRATCH_BYTES;
+  int bad = 0, fwd = 0, bwd = 0, shared = 0, split = 0;
+  for (int i = 0; i < 4000; ++i) {
+    const int n = pick({4, 8, 8, 12, 16}), r = static_cast<int>(rng() % n);
+    tasp_schedule_t* s = nullptr;
+    if (tasp_schedule_create(n, r, &s) != TASP_OK) return 2;
+    tasp_attn_args a{};
+    a.q = a.k = a.v = a.out = reinterpret_cast<void*>(256);
+    a.d = pick({64, 128});
+    a.Hkv = pick({1, 1, 2, 3, 4, 8});
+    a.Hq = a.Hkv * pick({1, 1, 2, 4, 8});
+    a.mask_mode = pick({TASP_MASK_FULL, TASP_MASK_ZIGZAG_CAUSAL});
+    a.fuse_merge = pick({0, 1});
+    a.batch = pick({1, 1, 2, 4});
+    const int64_t rows = kJoinRows << (rng() % 3);
+    a.S = n * (rows + 2 * (1 + rng() % (rows / 2)));                   // 4 098 to 32 768 local rows
+    auto report = [&](const char* what, const Plan& x, const Plan& y) {
+      if (bad++ < 10)
+        std::printf("%s: n=%d S=%lld %d/%d d=%d dtype=%d mask=%d batch=%d fuse_merge=%d: tile %d shares %d %d kv %d, not %d %d %d %d\n", what, n, (long long)a.S, a.Hq, a.Hkv,
+                    a.d, a.dtype, a.mask_mode, a.batch, a.fuse_merge, x.tile, x.n0, x.n1, x.kv, y.tile, y.n0, y.n1, y.kv);
+    };
+    a.dtype = TASP_DTYPE_FP32;
+    const size_t need = tasp_chunk_attn_workspace_bytes(s, &a);
+    if (joins(s, &a) && need <= fixed) {
+      const Plan best = forward(s, a, 0);
+      ++fwd;
+      shared += best.n0 > 1 || best.n1 > 1;
+      if (need > 0) {
+        const Plan st = forward(s, a, fixed);
+        if (!same(best, st)) report("forward, static", best, st);
+      } else {                       // in turn: as many, or as many more as one set of sums asks for (d = 128)
+        const Plan st = forward_none(s, a);
+        const int least = a.d == 128 ? static_cast<int>((a.S + tasp::kSumTiles * 32 - 1) / (tasp::kSumTiles * 32)) : 1;
+        if (!st.ok || st.tile != best.tile || st.n0 < best.n0 || st.n1 < best.n1 || st.n0 > std::max(best.n0, least) || st.n1 > std::max(best.n1, least)) report("forward, in turn", best, st);
+      }
+      if (best.bytes > std::max(tasp_chunk_attn_best_workspace_bytes(s, &a), need)) report("forward, bytes", best, best);
+      const Plan few = forward(s, a, std::max<size_t>(need, 1));
+      if (few.ok && few.bytes > std::max<size_t>(need, 1)) report("forward, least", few, few);
+    }
+    for (int dtype : {TASP_DTYPE_FP32, TASP_DTYPE_BF16}) {
+      a.dtype = dtype;
+      if (!joins(s, &a, true)) continue;
+      tasp_attn_bwd_args b{};
+      b.q = b.k = b.v = b.out = b.dout = b.dq = b.dk = b.dv = reinterpret_cast<void*>(256);
+      b.lse = reinterpret_cast<float*>(256);
+      b.S = a.S; b.Hq = a.Hq; b.Hkv = a.Hkv; b.d = a.d; b.dtype = dtype; b.mask_mode = a.mask_mode; b.batch = a.batch;
+      const Plan bb = backward(s, b, 0);
+      if (!bb.ok) { report("backward, refused", bb, bb); continue; }
+      ++bwd;
+      split += bb.n0 > 1 || bb.kv > 0;
+      const Plan more = backward(s, b, std::max(fixed, tasp_chunk_attn_bwd_workspace_bytes(s, &b)));
+      if (!same(bb, more)) report("backward, room", bb, more);
+      if (!backward(s, b, tasp_chunk_attn_bwd_workspace_bytes(s, &b)).ok) report("backward, least", bb, bb);
+    }
+    tasp_schedule_destroy(s);
+  }
+  std::printf("%d forward (%d with shares), %d backward (%d split), %d differ\n", fwd, shared, bwd, split, bad);
+  return bad != 0 || fwd < 1200 || shared < 300 || bwd < 5000 || split < 300;
 }
 """
 
@@ -340,6 +407,11 @@ def _run(tmp_path, program):
 
 def test_plan_follows_from_the_shape(tmp_path):
     _run(tmp_path, PLAN)
+
+
+def test_plan_follows_from_the_shape_with_many_rows(tmp_path):
+    """The same where the library joins the steps of calls with more than 4 096 local rows."""
+    print(run_planner(tmp_path, PLAN_LONG))
 
 
 def test_a_step_takes_the_faster_kernel(tmp_path):
