@@ -31,12 +31,12 @@
 
 #include "gfx950.hpp"
 #include "internal.hpp"
+#include "pipeline.hpp"
 
 namespace tasp {
 namespace {
 
 constexpr int BT = 64;             // streamed rows per tile
-constexpr float kLog2e = 1.4426950408889634f;
 
 template <int D, int NW>
 struct BCfg {
@@ -66,13 +66,6 @@ __device__ inline void wait_all_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: 
 
 __device__ inline bf16x8 lds_row8(const unsigned char* p) {
   return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(p));
-}
-// A operand of Y^T E: 32 columns of Y (rows of Y^T) by 16 rows of Y, from two transposing reads
-// eight rows apart.
-__device__ inline bf16x8 lds_tr8(const unsigned char* lo, const unsigned char* hi) {
-  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lds_void_ptr)const_cast<unsigned char*>(lo));
-  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lds_void_ptr)const_cast<unsigned char*>(hi));
-  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 __device__ inline f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);

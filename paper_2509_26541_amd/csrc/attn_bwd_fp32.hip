@@ -22,12 +22,11 @@
 
 #include "gfx950.hpp"
 #include "internal.hpp"
+#include "pipeline.hpp"
 
 namespace tasp {
 namespace {
 
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
 constexpr int BX = 64, BT = 64;          // X rows of a workgroup, Y rows of a tile
 constexpr int NTHREADS = 256;
 
@@ -39,12 +38,6 @@ struct FCfg {
   static constexpr int NJ = UNITS / 2, NDB = D / 32;
 };
 
-__device__ inline f32x16 zero16() {
-  f32x16 z;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) z[i] = 0.f;
-  return z;
-}
 __device__ inline f32x16 mfma(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
 
 __device__ inline float wave_sum(float x) {

@@ -24,14 +24,10 @@
 
 #include "gfx950.hpp"
 #include "internal.hpp"
+#include "pipeline.hpp"
 
 namespace tasp {
 namespace {
-
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
-constexpr float kRescaleGap = 8.0f;      // the running max is only raised when it grew by more than 2^8
-constexpr float kNegBig = -1.0e30f;
 
 template <int D>
 struct RunCfg {
@@ -47,34 +43,6 @@ struct RunCfg {
   __device__ static int swz_k(int r, int u) { return u ^ ((r / RPL) % UNITS); }
   __device__ static int swz_v(int r, int u) { return u ^ (4 * ((r / RPL) % (UNITS / 4))); }
 };
-
-__device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-__device__ inline f32x16 zero16() {
-  f32x16 z;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) z[i] = 0.f;
-  return z;
-}
-// Matrix instructions as volatile assembly: program order is the schedule, and an accumulator stays where it is.  The compiler
-// does not know them, so the wait states around them are placed by hand: vector result -> matrix operand 2, matrix result -> vector
-// operand 12.
-// W >= 0: the operand a comes from LDS reads, and at most W younger LDS instructions may be outstanding.
-template <int W>
-__device__ __forceinline__ void mfma_first(f32x16& d, const u32x4& a, const u32x4& b) {
-  if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "v"(b), "n"(W < 0 ? 0 : W));
-  else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "v"(b));
-}
-template <int W>
-__device__ __forceinline__ void mfma_add(f32x16& d, const u32x4& a, const u32x4& b) {
-  if constexpr (W >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b), "n"(W < 0 ? 0 : W));
-  else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
-}
-template <int IMM>
-__device__ __forceinline__ void lds_read_b128(u32x4& d, unsigned addr) { asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(IMM)); }
-template <int IMM>
-__device__ __forceinline__ void lds_read_tr_b64(u32x2& d, unsigned addr) { asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(IMM)); }
-__device__ __forceinline__ void fence_scores(f32x16& a, f32x16& b) { asm volatile("s_nop 15" : "+v"(a), "+v"(b)); }
-__device__ __forceinline__ void fence_p(u32x4& f) { asm volatile("s_nop 1" : "+v"(f)); }
 
 // One block of query rows of a launch (AttnTask), and how its keys are dealt.
 struct RunTask {
@@ -303,8 +271,8 @@ __global__ __launch_bounds__(RunCfg<D>::NTHREADS, D == 64 ? 3 : 2) void attn_run
     __builtin_amdgcn_sched_barrier(0);
     static_for<NF>([&](auto ff) __attribute__((always_inline)) {
       constexpr int F = decltype(ff)::value, ks = F / 2, kb = F % 2;
-      if constexpr (ks == 0) mfma_first<younger(F, NF + NV)>(S_next[kb], fk[F % PD], qf[ks]);
-      else mfma_add<younger(F, NF + NV)>(S_next[kb], fk[F % PD], qf[ks]);
+      if constexpr (ks == 0) mfma_s_first<false, younger(F, NF + NV)>(S_next[kb], fk[F % PD], qf[ks]);
+      else mfma_s<false, younger(F, NF + NV)>(S_next[kb], fk[F % PD], qf[ks]);
       read(std::integral_constant<int, F + PD>{}, sk, ss);
       exps(std::integral_constant<int, PRE + (EK - PRE) * F / NF>{}, std::integral_constant<int, PRE + (EK - PRE) * (F + 1) / NF>{}, S);
       __builtin_amdgcn_sched_barrier(0);
@@ -313,9 +281,9 @@ __global__ __launch_bounds__(RunCfg<D>::NTHREADS, D == 64 ? 3 : 2) void attn_run
     });
     static_for<NV>([&](auto ff) __attribute__((always_inline)) {
       constexpr int F = decltype(ff)::value, gg = F / NDB, db = F % NDB;
-      if constexpr (F == VS) { fence_scores(S_next[0], S_next[1]); mask(t + 1, S_next); }
+      if constexpr (F == VS) { fence_s(S_next[0], S_next[1]); mask(t + 1, S_next); }
       if constexpr (db == 0) fence_p(pf[gg]);
-      mfma_add<younger(NF + F, NF + NV)>(o[db], v_fragment(std::integral_constant<int, NF + F>{}), pf[gg]);
+      mfma_s<false, younger(NF + F, NF + NV)>(o[db], v_fragment(std::integral_constant<int, NF + F>{}), pf[gg]);
       read(std::integral_constant<int, NF + F + PD>{}, sk, ss);
       if constexpr (F < VE) exps(std::integral_constant<int, EK + (32 - EK) * F / VE>{}, std::integral_constant<int, EK + (32 - EK) * (F + 1) / VE>{}, S);
       if constexpr (F == VE) add_up();
@@ -338,7 +306,7 @@ __global__ __launch_bounds__(RunCfg<D>::NTHREADS, D == 64 ? 3 : 2) void attn_run
     static_for<NV>([&](auto ff) __attribute__((always_inline)) {
       constexpr int F = decltype(ff)::value, gg = F / NDB, db = F % NDB;
       if constexpr (db == 0) fence_p(pf[gg]);
-      mfma_add<younger(NF + F, NF + NV)>(o[db], v_fragment(std::integral_constant<int, NF + F>{}), pf[gg]);
+      mfma_s<false, younger(NF + F, NF + NV)>(o[db], v_fragment(std::integral_constant<int, NF + F>{}), pf[gg]);
       read(std::integral_constant<int, NF + F + PD>{}, ss, ss);
       if constexpr (gg < 3) exps(std::integral_constant<int, 8 + 8 * F / NDB>{}, std::integral_constant<int, 8 + 8 * (F + 1) / NDB>{}, S);
       __builtin_amdgcn_sched_barrier(0);
@@ -352,11 +320,11 @@ __global__ __launch_bounds__(RunCfg<D>::NTHREADS, D == 64 ? 3 : 2) void attn_run
     static_for<PD>([&](auto f) __attribute__((always_inline)) { read(f, stage0, stage0); });
     static_for<NF>([&](auto ff) __attribute__((always_inline)) {
       constexpr int F = decltype(ff)::value, ks = F / 2, kb = F % 2;
-      if constexpr (ks == 0) mfma_first<younger(F, NF)>(Sa[kb], fk[F % PD], qf[ks]);
-      else mfma_add<younger(F, NF)>(Sa[kb], fk[F % PD], qf[ks]);
+      if constexpr (ks == 0) mfma_s_first<false, younger(F, NF)>(Sa[kb], fk[F % PD], qf[ks]);
+      else mfma_s<false, younger(F, NF)>(Sa[kb], fk[F % PD], qf[ks]);
       if constexpr (F + PD < NF) read(std::integral_constant<int, F + PD>{}, stage0, stage0);
     });
-    fence_scores(Sa[0], Sa[1]);
+    fence_s(Sa[0], Sa[1]);
     mask(0, Sa);
     static_for<16>([&](auto i) __attribute__((always_inline)) { max_step(i, Sa); });
     if (n_tiles > 1) __syncthreads();          // everybody has read K(0)

@@ -38,19 +38,16 @@
 
 #include "gfx950.hpp"
 #include "internal.hpp"
+#include "pipeline.hpp"
 
 namespace tasp {
 namespace {
 
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLog2eLow = 1.92596298909e-8f;      // what it leaves of log2(e)
-constexpr float kLn2 = 0.6931471805599453f;
-constexpr float kRescaleGap = 8.0f;      // the running max is only raised when it grew by more than 2^8
+constexpr float kLog2eLow = 1.92596298909e-8f;      // what kLog2e leaves of log2(e)
 constexpr float kRescaleGapF32 = 2.0f;   // fp32: 2^2, see kHuge
 constexpr int kHuge = (104 + 127) << 23; // fp32: bits of 2^104.  Rows with a value that large are left to the end, see the loop
 constexpr float kVScale = 65536.f;       // fp32: V is taken times 2^16
-constexpr float kLn2Low = -1.904654323e-9f;          // and of ln(2)
-constexpr float kNegBig = -1.0e30f;
+constexpr float kLn2Low = -1.904654323e-9f;          // and kLn2 of ln(2)
 constexpr int CHUNK = 512;               // keys located at a time
 constexpr int RUNS = 512;                // fp32: entries of the table of tiles with something left to the end
 
@@ -81,18 +78,11 @@ struct TCfg {
   __device__ static int swz_v(int r, int u) { return u ^ (4 * ((r / RPL) % (UNITS / 4))); }
 };
 
-__device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 // The lane's number, formed anew: for code off the ordinary way, so that no register holds it for that.
 __device__ __forceinline__ int lane_id() {
   int l;
   asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
   return l;
-}
-__device__ inline f32x16 zero16() {
-  f32x16 z;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) z[i] = 0.f;
-  return z;
 }
 // Floats as three bf16 each, x = x1 + x2 + x3 exactly (8 bits each, rounded to nearest, so that the signs of the later ones
 // vary): x2 is at most 2^-8 x and x3 2^-16 x.  The next piece of eight floats, which are left with the rest.
@@ -130,11 +120,6 @@ __device__ __forceinline__ int dpp_max(int x) { return max(x, __builtin_amdgcn_u
 __device__ __forceinline__ int max32(int x) {
   x = dpp_max<0x118>(dpp_max<0x114>(dpp_max<0x112>(dpp_max<0x111>(x))));
   return max(__builtin_amdgcn_readlane(x, 15), __builtin_amdgcn_readlane(x, 31));
-}
-__device__ inline bf16x8 lds_tr8(const unsigned char* lo, const unsigned char* hi) {
-  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lds_void_ptr)const_cast<unsigned char*>(lo));
-  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lds_void_ptr)const_cast<unsigned char*>(hi));
-  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
 // One more (normalised) pair into running sums that are kept unnormalised against their running maximum: the sums are
