@@ -250,7 +250,9 @@ double makespan(double n0, double l0, double n1, double l1, double slots) {
 // last row of task t sees.  Shares are weighed by when the last workgroup would be done: R workgroups of a CU side by side,
 // each at 1 / R of its rate, one by itself at 1 / alone; a workgroup's fixed cost (set-up, first fetches, epilogue) as so many
 // keys more; and with shares the launch that adds them up and the way of the partial pairs through memory.
-// Over 110 drawn shapes (profiles/shares_of_the_keys.txt) the choice takes for one sequence, over the best of up to 40 ways, which is partly the
+// The bf16 figures were fitted to attn_tile_kernel, which took these calls before; fitted anew to attn_run_kernel they gain less than 1 % in the
+// mean, though three of its workgroups share a CU at d = 64 where R says two.
+// Over 110 drawn shapes (bf16: with attn_tile_kernel; profiles/shares_of_the_keys.txt) the choice takes for one sequence, over the best of up to 40 ways, which is partly the
 // luckiest, 0.97 (fp32, d = 64), 0.98 (128), 1.02 (bf16, both d) in the mean and 1.19 at most; batches of two to four that are planned as one
 // sequence 1.10 to 1.15.
 void deal_keys(const AttnLaunch& lp, int d, bool fp32, const int64_t* keys, size_t room, int32_t* n_split, int64_t B) {
