@@ -43,6 +43,33 @@ TILE_MIX = {128: {"mfma": 32, "valu": 107, "exp": 33, "lds_kib": 32},
             64: {"mfma": 16, "valu": 105, "exp": 33, "lds_kib": 16}}
 
 
+CSRC = os.path.join(ROOT, "paper_2509_26541_amd", "csrc")
+
+
+def read_source(name):
+    with open(os.path.join(CSRC, name), "rb") as f:
+        return f.read()
+
+
+def kernel_headers():
+    """The headers of the library that the large attention kernel's source includes, directly or through one of them."""
+    import re
+    found, todo = set(), ["attn_bf16.hip"]
+    while todo:
+        for name in re.findall(r'#include "([\w.]+)"', read_source(todo.pop()).decode()):
+            if name not in found and os.path.exists(os.path.join(CSRC, name)):
+                found.add(name)
+                todo.append(name)
+    return sorted(found)
+
+
+def kernel_hashes():
+    """What that kernel is made from, as hbm_traffic.json records it."""
+    import hashlib
+    sha16 = lambda data: hashlib.sha256(data).hexdigest()[:16]
+    return {"attn_bf16_hip_sha16": sha16(read_source("attn_bf16.hip")), "headers_sha16": sha16(b"".join(read_source(n) for n in kernel_headers()))}
+
+
 def valu_peak_tflops(d):
     mix = TILE_MIX[d]
     cycles = sum(PORT_CYCLES[k] * n for k, n in mix.items())
@@ -265,26 +292,24 @@ def main():
     # HBM bytes per attention launch measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (scaled by
     # the copy-kernel calibration); the figures live in paper_2509_26541_amd/hbm_traffic.json, the
     # summaries they come from in profiles/
-    # (null when the kernel source has changed since they were taken: the file records its hash)
+    # (null when the kernel's source or a header of it has changed since they were taken: the file records their hashes)
     traffic = None
     tpath = os.path.join(ROOT, "paper_2509_26541_amd", "hbm_traffic.json")
     if os.path.exists(tpath) and args.batch == 1 and args.nodes <= 1 and args.order == "tasp" and args.fuse_merge and not args.fuse_steps:   # what was profiled
-        import hashlib
-        with open(os.path.join(ROOT, "paper_2509_26541_amd", "csrc", "attn_bf16.hip"), "rb") as f:
-            sha = hashlib.sha256(f.read()).hexdigest()[:16]
         with open(tpath) as f:
             rec = json.load(f).get(w.name, {})
-        if rec.get("attn_bf16_hip_sha16") == sha:
+        if all(rec.get(k) == v for k, v in kernel_hashes().items()):
             traffic = rec.get("attn_bytes_per_launch")
+    large = is_bf16 and w.L > FEW_ROWS and not args.fuse_steps       # the launches are attn_bf16_kernel's; joined ones may be either kernel's
     roofline = {
-        "bound": "mfma", "kernel": "attn_tile_kernel" if not is_bf16 else "attn_bf16_kernel" if w.L > FEW_ROWS else "attn_bf16_kernel or attn_run_kernel",
+        "bound": "mfma", "kernel": "attn_tile_kernel" if not is_bf16 else "attn_bf16_kernel" if large else "attn_bf16_kernel or attn_run_kernel",
         "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak, "traffic": traffic,
         "avg_launch_ms": attn_avg_ms, "launches_per_call": attn_n // n_prof,
     }
     # the vector issue port, the pipe that actually bounds the large bf16 kernel (above all at d = 64); the port
-    # prices are that kernel's, so with few local rows, where another one may run, there is no such line
+    # prices are that kernel's, so with joined steps, where another one may run, there is no such line
     roofline_valu = None
-    if is_bf16 and w.L > FEW_ROWS:
+    if large:
         vp = valu_peak_tflops(w.d)
         roofline_valu = {"bound": "valu", "kernel": "attn_bf16_kernel", "achieved": achieved, "peak": vp, "unit": "TFLOP/s",
                          "frac": achieved / vp, "port_cycles": PORT_CYCLES, "per_tile_and_wavefront": TILE_MIX[w.d],
