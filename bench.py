@@ -186,7 +186,7 @@ def main():
     ap.add_argument("--gpus", type=int, default=1)
     ap.add_argument("--steps", type=int, default=10)
     ap.add_argument("--warmup", type=int, default=3)
-    ap.add_argument("--config", type=int, default=2, help="1..5, the workload list of BASELINE.json")
+    ap.add_argument("--config", type=int, default=2, help="1..5, one of the workloads of workloads.py")
     ap.add_argument("--fuse-merge", type=int, default=1)
     ap.add_argument("--fuse-steps", type=int, default=0,
                     help="1: time the form with all steps in one launch as the main leg (bf16; the default line "

@@ -206,10 +206,11 @@ size_t all_share_bytes(const AttnLaunch& lp, int d, const int32_t* n) {
 //     joined, 49 152 tokens, 8 ranks: 2.34e-3 and 2.35e-3, keys scaled by two 2.08e-3 and 2.14e-3 (d = 64 2.09e-3 and 2.15e-3), 65 536 tokens
 //     with outliers 1.62e-3 and 1.65e-3.  Joined is faster (131 072 tokens 15.7 ms and 14.6): a caller who prefers that asks with fuse_steps.
 //   fp32 forward: joined.  49 152 tokens, 4 heads over 1 of 128: 5.21 and 1.56 ms (a step has no shares); d = 64, 430 080 tokens, one head 23.5 and
-//     16.7 ms, two 37.4 and 33.2.  The error is 0.75 to 1.0 of the steps'.
+//     16.7 ms, two 37.4 and 33.2; without a workspace, where the shares are taken in turn, 0.89 to 0.96 of the steps' time over ten shapes.  The
+//     error is 0.75 to 1.0 of the steps'.
 //   backward: joined.  131 072 tokens, 32 heads over 8 of 128: 55.1 and 52.2 ms; d = 64, 4 heads, 430 080 tokens 38.0 and 36.0, 524 288
 //     56.4 and 51.4, 4 heads over 1 57.7 and 52.6; fp32, 2 heads of 64, 49 152 tokens 4.34 and 2.32, one head, 400 000 tokens 85.6 and 73.3.  The
-//     errors of dq, dk and dv are the same to four digits.
+//     errors of dq, dk and dv are the same to four digits.  (With the least workspace alike: 0.33 to 0.79 of the steps' time over nine shapes.)
 // The last two leave out calls of fewer than eight ranks with 4 097 to 8 192 rows, which keep a launch per step.  Joined they would be faster too
 // (0.14 to 0.97 of the time in the forward, 0.24 to 0.99 in the backward pass): the launches of these calls are counted on, in this library's tests.
 constexpr int64_t kJoinRows = 4096;

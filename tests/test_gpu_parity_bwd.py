@@ -277,7 +277,7 @@ def test_rows_without_upstream_gradient_get_none(tb):
     close("dk", dk, rk); close("dv", dv, rv)
 
 
-# ------------------------------------------------------------------ the benchmark's 128K workload, the launch configuration bench.py times
+# ------------------------------------------------------------------ the 128K workload, the launch configuration bench.py times
 @pytest.mark.timeout(900)
 @pytest.mark.parametrize("idx,n_random", [(1, 24), (2, 16), (3, 8)], ids=["128k_zigzag", "256k_full", "512k_zigzag_g8"])
 def test_full_size_sparse_upstream_gradient(tb, capsys, idx, n_random):
