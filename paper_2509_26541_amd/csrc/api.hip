@@ -204,7 +204,7 @@ size_t all_share_bytes(const AttnLaunch& lp, int d, const int32_t* n) {
 //   bf16 forward: step by step.  Each step's output is divided by a sum that takes its own largest probabilities as they were rounded
 //     (r_fix in attn_bf16.hip); one launch has one such division, for all keys.  Relative error of the output against 64 bits, step by step and
 //     joined, 49 152 tokens, 8 ranks: 2.34e-3 and 2.35e-3, keys scaled by two 2.08e-3 and 2.14e-3 (d = 64 2.09e-3 and 2.15e-3), 65 536 tokens
-//     with outliers 1.62e-3 and 1.65e-3.  Joined is faster (131 072 tokens 15.7 ms and 14.6): a caller who prefers that asks with fuse_steps.
+//     with outliers 1.61e-3 and 1.65e-3.  Joined is faster (131 072 tokens 15.1 ms and 13.9): a caller who prefers that asks with fuse_steps.
 //   fp32 forward: joined.  49 152 tokens, 4 heads over 1 of 128: 5.21 and 1.56 ms (a step has no shares); d = 64, 430 080 tokens, one head 23.5 and
 //     16.7 ms, two 37.4 and 33.2; without a workspace, where the shares are taken in turn, 0.89 to 0.96 of the steps' time over ten shapes.  The
 //     error is 0.75 to 1.0 of the steps'.
